@@ -451,3 +451,19 @@ def test_measured_compute_rate_feeds_the_scheduler():
     # a slower device rate can only raise the modelled ring time
     arr_slow = dict(arr, c=np.full(8, c_d / 4))
     assert hexi.hexi_sched_cost(arr_slow, model, plan["groups"], plan["l_group"], plan["s_pre"], plan["n_heads"])[3] >= t_ring
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 1, 1, 1), (2, 2, 15, 17), (3, 1, 16, 128), (2, 1, 17, 129), (2, 1, 129, 15), (4, 2, 300, 257), (16, 16, 1000, 1010)])
+def test_f32_workgroup_shapes(nq, nkv, lq, lc, d):
+    # lengths at the edges of the fp32 kernels' 16-row blocks and 128-row (split) / 32-row (shared) tiles; the last size
+    # is dealt to the shared shape (256 workgroups of 64 rows), the others to the split one.  The second chunk is diagonal.
+    w = _custom(f"f32_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
+    run, inputs, ref = _run_and_compare(w, seed=lq * 1000 + lc + d)
+    # dk / dv under HEXI_ACCUMULATE: the running value plus the gradient; dq_acc adds up over calls
+    for j, ch in enumerate(w.chunks):
+        dk, dv, dq = torch.full_like(run.dk[j], 0.5), torch.full_like(run.dv[j], -0.25), torch.full_like(run.dq, 1.0)
+        hexi.hexi_attn_bwd_chunk(run.desc[j], w.q_segs, ch, run.q, run.k[j], run.v[j], None, run.d_o, run.lse, run.delta, dq, dk, dv,
+                                 flags=hexi.HEXI_ACCUMULATE)
+        check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "f32")
+        check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "f32")
