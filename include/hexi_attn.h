@@ -243,7 +243,8 @@ int hexi_sched_solve(const hexi_cluster* cluster, const hexi_model* model, const
  * Tuning / test knob of hexi_attn_bwd_chunk's dK/dV part (the GQA sum over the n_d local heads of a
  * group, Sec. 3.2): the number of q heads of one kv head that a workgroup walks into the same
  * accumulators.  0 = chosen by the library per call (the default); n >= 1 = at most n (clamped to
- * the largest group).  The initial value is read once, when the library is loaded, from the
+ * the largest group), in the 128-key workgroups also where a small launch would take smaller ones.
+ * The initial value is read once, when the library is loaded, from the
  * environment variable HEXI_DKDV_RUN_LEN.  Process-wide; not synchronised with calls in flight on
  * other threads.  Returns the previous value.
  */

@@ -243,8 +243,7 @@ HEXI_EXPORT int hexi_attn_bwd_chunk(const hexi_attn_desc* desc, const hexi_range
         if (chunk_in_future(a.g)) {
             if (!a.accumulate && want_dkdv) {
                 const long long n = (long long)a.g.lc * a.g.nkv * a.g.d;
-                e = hexi_launch_fill_f32(dk, n, 0.f, s);
-                if (e == hipSuccess) e = hexi_launch_fill_f32(dv, n, 0.f, s);
+                e = hexi_launch_zero2_f32(dk, dv, n, s);
             }
         } else {
             e = desc->dtype == HEXI_F32 ? hexi_launch_bwd_f32(a, s) : hexi_launch_bwd_bf16(a, s);

@@ -30,6 +30,7 @@
 // run).  When a kv head has a single run its tiles are written with plain stores; otherwise the runs add theirs
 // with fp32 atomics, and dk/dv must be zero-filled (or hold the running sum under HEXI_ACCUMULATE) before the
 // launch.  The host picks the run length: as long as possible while the launch still has a few workgroups per CU.
+#include <cmath>
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 
@@ -417,8 +418,6 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
             --run_len;
         if (const int forced = hexi_dkdv_run_len; forced >= 1)      // tuning / test override of the heuristic
             run_len = forced < max_cnt ? forced : max_cnt;
-        HeadRuns runs;
-        const bool shared = hexi_build_head_runs(a.g.kv_of_q, a.g.nq, a.g.nkv, run_len, &runs);
         // cost of a unit: the q tiles its key tile sees, once per head of the run, plus the prologue and epilogue
         // (about 20 tiles' worth)
         float seen[4096];
@@ -428,19 +427,57 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
             const int n_all = n_qtiles - seg_rows_le(a.g.qs, k_min - 1) / TM;
             seen[t] = (float)(n_all > 0 ? n_all : 0);
         }
+        // Launches that do not fill the chip take the split kernel's 32-key workgroups instead (whole groups where
+        // they fill it: no atomics).  Estimated times in us, fitted like those of the forward launcher.  Measured, head_dim 128,
+        // us of 128 / 32 keys: 300 rows x 700 keys x 4 / 2 heads 23.9 / 11.5; 512 x 1024 x 24 / 8 46 / 21; 1024 x 1024 x 24 / 8
+        // 56 / 36; 2048 x 2048 x 24 / 8 158 / 123; 4096 x 4096 x 12 / 3 245 / 270; head_dim 64: 1024 x 1024 x 24 / 8 37 / 22,
+        // 4096 x 4096 x 24 / 8 272 / 292.  A forced run length keeps the 128-key workgroups that it is defined for.
+        bool split_keys = false;
+        if (hexi_dkdv_run_len < 1 && (long long)n_runs_for(run_len) * n_kv_tiles < 2048 && n_kv_tiles <= 4096) {
+            const bool wide = a.g.d == 128;
+            const double fill_us = 6.0;                        // zero-filling dk and dv where runs add into them
+            const double atomic_us = (double)a.g.lc * a.g.d * 8.0 / 1.2e6;     // one run's atomics (1.2 TB/s)
+            auto estimate = [&](int len, int keys) {
+                const long long n_runs = n_runs_for(len);
+                double sum = 0.0, longest = 0.0;
+                long long n = 0;
+                for (int t = 0; t < n_kv_tiles; ++t) {
+                    if (seen[t] < 1.0f) continue;
+                    const int cols = t == n_kv_tiles - 1 ? a.g.lc - t * WG_KEYS : WG_KEYS;
+                    const long long k = n_runs * ((cols + keys - 1) / keys);
+                    const double x = keys == WG_KEYS ? (wide ? 3.0 + 1.8 * len * seen[t] : 2.0 + 1.35 * len * seen[t])
+                                                     : (wide ? 3.0 + 2.2 * ceil(len * seen[t] / 4.0) : 1.0 + 1.5 * ceil(len * seen[t] / 4.0));
+                    sum += x * (double)k;
+                    n += k;
+                    longest = x > longest ? x : longest;
+                }
+                return (keys == WG_KEYS ? 11.0 : 3.0) + (len < max_cnt || unused ? fill_us : 0.0) + (keys < WG_KEYS && len < max_cnt ? atomic_us * n_runs : 0.0) + hexi_makespan(sum, longest, n);
+            };
+            double best = estimate(run_len, WG_KEYS);
+            for (int len = max_cnt; len >= 1; --len) {
+                if (max_cnt % len != 0) continue;
+                const double t = estimate(len, 32);
+                if (t < best) { best = t; run_len = len; split_keys = true; }
+            }
+        }
+        HeadRuns runs;
+        const bool shared = hexi_build_head_runs(a.g.kv_of_q, a.g.nq, a.g.nkv, run_len, &runs);
         unsigned grid = 0;
-        const XcdSplit split = hexi_split_units(runs.n * n_kv_tiles, [&](int u) {
+        XcdSplit split;
+        if (!split_keys) split = hexi_split_units(runs.n * n_kv_tiles, [&](int u) {
             const int run = u / n_kv_tiles, t = u - run * n_kv_tiles;
             return (float)runs.len[run] * seen[t < n_known ? t : n_known - 1] + 20.0f;
         }, &grid);
         if ((shared || unused) && !a.accumulate) {
             const long long n = (long long)a.g.lc * a.g.nkv * a.g.d;
-            hipError_t e = hexi_launch_fill_f32(a.dk, n, 0.f, s);
-            if (e == hipSuccess) e = hexi_launch_fill_f32(a.dv, n, 0.f, s);
+            const hipError_t e = hexi_launch_zero2_f32(a.dk, a.dv, n, s);
             if (e != hipSuccess) return e;
         }
         if (a.g.d != 128 && a.g.d != 64) return hipErrorInvalidValue;
-        if (grid > 0) {
+        if (split_keys) {
+            const hipError_t e = hexi_launch_bwd_dkdv_split_bf16(a, runs, shared, s);
+            if (e != hipSuccess) return e;
+        } else if (grid > 0) {
             if (a.g.d == 128) {
                 if (shared) bwd_dkdv_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
                 else bwd_dkdv_bf16_kernel<128, false><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);

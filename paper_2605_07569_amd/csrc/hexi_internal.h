@@ -127,6 +127,15 @@ inline bool hexi_build_head_runs(const signed char* kv_of_q, int nq, int nkv, in
     return shared;
 }
 
+// Time of a launch of n units, one per CU at a time, that take `sum` in total and at most `longest` each: whole rounds
+// of the mean unit on 256 CUs (the launches start the longest units first), or the longest one.
+inline double hexi_makespan(double sum, double longest, long long n)
+{
+    if (n <= 0) return 0.0;
+    const double rounds = sum / (double)n * (double)((n + 255) / 256);
+    return rounds > longest ? rounds : longest;
+}
+
 // Forced number of q heads per dK/dV workgroup run (0: the launcher chooses); see hexi_set_dkdv_run_len().
 extern int hexi_dkdv_run_len;
 
@@ -136,11 +145,16 @@ hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s);      // dK/dV kernel, then the dQ kernel
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);
+// the same steps with 32 or 64 (`rows`) stationary rows per workgroup, for launches that do not fill the chip otherwise
+hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, int rows, hipStream_t s);
+hipError_t hexi_launch_bwd_dq_split_bf16(const BwdArgs& a, int rows, hipStream_t s);
+hipError_t hexi_launch_bwd_dkdv_split_bf16(const BwdArgs& a, const HeadRuns& runs, bool shared, hipStream_t s);
 hipError_t hexi_launch_merge(long long n_rows, int nq, int d, float* o_acc, float* lse_acc, const float* o_part,
                              const float* lse_part, void* o_final, int o_final_dtype, hipStream_t s);
 hipError_t hexi_launch_delta(long long lq, int nq, int d, const float* o, const void* d_o, int dtype,
                              long long stride_tok, long long stride_head, float* delta, hipStream_t s);
 hipError_t hexi_launch_fill_f32(float* p, long long n, float value, hipStream_t s);
+hipError_t hexi_launch_zero2_f32(float* p, float* q, long long n, hipStream_t s);     // both 16-byte aligned, n a multiple of 4
 // pack (x -> packed) or unpack (packed -> y, which has x's layout); host tables, validated by the caller
 hipError_t hexi_launch_a2a(bool pack, const void* x, void* packed, void* y, long long s, int n_heads_total, int row_bytes,
                            long long x_stride_bytes, int n_ranks, const int* heads_per_rank, const int* head_list, hipStream_t st);

@@ -148,3 +148,27 @@ hipError_t hexi_launch_fill_f32(float* p, long long n, float value, hipStream_t 
     fill_kernel<<<(unsigned)blocks, 256, 0, s>>>(p, n, value);
     return hipGetLastError();
 }
+
+namespace {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Two buffers of n4 16-byte pieces set to zero in one launch (dk and dv of a chunk): 4 pieces per thread.
+__global__ void __launch_bounds__(256) zero2_kernel(f32x4_t* __restrict__ p, f32x4_t* __restrict__ q, long long n4)
+{
+    f32x4_t* out = blockIdx.y ? q : p;
+    const long long i = (long long)blockIdx.x * 1024 + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i + 256 * u < n4) out[i + 256 * u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+}
+
+}  // namespace
+
+hipError_t hexi_launch_zero2_f32(float* p, float* q, long long n, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    const long long n4 = n / 4;
+    zero2_kernel<<<dim3((unsigned)((n4 + 1023) / 1024), 2), 256, 0, s>>>(reinterpret_cast<f32x4_t*>(p), reinterpret_cast<f32x4_t*>(q), n4);
+    return hipGetLastError();
+}

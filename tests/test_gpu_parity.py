@@ -467,3 +467,21 @@ def test_f32_workgroup_shapes(nq, nkv, lq, lc, d):
                                  flags=hexi.HEXI_ACCUMULATE)
         check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "f32")
         check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "f32")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 2, 31, 33), (3, 1, 32, 64), (2, 1, 95, 257), (24, 8, 500, 1000), (8, 1, 600, 600)])
+def test_bf16_split_workgroup_shapes(nq, nkv, lq, lc, d):
+    # lengths around the 32-row blocks of the kernels for small launches, fewer and more of them than a workgroup has
+    # wavefronts; the fourth size takes the 64-row workgroups of the forward and dQ kernels, the last one cuts its group of
+    # heads into runs that add their dk / dv.  The second chunk is diagonal and in two segments.
+    w = _custom(f"split_{nq}_{lq}_{lc}_{d}", "bf16", nq, nkv, d, lc + lq + 7, [(lc, lq // 2), (lc + lq // 2 + 7, lq - lq // 2)],
+                [[(0, lc)], [(lc, lq // 2 + 7), (lc + lq // 2 + 7, lq - lq // 2)]])
+    run, inputs, ref = _run_and_compare(w, seed=lq * 1000 + lc + d)
+    # dk / dv under HEXI_ACCUMULATE: the running value plus the gradient
+    for j, ch in enumerate(w.chunks):
+        dk, dv, dq = torch.full_like(run.dk[j], 0.5), torch.full_like(run.dv[j], -0.25), torch.zeros_like(run.dq)
+        hexi.hexi_attn_bwd_chunk(run.desc[j], w.q_segs, ch, run.q, run.k[j], run.v[j], None, run.d_o, run.lse, run.delta, dq, dk, dv,
+                                 flags=hexi.HEXI_ACCUMULATE)
+        check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "bf16")
+        check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "bf16")
