@@ -388,6 +388,10 @@ __global__ void __launch_bounds__(512) bwd_dkdv_bf16_kernel(const BwdArgs a, con
 
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
 {
+    const int dq_rows = a.want_dq ? hexi_bwd_dq_split_rows(a.g) : 0;
+    bool dq_done = !a.want_dq;
+    HeadRuns runs;
+    runs.n = 0;
     if (a.want_dkdv) {
         const int n_kv_tiles = (a.g.lc + WG_KEYS - 1) / WG_KEYS;
         // q heads per kv head, in head order
@@ -460,7 +464,6 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
                 if (t < best) { best = t; run_len = len; split_keys = true; }
             }
         }
-        HeadRuns runs;
         const bool shared = hexi_build_head_runs(a.g.kv_of_q, a.g.nq, a.g.nkv, run_len, &runs);
         unsigned grid = 0;
         XcdSplit split;
@@ -475,8 +478,9 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
         }
         if (a.g.d != 128 && a.g.d != 64) return hipErrorInvalidValue;
         if (split_keys) {
-            const hipError_t e = hexi_launch_bwd_dkdv_split_bf16(a, runs, shared, s);
+            const hipError_t e = hexi_launch_bwd_split_bf16(a, dq_rows, runs, shared, s);     // with the dQ, if that is split too
             if (e != hipSuccess) return e;
+            dq_done |= dq_rows > 0;
         } else if (grid > 0) {
             if (a.g.d == 128) {
                 if (shared) bwd_dkdv_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
@@ -489,5 +493,7 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return a.want_dq ? hexi_launch_bwd_dq_bf16(a, s) : hipSuccess;
+    if (dq_done) return hipSuccess;
+    runs.n = 0;
+    return dq_rows > 0 ? hexi_launch_bwd_split_bf16(a, dq_rows, runs, false, s) : hexi_launch_bwd_dq_bf16(a, s);
 }

@@ -665,13 +665,33 @@ __global__ void __launch_bounds__(512) bwd_dq_bf16_kernel(const BwdArgs a, const
     }
 }
 
+// Cost of the units of one head, longest q tile first: the key tiles its q tile streams, plus the prologue and epilogue (about
+// six tiles' worth); a unit that sees nothing of the chunk returns at once.  Returns the number of entries filled (longer
+// shards: the remaining tiles count like the last known one).
+int unit_costs(const AttnGeom& g, int n_q_tiles, float (&cost)[4096])
+{
+    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;
+    for (int p = 0; p < n_known; ++p) {
+        const int q_tile = n_q_tiles - 1 - p;
+        const int last_row = (q_tile * WG_ROWS + WG_ROWS < g.lq ? q_tile * WG_ROWS + WG_ROWS : g.lq) - 1;
+        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + TN - 1) / TN;
+        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
+    }
+    return n_known;
+}
+
+}  // namespace
+
 // Rows per workgroup of the split kernels (32 or 64) where they are expected to finish first, else 0: the forward
 // launcher's rule with this kernel's times.  Measured, head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 /
 // 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9; 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim
 // 64: 1024 x 1024 x 24 30 / 23 / 23; 4096 x 4096 x 24 199 / 193 / 214.
-int split_rows(const AttnGeom& g, int n_q_tiles, const float* cost)
+int hexi_bwd_dq_split_rows(const AttnGeom& g)
 {
+    const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
     if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;
+    float cost[4096];
+    unit_costs(g, n_q_tiles, cost);
     const bool wide = g.d == 128;
     struct Shape { double sum = 0, longest = 0; long long n = 0; void add(double t, long long k) { sum += t * k; n += k; longest = t > longest ? t : longest; } } b256, b64, b32;
     for (int p = 0; p < n_q_tiles; ++p) {
@@ -692,23 +712,12 @@ int split_rows(const AttnGeom& g, int n_q_tiles, const float* cost)
     return t64 < t32 ? 64 : 32;
 }
 
-}  // namespace
-
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
-    // cost of a unit: the key tiles its q tile streams, plus the prologue and epilogue (about six tiles' worth); a
-    // unit that sees nothing of the chunk returns at once
     float cost[4096];
-    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;     // (longer shards: the remaining tiles count like the last known one)
-    for (int p = 0; p < n_known; ++p) {
-        const int q_tile = n_q_tiles - 1 - p;
-        const int last_row = (q_tile * WG_ROWS + WG_ROWS < g.lq ? q_tile * WG_ROWS + WG_ROWS : g.lq) - 1;
-        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + TN - 1) / TN;
-        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
-    }
-    if (const int rows = split_rows(g, n_q_tiles, cost); rows > 0) return hexi_launch_bwd_dq_split_bf16(a, rows, s);
+    const int n_known = unit_costs(g, n_q_tiles, cost);
     unsigned grid = 0;
     const XcdSplit split = hexi_split_units(g.nq * n_q_tiles, [&](int u) { const int p = u % n_q_tiles; return cost[p < n_known ? p : n_known - 1]; }, &grid);
     if (grid == 0) return hipSuccess;

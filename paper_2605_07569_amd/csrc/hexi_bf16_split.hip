@@ -380,22 +380,22 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
 }
 
 // dQ: dP^T = V dO^T, S^T = K Q^T, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
+template <class C> union DqSmem {
+    unsigned char t[C::S][C::NBUF][2 * C::TILE_BYTES];     // K and V block of each split
+    float stage[C::STAGE_FLOATS];
+};
+
 template <int D, int R>
-__global__ void __launch_bounds__(512, D == 64 ? 4 : 2) bwd_dq_split_bf16_kernel(const BwdArgs a, const int n_q_tiles)
+__device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int q_tile, DqSmem<SplitCfg<D, R>>& sm)
 {
     using C = SplitCfg<D, R>;
     constexpr int S = C::S;
     const AttnGeom& g = a.g;
-    __shared__ __attribute__((aligned(1024))) union {
-        unsigned char t[S][C::NBUF][2 * C::TILE_BYTES];    // K and V block of each split
-        float stage[C::STAGE_FLOATS];
-    } sm;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rb = wave % R, sp = wave / R;
     const int l32 = lane & 31, hh = lane >> 5;
-    const int h = blockIdx.x;
-    const int wg_row0 = (n_q_tiles - 1 - (int)blockIdx.y) * C::ROWS, row0 = wg_row0 + TB * rb;
+    const int wg_row0 = q_tile * C::ROWS, row0 = wg_row0 + TB * rb;
     const int kvh = arg_byte(g.kv_of_q, h);
     const int my_row = row0 + l32;
     const int my_row_c = my_row < g.lq ? my_row : g.lq - 1;
@@ -513,24 +513,24 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) bwd_dq_split_bf16_kernel
 
 // dK / dV of 32 keys from the q rows of a run of heads: S = Q K^T, dP = dO V^T, dV += P^T dO, dK += dS^T Q.  The keys'
 // own K and V rows stay in LDS (dK and dV take 128 of a wavefront's 256 registers at D = 128).
+template <class C> union DkdvSmem {
+    struct {
+        unsigned char t[NW][2 * C::TILE_BYTES];            // Q and dO block of each wavefront
+        unsigned char kv[2 * C::TILE_BYTES];               // the workgroup's K and V rows
+        float lse[NW][64], delta[NW][64];                  // row scalars of each wavefront's block (32 used; a transfer writes 64)
+    } m;
+    float stage[C::STAGE_FLOATS];
+};
+
 template <int D, bool ATOMIC_DKV>
-__global__ void __launch_bounds__(512) bwd_dkdv_split_bf16_kernel(const BwdArgs a, const HeadRuns runs)
+__device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs, const int run, const int kv_tile, DkdvSmem<SplitCfg<D, 1>>& sm)
 {
     using C = SplitCfg<D, 1>;
     const AttnGeom& g = a.g;
-    __shared__ __attribute__((aligned(1024))) union {
-        struct {
-            unsigned char t[NW][2 * C::TILE_BYTES];        // Q and dO block of each wavefront
-            unsigned char kv[2 * C::TILE_BYTES];           // the workgroup's K and V rows
-            float lse[NW][64], delta[NW][64];              // row scalars of each wavefront's block (32 used; a transfer writes 64)
-        } m;
-        float stage[C::STAGE_FLOATS];
-    } sm;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hh = lane >> 5;
-    const int run = blockIdx.x;
-    const int col0 = (int)blockIdx.y * TB;      // the first keys, which the most rows see, first
+    const int col0 = kv_tile * TB;
     const int n_heads = arg_byte(runs.len, run);
     const int kvh = arg_byte(g.kv_of_q, arg_byte(runs.first, run));
     const int my_col = col0 + l32;
@@ -666,6 +666,22 @@ __global__ void __launch_bounds__(512) bwd_dkdv_split_bf16_kernel(const BwdArgs 
     write_out(a.dk, dk, g.scale);
 }
 
+// One launch for both halves of a backward step: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first), the
+// others dQ units of 32 R rows.  Within each, heads (runs) side by side and the longest tiles first.
+template <int D, int R, bool ATOMIC_DKV>
+__global__ void __launch_bounds__(512) bwd_split_bf16_kernel(const BwdArgs a, const HeadRuns runs, const unsigned n_dkdv, const int n_q_tiles)
+{
+    __shared__ __attribute__((aligned(1024))) union { DkdvSmem<SplitCfg<D, 1>> dkdv; DqSmem<SplitCfg<D, R>> dq; } sm;
+    if (blockIdx.x < n_dkdv) {
+        const int tile = uniform((int)(blockIdx.x / (unsigned)runs.n));
+        dkdv_unit<D, ATOMIC_DKV>(a, runs, (int)blockIdx.x - tile * runs.n, tile, sm.dkdv);
+    } else {
+        const unsigned unit = blockIdx.x - n_dkdv;
+        const int tile = uniform((int)(unit / (unsigned)a.g.nq));
+        dq_unit<D, R>(a, (int)unit - tile * a.g.nq, n_q_tiles - 1 - tile, sm.dq);
+    }
+}
+
 }  // namespace
 
 hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, int rows, hipStream_t s)
@@ -680,29 +696,20 @@ hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, int rows, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t hexi_launch_bwd_dq_split_bf16(const BwdArgs& a, int rows, hipStream_t s)
+// dq_rows: rows per dQ workgroup (32 or 64; 0: no dQ); runs: the head runs of the dK / dV workgroups (none: no dK / dV)
+hipError_t hexi_launch_bwd_split_bf16(const BwdArgs& a, int dq_rows, const HeadRuns& runs, bool shared, hipStream_t s)
 {
-    const int n_q_tiles = (a.g.lq + rows - 1) / rows;
-    const dim3 grid((unsigned)a.g.nq, (unsigned)n_q_tiles);
-    if (a.g.d == 128 && rows == 32) bwd_dq_split_bf16_kernel<128, 1><<<grid, 512, 0, s>>>(a, n_q_tiles);
-    else if (a.g.d == 128 && rows == 64) bwd_dq_split_bf16_kernel<128, 2><<<grid, 512, 0, s>>>(a, n_q_tiles);
-    else if (a.g.d == 64 && rows == 32) bwd_dq_split_bf16_kernel<64, 1><<<grid, 512, 0, s>>>(a, n_q_tiles);
-    else if (a.g.d == 64 && rows == 64) bwd_dq_split_bf16_kernel<64, 2><<<grid, 512, 0, s>>>(a, n_q_tiles);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t hexi_launch_bwd_dkdv_split_bf16(const BwdArgs& a, const HeadRuns& runs, bool shared, hipStream_t s)
-{
-    const dim3 grid((unsigned)runs.n, (unsigned)((a.g.lc + TB - 1) / TB));
-    if (a.g.d == 128) {
-        if (shared) bwd_dkdv_split_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs);
-        else bwd_dkdv_split_bf16_kernel<128, false><<<grid, 512, 0, s>>>(a, runs);
-    } else if (a.g.d == 64) {
-        if (shared) bwd_dkdv_split_bf16_kernel<64, true><<<grid, 512, 0, s>>>(a, runs);
-        else bwd_dkdv_split_bf16_kernel<64, false><<<grid, 512, 0, s>>>(a, runs);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const int n_q_tiles = dq_rows > 0 ? (a.g.lq + dq_rows - 1) / dq_rows : 0;
+    const unsigned n_dkdv = (unsigned)((a.g.lc + TB - 1) / TB) * (unsigned)runs.n;
+    const unsigned grid = n_dkdv + (unsigned)n_q_tiles * (unsigned)a.g.nq;
+    if (grid == 0) return hipSuccess;
+    auto launch = [&](auto d, auto r) {
+        constexpr int D = decltype(d)::value, R = decltype(r)::value;
+        if (shared) bwd_split_bf16_kernel<D, R, true><<<grid, 512, 0, s>>>(a, runs, n_dkdv, n_q_tiles);
+        else bwd_split_bf16_kernel<D, R, false><<<grid, 512, 0, s>>>(a, runs, n_dkdv, n_q_tiles);
+        return hipGetLastError();
+    };
+    if (a.g.d == 128) return dq_rows == 64 ? launch(IC<128>{}, IC<2>{}) : launch(IC<128>{}, IC<1>{});
+    if (a.g.d == 64) return dq_rows == 64 ? launch(IC<64>{}, IC<2>{}) : launch(IC<64>{}, IC<1>{});
+    return hipErrorInvalidValue;
 }
