@@ -160,14 +160,8 @@ template <class C, bool STREAM_FIRST> __device__ __forceinline__ void col_produc
     }
 }
 
-// Row fragments of a stationary row in registers: lane (row l32, half hh) holds columns 16 ks + 8 hh .. + 7.
-template <int NKS> __device__ __forceinline__ void load_frags(bf16x8 (&f)[NKS], const uint16_t* p)
-{
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) pin(f[ks]);       // complete before the first transfer into LDS is issued
-}
+// Keeps the compiler from turning the (wave-uniform) branch it stands in into selects that every block would execute.
+__device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
 // Entry i of a byte table in the kernel arguments, through an aligned 32-bit read (a byte read would go through the vector
 // memory path: it would hold up the first transfers by its latency, and wait for every transfer in flight in a loop).
@@ -178,6 +172,27 @@ __device__ __forceinline__ int arg_byte(const void* table, int i)
 static_assert(offsetof(AttnGeom, kv_of_q) % 4 == 0 && offsetof(HeadRuns, first) % 4 == 0 && offsetof(HeadRuns, next) % 4 == 0 &&
               offsetof(HeadRuns, len) % 4 == 0 && HEXI_MAX_HEADS % 4 == 0, "the tables are read in words");
 
+// seg_pos_of_row and seg_rows_le with the first two segments in a straight line: their table entries are then read together
+// at the start of the kernel, not one after the other (a table's unused row0 entries hold the total, so a second segment
+// that does not exist changes nothing).
+__device__ __forceinline__ int pos_of_row(const SegTable& t, int row)
+{
+    int p = row >= t.row0[1] ? t.start[1] + (row - t.row0[1]) : t.start[0] + row;
+    for (int s = 2; s < t.n; ++s)
+        if (row >= t.row0[s]) p = t.start[s] + (row - t.row0[s]);
+    return p;
+}
+__device__ __forceinline__ int rows_le(const SegTable& t, int p)
+{
+    auto in_seg = [&](int s) {
+        const int len = t.row0[s + 1] - t.row0[s], k = p - t.start[s] + 1;
+        return k < 0 ? 0 : (k > len ? len : k);
+    };
+    int c = in_seg(0) + in_seg(1);
+    for (int s = 2; s < t.n; ++s) c += in_seg(s);
+    return c;
+}
+
 // What the rows of a q tile see of the chunk (prefixes of its keys).
 struct Visible {
     int mine;       // keys the lane's row sees (0 for padding rows)
@@ -187,7 +202,7 @@ struct Visible {
     {
         // lanes 0..31 look up the wavefront's rows, the others the workgroup's last row
         const int row = hh == 0 ? (row0 + l32 < g.lq ? row0 + l32 : g.lq - 1) : wg_last_row;
-        const int n = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row));
+        const int n = rows_le(g.ks, pos_of_row(g.qs, row));
         n_all = __builtin_amdgcn_readlane(n, 32);
         n_full = row0 < g.lq ? __builtin_amdgcn_readlane(n, 0) / TB : 0;
         mine = __shfl(n, l32, 64);
@@ -235,16 +250,21 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
 #pragma unroll
     for (int ks = 0; ks < C::NKS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
 
-    const Visible vis(g, row0, (wg_row0 + C::ROWS < g.lq ? wg_row0 + C::ROWS : g.lq) - 1, l32, hh);
-    const int n_blocks = (vis.n_all + TB - 1) / TB;
-    if (n_blocks == 0 && a.accumulate) return;             // merging an empty partial is the identity
-
     const uint32_t lds = (uint32_t)(uintptr_t)(&sm.t[0][0][0]) + sp * C::NBUF * 2 * C::TILE_BYTES;
     const LaneAddr<C> la(lane, lds);
     const BlockFetch<C> fetch(lane, g.kv_stride_tok);
     // R = 1: the wavefront fetches K and V of its blocks; R = 2: one wavefront of a split K, the other V
     auto fetch_k = [&](int b, int buf) { if (R == 1 || rb == 0) fetch.issue(k, g.kv_stride_tok, b * TB, g.lc, lds + buf * 2 * C::TILE_BYTES); };
     auto fetch_v = [&](int b, int buf) { if (R == 1 || rb == 1) fetch.issue(v, g.kv_stride_tok, b * TB, g.lc, lds + buf * 2 * C::TILE_BYTES + C::TILE_BYTES); };
+
+    // the first block is asked for before it is known that some row sees it
+    if (sp * TB < g.lc) { fetch_k(sp, 0); fetch_v(sp, 0); }
+    const Visible vis(g, row0, (wg_row0 + C::ROWS < g.lq ? wg_row0 + C::ROWS : g.lq) - 1, l32, hh);
+    const int n_blocks = (vis.n_all + TB - 1) / TB;
+    if (n_blocks == 0 && a.accumulate) {                   // merging an empty partial is the identity
+        wait_transfers<0>();
+        return;
+    }
 
     f32x16 oacc[C::NDB];
 #pragma unroll
@@ -258,6 +278,7 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
     // probabilities of block b, rounded to bf16 operand slots
     auto softmax = [&](f32x16& s, int b, bf16x8 (&pf)[2]) __attribute__((always_inline)) {
         if (b >= vis.n_full) {
+            keep_branch();
             const int n = vis.mine - b * TB - 4 * hh;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
@@ -288,7 +309,6 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
         }
     };
 
-    if (sp < n_blocks) { fetch_k(sp, 0); fetch_v(sp, 0); }
 #pragma unroll
     for (int ks = 0; ks < C::NKS; ++ks) pin(qf[ks]);       // no wait for these inside the loop
     if constexpr (R == 1) {
@@ -308,18 +328,24 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
         }
     } else {
         const int n_steps = (n_blocks + S - 1) / S;        // the same for all wavefronts of the workgroup
-        for (int st = 0; st < n_steps; ++st) {
-            const int b = st * S + sp, buf = st & 1;
+        auto step = [&](auto bufc, int st) __attribute__((always_inline)) {
+            constexpr int buf = decltype(bufc)::value;
+            constexpr uint32_t tile = buf * 2 * C::TILE_BYTES;
+            const int b = st * S + sp;
             wait_transfers<0>();
             wg_barrier();                                  // the step's blocks have landed, and everyone is done with the other buffer
             if (b + S < n_blocks) { fetch_k(b + S, buf ^ 1); fetch_v(b + S, buf ^ 1); }
             if (b < n_blocks) {
-                f32x16 s = row_product<C>(la, buf * 2 * C::TILE_BYTES, [&](int ks) { return qf[ks]; });
+                f32x16 s = row_product<C>(la, tile, [&](int ks) { return qf[ks]; });
                 bf16x8 pf[2];
                 softmax(s, b, pf);
-                col_product<C, true>(oacc, la, buf * 2 * C::TILE_BYTES + C::TILE_BYTES, pf);
+                col_product<C, true>(oacc, la, tile + C::TILE_BYTES, pf);
             }
             reads_done();
+        };
+        for (int st = 0; st < n_steps; st += 2) {          // two steps at a time: the buffer is a compile-time offset of the reads
+            step(IC<0>{}, st);
+            if (st + 1 < n_steps) step(IC<1>{}, st + 1);
         }
     }
 
@@ -327,6 +353,7 @@ __global__ void __launch_bounds__(512, D == 64 ? 4 : 2) fwd_split_bf16_kernel(co
     // Wavefront s R + rb staged split s of row block rb: statistics of a row of the workgroup in split s at s ROWS + row.
     const float l_run = sum_across_halves((ps[0] + ps[1]) + (ps[2] + ps[3]));
     const float lr_run = sum_across_halves((psr[0] + psr[1]) + (psr[2] + psr[3]));
+    wait_transfers<0>();                               // (a first block that no row sees)
     __syncthreads();                                   // every wavefront is done with its blocks
     stage_transposed<C>(&sm.e.stage[wave * TB * C::PITCH], oacc, l32, hh, 1.0f);
     if (hh == 0) { sm.e.m[wave * TB + l32] = m_run; sm.e.l[wave * TB + l32] = l_run; sm.e.lr[wave * TB + l32] = lr_run; }
@@ -411,15 +438,19 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     const float lse = a.lse[(long long)h * g.lq + my_row_c];
     const float delta = a.delta[(long long)h * g.lq + my_row_c];
 
-    const Visible vis(g, row0, (wg_row0 + C::ROWS < g.lq ? wg_row0 + C::ROWS : g.lq) - 1, l32, hh);
-    const int n_blocks = (vis.n_all + TB - 1) / TB;
-    if (n_blocks == 0) return;                             // dq_acc unchanged
-
     const uint32_t lds = (uint32_t)(uintptr_t)(&sm.t[0][0][0]) + sp * C::NBUF * 2 * C::TILE_BYTES;
     const LaneAddr<C> la(lane, lds);
     const BlockFetch<C> fetch(lane, g.kv_stride_tok);
     auto fetch_k = [&](int b, int buf) { if (R == 1 || rb == 0) fetch.issue(k, g.kv_stride_tok, b * TB, g.lc, lds + buf * 2 * C::TILE_BYTES); };
     auto fetch_v = [&](int b, int buf) { if (R == 1 || rb == 1) fetch.issue(v, g.kv_stride_tok, b * TB, g.lc, lds + buf * 2 * C::TILE_BYTES + C::TILE_BYTES); };
+    if (sp * TB < g.lc) { fetch_v(sp, 0); fetch_k(sp, 0); }
+    const Visible vis(g, row0, (wg_row0 + C::ROWS < g.lq ? wg_row0 + C::ROWS : g.lq) - 1, l32, hh);
+    const int n_blocks = (vis.n_all + TB - 1) / TB;
+    if (n_blocks == 0) {                                   // dq_acc unchanged
+        wait_transfers<0>();
+        return;
+    }
+
     const float c_log2 = g.scale * LOG2E;
 
     f32x16 dq[C::NDB];
@@ -427,7 +458,6 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
-    if (sp < n_blocks) { fetch_v(sp, 0); fetch_k(sp, 0); }
 #pragma unroll
     for (int ks = 0; ks < C::NKS; ++ks) { pin(gf[ks]); pin(qf[ks]); }
     const float neg_l = -lse * LOG2E;
@@ -439,6 +469,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
 #pragma unroll
         for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(fmaf(s[r], c_log2, neg_l)) * (dp[r] - delta);
         if (b >= vis.n_full) {
+            keep_branch();
             const int n = vis.mine - b * TB - 4 * hh;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
@@ -483,9 +514,10 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
         }
     } else {
         const int n_steps = (n_blocks + S - 1) / S;
-        for (int st = 0; st < n_steps; ++st) {
-            const int b = st * S + sp, buf = st & 1;
-            const uint32_t tile = buf * 2 * C::TILE_BYTES;
+        auto step = [&](auto bufc, int st) __attribute__((always_inline)) {
+            constexpr int buf = decltype(bufc)::value;
+            constexpr uint32_t tile = buf * 2 * C::TILE_BYTES;
+            const int b = st * S + sp;
             wait_transfers<0>();
             wg_barrier();
             if (b + S < n_blocks) { fetch_v(b + S, buf ^ 1); fetch_k(b + S, buf ^ 1); }
@@ -495,8 +527,13 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
                 accumulate(s, dp, b, tile);
             }
             reads_done();
+        };
+        for (int st = 0; st < n_steps; st += 2) {
+            step(IC<0>{}, st);
+            if (st + 1 < n_steps) step(IC<1>{}, st + 1);
         }
     }
+    wait_transfers<0>();                                   // (a first block that no row sees)
     __syncthreads();
     stage_transposed<C>(&sm.stage[wave * TB * C::PITCH], dq, l32, hh, g.scale);
     __syncthreads();
@@ -512,7 +549,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
 }
 
 // dK / dV of 32 keys from the q rows of a run of heads: S = Q K^T, dP = dO V^T, dV += P^T dO, dK += dS^T Q.  The keys'
-// own K and V rows stay in LDS (dK and dV take 128 of a wavefront's 256 registers at D = 128).
+// own K and V rows stay in LDS at D = 128 (dK and dV take 128 of a wavefront's 256 registers there).
 template <class C> union DkdvSmem {
     struct {
         unsigned char t[NW][2 * C::TILE_BYTES];            // Q and dO block of each wavefront
@@ -534,12 +571,12 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs
     const int n_heads = arg_byte(runs.len, run);
     const int kvh = arg_byte(g.kv_of_q, arg_byte(runs.first, run));
     const int my_col = col0 + l32;
-    const int last_col = (col0 + TB < g.lc ? col0 + TB : g.lc) - 1;
     // the rows that see a key are a suffix of the shard: [my_first, lq); no row before row_first sees any of the keys,
     // all rows from row_full on see all of them
-    const int my_first = my_col < g.lc ? seg_rows_le(g.qs, seg_pos_of_row(g.ks, my_col) - 1) : 0x7fffffff;
-    const int row_first = uniform(seg_rows_le(g.qs, seg_pos_of_row(g.ks, col0) - 1));
-    const int row_full = uniform(col0 + TB <= g.lc ? seg_rows_le(g.qs, seg_pos_of_row(g.ks, last_col) - 1) : 0x7fffffff);
+    const int first = rows_le(g.qs, pos_of_row(g.ks, my_col < g.lc ? my_col : g.lc - 1) - 1);
+    const int my_first = my_col < g.lc ? first : 0x7fffffff;
+    const int row_first = __builtin_amdgcn_readlane(first, 0);
+    const int row_full = col0 + TB <= g.lc ? __builtin_amdgcn_readlane(first, TB - 1) : 0x7fffffff;
     const int blk0 = row_first / TB;
     const int n_all = row_first < g.lq ? (g.lq + TB - 1) / TB - blk0 : 0;      // blocks of one head
 
@@ -558,6 +595,10 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs
     uint32_t kv_row[C::NKS];
 #pragma unroll
     for (int ks = 0; ks < C::NKS; ++ks) kv_row[ks] = la.row[ks] - lds + lds_kv;
+    constexpr bool KV_REGS = D == 64;                      // the fragments of K and V fit the registers
+    bf16x8 kf[KV_REGS ? C::NKS : 1], vf[KV_REGS ? C::NKS : 1];
+    auto k_frag = [&](int ks) { if constexpr (KV_REGS) return kf[ks]; else return lds_b128(kv_row[ks]); };
+    auto v_frag = [&](int ks) { if constexpr (KV_REGS) return vf[ks]; else return lds_b128(kv_row[ks] + C::TILE_BYTES); };
 
     f32x16 dk[C::NDB], dv[C::NDB];
 #pragma unroll
@@ -591,6 +632,10 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
+    if constexpr (KV_REGS) {
+#pragma unroll
+        for (int ks = 0; ks < C::NKS; ++ks) { kf[ks] = lds_b128(kv_row[ks]); vf[ks] = lds_b128(kv_row[ks] + C::TILE_BYTES); }
+    }
     while (left > 0) {
         const int row = (blk0 + t) * TB;
         t += NW;
@@ -598,9 +643,9 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs
         const bool more = left > 0;
         const int next_row = (blk0 + t) * TB;
         wait_transfers<C::XFERS>();                    // dO, LSE and Delta have landed, Q may still be in flight
-        const f32x16 dp = row_product<C>(la, C::TILE_BYTES, [&](int ks) { return lds_b128(kv_row[ks] + C::TILE_BYTES); });
+        const f32x16 dp = row_product<C>(la, C::TILE_BYTES, v_frag);
         wait_transfers<0>();
-        const f32x16 s = row_product<C>(la, 0, [&](int ks) { return lds_b128(kv_row[ks]); });
+        const f32x16 s = row_product<C>(la, 0, k_frag);
         const bool masked = row < row_full || row + TB > g.lq;
         bf16x8 pf[2], df[2];
 #pragma unroll
@@ -612,13 +657,15 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const HeadRuns& runs
                 const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sm.m.lse[wave][r0]);
                 const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sm.m.delta[wave][r0]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int x = 4 * rb + e;
-                    p[x] = fast_exp2(fmaf(s[8 * u + x], scale_log2, l4[e] * -LOG2E));
-                    // (a row that sees nothing anywhere, LSE = -inf, is masked in every block)
-                    if (masked) p[x] = row + r0 + e >= my_first && row + r0 + e < g.lq ? p[x] : 0.f;
-                    ds[x] = p[x] * (dp[8 * u + x] - d4[e]);
+                for (int e = 0; e < 4; ++e) p[4 * rb + e] = fast_exp2(fmaf(s[8 * u + 4 * rb + e], scale_log2, l4[e] * -LOG2E));
+                if (masked) {      // (a row that sees nothing anywhere, LSE = -inf, is masked in every block)
+                    keep_branch();
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (row + r0 + e < my_first || row + r0 + e >= g.lq) p[4 * rb + e] = 0.f;
                 }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ds[4 * rb + e] = p[4 * rb + e] * (dp[8 * u + 4 * rb + e] - d4[e]);
             }
             pf[u] = pack_bf16x8(p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]);
             df[u] = pack_bf16x8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
