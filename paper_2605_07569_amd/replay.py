@@ -38,13 +38,14 @@ class ShardRun:
         self.desc = [hexi.desc_for(self.q, kc, w.scale, w.kv_of_q) for kc in self.k]
 
     def forward(self):
+        # the first chunk initialises the running (o, lse): merging it into (0, -inf) would give the same bits
         w = self.w
-        self.o.zero_()
-        self.lse.fill_(float("-inf"))
         for j, ch in enumerate(w.chunks):
-            if self.fused:
+            if self.fused or j == 0:
                 hexi.hexi_attn_fwd_chunk(self.desc[j], w.q_segs, ch, self.q, self.k[j], self.v[j], self.o, self.lse,
-                                         flags=hexi.HEXI_ACCUMULATE)
+                                         flags=hexi.HEXI_ACCUMULATE if j else 0)
+                if self.partials is not None and not self.fused:
+                    self.partials.append((self.o.clone(), self.lse.clone()))
             else:
                 hexi.hexi_attn_fwd_chunk(self.desc[j], w.q_segs, ch, self.q, self.k[j], self.v[j], self.o_part, self.lse_part)
                 if self.partials is not None:
