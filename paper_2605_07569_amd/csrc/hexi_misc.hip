@@ -1,14 +1,16 @@
 // HBM-bound elementwise kernels: two-term log-sum-exp merge, Delta = rowsum(dO * O), fill.
 #include "hexi_internal.h"
 #include <hip/hip_bf16.h>
+#include <type_traits>
 
 namespace {
 
-// One thread per 4 consecutive head_dim elements of one (row, head); this pass only reads the lse
-// arrays (merge_lse_kernel rewrites lse_acc afterwards, so no thread ever sees a replaced value).
+// One thread per 4 consecutive head_dim elements of one (row, head).  WITH_LSE: the head_dim / 4 threads of a (row, head) are
+// lanes of one wavefront (a power of two up to 64), all of which have read lse_acc before the first of them rewrites it.
+// Otherwise this pass only reads the lse arrays and merge_lse_kernel rewrites lse_acc afterwards.
 // o_*: [n_rows][nq][d] fp32, lse_*: [nq][n_rows].  Weights are formed as e_a/(e_a+e_b) with
 // e_x = exp(lse_x - max), which keeps them exact convex weights; -inf on one side is the identity.
-template <int OUT_MODE>  // 0: no o_final, 1: fp32 o_final, 2: bf16 o_final
+template <int OUT_MODE, bool WITH_LSE>  // 0: no o_final, 1: fp32 o_final, 2: bf16 o_final
 __global__ void __launch_bounds__(256) merge_kernel(long long n_vec, int nq, int d4, long long n_rows,
                                                     float* __restrict__ o_acc, float* __restrict__ lse_acc,
                                                     const float* __restrict__ o_part, const float* __restrict__ lse_part,
@@ -38,6 +40,8 @@ __global__ void __launch_bounds__(256) merge_kernel(long long n_vec, int nq, int
         r = make_float4(wa * oa.x + wb * ob.x, wa * oa.y + wb * ob.y, wa * oa.z + wb * ob.z, wa * oa.w + wb * ob.w);
     }
     { const nt_f32x4 r_v = {r.x, r.y, r.z, r.w}; __builtin_nontemporal_store(r_v, reinterpret_cast<nt_f32x4*>(o_acc) + idx); }
+    // m + log(e_a + e_b), as merge_lse_kernel forms it
+    if (WITH_LSE && c4 == 0) lse_acc[li] = (m == -INFINITY) ? -INFINITY : m + logf(expf(a - m) + expf(b - m));
     if (OUT_MODE == 1) reinterpret_cast<float4*>(o_final)[idx] = r;
     if (OUT_MODE == 2) {
         __hip_bfloat16 t[4] = {__float2bfloat16(r.x), __float2bfloat16(r.y), __float2bfloat16(r.z), __float2bfloat16(r.w)};
@@ -63,14 +67,17 @@ hipError_t hexi_launch_merge(long long n_rows, int nq, int d, float* o_acc, floa
     const int d4 = d / 4;
     const long long n_vec = n_rows * nq * d4;
     const unsigned grid = (unsigned)((n_vec + 255) / 256);
-    if (!o_final)
-        merge_kernel<0><<<grid, 256, 0, s>>>(n_vec, nq, d4, n_rows, o_acc, lse_acc, o_part, lse_part, nullptr);
-    else if (o_final_dtype == HEXI_F32)
-        merge_kernel<1><<<grid, 256, 0, s>>>(n_vec, nq, d4, n_rows, o_acc, lse_acc, o_part, lse_part, o_final);
-    else
-        merge_kernel<2><<<grid, 256, 0, s>>>(n_vec, nq, d4, n_rows, o_acc, lse_acc, o_part, lse_part, o_final);
+    const bool with_lse = d4 <= 64 && (d4 & (d4 - 1)) == 0;
+    auto launch = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        if (with_lse) merge_kernel<MODE, true><<<grid, 256, 0, s>>>(n_vec, nq, d4, n_rows, o_acc, lse_acc, o_part, lse_part, o_final);
+        else merge_kernel<MODE, false><<<grid, 256, 0, s>>>(n_vec, nq, d4, n_rows, o_acc, lse_acc, o_part, lse_part, o_final);
+    };
+    if (!o_final) launch(std::integral_constant<int, 0>{});
+    else if (o_final_dtype == HEXI_F32) launch(std::integral_constant<int, 1>{});
+    else launch(std::integral_constant<int, 2>{});
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || with_lse) return e;
     const long long n = n_rows * nq;
     merge_lse_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, lse_acc, lse_part);
     return hipGetLastError();
