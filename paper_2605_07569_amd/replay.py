@@ -35,29 +35,29 @@ class ShardRun:
             self.o_part = torch.empty_like(self.o)
             self.lse_part = torch.empty_like(self.lse)
         self.partials = [] if keep_partials else None
+        self.q_range = hexi.make_range(w.q_segs)[0]
+        self.kv_range = [hexi.make_range(ch)[0] for ch in w.chunks]
         self.desc = [hexi.desc_for(self.q, kc, w.scale, w.kv_of_q) for kc in self.k]
 
     def forward(self):
         # the first chunk initialises the running (o, lse): merging it into (0, -inf) would give the same bits
-        w = self.w
-        for j, ch in enumerate(w.chunks):
+        for j, kv in enumerate(self.kv_range):
             if self.fused or j == 0:
-                hexi.hexi_attn_fwd_chunk(self.desc[j], w.q_segs, ch, self.q, self.k[j], self.v[j], self.o, self.lse,
+                hexi.hexi_attn_fwd_chunk(self.desc[j], self.q_range, kv, self.q, self.k[j], self.v[j], self.o, self.lse,
                                          flags=hexi.HEXI_ACCUMULATE if j else 0)
                 if self.partials is not None and not self.fused:
                     self.partials.append((self.o.clone(), self.lse.clone()))
             else:
-                hexi.hexi_attn_fwd_chunk(self.desc[j], w.q_segs, ch, self.q, self.k[j], self.v[j], self.o_part, self.lse_part)
+                hexi.hexi_attn_fwd_chunk(self.desc[j], self.q_range, kv, self.q, self.k[j], self.v[j], self.o_part, self.lse_part)
                 if self.partials is not None:
                     self.partials.append((self.o_part.clone(), self.lse_part.clone()))
                 hexi.hexi_attn_merge_lse(self.o, self.lse, self.o_part, self.lse_part)
 
     def backward(self):
-        w = self.w
         self.dq.zero_()
-        for j, ch in enumerate(w.chunks):
+        for j, kv in enumerate(self.kv_range):
             flags = hexi.HEXI_COMPUTE_DELTA if j == 0 else 0
-            hexi.hexi_attn_bwd_chunk(self.desc[j], w.q_segs, ch, self.q, self.k[j], self.v[j], self.o, self.d_o,
+            hexi.hexi_attn_bwd_chunk(self.desc[j], self.q_range, kv, self.q, self.k[j], self.v[j], self.o, self.d_o,
                                      self.lse, self.delta, self.dq, self.dk[j], self.dv[j], flags=flags)
 
     def step(self):
