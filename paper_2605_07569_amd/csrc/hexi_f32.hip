@@ -1,7 +1,7 @@
 // fp32 path (no reduced precision anywhere): the contractions run on the fp32 matrix instruction
 // v_mfma_f32_16x16x4_f32, whose products and sums are ordinary fp32 fused multiply-adds at twice the rate of the
-// vector unit's.  Three kernels: forward, dQ (both q-stationary) and dK/dV (key-stationary; P is recomputed from the
-// saved global LSE in both backward kernels), none of which uses atomics, so every output has a fixed summation order.
+// vector unit's.  Forward, dQ (both q-stationary) and dK/dV (key-stationary, one kernel with dQ; P is recomputed from the
+// saved global LSE in both), none of which uses atomics, so every output has a fixed summation order.
 //
 // Shape of a workgroup.  A wavefront owns 16 stationary rows (q rows, or keys in the dK/dV kernel): their operand
 // fragments and output accumulators live in its registers.  The other operand's rows are streamed through LDS by
@@ -17,8 +17,8 @@
 // scores (4 per lane) is ~40 operations against 2048 cycles of MFMA (D = 128).  Measured, executed flops of a launch that
 // fills the chip (4096 rows x 4096 keys x 16 heads x 128, shared shape): forward 121, dQ 134, dK/dV 134 TFLOP/s.  The plain-FMA
 // kernels before these read both operands of every product from LDS element by element and put 64 x nq / nkv rows
-// in flight per workgroup: 3055 rows x 12011 keys, 6 / 2 heads, forward + backward 54.8 ms, now 3.24 ms; 1024 rows x 2048
-// keys, 4 heads of 64: 1486 us, now 133 us (bound there by launch latency and by 2 wavefronts per SIMD walking 8 blocks each).
+// in flight per workgroup: 3055 rows x 12011 keys, 6 / 2 heads, forward + backward 54.8 ms, now 2.77 ms; 1024 rows x 2048
+// keys, 4 heads of 64: 1486 us, now 113 us (bound there by launch latency and by 2 wavefronts per SIMD walking 8 blocks each).
 //
 // v_mfma_f32_16x16x4_f32 layout (lane = 16 g + l): A: row l, contraction slot g; B: column l, slot g; C: column l,
 // register r holds row 4 g + r.  The contraction index may be permuted as long as A and B agree:
@@ -370,24 +370,26 @@ __global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) fwd_f32_kernel(co
 }
 
 // dQ: S^T = K Q^T and dP^T = V dO^T per tile, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
+template <class C> struct DqSmem {
+    union {
+        struct { unsigned char k[C::NBUF][C::TILE_BYTES], v[C::NBUF][C::TILE_BYTES]; } t;
+        float stage[C::STAGE_FLOATS];
+    };
+    int kpos[2][C::TK];
+};
+
 template <int D, bool SPLIT>
-__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_dq_f32_kernel(const BwdArgs a, const int n_q_tiles)
+__device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int q_tile, DqSmem<F32Cfg<D, SPLIT>>& sm)
 {
     using C = F32Cfg<D, SPLIT>;
     constexpr int NW = C::NW, S = C::S, TK = C::TK, NBLK = C::NBLK;
     const AttnGeom& g = a.g;
-    __shared__ __attribute__((aligned(1024))) union {
-        struct { unsigned char k[C::NBUF][C::TILE_BYTES], v[C::NBUF][C::TILE_BYTES]; } t;
-        float stage[C::STAGE_FLOATS];
-    } sm;
-    __shared__ int kpos[2][TK];
+    auto& kpos = sm.kpos;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rb = wave % C::R, sp = wave / C::R;
     const int grp = lane >> 4, l16 = lane & 15;
-    const int h = blockIdx.x % g.nq;
-    const int q_tile = n_q_tiles - 1 - blockIdx.x / g.nq;
     const int kvh = g.kv_of_q[h];
     const int row0 = q_tile * C::ROWS;
     const int my_row = row0 + 16 * rb + l16;
@@ -474,26 +476,30 @@ __global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_dq_f32_kernel
 
 // dK / dV: the stationary rows are keys, the streamed rows q rows (of every q head that reads the kv head, one head
 // after the other): S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.
+template <class C> struct DkdvSmem {
+    union {
+        struct { unsigned char q[C::NBUF][C::TILE_BYTES], g[C::NBUF][C::TILE_BYTES]; } t;
+        float stage[C::STAGE_FLOATS];
+    };
+    __attribute__((aligned(16))) float lse[2][C::PRIVATE ? 64 * C::NW : 64], delta[2][C::PRIVATE ? 64 * C::NW : 64];
+    __attribute__((aligned(16))) int qpos[2][C::TK];
+};
+
 template <int D, bool SPLIT>
-__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_dkdv_f32_kernel(const BwdArgs a)
+__device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, DkdvSmem<F32Cfg<D, SPLIT>>& sm)
 {
     using C = F32Cfg<D, SPLIT>;
     constexpr int NW = C::NW, S = C::S, TM = C::TK, NBLK = C::NBLK;
     const AttnGeom& g = a.g;
-    __shared__ __attribute__((aligned(1024))) union {
-        struct { unsigned char q[C::NBUF][C::TILE_BYTES], g[C::NBUF][C::TILE_BYTES]; } t;
-        float stage[C::STAGE_FLOATS];
-    } sm;
     constexpr int SET = C::PRIVATE ? 64 : 0;      // row scalars: one set of 64 lanes per wavefront, or one for all
-    __shared__ __attribute__((aligned(16))) float lse[2][C::PRIVATE ? 64 * NW : 64], delta[2][C::PRIVATE ? 64 * NW : 64];
-    __shared__ __attribute__((aligned(16))) int qpos[2][TM];
+    auto &lse = sm.lse, &delta = sm.delta;
+    auto& qpos = sm.qpos;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rb = wave % C::R, sp = wave / C::R;
     const int grp = lane >> 4, l16 = lane & 15;
-    const int kvh = blockIdx.x % g.nkv;
-    const int col0 = (blockIdx.x / g.nkv) * C::ROWS;      // the first keys, which the most rows see, first
+    const int col0 = kv_tile * C::ROWS;
     const int my_col = col0 + 16 * rb + l16;
     const int my_col_c = my_col < g.lc ? my_col : g.lc - 1;
     const int my_kpos = my_col < g.lc ? seg_pos_of_row(g.ks, my_col) : 0x7fffffff;
@@ -603,6 +609,25 @@ __global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_dkdv_f32_kern
     write_out(a.dk, dk, g.scale);
 }
 
+// The backward step in one launch: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first), the others dQ units; heads
+// side by side, the longest tiles first.  As two launches, each left CUs idle at its end: 2600 keys of 2 kv heads are 324
+// workgroups of equal length, two rounds of 256 CUs with the second one a quarter full.  3055 rows x 12011 keys, 6 / 2 heads,
+// forward + backward: 3.24 -> 2.77 ms.
+template <int D, bool SPLIT>
+__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_f32_kernel(const BwdArgs a, const unsigned n_dkdv, const int n_q_tiles)
+{
+    using C = F32Cfg<D, SPLIT>;
+    __shared__ __attribute__((aligned(1024))) union { DkdvSmem<C> dkdv; DqSmem<C> dq; } sm;
+    if (blockIdx.x < n_dkdv) {
+        const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x / (unsigned)a.g.nkv);
+        dkdv_unit<D, SPLIT>(a, (int)blockIdx.x - tile * a.g.nkv, tile, sm.dkdv);
+    } else {
+        const unsigned unit = blockIdx.x - n_dkdv;
+        const int tile = __builtin_amdgcn_readfirstlane(unit / (unsigned)a.g.nq);
+        dq_unit<D, SPLIT>(a, (int)unit - tile * a.g.nq, n_q_tiles - 1 - tile, sm.dq);
+    }
+}
+
 // Which shape: the one with the shorter makespan on 256 CUs when all workgroups are equally long (shared: two share a
 // CU; split: one takes all of it), the split one being a little slower per row (measured on a launch that fills the chip
 // either way, 4096 x 4096 x 16 heads x 128: forward 109 against 120 TFLOP/s, dQ 130 / 132, dK/dV 125 / 132).
@@ -635,20 +660,19 @@ hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s)
 
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s)
 {
-    if (a.want_dkdv) {
-        hipError_t e = with_cfg(a.g.d, f32_split(a.g.lc, a.g.nkv), [&](auto d, auto split) {
-            constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(split)::value;
+    const bool kv_split = f32_split(a.g.lc, a.g.nkv), q_split = f32_split(a.g.lq, a.g.nq);
+    auto launch = [&](bool split, bool dkdv, bool dq) {
+        return with_cfg(a.g.d, split, [&](auto d, auto sp) {
+            constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(sp)::value;
             using C = F32Cfg<D, SPLIT>;
-            const int n_tiles = (a.g.lc + C::ROWS - 1) / C::ROWS;
-            bwd_dkdv_f32_kernel<D, SPLIT><<<(unsigned)(n_tiles * a.g.nkv), 64 * C::NW, 0, s>>>(a);
+            const int n_q_tiles = (a.g.lq + C::ROWS - 1) / C::ROWS;
+            const unsigned n_dkdv = dkdv ? (unsigned)((a.g.lc + C::ROWS - 1) / C::ROWS * a.g.nkv) : 0u;
+            const unsigned n_dq = dq ? (unsigned)(n_q_tiles * a.g.nq) : 0u;
+            bwd_f32_kernel<D, SPLIT><<<n_dkdv + n_dq, 64 * C::NW, 0, s>>>(a, n_dkdv, n_q_tiles);
         });
-        if (e != hipSuccess) return e;
-    }
-    if (!a.want_dq) return hipSuccess;
-    return with_cfg(a.g.d, f32_split(a.g.lq, a.g.nq), [&](auto d, auto split) {
-        constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(split)::value;
-        using C = F32Cfg<D, SPLIT>;
-        const int n_q_tiles = (a.g.lq + C::ROWS - 1) / C::ROWS;
-        bwd_dq_f32_kernel<D, SPLIT><<<(unsigned)(n_q_tiles * a.g.nq), 64 * C::NW, 0, s>>>(a, n_q_tiles);
-    });
+    };
+    if (a.want_dkdv && a.want_dq && kv_split == q_split) return launch(kv_split, true, true);
+    hipError_t e = a.want_dkdv ? launch(kv_split, true, false) : hipSuccess;
+    if (e == hipSuccess && a.want_dq) e = launch(q_split, false, true);
+    return e;
 }
