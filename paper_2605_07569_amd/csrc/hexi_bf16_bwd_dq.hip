@@ -682,34 +682,29 @@ int unit_costs(const AttnGeom& g, int n_q_tiles, float (&cost)[4096])
 
 }  // namespace
 
-// Rows per workgroup of the split kernels (32 or 64) where they are expected to finish first, else 0: the forward
-// launcher's rule with this kernel's times.  Measured, head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 /
-// 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9; 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim
-// 64: 1024 x 1024 x 24 30 / 23 / 23; 4096 x 4096 x 24 199 / 193 / 214.
-int hexi_bwd_dq_split_rows(const AttnGeom& g)
+// Fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads, like the forward launcher's estimates.  Measured,
+// head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 / 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9;
+// 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim 64: 1024 x 1024 x 24 30 / 23 / 23;
+// 2048 x 4096 x 24 112 / 116.
+bool hexi_bwd_dq_times(const AttnGeom& g, DqTimes* t)
 {
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
-    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;
+    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return false;     // four rounds of full-size units: their tail no longer matters
     float cost[4096];
     unit_costs(g, n_q_tiles, cost);
     const bool wide = g.d == 128;
-    struct Shape { double sum = 0, longest = 0; long long n = 0; void add(double t, long long k) { sum += t * k; n += k; longest = t > longest ? t : longest; } } b256, b64, b32;
+    UnitTimes b256;
     for (int p = 0; p < n_q_tiles; ++p) {
         const double nt = cost[p] - 6.0;
         if (nt < 1.0) continue;
         const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * WG_ROWS : WG_ROWS;
         b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
-        b64.add(wide ? 2.0 + 1.85 * ceil(nt / 2.0) : 1.0 + 0.98 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
-        b32.add(wide ? 2.0 + 2.1 * ceil(nt / 4.0) : 1.0 + 1.2 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
+        t->rows64.add(wide ? 2.0 + 1.85 * ceil(nt / 2.0) : 1.0 + 1.14 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
+        t->rows32.add(wide ? 2.0 + 2.1 * ceil(nt / 4.0) : 1.0 + 1.4 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
     }
-    if (b256.n == 0) return 0;
-    const double load = b256.sum / (256.0 * b256.longest);
-    const double busy = load < 1.0 ? load * load : 1.0;
-    const double per_tile = wide ? 1.8 + 0.7 * busy : 1.1 + 0.35 * busy;
-    const double t256 = (wide ? 11.0 : 7.0) + per_tile * hexi_makespan(b256.sum, b256.longest, b256.n);
-    const double t64 = 3.0 + hexi_makespan(b64.sum, b64.longest, b64.n), t32 = 3.0 + hexi_makespan(b32.sum, b32.longest, b32.n);
-    if (t256 <= t64 && t256 <= t32) return 0;
-    return t64 < t32 ? 64 : 32;
+    if (b256.n == 0) return true;
+    t->t256 = wide ? 11.0 + b256.makespan(1.8, 2.2) : 7.0 + b256.makespan(1.1, 1.45);
+    return true;
 }
 
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s)

@@ -480,7 +480,7 @@ int split_rows(const AttnGeom& g, int n_q_tiles, const float* cost)
 {
     if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;     // four rounds of full-size units: their tail no longer matters
     const bool wide = g.d == 128;
-    struct Shape { double sum = 0, longest = 0; long long n = 0; void add(double t, long long k) { sum += t * k; n += k; longest = t > longest ? t : longest; } } b256, b64, b32;
+    UnitTimes b256, b64, b32;
     for (int p = 0; p < n_q_tiles; ++p) {
         const double nt = cost[p] - 6.0;
         if (nt < 1.0) continue;                                                // sees nothing of the chunk
@@ -490,12 +490,8 @@ int split_rows(const AttnGeom& g, int n_q_tiles, const float* cost)
         b32.add(wide ? 2.0 + 1.8 * ceil(nt / 4.0) : 1.0 + 0.7 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
     }
     if (b256.n == 0) return 0;
-    // a full-size unit's time per tile grows with the share of the chip that is busy (clock and L2)
-    const double load = b256.sum / (256.0 * b256.longest);
-    const double busy = load < 1.0 ? load * load : 1.0;
-    const double per_tile = wide ? 1.39 + 0.65 * busy : 0.85 + 0.2 * busy;
-    const double t256 = (wide ? 7.0 : 6.0) + per_tile * hexi_makespan(b256.sum, b256.longest, b256.n);
-    const double t64 = 3.0 + hexi_makespan(b64.sum, b64.longest, b64.n), t32 = 3.0 + hexi_makespan(b32.sum, b32.longest, b32.n);
+    const double t256 = wide ? 7.0 + b256.makespan(1.39, 1.76) : 6.0 + b256.makespan(0.85, 1.05);
+    const double t64 = 3.0 + b64.makespan(), t32 = 3.0 + b32.makespan();
     if (t256 <= t64 && t256 <= t32) return 0;
     return t64 < t32 ? 64 : 32;
 }
