@@ -479,8 +479,8 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
 #pragma unroll
         for (int u = 0; u < 2; ++u) hi[u] = pack_bf16x8(ds[8 * u], ds[8 * u + 1], ds[8 * u + 2], ds[8 * u + 3], ds[8 * u + 4], ds[8 * u + 5], ds[8 * u + 6], ds[8 * u + 7]);
         col_product<C, true>(dq, la, tile, hi);
-        // Blocks with some |bf16(dS)| >= 2 (bit 14 of the pattern) also add the residuals dS - bf16(dS), as a second bf16
-        // operand: what is left of them is below 2^-17 |dS| (the large kernel adds them in fp32).
+        // Blocks with some |bf16(dS)| >= 2 (bit 14 of the pattern) also add the residuals dS - bf16(dS), as two more bf16
+        // operands: three bf16 hold 24 bits, so dS reaches the product unrounded (the large kernel adds them in fp32).
         uint32_t big = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -488,15 +488,17 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
             big |= w.x | w.y | w.z | w.w;
         }
         if (__any((big & 0x40004000u) != 0u)) {
-            bf16x8 lo[2];
+            bf16x8 part[2] = {hi[0], hi[1]};
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                float x[8];
+            for (int n = 0; n < 2; ++n) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = ds[8 * u + e] - (float)hi[u][e];
-                lo[u] = pack_bf16x8(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]);
+                for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ds[8 * u + e] -= (float)part[u][e];
+                    part[u] = pack_bf16x8(ds[8 * u], ds[8 * u + 1], ds[8 * u + 2], ds[8 * u + 3], ds[8 * u + 4], ds[8 * u + 5], ds[8 * u + 6], ds[8 * u + 7]);
+                }
+                col_product<C, true>(dq, la, tile, part);
             }
-            col_product<C, true>(dq, la, tile, lo);
         }
     };
     if constexpr (R == 1) {

@@ -485,3 +485,47 @@ def test_bf16_split_workgroup_shapes(nq, nkv, lq, lc, d):
                                  flags=hexi.HEXI_ACCUMULATE)
         check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "bf16")
         check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "bf16")
+
+
+def _exact_ds_case(lq, lc, nq, nkv, d, seed):
+    """Inputs whose every step is exact in fp32: Q = 0 and LSE = 0 make P = 1, Delta = 0, and dP is an integer of up to 24
+    bits (dO holds its bytes, V picks three of them; 16 columns apart, so that each is the only product of its matrix
+    instruction), so dS = dP; key j < d is the unit vector e_j: column j of dq is scale * dS_ij, with scale a power of two."""
+    g = torch.Generator().manual_seed(seed)
+    q = torch.zeros((lq, nq, d))
+    byte = torch.randint(0, 256, (lq, nq, 3, 3), generator=g).double()      # [..., byte, choice]
+    byte[..., 0, :] = byte[..., 0, :].clamp(min=1.0)
+    sign = (1 - 2 * torch.randint(0, 2, (lq, nq, 1, 1), generator=g)).double()
+    byte = byte * sign * torch.tensor([65536.0, 256.0, 1.0], dtype=torch.float64)[:, None]
+    d_o = torch.zeros((lq, nq, d), dtype=torch.float64)
+    for n in range(3):
+        d_o[..., 16 * n:16 * n + 3] = byte[..., n, :]
+    k, v = torch.zeros((lc, nkv, d)), torch.zeros((lc, nkv, d))
+    n = min(lc, d)
+    k[torch.arange(n), :, torch.arange(n)] = 1.0
+    for j in range(lc):
+        v[j, :, j % 3:48:16] = 1.0
+    q_segs = [(lc // 2, lq)]
+    visible = torch.arange(n)[None, :] <= torch.arange(lc // 2, lc // 2 + lq)[:, None]
+    want = torch.zeros((lq, nq, d), dtype=torch.float64)
+    want[..., :n] = 0.125 * byte.sum(2)[..., torch.arange(n) % 3] * visible[:, None, :]
+    b16 = lambda t: t.to(torch.bfloat16).to(DEV)
+    return b16(q), b16(d_o), b16(k), b16(v), q_segs, want
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lq,lc,nq,nkv", [(1, 1, 1, 1), (40, 100, 2, 1), (300, 700, 4, 2), (512, 1000, 24, 8), (300, 2100, 128, 8)])
+def test_large_ds_reaches_dq_unrounded(lq, lc, nq, nkv, d):
+    # a dS of 24 significant bits must come out of the dQ kernels bit for bit (a residual rounded to bf16 loses up to
+    # 2^-18 of it)
+    q, d_o, k, v, q_segs, want = _exact_ds_case(lq, lc, nq, nkv, d, lq + lc + d)
+    kv_segs = [(0, lc)]
+    lse, delta = torch.zeros((nq, lq), device=DEV), torch.zeros((nq, lq), device=DEV)
+    dq = torch.zeros((lq, nq, d), device=DEV)
+    print(f"\n  exact dS: {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
+    hexi.hexi_attn_bwd_chunk(hexi.desc_for(q, k, 0.125), q_segs, kv_segs, q, k, v, None, d_o, lse, delta, dq, None, None,
+                             flags=hexi.HEXI_SKIP_DKDV)
+    torch.cuda.synchronize()
+    got = dq.cpu().double()
+    wrong = int((got != want).sum())
+    assert wrong == 0, (wrong, float(((got - want).abs() / want.abs().clamp(min=1.0)).max()))
