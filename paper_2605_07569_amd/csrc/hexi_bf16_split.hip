@@ -460,7 +460,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < C::NKS; ++ks) { pin(gf[ks]); pin(qf[ks]); }
-    const float neg_l = -lse * LOG2E;
+    const float neg_l = lse == -INFINITY ? -INFINITY : -lse * LOG2E;       // a row whose LSE is infinite has P = 0
     asm volatile("" ::"v"(neg_l), "v"(delta));
 
     // dQ^T += K^T dS^T of block b, whose K image is at byte `tile`

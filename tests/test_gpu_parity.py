@@ -529,3 +529,50 @@ def test_large_ds_reaches_dq_unrounded(lq, lc, nq, nkv, d):
     got = dq.cpu().double()
     wrong = int((got != want).sum())
     assert wrong == 0, (wrong, float(((got - want).abs() / want.abs().clamp(min=1.0)).max()))
+
+
+def _bwd_reference(q, k, v, d_o, q_pos, kv_pos, lse, delta, scale, group):
+    """dq, dk, dv in float64 from the given LSE [nq, lq] and Delta; P = 0 where the LSE is infinite.  Heads h read kv head h // group."""
+    q, k, v, d_o = (t.double() for t in (q, k, v, d_o))
+    nkv = k.shape[1]
+    kk, vv = k.repeat_interleave(group, 1), v.repeat_interleave(group, 1)
+    s = torch.matmul(q.permute(1, 0, 2), kk.permute(1, 2, 0).contiguous()) * scale
+    dead = ~torch.isfinite(lse)
+    p = torch.exp(s - torch.where(dead, torch.zeros_like(lse), lse).double()[..., None])
+    p = torch.where(dead[..., None] | (kv_pos[None, None, :] > q_pos[None, :, None]), torch.zeros_like(p), p)
+    dp = torch.matmul(d_o.permute(1, 0, 2), vv.permute(1, 2, 0).contiguous())
+    ds = p * (dp - delta.double()[..., None])
+    dq = scale * torch.matmul(ds, kk.permute(1, 0, 2).contiguous()).permute(1, 0, 2)
+    per_kv = lambda t: t.permute(1, 0, 2).reshape(k.shape[0], nkv, group, -1).sum(2)
+    dk = scale * per_kv(torch.matmul(ds.transpose(1, 2).contiguous(), q.permute(1, 0, 2).contiguous()))
+    return dq, dk, per_kv(torch.matmul(p.transpose(1, 2).contiguous(), d_o.permute(1, 0, 2).contiguous()))
+
+
+def _infinite_lse_case(dtype, lq, lc, nq, nkv, d, dead):
+    """One chunk, every row of which sees keys; LSE is `dead` on a third of the rows, on whole and on partial row blocks."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(lq + 31 * lc + d)
+    rnd = lambda *s: torch.randn(s, generator=g).to(dt)
+    q, d_o, k, v = rnd(lq, nq, d), rnd(lq, nq, d), rnd(lc, nkv, d), rnd(lc, nkv, d)
+    q_pos, kv_pos = torch.arange(lc // 2, lc // 2 + lq), torch.arange(lc)
+    scale = d ** -0.5
+    s = torch.matmul(q.double().permute(1, 0, 2), k.double().repeat_interleave(nq // nkv, 1).permute(1, 2, 0).contiguous()) * scale
+    lse = torch.logsumexp(torch.where(kv_pos[None, None, :] > q_pos[None, :, None], torch.full_like(s, -float("inf")), s), 2).float()
+    delta = torch.randn((nq, lq), generator=g) * 0.1
+    lse[:, ::7] = dead
+    lse[:, lq // 2:lq // 2 + lq // 5 + 1] = dead
+    ref = _bwd_reference(q, k, v, d_o, q_pos, kv_pos, lse, delta, scale, nq // nkv)
+    dev = [t.to(DEV) for t in (q, k, v, d_o, lse, delta)]
+    return dev, [(lc // 2, lq)], [(0, lc)], scale, ref
+
+
+@pytest.mark.parametrize("dead", [-float("inf"), float("inf")])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (512, 1000, 24, 8, 128), (512, 1000, 24, 8, 64)])
+def test_bf16_dq_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
+    # a row switched off through its LSE contributes nothing, whether or not it sees keys
+    (q, k, v, d_o, lse, delta), qs, ks, scale, ref = _infinite_lse_case("bf16", lq, lc, nq, nkv, d, dead)
+    dq = torch.zeros((lq, nq, d), device=DEV)
+    print(f"\n  infinite LSE: bf16 {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
+    hexi.hexi_attn_bwd_chunk(hexi.desc_for(q, k, scale), qs, ks, q, k, v, None, d_o, lse, delta, dq, None, None, flags=hexi.HEXI_SKIP_DKDV)
+    check("dq", dq.cpu(), ref[0], "bf16")
+    assert torch.all(dq.permute(1, 0, 2)[~torch.isfinite(lse)] == 0)
