@@ -53,6 +53,14 @@ __device__ __forceinline__ float sum_over_groups(float x)
     return sum_across_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
+// -LSE * log2(e) as two floats.  A row whose LSE is infinite (one that sees nothing anywhere, or that is switched off) has P = 0.
+__device__ __forceinline__ void neg_lse_log2(float l, float& hi, float& lo)
+{
+    const bool live = fabsf(l) != INFINITY;
+    hi = live ? -l * LOG2E_HI : -INFINITY;
+    lo = live ? fmaf(-l, LOG2E_HI, -hi) - l * LOG2E_LO : 0.f;
+}
+
 template <int D_, bool SPLIT> struct F32Cfg {
     static constexpr int D = D_;
     static_assert(D == 64 || D == 128, "head_dim 64 or 128");
@@ -410,10 +418,8 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     load_rows(qf, static_cast<const float*>(a.q) + q_off, grp);
     load_rows(gf, static_cast<const float*>(a.d_o) + q_off, grp);
     const float c_hi = g.scale * LOG2E_HI, c_lo = fmaf(g.scale, LOG2E_HI, -c_hi) + g.scale * LOG2E_LO;
-    // -LSE * log2(e) as two floats; padding rows and rows that see nothing anywhere (LSE = -inf): P = 0
-    const bool live = my_row < g.lq && l != -INFINITY;
-    const float nl_hi = live ? -l * LOG2E_HI : -INFINITY;
-    const float nl_lo = live ? fmaf(-l, LOG2E_HI, -nl_hi) - l * LOG2E_LO : 0.f;
+    float nl_hi, nl_lo;
+    neg_lse_log2(l, nl_hi, nl_lo);
 
     const LaneAddr<C> la(grp, l16);
     const TileFetch<C> fetch(wave, lane, g.kv_stride_tok);
@@ -545,8 +551,7 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const
         for (int h = next_head(-1); h < g.nq;) {
             tile_landed<C>();
             if (C::NBUF == 2 && fetch_h < g.nq) fetch_tile(buf ^ 1);
-            // (the last tile may hold padding rows, whose position is -1; a row that sees nothing anywhere, LSE = -inf,
-            // is masked in every tile, so what its P evaluates to does not matter)
+            // (the last tile may hold padding rows, whose position is -1)
             const bool masked = t * TM < row_full || key_ragged || t == n_qtiles - 1;
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
@@ -568,9 +573,9 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const
                 f32x4 p, ds;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float nl = -l4[r] * LOG2E_HI;
-                    const float nl_lo = fmaf(-l4[r], LOG2E_HI, -nl) - l4[r] * LOG2E_LO;
-                    p[r] = fast_exp2(fmaf(sd[0][r], c_hi, nl) + fmaf(sd[0][r], c_lo, nl_lo));
+                    float nl_hi, nl_lo;
+                    neg_lse_log2(l4[r], nl_hi, nl_lo);
+                    p[r] = fast_exp2(fmaf(sd[0][r], c_hi, nl_hi) + fmaf(sd[0][r], c_lo, nl_lo));
                 }
                 if (masked) {
                     const int4 q4 = *reinterpret_cast<const int4*>(&qpos[buf][16 * blk + 4 * grp]);

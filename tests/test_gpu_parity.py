@@ -576,3 +576,16 @@ def test_bf16_dq_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
     hexi.hexi_attn_bwd_chunk(hexi.desc_for(q, k, scale), qs, ks, q, k, v, None, d_o, lse, delta, dq, None, None, flags=hexi.HEXI_SKIP_DKDV)
     check("dq", dq.cpu(), ref[0], "bf16")
     assert torch.all(dq.permute(1, 0, 2)[~torch.isfinite(lse)] == 0)
+
+
+@pytest.mark.parametrize("dead", [-float("inf"), float("inf")])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)])
+def test_f32_backward_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
+    # the same in fp32, in both workgroup shapes, dk and dv included
+    (q, k, v, d_o, lse, delta), qs, ks, scale, ref = _infinite_lse_case("f32", lq, lc, nq, nkv, d, dead)
+    dq, dk, dv = torch.zeros((lq, nq, d), device=DEV), torch.empty((lc, nkv, d), device=DEV), torch.empty((lc, nkv, d), device=DEV)
+    print(f"\n  infinite LSE: f32 {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
+    hexi.hexi_attn_bwd_chunk(hexi.desc_for(q, k, scale), qs, ks, q, k, v, None, d_o, lse, delta, dq, dk, dv)
+    for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
+        check(name, got.cpu(), want, "f32")
+    assert torch.all(dq.permute(1, 0, 2)[~torch.isfinite(lse)] == 0)
