@@ -61,6 +61,13 @@ __device__ __forceinline__ void neg_lse_log2(float l, float& hi, float& lo)
     lo = live ? fmaf(-l, LOG2E_HI, -hi) - l * LOG2E_LO : 0.f;
 }
 
+// P of a score: 2^(s (c_hi + c_lo) + nl_hi + nl_lo).  The low product takes a finite score: one that overflowed to -inf has
+// P = 0, also where c_lo is negative or zero (inf - inf, 0 x inf).
+__device__ __forceinline__ float prob(float s, float c_hi, float c_lo, float nl_hi, float nl_lo)
+{
+    return fast_exp2(fmaf(s, c_hi, nl_hi) + fmaf(max2(s, -3.402823466e38f), c_lo, nl_lo));
+}
+
 template <int D_, bool SPLIT> struct F32Cfg {
     static constexpr int D = D_;
     static_assert(D == 64 || D == 128, "head_dim 64 or 128");
@@ -457,7 +464,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
             f32x4 ds;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = fast_exp2(fmaf(sd[0][r], c_hi, nl_hi) + fmaf(sd[0][r], c_lo, nl_lo));
+                const float p = prob(sd[0][r], c_hi, c_lo, nl_hi, nl_lo);
                 ds[r] = pv[r] > my_pos ? 0.f : p * (sd[1][r] - delta);
             }
             f32x4 (*const accs[1])[4 * C::NH] = {&acc};
@@ -575,7 +582,7 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const
                 for (int r = 0; r < 4; ++r) {
                     float nl_hi, nl_lo;
                     neg_lse_log2(l4[r], nl_hi, nl_lo);
-                    p[r] = fast_exp2(fmaf(sd[0][r], c_hi, nl_hi) + fmaf(sd[0][r], c_lo, nl_lo));
+                    p[r] = prob(sd[0][r], c_hi, c_lo, nl_hi, nl_lo);
                 }
                 if (masked) {
                     const int4 q4 = *reinterpret_cast<const int4*>(&qpos[buf][16 * blk + 4 * grp]);

@@ -589,3 +589,37 @@ def test_f32_backward_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
     for name, got, want in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
         check(name, got.cpu(), want, "f32")
     assert torch.all(dq.permute(1, 0, 2)[~torch.isfinite(lse)] == 0)
+
+
+@pytest.mark.parametrize("scale", [64 ** -0.5, 128 ** -0.5, 0.1, 0.05, 1.0])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)])
+def test_f32_scores_that_overflow_downwards(lq, lc, nq, nkv, d, scale):
+    # every seventh key's score is -1e40, i.e. -inf in fp32: the key weighs nothing, forward and backward, whatever the sign of
+    # the low half of scale * log2(e)
+    g = torch.Generator().manual_seed(lq + d)
+    q, d_o = torch.randn((lq, nq, d), generator=g), torch.randn((lq, nq, d), generator=g)
+    k, v = torch.randn((lc, nkv, d), generator=g), torch.randn((lc, nkv, d), generator=g)
+    q[..., 0] = 1e20
+    k[..., 0] = 0.0
+    k[3::7, :, 0] = -1e20
+    qs, ks = [(lc // 2, lq)], [(0, lc)]
+    run = {n: t.to(DEV) for n, t in dict(q=q, k=k, v=v, d_o=d_o).items()}
+    o, lse, delta = torch.empty((lq, nq, d), device=DEV), torch.empty((nq, lq), device=DEV), torch.empty((nq, lq), device=DEV)
+    dq, dk, dv = torch.zeros((lq, nq, d), device=DEV), torch.empty((lc, nkv, d), device=DEV), torch.empty((lc, nkv, d), device=DEV)
+    desc = hexi.desc_for(run["q"], run["k"], scale)
+    hexi.hexi_attn_fwd_chunk(desc, qs, ks, run["q"], run["k"], run["v"], o, lse)
+    hexi.hexi_attn_bwd_chunk(desc, qs, ks, run["q"], run["k"], run["v"], o, run["d_o"], lse, delta, dq, dk, dv, flags=hexi.HEXI_COMPUTE_DELTA)
+    got = [t.cpu() for t in (o, lse, dq, dk, dv)]
+    # the reference: without those keys (Q's first column meets zeros only)
+    keep = torch.tensor([j for j in range(lc) if j % 7 != 3])
+    s32 = float(np.float32(scale))
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc // 2, lc // 2 + lq), to64(k[keep]), to64(v[keep]), keep.numpy(), s32)
+    ref = oracle.attn_bwd(to64(q), np.arange(lc // 2, lc // 2 + lq), to64(k[keep]), to64(v[keep]), keep.numpy(), to64(d_o), s32)
+    check("o", got[0], o_ref, "f32")
+    check("lse", got[1], lse_ref, "f32")
+    check("dq", got[2], ref["dq"], "f32")
+    # (column 0 of dk holds sums of 1e20-sized terms; the others are ordinary)
+    check("dk", got[3][keep][..., 1:], ref["dk"][..., 1:], "f32")
+    check("dv", got[4][keep], ref["dv"], "f32")
+    drop = torch.tensor([j for j in range(lc) if j % 7 == 3])
+    assert torch.all(got[3][drop] == 0) and torch.all(got[4][drop] == 0)
