@@ -1,7 +1,7 @@
 // fp32 path (no reduced precision anywhere): the contractions run on the fp32 matrix instruction
 // v_mfma_f32_16x16x4_f32, whose products and sums are ordinary fp32 fused multiply-adds at twice the rate of the
 // vector unit's.  Forward, dQ (both q-stationary) and dK/dV (key-stationary, one kernel with dQ; P is recomputed from the
-// saved global LSE in both), none of which uses atomics, so every output has a fixed summation order.
+// saved global LSE in both).  No sum is spread over workgroups, so every output has a fixed summation order.
 //
 // Shape of a workgroup.  A wavefront owns 16 stationary rows (q rows, or keys in the dK/dV kernel): their operand
 // fragments and output accumulators live in its registers.  The other operand's rows are streamed through LDS by
@@ -476,14 +476,15 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     __syncthreads();
     stage_rows<C>(&sm.stage[wave * 16 * C::PITCH], acc, grp, l16, g.scale);
     __syncthreads();
-    for (int i = tid; i < C::ROWS * C::PIECES; i += 64 * NW) {
-        const int r = i / C::PIECES, c = 4 * (i % C::PIECES);
+    // Added with atomics, consecutive lanes on consecutive floats: chunks of one shard may be in flight on several streams.
+    // One addition per element and call, so calls in stream order still have a fixed order.
+    for (int i = tid; i < C::ROWS * D; i += 64 * NW) {
+        const int r = i / D, c = i % D;
         if (row0 + r >= g.lq) continue;
-        f32x4 x = *reinterpret_cast<const f32x4*>(&sm.stage[r * C::PITCH + c]);
+        float x = sm.stage[r * C::PITCH + c];
 #pragma unroll
-        for (int s = 1; s < S; ++s) x += *reinterpret_cast<const f32x4*>(&sm.stage[(s * C::ROWS + r) * C::PITCH + c]);
-        f32x4* op = reinterpret_cast<f32x4*>(a.dq + ((long long)(row0 + r) * g.nq + h) * D + c);
-        *op += x;
+        for (int s = 1; s < S; ++s) x += sm.stage[(s * C::ROWS + r) * C::PITCH + c];
+        global_atomic_add(a.dq + ((long long)(row0 + r) * g.nq + h) * D + c, x);
     }
 }
 

@@ -623,3 +623,20 @@ def test_f32_scores_that_overflow_downwards(lq, lc, nq, nkv, d, scale):
     check("dv", got[4][keep], ref["dv"], "f32")
     drop = torch.tensor([j for j in range(lc) if j % 7 == 3])
     assert torch.all(got[3][drop] == 0) and torch.all(got[4][drop] == 0)
+
+
+@pytest.mark.parametrize("nq,nkv,lq,d", [(4, 2, 200, 128), (4, 4, 333, 64), (16, 16, 1000, 64)])
+def test_f32_dq_of_chunks_on_two_streams(nq, nkv, lq, d):
+    # chunks of one shard may add to the same dq from several streams in fp32, in both workgroup shapes
+    n_chunks, lc = 8, 150
+    w = _custom(f"streams_{nq}_{lq}_{d}", "f32", nq, nkv, d, n_chunks * lc + lq, [(n_chunks * lc, lq)],
+                [[(j * lc, lc)] for j in range(n_chunks)] + [[(n_chunks * lc, lq)]])
+    run, inputs, ref = _run_and_compare(w, seed=lq + d)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    run.dq.zero_()
+    torch.cuda.synchronize()
+    for j, ch in enumerate(w.chunks):
+        hexi.hexi_attn_bwd_chunk(run.desc[j], w.q_segs, ch, run.q, run.k[j], run.v[j], None, run.d_o, run.lse, run.delta, run.dq,
+                                 run.dk[j], run.dv[j], stream=streams[j % 2].cuda_stream)
+    torch.cuda.synchronize()
+    check("dq", run.dq.cpu(), ref["dq"], "f32")
