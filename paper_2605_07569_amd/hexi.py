@@ -110,8 +110,8 @@ def _check(rc):
 
 
 def make_range(segs: Sequence[Tuple[int, int]]):
-    """[(start, len), ...] -> (hexi_range, keepalive).  A hexi_range made here is passed through: the calls below take one in
-    the place of a segment list (building it is most of a small call's host time: 3.5 us of about 11)."""
+    """[(start, len), ...] -> (hexi_range, keepalive).  A hexi_range made here is passed through: the calls below that take a
+    segment list take one in its place (building it is most of a small call's host time: 3.5 us of about 11)."""
     if isinstance(segs, hexi_range):
         return segs, segs
     arr = (hexi_seg * max(1, len(segs)))(*[(int(s), int(n)) for s, n in segs])
@@ -166,7 +166,7 @@ def hexi_shard_mask(q_segs, kv_segs, tile_m=0, tile_n=0, want_pos=True, want_cla
     lib = load()
     qr, _k1 = make_range(q_segs)
     kr, _k2 = make_range(kv_segs)
-    lq, lc = sum(int(n) for _, n in q_segs), sum(int(n) for _, n in kv_segs)
+    lq, lc = (sum(r.segs[i].len for i in range(r.n_segs)) for r in (qr, kr))
     q_pos = np.empty(max(lq, 0), dtype=np.int32) if want_pos else None
     kv_pos = np.empty(max(lc, 0), dtype=np.int32) if want_pos else None
     cls = None

@@ -98,6 +98,14 @@ def test_shard_mask_unaligned_and_degenerate():
         assert r["n_pairs"] == n and np.array_equal(r["tile_class"], cls)
 
 
+def test_shard_mask_takes_prepared_ranges():
+    qs, ks = [(37, 1), (100, 130)], [(0, 77), (90, 50)]
+    want = hexi.hexi_shard_mask(qs, ks, 16, 8)
+    got = hexi.hexi_shard_mask(hexi.make_range(qs)[0], hexi.make_range(ks)[0], 16, 8)
+    assert got["n_pairs"] == want["n_pairs"]
+    assert all(np.array_equal(got[n], want[n]) for n in ("q_pos", "kv_pos", "tile_class"))
+
+
 def test_range_validation_errors():
     for bad in ([], [(0, 0)], [(-1, 4)], [(10, 5), (12, 3)], [(10, 5), (2, 3)], [(0, 1)] * 17):
         with pytest.raises(hexi.HexiError) as e:
