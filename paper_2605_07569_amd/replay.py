@@ -41,6 +41,9 @@ class ShardRun:
 
     def forward(self):
         # the first chunk initialises the running (o, lse): merging it into (0, -inf) would give the same bits
+        if not self.kv_range:
+            self.o.zero_()
+            self.lse.fill_(float("-inf"))
         for j, kv in enumerate(self.kv_range):
             if self.fused or j == 0:
                 hexi.hexi_attn_fwd_chunk(self.desc[j], self.q_range, kv, self.q, self.k[j], self.v[j], self.o, self.lse,

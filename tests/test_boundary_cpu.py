@@ -106,6 +106,16 @@ def test_shard_mask_takes_prepared_ranges():
     assert all(np.array_equal(got[n], want[n]) for n in ("q_pos", "kv_pos", "tile_class"))
 
 
+def test_replay_without_chunks_gives_the_empty_result():
+    import torch
+    from paper_2605_07569_amd import replay
+    w = wl.Workload("none", "f32", 2, 1, 64, 16, [(0, 8)], [])
+    run = replay.ShardRun(w, wl.make_inputs(w), "cpu")
+    run.o.fill_(3.0); run.lse.fill_(3.0); run.dq.fill_(3.0)
+    run.step()
+    assert torch.all(run.o == 0) and torch.all(run.lse == float("-inf")) and torch.all(run.dq == 0)
+
+
 def test_range_validation_errors():
     for bad in ([], [(0, 0)], [(-1, 4)], [(10, 5), (12, 3)], [(10, 5), (2, 3)], [(0, 1)] * 17):
         with pytest.raises(hexi.HexiError) as e:
