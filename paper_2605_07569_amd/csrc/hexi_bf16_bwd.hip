@@ -30,14 +30,14 @@
 // run).  When a kv head has a single run its tiles are written with plain stores; otherwise the runs add theirs
 // with fp32 atomics, and dk/dv must be zero-filled (or hold the running sum under HEXI_ACCUMULATE) before the
 // launch.  The host picks the run length: as long as possible while the launch still has a few workgroups per CU.
-#include <cmath>
 #include "hexi_internal.h"
+#include "hexi_shapes.h"
 #include "hexi_mfma.h"
 
 namespace {
 
-constexpr int WG_KEYS = 128;     // keys per workgroup: 2 groups x 2 pairs x 32
-constexpr int TM = 64;           // q rows per tile
+constexpr int WG_KEYS = hexi_shapes::KV_TILE;     // keys per workgroup: 2 groups x 2 pairs x 32
+constexpr int TM = hexi_shapes::Q_STREAM_TILE;     // q rows per tile
 constexpr int NB = 3;            // LDS buffers per tensor
 constexpr float LOG2E = 1.4426950408889634f;
 
@@ -388,137 +388,40 @@ __global__ void __launch_bounds__(512) bwd_dkdv_bf16_kernel(const BwdArgs a, con
 
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
 {
-    // The shapes of both halves are chosen for the whole step, whichever of them this call runs: a half gives the same bits
-    // alone and with the other.
-    // dQ: rows per split workgroup, or 0 for the 256-row ones; by itself, the shape that is expected to finish first
-    DqTimes dqt;
-    int dq_rows = 0;
-    double dq_us = 0.0;
-    const bool dq_small = hexi_bwd_dq_times(a.g, &dqt);
-    if (dq_small) {
-        const double t64 = 3.0 + dqt.rows64.makespan(), t32 = 3.0 + dqt.rows32.makespan();
-        dq_us = dqt.t256;
-        if (t64 < dq_us) { dq_us = t64; dq_rows = 64; }
-        if (t32 < dq_us) { dq_us = t32; dq_rows = 32; }
-    }
+    BwdPlan plan;
+    hexi_plan_bwd(a.g, hexi_dkdv_run_len, &plan);
+    const int dq_rows = plan.dq_rows, n_kv_tiles = plan.n_kv_tiles;
     bool dq_done = !a.want_dq;
     HeadRuns runs;
-    runs.n = 0;
-    {
-        const int n_kv_tiles = (a.g.lc + WG_KEYS - 1) / WG_KEYS;
-        // q heads per kv head, in head order
-        int cnt[HEXI_MAX_HEADS] = {0};
-        int max_cnt = 0;
-        bool unused = false;
-        for (int h = 0; h < a.g.nq; ++h) {
-            const int c = ++cnt[a.g.kv_of_q[h]];
-            max_cnt = c > max_cnt ? c : max_cnt;
-        }
-        for (int kh = 0; kh < a.g.nkv; ++kh) unused |= (cnt[kh] == 0);   // a kv head no local q head reads: zero gradient
-        // Run length: the longest divisor of the largest group's size (so that its runs are equally long) for which
-        // the launch still has about three workgroups per CU and a workgroup walks at most 512 q tiles.  A run
-        // amortises the workgroup's prologue and epilogue (about 20 tiles' worth) and, when it covers the whole
-        // group, needs no atomics; but the workgroups of an XCD stream the same Q / dO tiles only while they stay
-        // in step, and long tile sequences let them drift apart (measured: more L2 misses, slower launches).
-        auto n_runs_for = [&](int len) {
-            int n = 0;
-            for (int kh = 0; kh < a.g.nkv; ++kh) n += (cnt[kh] + len - 1) / len;
-            return n;
-        };
-        // q tiles that see the chunk's first key: the longest tile sequence of one head
-        const int n_qtiles = (a.g.lq + TM - 1) / TM;
-        const int max_tiles = a.g.lc > 0 ? n_qtiles - seg_rows_le(a.g.qs, seg_pos_of_row(a.g.ks, 0) - 1) / TM : 0;
-        int run_len = max_cnt;
-        while (run_len > 1 && (max_cnt % run_len != 0 || (long long)run_len * max_tiles > 512 ||
-                               (long long)n_runs_for(run_len) * n_kv_tiles < 3 * 256))
-            --run_len;
-        if (const int forced = hexi_dkdv_run_len; forced >= 1)      // tuning / test override of the heuristic
-            run_len = forced < max_cnt ? forced : max_cnt;
-        // cost of a unit: the q tiles its key tile sees, once per head of the run, plus the prologue and epilogue
-        // (about 20 tiles' worth)
-        float seen[4096];
-        const int n_known = n_kv_tiles < 4096 ? n_kv_tiles : 4096;     // (longer chunks: the remaining tiles count like the last known one)
-        for (int t = 0; t < n_known; ++t) {
-            const int k_min = seg_pos_of_row(a.g.ks, t * WG_KEYS);
-            const int n_all = n_qtiles - seg_rows_le(a.g.qs, k_min - 1) / TM;
-            seen[t] = (float)(n_all > 0 ? n_all : 0);
-        }
-        // Launches that do not fill the chip take the split kernel's 32-key workgroups instead (whole groups where
-        // they fill it: no atomics), in one launch with split dQ workgroups where that is shorter: the two kinds of unit
-        // fill each other's last rounds.  Estimated times in us, fitted like those of the forward launcher.  Measured, head_dim 128,
-        // us of 128 / 32 keys: 300 rows x 700 keys x 4 / 2 heads 23.9 / 11.5; 512 x 1024 x 24 / 8 46 / 21; 1024 x 1024 x 24 / 8
-        // 56 / 36; 2048 x 2048 x 24 / 8 158 / 123; 4096 x 4096 x 12 / 3 245 / 270; head_dim 64: 1024 x 1024 x 24 / 8 37 / 22,
-        // 4096 x 4096 x 24 / 8 272 / 292.  A forced run length keeps the 128-key workgroups that it is defined for.
-        bool split_keys = false;
-        if (hexi_dkdv_run_len < 1 && (long long)n_runs_for(run_len) * n_kv_tiles < 2048 && n_kv_tiles <= 4096) {
-            const bool wide = a.g.d == 128;
-            const double fill_us = 6.0;                        // zero-filling dk and dv where runs add into them
-            const double atomic_us = (double)a.g.lc * a.g.d * 8.0 / 1.2e6;     // one run's atomics (1.2 TB/s)
-            auto units = [&](int len, int keys) {
-                const long long n_runs = n_runs_for(len);
-                UnitTimes u;
-                for (int t = 0; t < n_kv_tiles; ++t) {
-                    if (seen[t] < 1.0f) continue;
-                    const int cols = t == n_kv_tiles - 1 ? a.g.lc - t * WG_KEYS : WG_KEYS;
-                    u.add(keys == WG_KEYS ? (wide ? 3.0 + 1.8 * len * seen[t] : 2.0 + 1.5 * len * seen[t])
-                                          : (wide ? 3.0 + 2.2 * ceil(len * seen[t] / 4.0) : 1.0 + 1.5 * ceil(len * seen[t] / 4.0)),
-                          n_runs * ((cols + keys - 1) / keys));
-                }
-                return u;
-            };
-            // dK / dV units, then dQ units, in one launch.  More than a round of them: all work shared out, a tenth longer
-            // than the units take among their like (measured 1.1 to 1.3 at head_dim 128), plus half a unit of tail; 64-row dQ units then (as
-            // 32-row ones they stream twice as much beside the dK / dV units: 54 us against 46 at 512 x 1024 x 24 / 8).
-            auto joint = [&](const UnitTimes& kv, const UnitTimes& dq) {
-                const double longest = kv.longest > dq.longest ? kv.longest : dq.longest;
-                if (kv.n + dq.n <= 256) return longest;
-                const double shared_out = (wide ? 1.1 : 1.0) * (kv.sum + dq.sum) / 256.0 + (dq.n > 0 ? 0.5 * dq.sum / (double)dq.n : 0.0);
-                return shared_out > longest ? shared_out : longest;
-            };
-            double best = 11.0 + (run_len < max_cnt || unused ? fill_us : 0.0) + units(run_len, WG_KEYS).makespan() + dq_us;
-            for (int len = max_cnt; len >= 1; --len) {
-                if (max_cnt % len != 0) continue;
-                const UnitTimes kv = units(len, 32);
-                const double t0 = 3.0 + (len < max_cnt || unused ? fill_us : 0.0) + (len < max_cnt ? atomic_us * n_runs_for(len) : 0.0);
-                auto consider = [&](double t, int rows) {
-                    if (t < best) { best = t; run_len = len; split_keys = true; dq_rows = rows; }
-                };
-                consider(t0 + kv.makespan() + dqt.t256, 0);
-                if (dq_small && dqt.rows64.n > 0) {
-                    consider(t0 + joint(kv, dqt.rows64), 64);
-                    if (kv.n + dqt.rows32.n <= 256) consider(t0 + joint(kv, dqt.rows32), 32);
-                }
-            }
-        }
-        const bool shared = hexi_build_head_runs(a.g.kv_of_q, a.g.nq, a.g.nkv, run_len, &runs);
-        unsigned grid = 0;
-        XcdSplit split;
-        if (!split_keys && a.want_dkdv) split = hexi_split_units(runs.n * n_kv_tiles, [&](int u) {
+    const bool shared = hexi_build_head_runs(a.g.kv_of_q, a.g.nq, a.g.nkv, plan.run_len, &runs);
+    unsigned grid = 0;
+    XcdSplit split;
+    if (!plan.split_keys && a.want_dkdv)
+        split = hexi_split_units(runs.n * n_kv_tiles, [&](int u) {
             const int run = u / n_kv_tiles, t = u - run * n_kv_tiles;
-            return (float)runs.len[run] * seen[t < n_known ? t : n_known - 1] + 20.0f;
+            return (float)runs.len[run] * plan.seen[t < plan.n_known ? t : plan.n_known - 1] + 20.0f;
         }, &grid);
-        if ((shared || unused) && !a.accumulate && a.want_dkdv) {
-            const long long n = (long long)a.g.lc * a.g.nkv * a.g.d;
-            const hipError_t e = hexi_launch_zero2_f32(a.dk, a.dv, n, s);
-            if (e != hipSuccess) return e;
-        }
-        if (a.g.d != 128 && a.g.d != 64) return hipErrorInvalidValue;
-        if (split_keys && a.want_dkdv) {
-            const hipError_t e = hexi_launch_bwd_split_bf16(a, a.want_dq ? dq_rows : 0, runs, shared, s);     // with the dQ, if that is split too
-            if (e != hipSuccess) return e;
-            dq_done |= dq_rows > 0;
-        } else if (grid > 0) {
-            if (a.g.d == 128) {
-                if (shared) bwd_dkdv_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
-                else bwd_dkdv_bf16_kernel<128, false><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
-            } else {
-                if (shared) bwd_dkdv_bf16_kernel<64, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
-                else bwd_dkdv_bf16_kernel<64, false><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
-            }
-        }
-        hipError_t e = hipGetLastError();
+    if ((shared || plan.unused) && !a.accumulate && a.want_dkdv) {
+        const long long n = (long long)a.g.lc * a.g.nkv * a.g.d;
+        const hipError_t e = hexi_launch_zero2_f32(a.dk, a.dv, n, s);
         if (e != hipSuccess) return e;
     }
+    if (a.g.d != 128 && a.g.d != 64) return hipErrorInvalidValue;
+    if (plan.split_keys && a.want_dkdv) {
+        const hipError_t e = hexi_launch_bwd_split_bf16(a, a.want_dq ? dq_rows : 0, runs, shared, s);     // with the dQ, if that is split too
+        if (e != hipSuccess) return e;
+        dq_done |= dq_rows > 0;
+    } else if (grid > 0) {
+        if (a.g.d == 128) {
+            if (shared) bwd_dkdv_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
+            else bwd_dkdv_bf16_kernel<128, false><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
+        } else {
+            if (shared) bwd_dkdv_bf16_kernel<64, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
+            else bwd_dkdv_bf16_kernel<64, false><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
+        }
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (dq_done) return hipSuccess;
     runs.n = 0;
     return dq_rows > 0 ? hexi_launch_bwd_split_bf16(a, dq_rows, runs, false, s) : hexi_launch_bwd_dq_bf16(a, s);

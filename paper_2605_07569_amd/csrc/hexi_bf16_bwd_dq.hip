@@ -18,16 +18,16 @@
 //   V(b): P^T and dS^T of block b, dS^T rounded to bf16 operand slots.
 // The vector-phase group also issues the direct global->LDS loads: during the first block of tile j, group 1
 // requests K of tile j + 3 and group 0 requests V of tile j + 3 (four LDS buffers per tensor).
-#include <cmath>
 #include "hexi_internal.h"
+#include "hexi_shapes.h"
 #include "hexi_mfma.h"
 
 namespace {
 
-constexpr int TN = 64;             // keys per LDS tile (two 32-key blocks)
+constexpr int TN = hexi_shapes::KV_STREAM_TILE;     // keys per LDS tile (two 32-key blocks)
 constexpr int NB = 4;              // LDS buffers per tensor
 constexpr int GROUP_ROWS = 128;    // q rows per wavefront group (32 per wavefront)
-constexpr int WG_ROWS = 256;       // q rows per workgroup
+constexpr int WG_ROWS = hexi_shapes::Q_TILE;     // q rows per workgroup
 constexpr int AHEAD = 3;           // tile j + 3 is requested during tile j
 constexpr float LOG2E = 1.4426950408889634f;
 
@@ -665,54 +665,14 @@ __global__ void __launch_bounds__(512) bwd_dq_bf16_kernel(const BwdArgs a, const
     }
 }
 
-// Cost of the units of one head, longest q tile first: the key tiles its q tile streams, plus the prologue and epilogue (about
-// six tiles' worth); a unit that sees nothing of the chunk returns at once.  Returns the number of entries filled (longer
-// shards: the remaining tiles count like the last known one).
-int unit_costs(const AttnGeom& g, int n_q_tiles, float (&cost)[4096])
-{
-    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;
-    for (int p = 0; p < n_known; ++p) {
-        const int q_tile = n_q_tiles - 1 - p;
-        const int last_row = (q_tile * WG_ROWS + WG_ROWS < g.lq ? q_tile * WG_ROWS + WG_ROWS : g.lq) - 1;
-        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + TN - 1) / TN;
-        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
-    }
-    return n_known;
-}
-
 }  // namespace
-
-// Fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads, like the forward launcher's estimates.  Measured,
-// head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 / 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9;
-// 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim 64: 1024 x 1024 x 24 30 / 23 / 23;
-// 2048 x 4096 x 24 112 / 116.
-bool hexi_bwd_dq_times(const AttnGeom& g, DqTimes* t)
-{
-    const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
-    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return false;     // four rounds of full-size units: their tail no longer matters
-    float cost[4096];
-    unit_costs(g, n_q_tiles, cost);
-    const bool wide = g.d == 128;
-    UnitTimes b256;
-    for (int p = 0; p < n_q_tiles; ++p) {
-        const double nt = cost[p] - 6.0;
-        if (nt < 1.0) continue;
-        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * WG_ROWS : WG_ROWS;
-        b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
-        t->rows64.add(wide ? 2.0 + 1.85 * ceil(nt / 2.0) : 1.0 + 1.14 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
-        t->rows32.add(wide ? 2.0 + 2.1 * ceil(nt / 4.0) : 1.0 + 1.4 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
-    }
-    if (b256.n == 0) return true;
-    t->t256 = wide ? 11.0 + b256.makespan(1.8, 2.2) : 7.0 + b256.makespan(1.1, 1.45);
-    return true;
-}
 
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
     float cost[4096];
-    const int n_known = unit_costs(g, n_q_tiles, cost);
+    const int n_known = hexi_q_unit_costs(g, n_q_tiles, cost);
     unsigned grid = 0;
     const XcdSplit split = hexi_split_units(g.nq * n_q_tiles, [&](int u) { const int p = u % n_q_tiles; return cost[p < n_known ? p : n_known - 1]; }, &grid);
     if (grid == 0) return hipSuccess;

@@ -28,16 +28,16 @@
 // against [2^-60, 2^60]; if any row of the workgroup fails, the whole workgroup repeats its tiles with
 // the exact online-softmax path (running maximum, lazy rescale).  Rows in the fast path keep two sums:
 // the exact one defines the LSE, the one of the bf16-rounded probabilities normalises O.
-#include <cmath>
 #include "hexi_internal.h"
+#include "hexi_shapes.h"
 #include "hexi_mfma.h"
 
 namespace {
 
-constexpr int TN = 64;             // keys per tile
+constexpr int TN = hexi_shapes::KV_STREAM_TILE;     // keys per tile
 constexpr int NB = 4;              // LDS buffers per tensor
 constexpr int GROUP_ROWS = 128;    // q rows per wavefront group (32 per wavefront)
-constexpr int WG_ROWS = 256;       // q rows per workgroup
+constexpr int WG_ROWS = hexi_shapes::Q_TILE;     // q rows per workgroup
 // LDS rows are padded instead of swizzled, so that every operand fragment sits at (one per-lane base
 // register) + (compile-time offset): K rows take 2 D + 16 bytes (272 or 144: 16 consecutive rows then spread
 // over all 64 banks for the 128-bit row reads), V rows 2 D + 64 bytes (320 or 192: the 4 rows x 64 bytes of a
@@ -471,36 +471,12 @@ __global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const in
     }
 }
 
-// Rows per workgroup of the split kernels (32 or 64) where they are expected to finish first, else 0.  Estimated times of
-// the three shapes in us, fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads; nt: key tiles that a
-// 256-row unit streams.  Measured, head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 27.5 / 12.3 / 9.7;
-// 512 x 1024 x 24 32.0 / 16.3 / 20.8; 1024 x 1024 x 24 35 / 30.6 / 31.6; 2048 x 2048 x 24 69 / 78 / 99; head_dim 64:
-// 1024 x 1024 x 24 24.2 / 16.8 / 16.9; 4096 x 4096 x 24 155 / 142 / 159 (384 units of 256 rows: a half-empty second round).
-int split_rows(const AttnGeom& g, int n_q_tiles, const float* cost)
-{
-    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;     // four rounds of full-size units: their tail no longer matters
-    const bool wide = g.d == 128;
-    UnitTimes b256, b64, b32;
-    for (int p = 0; p < n_q_tiles; ++p) {
-        const double nt = cost[p] - 6.0;
-        if (nt < 1.0) continue;                                                // sees nothing of the chunk
-        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * WG_ROWS : WG_ROWS;
-        b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
-        b64.add(wide ? 2.0 + 1.42 * ceil(nt / 2.0) : 1.0 + 0.66 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
-        b32.add(wide ? 2.0 + 1.8 * ceil(nt / 4.0) : 1.0 + 0.7 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
-    }
-    if (b256.n == 0) return 0;
-    const double t256 = wide ? 7.0 + b256.makespan(1.39, 1.76) : 6.0 + b256.makespan(0.85, 1.05);
-    const double t64 = 3.0 + b64.makespan(), t32 = 3.0 + b32.makespan();
-    if (t256 <= t64 && t256 <= t32) return 0;
-    return t64 < t32 ? 64 : 32;
-}
-
 }  // namespace
 
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
+    if (const int rows = hexi_fwd_split_rows(g); rows > 0) return hexi_launch_fwd_split_bf16(a, rows, s);
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
     // cost of a unit: the key tiles its q tile streams, plus the prologue and epilogue (about six tiles' worth);
     // a unit that sees nothing of the chunk returns at once under HEXI_ACCUMULATE and only writes zeros otherwise
@@ -512,7 +488,6 @@ hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s)
         const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + TN - 1) / TN;
         cost[p] = nt > 0 ? (float)nt + 6.0f : (a.accumulate ? 0.25f : 2.0f);
     }
-    if (const int rows = split_rows(g, n_q_tiles, cost); rows > 0) return hexi_launch_fwd_split_bf16(a, rows, s);
     unsigned grid = 0;
     const XcdSplit split = hexi_split_units(g.nq * n_q_tiles, [&](int u) { const int p = u % n_q_tiles; return cost[p < n_known ? p : n_known - 1]; }, &grid);
     if (grid == 0) return hipSuccess;

@@ -127,38 +127,6 @@ inline bool hexi_build_head_runs(const signed char* kv_of_q, int nq, int nkv, in
     return shared;
 }
 
-// Time of a launch of n units, one per CU at a time, that take `sum` in total and at most `longest` each: whole rounds
-// of the mean unit on 256 CUs (the launches start the longest units first), or the longest one.
-inline double hexi_makespan(double sum, double longest, long long n)
-{
-    if (n <= 0) return 0.0;
-    const double rounds = sum / (double)n * (double)((n + 255) / 256);
-    return rounds > longest ? rounds : longest;
-}
-
-// The units of a launch shape: estimated times in us.
-struct UnitTimes {
-    double sum = 0.0, longest = 0.0;
-    long long n = 0;
-    void add(double t, long long k) { sum += t * (double)k; n += k; longest = t > longest ? t : longest; }
-    double makespan() const { return hexi_makespan(sum, longest, n); }
-    // the same for units whose speed depends on how much of the chip is busy: `lo` per unit of `sum` in a round that leaves
-    // most CUs idle, `hi` in one that uses three quarters of them or more
-    double makespan(double lo, double hi) const
-    {
-        if (n <= 0) return 0.0;
-        const double rest = (double)(n % 256) / 192.0, f = rest < 1.0 ? rest * rest : 1.0;
-        const double t = sum / (double)n * ((double)(n / 256) * hi + (rest > 0.0 ? lo + (hi - lo) * f : 0.0));
-        return t > longest * lo ? t : longest * lo;
-    }
-};
-// Estimated times of a step's dQ: a launch of 256-row workgroups (us, 0 where nothing is visible), and the units of the split
-// kernel's 64- and 32-row ones.
-struct DqTimes {
-    double t256 = 0.0;
-    UnitTimes rows64, rows32;
-};
-
 // Forced number of q heads per dK/dV workgroup run (0: the launcher chooses); see hexi_set_dkdv_run_len().
 extern int hexi_dkdv_run_len;
 
@@ -167,7 +135,6 @@ hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s);      // dK/dV kernel, then the dQ kernel
-bool hexi_bwd_dq_times(const AttnGeom& g, DqTimes* t);      // false: too large for the split kernel
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);      // 256-row workgroups
 // the same steps with 32 or 64 (`rows`) stationary rows per workgroup, for launches that do not fill the chip otherwise
 hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, int rows, hipStream_t s);

@@ -1,0 +1,233 @@
+// Which workgroup shapes a bf16 ring step is launched with, from its sizes: the rules of the launchers, host code alone.
+#pragma once
+#include <cmath>
+#include "hexi_internal.h"
+
+namespace hexi_shapes {
+constexpr int Q_TILE = 256;            // q rows of the large forward and dQ workgroups
+constexpr int KV_STREAM_TILE = 64;     // keys per tile that they stream
+constexpr int KV_TILE = 128;           // keys of the large dK / dV workgroups
+constexpr int Q_STREAM_TILE = 64;      // q rows per tile that they stream
+}  // namespace hexi_shapes
+
+// Time of a launch of n units, one per CU at a time, that take `sum` in total and at most `longest` each: whole rounds
+// of the mean unit on 256 CUs (the launches start the longest units first), or the longest one.
+inline double hexi_makespan(double sum, double longest, long long n)
+{
+    if (n <= 0) return 0.0;
+    const double rounds = sum / (double)n * (double)((n + 255) / 256);
+    return rounds > longest ? rounds : longest;
+}
+
+// The units of a launch shape: estimated times in us.
+struct UnitTimes {
+    double sum = 0.0, longest = 0.0;
+    long long n = 0;
+    void add(double t, long long k) { sum += t * (double)k; n += k; longest = t > longest ? t : longest; }
+    double makespan() const { return hexi_makespan(sum, longest, n); }
+    // the same for units whose speed depends on how much of the chip is busy: `lo` per unit of `sum` in a round that leaves
+    // most CUs idle, `hi` in one that uses three quarters of them or more
+    double makespan(double lo, double hi) const
+    {
+        if (n <= 0) return 0.0;
+        const double rest = (double)(n % 256) / 192.0, f = rest < 1.0 ? rest * rest : 1.0;
+        const double t = sum / (double)n * ((double)(n / 256) * hi + (rest > 0.0 ? lo + (hi - lo) * f : 0.0));
+        return t > longest * lo ? t : longest * lo;
+    }
+};
+// Estimated times of a step's dQ: a launch of 256-row workgroups (us, 0 where nothing is visible), and the units of the split
+// kernel's 64- and 32-row ones.
+struct DqTimes {
+    double t256 = 0.0;
+    UnitTimes rows64, rows32;
+};
+
+// Cost of the units of one head, longest q tile first: the key tiles its q tile streams, plus the prologue and epilogue (about
+// six tiles' worth); a unit that sees nothing of the chunk returns at once.  Returns the number of entries filled (longer
+// shards: the remaining tiles count like the last known one).
+inline int hexi_q_unit_costs(const AttnGeom& g, int n_q_tiles, float (&cost)[4096])
+{
+    using namespace hexi_shapes;
+    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;
+    for (int p = 0; p < n_known; ++p) {
+        const int q_tile = n_q_tiles - 1 - p;
+        const int last_row = (q_tile * Q_TILE + Q_TILE < g.lq ? q_tile * Q_TILE + Q_TILE : g.lq) - 1;
+        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + KV_STREAM_TILE - 1) / KV_STREAM_TILE;
+        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
+    }
+    return n_known;
+}
+
+// Rows per workgroup of the split kernels (32 or 64) where they are expected to finish first, else 0.  Estimated times of
+// the three shapes in us, fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads; nt: key tiles that a
+// 256-row unit streams.  Measured, head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 27.5 / 12.3 / 9.7;
+// 512 x 1024 x 24 32.0 / 16.3 / 20.8; 1024 x 1024 x 24 35 / 30.6 / 31.6; 2048 x 2048 x 24 69 / 78 / 99; head_dim 64:
+// 1024 x 1024 x 24 24.2 / 16.8 / 16.9; 4096 x 4096 x 24 155 / 142 / 159 (384 units of 256 rows: a half-empty second round).
+inline int hexi_fwd_split_rows(const AttnGeom& g)
+{
+    using namespace hexi_shapes;
+    const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
+    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;     // four rounds of full-size units: their tail no longer matters
+    float cost[4096];
+    hexi_q_unit_costs(g, n_q_tiles, cost);
+    const bool wide = g.d == 128;
+    UnitTimes b256, b64, b32;
+    for (int p = 0; p < n_q_tiles; ++p) {
+        const double nt = cost[p] - 6.0;
+        if (nt < 1.0) continue;                                                // sees nothing of the chunk
+        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * Q_TILE : Q_TILE;
+        b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
+        b64.add(wide ? 2.0 + 1.42 * ceil(nt / 2.0) : 1.0 + 0.66 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
+        b32.add(wide ? 2.0 + 1.8 * ceil(nt / 4.0) : 1.0 + 0.7 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
+    }
+    if (b256.n == 0) return 0;
+    const double t256 = wide ? 7.0 + b256.makespan(1.39, 1.76) : 6.0 + b256.makespan(0.85, 1.05);
+    const double t64 = 3.0 + b64.makespan(), t32 = 3.0 + b32.makespan();
+    if (t256 <= t64 && t256 <= t32) return 0;
+    return t64 < t32 ? 64 : 32;
+}
+
+// Fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads, like the forward launcher's estimates.  Measured,
+// head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 / 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9;
+// 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim 64: 1024 x 1024 x 24 30 / 23 / 23;
+// 2048 x 4096 x 24 112 / 116.
+inline bool hexi_bwd_dq_times(const AttnGeom& g, DqTimes* t)
+{
+    using namespace hexi_shapes;
+    const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
+    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return false;     // four rounds of full-size units: their tail no longer matters
+    float cost[4096];
+    hexi_q_unit_costs(g, n_q_tiles, cost);
+    const bool wide = g.d == 128;
+    UnitTimes b256;
+    for (int p = 0; p < n_q_tiles; ++p) {
+        const double nt = cost[p] - 6.0;
+        if (nt < 1.0) continue;
+        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * Q_TILE : Q_TILE;
+        b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
+        t->rows64.add(wide ? 2.0 + 1.85 * ceil(nt / 2.0) : 1.0 + 1.14 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
+        t->rows32.add(wide ? 2.0 + 2.1 * ceil(nt / 4.0) : 1.0 + 1.4 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
+    }
+    if (b256.n == 0) return true;
+    t->t256 = wide ? 11.0 + b256.makespan(1.8, 2.2) : 7.0 + b256.makespan(1.1, 1.45);
+    return true;
+}
+
+// How a backward step is launched.
+struct BwdPlan {
+    int dq_rows = 0;              // rows per dQ workgroup of the split kernel; 0: the 256-row workgroups
+    bool split_keys = false;      // dK / dV in the split kernel's 32-key workgroups instead of the 128-key ones
+    int run_len = 0;              // q heads per dK / dV workgroup
+    int run_len_128 = 0;          // the same if the 128-key workgroups are taken
+    bool unused = false;          // some kv head is read by no local q head: zero gradient
+    int n_kv_tiles = 0;           // 128-key tiles of the chunk
+    int n_known = 0;              // entries of seen
+    float seen[4096];             // 64-row q tiles of one head that a key tile sees
+};
+
+// The shapes of both halves are chosen for the whole step, whichever of them a call runs: a half gives the same bits alone and
+// with the other.  forced_run_len: hexi_set_dkdv_run_len().
+inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
+{
+    using namespace hexi_shapes;
+    // dQ: rows per split workgroup, or 0 for the 256-row ones; by itself, the shape that is expected to finish first
+    DqTimes dqt;
+    int& dq_rows = plan->dq_rows;
+    double dq_us = 0.0;
+    const bool dq_small = hexi_bwd_dq_times(g, &dqt);
+    if (dq_small) {
+        const double t64 = 3.0 + dqt.rows64.makespan(), t32 = 3.0 + dqt.rows32.makespan();
+        dq_us = dqt.t256;
+        if (t64 < dq_us) { dq_us = t64; dq_rows = 64; }
+        if (t32 < dq_us) { dq_us = t32; dq_rows = 32; }
+    }
+    const int n_kv_tiles = (g.lc + KV_TILE - 1) / KV_TILE;
+    plan->n_kv_tiles = n_kv_tiles;
+    // q heads per kv head, in head order
+    int cnt[HEXI_MAX_HEADS] = {0};
+    int max_cnt = 0;
+    bool& unused = plan->unused;
+    for (int h = 0; h < g.nq; ++h) {
+        const int c = ++cnt[g.kv_of_q[h]];
+        max_cnt = c > max_cnt ? c : max_cnt;
+    }
+    for (int kh = 0; kh < g.nkv; ++kh) unused |= (cnt[kh] == 0);   // a kv head no local q head reads: zero gradient
+    // Run length: the longest divisor of the largest group's size (so that its runs are equally long) for which
+    // the launch still has about three workgroups per CU and a workgroup walks at most 512 q tiles.  A run
+    // amortises the workgroup's prologue and epilogue (about 20 tiles' worth) and, when it covers the whole
+    // group, needs no atomics; but the workgroups of an XCD stream the same Q / dO tiles only while they stay
+    // in step, and long tile sequences let them drift apart (measured: more L2 misses, slower launches).
+    auto n_runs_for = [&](int len) {
+        int n = 0;
+        for (int kh = 0; kh < g.nkv; ++kh) n += (cnt[kh] + len - 1) / len;
+        return n;
+    };
+    // q tiles that see the chunk's first key: the longest tile sequence of one head
+    const int n_qtiles = (g.lq + Q_STREAM_TILE - 1) / Q_STREAM_TILE;
+    const int max_tiles = g.lc > 0 ? n_qtiles - seg_rows_le(g.qs, seg_pos_of_row(g.ks, 0) - 1) / Q_STREAM_TILE : 0;
+    int& run_len = plan->run_len;
+    run_len = max_cnt;
+    while (run_len > 1 && (max_cnt % run_len != 0 || (long long)run_len * max_tiles > 512 ||
+                           (long long)n_runs_for(run_len) * n_kv_tiles < 3 * 256))
+        --run_len;
+    if (forced_run_len >= 1)      // tuning / test override of the heuristic
+        run_len = forced_run_len < max_cnt ? forced_run_len : max_cnt;
+    plan->run_len_128 = run_len;
+    // cost of a unit: the q tiles its key tile sees, once per head of the run, plus the prologue and epilogue
+    // (about 20 tiles' worth)
+    float (&seen)[4096] = plan->seen;
+    const int n_known = n_kv_tiles < 4096 ? n_kv_tiles : 4096;     // (longer chunks: the remaining tiles count like the last known one)
+    plan->n_known = n_known;
+    for (int t = 0; t < n_known; ++t) {
+        const int k_min = seg_pos_of_row(g.ks, t * KV_TILE);
+        const int n_all = n_qtiles - seg_rows_le(g.qs, k_min - 1) / Q_STREAM_TILE;
+        seen[t] = (float)(n_all > 0 ? n_all : 0);
+    }
+    // Launches that do not fill the chip take the split kernel's 32-key workgroups instead (whole groups where
+    // they fill it: no atomics), in one launch with split dQ workgroups where that is shorter: the two kinds of unit
+    // fill each other's last rounds.  Estimated times in us, fitted like those of the forward launcher.  Measured, head_dim 128,
+    // us of 128 / 32 keys: 300 rows x 700 keys x 4 / 2 heads 23.9 / 11.5; 512 x 1024 x 24 / 8 46 / 21; 1024 x 1024 x 24 / 8
+    // 56 / 36; 2048 x 2048 x 24 / 8 158 / 123; 4096 x 4096 x 12 / 3 245 / 270; head_dim 64: 1024 x 1024 x 24 / 8 37 / 22,
+    // 4096 x 4096 x 24 / 8 272 / 292.  A forced run length keeps the 128-key workgroups that it is defined for.
+    bool& split_keys = plan->split_keys;
+    if (forced_run_len < 1 && (long long)n_runs_for(run_len) * n_kv_tiles < 2048 && n_kv_tiles <= 4096) {
+        const bool wide = g.d == 128;
+        const double fill_us = 6.0;                        // zero-filling dk and dv where runs add into them
+        const double atomic_us = (double)g.lc * g.d * 8.0 / 1.2e6;     // one run's atomics (1.2 TB/s)
+        auto units = [&](int len, int keys) {
+            const long long n_runs = n_runs_for(len);
+            UnitTimes u;
+            for (int t = 0; t < n_kv_tiles; ++t) {
+                if (seen[t] < 1.0f) continue;
+                const int cols = t == n_kv_tiles - 1 ? g.lc - t * KV_TILE : KV_TILE;
+                u.add(keys == KV_TILE ? (wide ? 3.0 + 1.8 * len * seen[t] : 2.0 + 1.5 * len * seen[t])
+                                      : (wide ? 3.0 + 2.2 * ceil(len * seen[t] / 4.0) : 1.0 + 1.5 * ceil(len * seen[t] / 4.0)),
+                      n_runs * ((cols + keys - 1) / keys));
+            }
+            return u;
+        };
+        // dK / dV units, then dQ units, in one launch.  More than a round of them: all work shared out, a tenth longer
+        // than the units take among their like (measured 1.1 to 1.3 at head_dim 128), plus half a unit of tail; 64-row dQ units then (as
+        // 32-row ones they stream twice as much beside the dK / dV units: 54 us against 46 at 512 x 1024 x 24 / 8).
+        auto joint = [&](const UnitTimes& kv, const UnitTimes& dq) {
+            const double longest = kv.longest > dq.longest ? kv.longest : dq.longest;
+            if (kv.n + dq.n <= 256) return longest;
+            const double shared_out = (wide ? 1.1 : 1.0) * (kv.sum + dq.sum) / 256.0 + (dq.n > 0 ? 0.5 * dq.sum / (double)dq.n : 0.0);
+            return shared_out > longest ? shared_out : longest;
+        };
+        double best = 11.0 + (run_len < max_cnt || unused ? fill_us : 0.0) + units(run_len, KV_TILE).makespan() + dq_us;
+        for (int len = max_cnt; len >= 1; --len) {
+            if (max_cnt % len != 0) continue;
+            const UnitTimes kv = units(len, 32);
+            const double t0 = 3.0 + (len < max_cnt || unused ? fill_us : 0.0) + (len < max_cnt ? atomic_us * n_runs_for(len) : 0.0);
+            auto consider = [&](double t, int rows) {
+                if (t < best) { best = t; run_len = len; split_keys = true; dq_rows = rows; }
+            };
+            consider(t0 + kv.makespan() + dqt.t256, 0);
+            if (dq_small && dqt.rows64.n > 0) {
+                consider(t0 + joint(kv, dqt.rows64), 64);
+                if (kv.n + dqt.rows32.n <= 256) consider(t0 + joint(kv, dqt.rows32), 32);
+            }
+        }
+    }
+}

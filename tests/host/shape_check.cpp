@@ -1,0 +1,52 @@
+// Host-side view of the launch rules (csrc/hexi_shapes.h).  Reads one ring step per line from stdin:
+//   head_dim nq nkv forced_run_len  n_q_segs (start len)...  n_kv_segs (start len)...  [kv_of_q ...]
+// and prints: rows per forward workgroup (0: 256), rows per dQ workgroup (0: 256), keys per dK / dV workgroup, q heads per dK / dV
+// workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take.
+#include <cstdio>
+#include <cstring>
+#include <iostream>
+#include <sstream>
+#include <string>
+#include "hexi_internal.h"
+#include "hexi_shapes.h"
+
+static SegTable read_segs(std::istringstream& is)
+{
+    SegTable t;
+    std::memset(&t, 0, sizeof(t));
+    is >> t.n;
+    int rows = 0;
+    for (int s = 0; s < t.n; ++s) {
+        int len;
+        is >> t.start[s] >> len;
+        t.row0[s] = rows;
+        rows += len;
+    }
+    for (int s = t.n; s <= HEXI_MAX_SEGS; ++s) t.row0[s] = rows;
+    t.total = rows;
+    return t;
+}
+
+int main()
+{
+    std::string line;
+    while (std::getline(std::cin, line)) {
+        std::istringstream is(line);
+        AttnGeom g;
+        std::memset(&g, 0, sizeof(g));
+        int forced;
+        is >> g.d >> g.nq >> g.nkv >> forced;
+        g.qs = read_segs(is);
+        g.ks = read_segs(is);
+        g.lq = g.qs.total; g.lc = g.ks.total;
+        int m;
+        for (int h = 0; h < g.nq; ++h) g.kv_of_q[h] = (signed char)((is >> m) ? m : h / (g.nq / g.nkv));
+        BwdPlan plan;
+        hexi_plan_bwd(g, forced, &plan);
+        HeadRuns runs;
+        const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len, &runs);
+        const bool shared_128 = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len_128, &runs);
+        std::printf("%d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared, (int)shared_128);
+    }
+    return 0;
+}

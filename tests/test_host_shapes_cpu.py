@@ -1,0 +1,45 @@
+"""The launch rules (which workgroup shapes a bf16 ring step takes), compiled for the host alone."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    hipcc = "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("shapes") / "shape_check")
+    subprocess.check_call([hipcc, "-O1", "-std=c++17", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                           "-I", os.path.join(ROOT, "include"),
+                           "-I", os.path.join(ROOT, "paper_2605_07569_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host", "shape_check.cpp"), "-o", exe])
+
+    def ask(steps):
+        """steps: (head_dim, nq, nkv, q_segs, kv_segs[, kv_of_q[, forced run length]]) -> dicts"""
+        lines = []
+        for d, nq, nkv, qs, ks, *more in steps:
+            segs = lambda x: f"{len(x)} " + " ".join(f"{s} {n}" for s, n in x)
+            m = " ".join(map(str, more[0])) if more and more[0] else ""
+            lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
+        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128")
+        return [dict(zip(names, map(int, line.split()))) for line in out if line]
+
+    return ask
+
+
+def _step(lq, lc, nq, nkv, d, off):
+    """rows [off, off + lq) against keys [0, lc)"""
+    return d, nq, nkv, [(off, lq)], [(0, lc)]
+
+
+def test_smallest_and_largest_launches(shapes):
+    small, large, forced = shapes([_step(300, 700, 4, 2, 128, 700), _step(16384, 16384, 24, 8, 128, 16384),
+                                   (128, 8, 1, [(1024, 512)], [(0, 512)], None, 3)])
+    assert small["fwd_rows"] == 32 and small["dq_rows"] == 32 and small["keys"] == 32
+    assert large["fwd_rows"] == 0 and large["dq_rows"] == 0 and large["keys"] == 128 and not large["atomic"]
+    assert forced["keys"] == 128 and forced["run_len"] == 3        # a forced run length keeps the 128-key workgroups
