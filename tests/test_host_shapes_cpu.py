@@ -41,5 +41,5 @@ def test_smallest_and_largest_launches(shapes):
     small, large, forced = shapes([_step(300, 700, 4, 2, 128, 700), _step(16384, 16384, 24, 8, 128, 16384),
                                    (128, 8, 1, [(1024, 512)], [(0, 512)], None, 3)])
     assert small["fwd_rows"] == 32 and small["dq_rows"] == 32 and small["keys"] == 32
-    assert large["fwd_rows"] == 0 and large["dq_rows"] == 0 and large["keys"] == 128 and not large["atomic"]
+    assert large["fwd_rows"] == 0 and large["dq_rows"] == 0 and large["keys"] == 128
     assert forced["keys"] == 128 and forced["run_len"] == 3        # a forced run length keeps the 128-key workgroups
