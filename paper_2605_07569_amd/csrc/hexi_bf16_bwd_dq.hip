@@ -671,8 +671,16 @@ hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
+    // cost of a unit: the key tiles its q tile streams, plus the prologue and epilogue (about six tiles' worth); a
+    // unit that sees nothing of the chunk returns at once
     float cost[4096];
-    const int n_known = hexi_q_unit_costs(g, n_q_tiles, cost);
+    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;     // (longer shards: the remaining tiles count like the last known one)
+    for (int p = 0; p < n_known; ++p) {
+        const int q_tile = n_q_tiles - 1 - p;
+        const int last_row = (q_tile * WG_ROWS + WG_ROWS < g.lq ? q_tile * WG_ROWS + WG_ROWS : g.lq) - 1;
+        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + TN - 1) / TN;
+        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
+    }
     unsigned grid = 0;
     const XcdSplit split = hexi_split_units(g.nq * n_q_tiles, [&](int u) { const int p = u % n_q_tiles; return cost[p < n_known ? p : n_known - 1]; }, &grid);
     if (grid == 0) return hipSuccess;

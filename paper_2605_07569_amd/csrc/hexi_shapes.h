@@ -42,52 +42,83 @@ struct DqTimes {
     UnitTimes rows64, rows32;
 };
 
-// Cost of the units of one head, longest q tile first: the key tiles its q tile streams, plus the prologue and epilogue (about
-// six tiles' worth); a unit that sees nothing of the chunk returns at once.  Returns the number of entries filled (longer
-// shards: the remaining tiles count like the last known one).
-inline int hexi_q_unit_costs(const AttnGeom& g, int n_q_tiles, float (&cost)[4096])
-{
-    using namespace hexi_shapes;
-    const int n_known = n_q_tiles < 4096 ? n_q_tiles : 4096;
-    for (int p = 0; p < n_known; ++p) {
-        const int q_tile = n_q_tiles - 1 - p;
-        const int last_row = (q_tile * Q_TILE + Q_TILE < g.lq ? q_tile * Q_TILE + Q_TILE : g.lq) - 1;
-        const int nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row)) + KV_STREAM_TILE - 1) / KV_STREAM_TILE;
-        cost[p] = nt > 0 ? (float)nt + 6.0f : 0.25f;
-    }
-    return n_known;
-}
+// The units of a launch by the length of their serial chains (key tiles, q tiles, or 32-row blocks per wavefront).
+struct Units {
+    double sum = 0.0, longest = 0.0;
+    long long n = 0;
+    void add(double chain, long long k) { sum += chain * (double)k; n += k; longest = chain > longest ? chain : longest; }
+};
 
-// Rows per workgroup of the split kernels (32 or 64) where they are expected to finish first, else 0.  Estimated times of
-// the three shapes in us, fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads; nt: key tiles that a
-// 256-row unit streams.  Measured, head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 27.5 / 12.3 / 9.7;
-// 512 x 1024 x 24 32.0 / 16.3 / 20.8; 1024 x 1024 x 24 35 / 30.6 / 31.6; 2048 x 2048 x 24 69 / 78 / 99; head_dim 64:
-// 1024 x 1024 x 24 24.2 / 16.8 / 16.9; 4096 x 4096 x 24 155 / 142 / 159 (384 units of 256 rows: a half-empty second round).
-inline int hexi_fwd_split_rows(const AttnGeom& g)
+// Time of a launch in us: a fixed part, rounds of units over 256 CUs, and its row-wise reads and writes.
+struct LaunchFit {
+    double fixed;
+    double unit;       // per round
+    double lo, hi;     // per chain step in a round that leaves most CUs idle, and in one that uses three quarters of them or more
+    double mb;         // per MB read and written once per row (q, o, dO, dq, dk, dv)
+
+    double us(const Units& u, double mbytes) const
+    {
+        if (u.n <= 0) return fixed;
+        const double mean = u.sum / (double)u.n, rest = (double)(u.n % 256) / 256.0;
+        const double busy = rest < 0.75 ? rest * rest / 0.5625 : 1.0;
+        double last = u.n % 256 ? 1.0 : 0.0;
+        if (u.n > 256) {           // units of unequal length fill each other's last round
+            const double uneven = 2.0 * (u.longest / mean - 1.0);
+            last *= 1.0 - (uneven < 1.0 ? uneven : 1.0) * (1.0 - rest);
+        }
+        const double full = (double)(u.n / 256);
+        const double t = (full + last) * unit + mean * (full * hi + last * (lo + (hi - lo) * busy));
+        const double chain = unit + u.longest * lo;
+        return fixed + (t > chain ? t : chain) + mbytes * mb;
+    }
+};
+
+// Fitted to 7300 calls (5300 with rows and keys drawn from 64 to 12000 over their logarithm, 1 to 64 heads, groups of 1 to 8, chunks
+// visible wholly, partly or diagonally; 2000 ring steps of zigzag, even and uneven shards), every shape measured for each: 4 to
+// 8 % rms off.  First index: head_dim 64, 128; second: 256, 64, 32 rows.
+namespace hexi_shapes {
+constexpr LaunchFit FWD[2][3] = {{{5.21, 3.75, 1.16, 1.13, 0.168}, {5.11, 0.429, 0.800, 0.613, 0.251}, {4.90, 0.669, 0.708, 0.686, 0.300}},
+                                 {{5.90, 7.31, 1.42, 1.60, 0.153}, {3.87, 3.25, 1.12, 1.20, 0.159}, {3.64, 3.51, 1.04, 1.29, 0.197}}};
+}  // namespace hexi_shapes
+
+// The units of a q-stationary launch (forward, dQ) in workgroups of 256, 64 and 32 rows.  false: too large for the split kernels
+// (four rounds of full-size units: their tail no longer matters).
+inline bool hexi_q_units(const AttnGeom& g, Units (&u)[3])
 {
     using namespace hexi_shapes;
     const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
-    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return 0;     // four rounds of full-size units: their tail no longer matters
-    float cost[4096];
-    hexi_q_unit_costs(g, n_q_tiles, cost);
-    const bool wide = g.d == 128;
-    UnitTimes b256, b64, b32;
-    for (int p = 0; p < n_q_tiles; ++p) {
-        const double nt = cost[p] - 6.0;
-        if (nt < 1.0) continue;                                                // sees nothing of the chunk
-        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * Q_TILE : Q_TILE;
-        b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
-        b64.add(wide ? 2.0 + 1.42 * ceil(nt / 2.0) : 1.0 + 0.66 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
-        b32.add(wide ? 2.0 + 1.8 * ceil(nt / 4.0) : 1.0 + 0.7 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));
+    if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return false;
+    for (int t = 0; t < n_q_tiles; ++t) {
+        const int rows = t == n_q_tiles - 1 ? g.lq - t * Q_TILE : Q_TILE;
+        const int seen = seg_rows_le(g.ks, seg_pos_of_row(g.qs, t * Q_TILE + rows - 1));
+        if (seen == 0) continue;
+        const int nt = (seen + KV_STREAM_TILE - 1) / KV_STREAM_TILE;
+        u[0].add(nt, g.nq);
+        u[1].add((nt + 1) / 2, (long long)g.nq * ((rows + 63) / 64));
+        u[2].add((nt + 3) / 4, (long long)g.nq * ((rows + 31) / 32));
     }
-    if (b256.n == 0) return 0;
-    const double t256 = wide ? 7.0 + b256.makespan(1.39, 1.76) : 6.0 + b256.makespan(0.85, 1.05);
-    const double t64 = 3.0 + b64.makespan(), t32 = 3.0 + b32.makespan();
-    if (t256 <= t64 && t256 <= t32) return 0;
-    return t64 < t32 ? 64 : 32;
+    return true;
 }
 
-// Fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads, like the forward launcher's estimates.  Measured,
+// Rows per forward workgroup of the split kernel (32 or 64), or 0 for the 256-row kernel, which is kept unless the other is expected
+// to be 5 % faster (of the 7300 calls 5 are then slower than in 256-row workgroups by more than 3 %, at most 10 %; an estimate
+// without the rows' own reads and writes left 116 so, at most 24 %).  32-row workgroups beyond three rounds stream too much: 666
+// rows x 6831 keys x 48 heads x 128: 150 / 212 / 243 us in 256 / 64 / 32 rows.  Others, head_dim 128: 300 x 700 x 4 heads
+// 27.5 / 12.3 / 9.7; 512 x 1024 x 24 32.0 / 16.3 / 20.8; 1024 x 1024 x 24 35 / 30.6 / 31.6; 2048 x 2048 x 24 69 / 78 / 99;
+// 1091 x 118 x 32 19.4 / 23.0 / 30.5; head_dim 64: 1024 x 1024 x 24 24.2 / 16.8 / 16.9; 6523 x 181 x 8 15.3 / 17.7 / 22.5.
+inline int hexi_fwd_split_rows(const AttnGeom& g)
+{
+    using namespace hexi_shapes;
+    Units u[3];
+    if (!hexi_q_units(g, u)) return 0;
+    const auto& fit = FWD[g.d == 128];
+    const double mb = (double)g.lq * g.nq * g.d * 6.0 * 1e-6;      // q read, o written
+    const double t256 = fit[0].us(u[0], mb), t64 = fit[1].us(u[1], mb), t32 = u[2].n <= 768 ? fit[2].us(u[2], mb) : INFINITY;
+    if (t256 <= 1.05 * (t64 < t32 ? t64 : t32)) return 0;
+    return t64 <= t32 ? 64 : 32;
+}
+
+// Estimates for the choice of a whole step's shapes, fitted to launches of 64 to 4096 rows x 96 to 4096 keys x 2 to 24 heads.  Measured,
 // head_dim 128, us of 256 / 64 / 32 rows: 300 x 700 x 4 heads 35.3 / 15.2 / 11.2; 512 x 1024 x 24 47.6 / 20.3 / 24.9;
 // 1024 x 1024 x 24 52 / 40 / 41; 2048 x 2048 x 24 95 / 104 / 111; head_dim 64: 1024 x 1024 x 24 30 / 23 / 23;
 // 2048 x 4096 x 24 112 / 116.
@@ -96,14 +127,12 @@ inline bool hexi_bwd_dq_times(const AttnGeom& g, DqTimes* t)
     using namespace hexi_shapes;
     const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
     if ((long long)g.nq * n_q_tiles >= 1024 || n_q_tiles > 4096) return false;     // four rounds of full-size units: their tail no longer matters
-    float cost[4096];
-    hexi_q_unit_costs(g, n_q_tiles, cost);
     const bool wide = g.d == 128;
     UnitTimes b256;
     for (int p = 0; p < n_q_tiles; ++p) {
-        const double nt = cost[p] - 6.0;
+        const int row0 = (n_q_tiles - 1 - p) * Q_TILE, rows = g.lq - row0 < Q_TILE ? g.lq - row0 : Q_TILE;
+        const double nt = (seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0 + rows - 1)) + KV_STREAM_TILE - 1) / KV_STREAM_TILE;
         if (nt < 1.0) continue;
-        const int rows = p == 0 ? g.lq - (n_q_tiles - 1) * Q_TILE : Q_TILE;
         b256.add((wide ? 2.0 : 6.0) + nt, g.nq);
         t->rows64.add(wide ? 2.0 + 1.85 * ceil(nt / 2.0) : 1.0 + 1.14 * ceil(nt / 2.0), (long long)g.nq * ((rows + 63) / 64));
         t->rows32.add(wide ? 2.0 + 2.1 * ceil(nt / 4.0) : 1.0 + 1.4 * ceil(nt / 4.0), (long long)g.nq * ((rows + 31) / 32));

@@ -43,3 +43,15 @@ def test_smallest_and_largest_launches(shapes):
     assert small["fwd_rows"] == 32 and small["dq_rows"] == 32 and small["keys"] == 32
     assert large["fwd_rows"] == 0 and large["dq_rows"] == 0 and large["keys"] == 128
     assert forced["keys"] == 128 and forced["run_len"] == 3        # a forced run length keeps the 128-key workgroups
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off,rows", [
+    # us measured in 256 / 64 / 32 rows per workgroup: 19.4 / 23.0 / 30.5, 20.0 / 23.7 / 31.5, 15.3 / 17.7 / 22.5,
+    # 14.1 / 16.2 / 21.4, 150 / 212 / 243: the 256-row kernel
+    (1091, 118, 32, 16, 128, 102, 0), (2450, 97, 16, 2, 128, 0, 0), (6523, 181, 8, 4, 64, 181, 0), (3254, 125, 16, 4, 64, 125, 0),
+    (666, 6831, 48, 16, 128, 6831, 0),
+    # 27.5 / 12.3 / 9.7, 32.0 / 16.3 / 20.8, 151 / 139 / 159, 60.6 / 78 / 99
+    (300, 700, 4, 2, 128, 700, 32), (512, 1024, 24, 8, 128, 1024, 64), (4096, 4096, 24, 8, 64, 4096, 64),
+    (2048, 2048, 24, 8, 128, 2048, 0)])
+def test_forward_takes_the_shape_measured_faster(shapes, lq, lc, nq, nkv, d, off, rows):
+    assert shapes([_step(lq, lc, nq, nkv, d, off)])[0]["fwd_rows"] == rows
