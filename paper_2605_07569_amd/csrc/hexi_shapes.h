@@ -73,12 +73,22 @@ struct LaunchFit {
     }
 };
 
+// dK / dV: whole groups of heads write their sums once; runs of heads clear dk and dv first and add with atomics.
+struct DkdvFit {
+    LaunchFit launch;
+    double atomic_mb, clear;       // per MB of atomics; the clearing launch
+};
+
 // Fitted to 7300 calls (5300 with rows and keys drawn from 64 to 12000 over their logarithm, 1 to 64 heads, groups of 1 to 8, chunks
 // visible wholly, partly or diagonally; 2000 ring steps of zigzag, even and uneven shards), every shape measured for each: 4 to
-// 8 % rms off.  First index: head_dim 64, 128; second: 256, 64, 32 rows.
+// 9 % rms off, 13 % for the 256-row dQ.  First index: head_dim 64, 128; second: 256, 64, 32 rows, or 128, 32 keys.
 namespace hexi_shapes {
 constexpr LaunchFit FWD[2][3] = {{{5.21, 3.75, 1.16, 1.13, 0.168}, {5.11, 0.429, 0.800, 0.613, 0.251}, {4.90, 0.669, 0.708, 0.686, 0.300}},
                                  {{5.90, 7.31, 1.42, 1.60, 0.153}, {3.87, 3.25, 1.12, 1.20, 0.159}, {3.64, 3.51, 1.04, 1.29, 0.197}}};
+constexpr LaunchFit DQ[2][3] = {{{10.9, 3.05, 1.31, 1.46, 0.168}, {3.20, 2.93, 0.833, 0.861, 0.126}, {3.16, 2.69, 0.727, 0.879, 0.128}},
+                                {{11.4, 13.0, 1.51, 2.11, 0.155}, {3.79, 5.09, 1.28, 1.47, 0.0999}, {3.66, 4.18, 1.21, 1.51, 0.127}}};
+constexpr DkdvFit DKDV[2][2] = {{{{2.29, 6.21, 1.32, 1.22, 0.166}, 0.485, 1.33}, {{3.36, 2.21, 1.26, 1.31, 0.166}, 0.288, 2.18}},
+                                {{{3.16, 10.2, 1.50, 1.72, 0.150}, 0.489, 1.46}, {{3.28, 3.83, 1.75, 2.12, 0.123}, 0.347, 2.67}}};
 }  // namespace hexi_shapes
 
 // The units of a q-stationary launch (forward, dQ) in workgroups of 256, 64 and 32 rows.  false: too large for the split kernels
@@ -154,9 +164,8 @@ struct BwdPlan {
     float seen[4096];             // 64-row q tiles of one head that a key tile sees
 };
 
-// The shapes of both halves are chosen for the whole step, whichever of them a call runs: a half gives the same bits alone and
-// with the other.  forced_run_len: hexi_set_dkdv_run_len().
-inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
+// The shapes of a whole step.  forced_run_len: hexi_set_dkdv_run_len().
+inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
 {
     using namespace hexi_shapes;
     // dQ: rows per split workgroup, or 0 for the 256-row ones; by itself, the shape that is expected to finish first
@@ -214,10 +223,11 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
     }
     // Launches that do not fill the chip take the split kernel's 32-key workgroups instead (whole groups where
     // they fill it: no atomics), in one launch with split dQ workgroups where that is shorter: the two kinds of unit
-    // fill each other's last rounds.  Estimated times in us, fitted like those of the forward launcher.  Measured, head_dim 128,
+    // fill each other's last rounds.  Estimated times in us, fitted like those of dQ.  Measured, head_dim 128,
     // us of 128 / 32 keys: 300 rows x 700 keys x 4 / 2 heads 23.9 / 11.5; 512 x 1024 x 24 / 8 46 / 21; 1024 x 1024 x 24 / 8
-    // 56 / 36; 2048 x 2048 x 24 / 8 158 / 123; 4096 x 4096 x 12 / 3 245 / 270; head_dim 64: 1024 x 1024 x 24 / 8 37 / 22,
-    // 4096 x 4096 x 24 / 8 272 / 292.  A forced run length keeps the 128-key workgroups that it is defined for.
+    // 56 / 34; 2048 x 2048 x 24 / 8 154 / 118; 4096 x 4096 x 12 / 3 256 / 239 (runs of one and of two heads); head_dim 64:
+    // 1024 x 1024 x 24 / 8 37 / 22, 4096 x 4096 x 24 / 8 270 / 260.  A forced run length keeps the 128-key workgroups that it is
+    // defined for.
     bool& split_keys = plan->split_keys;
     if (forced_run_len < 1 && (long long)n_runs_for(run_len) * n_kv_tiles < 2048 && n_kv_tiles <= 4096) {
         const bool wide = g.d == 128;
@@ -245,8 +255,9 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
             return shared_out > longest ? shared_out : longest;
         };
         double best = 11.0 + (run_len < max_cnt || unused ? fill_us : 0.0) + units(run_len, KV_TILE).makespan() + dq_us;
+        const int len_128 = run_len;
         for (int len = max_cnt; len >= 1; --len) {
-            if (max_cnt % len != 0) continue;
+            if (max_cnt % len != 0 || (len_128 >= max_cnt && len < max_cnt)) continue;     // whole groups stay whole: reproducible sums
             const UnitTimes kv = units(len, 32);
             const double t0 = 3.0 + (len < max_cnt || unused ? fill_us : 0.0) + (len < max_cnt ? atomic_us * n_runs_for(len) : 0.0);
             auto consider = [&](double t, int rows) {
@@ -257,6 +268,46 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, BwdPlan* plan)
                 consider(t0 + joint(kv, dqt.rows64), 64);
                 if (kv.n + dqt.rows32.n <= 256) consider(t0 + joint(kv, dqt.rows32), 32);
             }
+        }
+    }
+}
+
+// The shapes of a call for both halves or for one of them.  One by itself keeps the step's shape (and so the bits that it gives with
+// the other) where that is expected to be 15 % faster there than the large workgroups, and takes those where not: what a joint launch
+// gains for the step by filling last rounds, the half alone does not have.  Measured alone, us of the large / of the step's
+// workgroups: dQ of 7496 rows x 634 keys x 16 heads x 128 90 / 120, 7696 x 530 x 32 x 64 97 / 134; dK / dV of 7599 x 1171 x 24 / 8 x 64
+// 155 / 220, 5042 x 519 x 32 / 16 x 128 132 / 166.  Of the 7300 calls, 323 dQ and 125 dK / dV halves were more than 3 % slower than
+// in the large workgroups, up to 59 %; so 1 and 12, up to 18 %.
+inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, bool want_dkdv, BwdPlan* plan)
+{
+    using namespace hexi_shapes;
+    constexpr double MARGIN = 1.15;
+    hexi_plan_bwd_step(g, forced_run_len, plan);
+    if (want_dq && want_dkdv) return;
+    const bool wide = g.d == 128;
+    if (want_dq && plan->dq_rows > 0) {
+        Units u[3];
+        const int r = plan->dq_rows == 64 ? 1 : 2;
+        const double mb = (double)g.lq * g.nq * g.d * 12.0 * 1e-6;      // q and dO read, dq read and written
+        if (hexi_q_units(g, u) && MARGIN * DQ[wide][r].us(u[r], mb) >= DQ[wide][0].us(u[0], mb)) plan->dq_rows = 0;
+    }
+    if (want_dkdv && plan->split_keys) {
+        auto estimate = [&](int keys, int len) {
+            const DkdvFit& f = DKDV[wide][keys == KV_TILE ? 0 : 1];
+            HeadRuns runs;
+            const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, len, &runs);
+            Units u;
+            for (int t = 0; t < plan->n_known; ++t) {
+                if (plan->seen[t] < 1.0f) continue;
+                const int cols = t == plan->n_kv_tiles - 1 ? g.lc - t * KV_TILE : KV_TILE;
+                u.add(keys == KV_TILE ? len * plan->seen[t] : ceil(len * plan->seen[t] / 4.0), (long long)runs.n * ((cols + keys - 1) / keys));
+            }
+            const double run_mb = (double)g.lc * g.d * 8.0 * 1e-6;      // dk and dv of a run
+            return f.launch.us(u, run_mb * g.nkv) + (shared || plan->unused ? f.clear : 0.0) + (shared ? run_mb * runs.n * f.atomic_mb : 0.0);
+        };
+        if (MARGIN * estimate(32, plan->run_len) >= estimate(KV_TILE, plan->run_len_128)) {
+            plan->split_keys = false;
+            plan->run_len = plan->run_len_128;
         }
     }
 }

@@ -1,7 +1,8 @@
 // Host-side view of the launch rules (csrc/hexi_shapes.h).  Reads one ring step per line from stdin:
 //   head_dim nq nkv forced_run_len  n_q_segs (start len)...  n_kv_segs (start len)...  [kv_of_q ...]
 // and prints: rows per forward workgroup (0: 256), rows per dQ workgroup (0: 256), keys per dK / dV workgroup, q heads per dK / dV
-// workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take.
+// workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take; then, for
+// calls for one half alone, the rows per dQ workgroup and the keys per dK / dV workgroup.
 #include <cstdio>
 #include <cstring>
 #include <iostream>
@@ -42,11 +43,15 @@ int main()
         int m;
         for (int h = 0; h < g.nq; ++h) g.kv_of_q[h] = (signed char)((is >> m) ? m : h / (g.nq / g.nkv));
         BwdPlan plan;
-        hexi_plan_bwd(g, forced, &plan);
+        hexi_plan_bwd(g, forced, true, true, &plan);
         HeadRuns runs;
         const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len, &runs);
         const bool shared_128 = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len_128, &runs);
-        std::printf("%d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared, (int)shared_128);
+        BwdPlan dq_alone, dkdv_alone;
+        hexi_plan_bwd(g, forced, true, false, &dq_alone);
+        hexi_plan_bwd(g, forced, false, true, &dkdv_alone);
+        std::printf("%d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
+                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128);
     }
     return 0;
 }

@@ -26,7 +26,7 @@ def shapes(tmp_path_factory):
             m = " ".join(map(str, more[0])) if more and more[0] else ""
             lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
-        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128")
+        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone")
         return [dict(zip(names, map(int, line.split()))) for line in out if line]
 
     return ask
@@ -55,3 +55,29 @@ def test_smallest_and_largest_launches(shapes):
     (2048, 2048, 24, 8, 128, 2048, 0)])
 def test_forward_takes_the_shape_measured_faster(shapes, lq, lc, nq, nkv, d, off, rows):
     assert shapes([_step(lq, lc, nq, nkv, d, off)])[0]["fwd_rows"] == rows
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off,dq_alone,keys_alone", [
+    # a step in joint split launches whose halves are slower there by themselves; us of dQ in 256 / 64 rows, of dK / dV in 128 / 32 keys:
+    # 90 / 120; 97 / 134; 155 / 220; 38 / 50
+    (7496, 634, 16, 4, 128, 634, 0, None), (7696, 530, 32, 4, 64, 430, 0, None), (7599, 1171, 24, 8, 64, 0, None, 128),
+    (1016, 390, 64, 8, 64, 390, 0, 128),
+    # 50 / 21, 46 / 22; 35 / 15 (11 in 32 rows), 24 / 11.5: faster alone as well
+    (512, 1024, 24, 8, 128, 1024, 64, 32), (300, 700, 4, 2, 128, 700, 32, 32)])
+def test_a_half_by_itself_is_not_sent_to_a_slower_shape(shapes, lq, lc, nq, nkv, d, off, dq_alone, keys_alone):
+    got = shapes([_step(lq, lc, nq, nkv, d, off)])[0]
+    assert got["keys"] == 32 and (dq_alone is None or got["dq_alone"] == dq_alone) and (keys_alone is None or got["keys_alone"] == keys_alone)
+
+
+def test_no_step_gets_atomics_that_its_128_key_launch_would_not_have(shapes):
+    import random
+    rng = random.Random(11)
+    log_int = lambda lo, hi: round(2.0 ** rng.uniform(lo, hi))
+    steps = []
+    for _ in range(3000):
+        nkv = rng.choice([1, 2, 3, 8, 16])
+        nq = nkv * rng.choice([1, 2, 3, 4, 8])
+        if nq <= 128:
+            lq, lc = log_int(0, 14), log_int(0, 16)
+            steps.append(_step(lq, lc, nq, nkv, rng.choice([64, 128]), rng.choice([0, lc, rng.randrange(lc)])))
+    assert all(got["atomic"] <= got["atomic_128"] for got in shapes(steps))
