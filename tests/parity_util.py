@@ -65,3 +65,17 @@ def chunk_slices(w, j, x_global, n_keys):
             seg[:hi - s] = x_global[s:hi]
         parts.append(seg)
     return np.concatenate(parts, axis=0)
+
+
+# Ring steps (rows, keys, q heads, kv heads, head_dim) that the launchers give to the 256-row forward and dQ workgroups (dQ in a call
+# for it alone): 256 units, one round of the chip.  The smaller sizes of the other tests go to the kernels for small launches.
+# Row counts one past a tile, one short of it and whole tiles; key counts around the 64-key tiles, up to more than four of them, from
+# two (with a single key dS is zero, and dq nothing to be relative to).
+LARGE_STEPS = [(769, 2, 64, 8, 128), (800, 65, 64, 16, 128), (1023, 129, 64, 4, 128), (1024, 320, 64, 64, 128), (1793, 257, 32, 8, 128),
+               (769, 64, 64, 8, 64), (1000, 193, 64, 16, 64), (1024, 385, 64, 4, 64), (511, 577, 128, 16, 64)]
+
+
+# A shard (128 heads of 1800 rows: at 1024 units every step is large) and chunks in several segments, with holes, diagonal parts and
+# keys that only the last rows see; a kv head's q heads are not adjacent.
+LARGE_SHARD = dict(nq=128, nkv=8, q_segs=[(300, 400), (900, 1), (1000, 1399)],
+                   chunks=[[(0, 180), (290, 110)], [(500, 1), (890, 130)], [(2300, 150)]], kv_of_q=[(5 * h + h // 8) % 8 for h in range(128)])

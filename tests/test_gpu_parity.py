@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import check, chunk_slices, oracle_full, to64
+from parity_util import LARGE_SHARD, LARGE_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -245,9 +245,9 @@ def test_strided_inputs_and_accumulate_flags(run_len, force_run_len):
 
 @pytest.mark.parametrize("d", [128, 64])
 def test_dq_residuals_of_large_ds(d):
-    # The dQ kernel adds the rounding residuals of a 32-key block's dS when some |dS| >= 2.  With dO scaled by 64 (exact
+    # The dQ kernels add the rounding residuals of a 32-key block's dS when some |dS| >= 2.  With dO scaled by 64 (exact
     # in bf16; every gradient is linear in dO) nearly every block takes that path -- masked and unmasked tiles, ragged
-    # tails, both groups of a workgroup -- and dq / 64 must still match the oracle, more closely than without the scaling
+    # tails -- here in the kernel for small launches; test_large_workgroups_residuals has the 256-row one -- and dq / 64 must still match the oracle, more closely than without the scaling
     # (dS carried to fp32 accuracy instead of bf16); dk and dv, which have no such path, must come out as exactly 64 x
     # their unscaled values.
     w = _custom(f"residual_{d}", "bf16", 4, 2, d, 1500, [(60, 200), (700, 777)], [[(0, 333)], [(333, 617), (950, 27)], [(977, 523)]],
@@ -371,8 +371,9 @@ def test_forward_is_deterministic():
 
 @pytest.mark.parametrize("lq,lc", [(1, 1), (63, 65), (255, 64), (256, 129), (257, 300), (600, 192), (513, 1)])
 def test_workgroup_boundary_sizes(lq, lc):
-    # shard / chunk lengths just below, at and above the kernels' workgroup tiles (256 q rows, 128 / 64 keys):
-    # one, two and a fraction of a tile, a single row, a single key; two chunks so that the second is diagonal
+    # shard / chunk lengths just below, at and above multiples of 32, 64, 128 and 256 rows and keys, a single row, a single
+    # key; two chunks so that the second is diagonal (launches this small take 32- and 64-row workgroups; the 256-row
+    # ones: test_large_workgroups_boundary_sizes)
     l_tot = lc + lq
     q_segs = [(lc, lq)]
     chunks = [[(0, lc)], [(lc, lq)]]
@@ -382,11 +383,10 @@ def test_workgroup_boundary_sizes(lq, lc):
 
 @pytest.mark.parametrize("d", [128, 64])
 def test_forward_exact_softmax_fallback(d):
-    # The fast forward path fixes each row's softmax reference after its first key tile and repeats the
-    # workgroup with the exact online softmax when a row's sum leaves [2^-60, 2^60].  Keys beyond the first
-    # tile are scaled so that later scores exceed the first tile's maximum by far more than 2^100 (rows 0-255,
-    # both wave groups, upward), and a second shard does the reverse (first tile huge, the rest tiny: downward
-    # is harmless but must stay exact too).  Everything is compared with the oracle.
+    # Scores that leave the range of a fixed softmax reference: keys beyond the first 64 are scaled so that later scores
+    # exceed the earlier maximum by far more than 2^100, and a second shard does the reverse (the first keys huge, the rest
+    # tiny).  A launch this small runs the kernel with a running maximum per wavefront, whose parts differ by those
+    # factors when they are combined; the 256-row kernel's fallback: test_large_workgroups_softmax_fallback.
     dev = torch.device(DEV)
     g = torch.Generator().manual_seed(99)
     lq, lc, nq = 300, 640, 2
@@ -514,7 +514,8 @@ def _exact_ds_case(lq, lc, nq, nkv, d, seed):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("lq,lc,nq,nkv", [(1, 1, 1, 1), (40, 100, 2, 1), (300, 700, 4, 2), (512, 1000, 24, 8), (300, 2100, 128, 8)])
+@pytest.mark.parametrize("lq,lc,nq,nkv", [(1, 1, 1, 1), (40, 100, 2, 1), (300, 700, 4, 2), (512, 1000, 24, 8), (300, 2100, 128, 8),
+                                          (1024, 320, 64, 64), (1024, 385, 64, 4)])      # the last two: 256-row workgroups
 def test_large_ds_reaches_dq_unrounded(lq, lc, nq, nkv, d):
     # a dS of 24 significant bits must come out of the dQ kernels bit for bit (a residual rounded to bf16 loses up to
     # 2^-18 of it)
@@ -640,3 +641,143 @@ def test_f32_dq_of_chunks_on_two_streams(nq, nkv, lq, d):
                                  run.dk[j], run.dv[j], stream=streams[j % 2].cuda_stream)
     torch.cuda.synchronize()
     check("dq", run.dq.cpu(), ref["dq"], "f32")
+
+
+def _large_step_inputs(lq, lc, nq, nkv, d, seed, k_scale=1.0):
+    g = torch.Generator().manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g)
+    q, d_o, v = rnd(lq, nq, d), rnd(lq, nq, d), rnd(lc, nkv, d)
+    return [t.to(torch.bfloat16) for t in (q, d_o, rnd(lc, nkv, d) * k_scale, v)]
+
+
+def _large_backward(q, k, v, d_o, o, lse, q_segs, kv_segs, scale, kv_of_q=None, delta=None):
+    """dq, dk, dv of one step, the halves in calls of their own (dq in 256-row workgroups)."""
+    desc = hexi.desc_for(q, k, scale, kv_of_q)
+    flags = hexi.HEXI_COMPUTE_DELTA if delta is None else 0
+    delta = torch.empty_like(lse) if delta is None else delta
+    dq = torch.zeros(q.shape, dtype=torch.float32, device=DEV)
+    dk, dv = torch.empty(k.shape, dtype=torch.float32, device=DEV), torch.empty(k.shape, dtype=torch.float32, device=DEV)
+    hexi.hexi_attn_bwd_chunk(desc, q_segs, kv_segs, q, k, v, o, d_o, lse, delta, dq, None, None, flags=flags | hexi.HEXI_SKIP_DKDV)
+    hexi.hexi_attn_bwd_chunk(desc, q_segs, kv_segs, q, k, v, None, d_o, lse, delta, None, dk, dv, flags=hexi.HEXI_SKIP_DQ)
+    return dq, dk, dv
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", LARGE_STEPS)
+@pytest.mark.parametrize("diagonal", [False, True])
+def test_large_workgroups_boundary_sizes(lq, lc, nq, nkv, d, diagonal):
+    # 256-row workgroups: last q tiles of 1, 32 and 255 rows and whole ones; 1, 64, 65, ... keys; fully and partly visible
+    off = lc // 2 if diagonal else lc
+    print(f"\n  large step: {lq} x {lc} x {nq}/{nkv} x {d} at {off}", flush=True)
+    q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
+    qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+    o, lse = torch.empty(q.shape, dtype=torch.float32, device=DEV), torch.empty((nq, lq), device=DEV)
+    q_segs, kv_segs, scale = [(off, lq)], [(0, lc)], d ** -0.5
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(qd, kd, scale), q_segs, kv_segs, qd, kd, vd, o, lse)
+    dq, dk, dv = _large_backward(qd, kd, vd, gd, o, lse, q_segs, kv_segs, scale)
+    q_pos = np.arange(off, off + lq)
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), q_pos, to64(k), to64(v), np.arange(lc), scale)
+    ref = oracle.attn_bwd(to64(q), q_pos, to64(k), to64(v), np.arange(lc), to64(d_o), scale)
+    for name, got, want in (("o", o, o_ref), ("lse", lse, lse_ref), ("dq", dq, ref["dq"]), ("dk", dk, ref["dk"]), ("dv", dv, ref["dv"])):
+        # (a key seen by few rows among 64 heads has gradients of several units: the bf16 bound on a single element is relative there)
+        check(name, got.cpu(), want, "bf16", abs_factor=max(1.0, float(np.max(np.abs(want))) / 8) if name in ("dk", "dv") else 1.0)
+
+
+@pytest.mark.parametrize("d,run_len", [(64, 0), (64, 3), (128, 0), (128, 16)])
+def test_large_workgroups_segments_strides_and_head_map(d, run_len, force_run_len):
+    # strided q / dO and k / v, three-segment shard, chunks with holes and diagonal parts, accumulated o / lse / dq, dk / dv
+    # under HEXI_ACCUMULATE; dK / dV in the launcher's shape and in 128-key workgroups walking whole groups or runs with a remainder
+    force_run_len(run_len)
+    s = LARGE_SHARD
+    nq, nkv, q_segs, kv_of_q, scale = s["nq"], s["nkv"], s["q_segs"], s["kv_of_q"], d ** -0.5
+    print(f"\n  large shard: d={d} run_len={run_len}", flush=True)
+    g = torch.Generator().manual_seed(d + run_len)
+    rnd = lambda *x: torch.randn(x, generator=g).to(torch.bfloat16)
+    q_pos = np.concatenate([np.arange(a, a + n) for a, n in q_segs])
+    kv_pos = [np.concatenate([np.arange(a, a + n) for a, n in ch]) for ch in s["chunks"]]
+    lq = len(q_pos)
+    q, d_o = rnd(lq, nq, d), rnd(lq, nq, d)
+    ks, vs = [rnd(len(p), nkv, d) for p in kv_pos], [rnd(len(p), nkv, d) for p in kv_pos]
+
+    def strided(t):
+        big = torch.zeros((t.shape[0], t.shape[1] + 1, t.shape[2] + 8), dtype=t.dtype, device=DEV)
+        big[:, :-1, 8:] = t.to(DEV)
+        return big[:, :-1, 8:]
+
+    qd, gd, kd, vd = strided(q), strided(d_o), [strided(t) for t in ks], [strided(t) for t in vs]
+    o, lse = torch.zeros((lq, nq, d), device=DEV), torch.full((nq, lq), -float("inf"), device=DEV)
+    delta, dq = torch.empty((nq, lq), device=DEV), torch.zeros((lq, nq, d), device=DEV)
+    desc = [hexi.desc_for(qd, t, scale, kv_of_q) for t in kd]
+    for j, ch in enumerate(s["chunks"]):
+        hexi.hexi_attn_fwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], o, lse, flags=hexi.HEXI_ACCUMULATE)
+    dk, dv = [torch.full(t.shape, 0.5, device=DEV) for t in ks], [torch.full(t.shape, -0.25, device=DEV) for t in ks]
+    for j, ch in enumerate(s["chunks"]):
+        hexi.hexi_attn_bwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], o, gd, lse, delta, dq, None, None,
+                                 flags=hexi.HEXI_SKIP_DKDV | (hexi.HEXI_COMPUTE_DELTA if j == 0 else 0))
+        hexi.hexi_attn_bwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], None, gd, lse, delta, None, dk[j], dv[j],
+                                 flags=hexi.HEXI_SKIP_DQ | hexi.HEXI_ACCUMULATE)
+    k64, v64, p64 = np.concatenate([to64(t) for t in ks]), np.concatenate([to64(t) for t in vs]), np.concatenate(kv_pos)
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), q_pos, k64, v64, p64, scale, kv_of_q)
+    ref = oracle.attn_bwd(to64(q), q_pos, k64, v64, p64, to64(d_o), scale, kv_of_q)
+    check("o", o.cpu(), o_ref, "bf16")
+    check("lse", lse.cpu(), lse_ref, "bf16")
+    check("dq", dq.cpu(), ref["dq"], "bf16")
+    for name, got, want in (("dk", torch.cat(dk).cpu().numpy() - 0.5, ref["dk"]), ("dv", torch.cat(dv).cpu().numpy() + 0.25, ref["dv"])):
+        check(name, got, want, "bf16", abs_factor=max(1.0, float(np.max(np.abs(want))) / 8))
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(1024, 320, 64, 64, 128), (1024, 385, 64, 4, 64)])
+def test_large_workgroups_softmax_fallback(lq, lc, nq, nkv, d):
+    # The 256-row forward kernel fixes each row's softmax reference at its first key tile and repeats the workgroup with the
+    # exact online softmax when a row's sum leaves [2^-60, 2^60].  Every second kv head scales the keys beyond the first
+    # tile so that later scores exceed the first tile's maximum by far more than 2^100; the others do the reverse.
+    q, _, k, v = _large_step_inputs(lq, lc, nq, nkv, d, 99)
+    q = (q.float() * 3).to(torch.bfloat16)
+    k = k.float()
+    k[64:, ::2] *= 60.0
+    k[:64, 1::2] *= 60.0
+    k[64:, 1::2] *= 0.02
+    k = k.to(torch.bfloat16)
+    print(f"\n  large fallback: {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    o, lse = torch.empty(q.shape, dtype=torch.float32, device=DEV), torch.empty((nq, lq), device=DEV)
+    for off in (lc, lc // 2):
+        hexi.hexi_attn_fwd_chunk(hexi.desc_for(qd, kd, d ** -0.5), [(off, lq)], [(0, lc)], qd, kd, vd, o, lse)
+        o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(off, off + lq), to64(k), to64(v), np.arange(lc), d ** -0.5)
+        assert float(np.max(lse_ref) - np.min(lse_ref)) > 50.0
+        check("o", o.cpu(), o_ref, "bf16")
+        check("lse", lse.cpu(), lse_ref, "bf16")
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(1024, 320, 64, 64, 128), (1024, 385, 64, 4, 64)])
+def test_large_workgroups_residuals(lq, lc, nq, nkv, d):
+    # test_dq_residuals_of_large_ds in the 256-row dQ kernel, whose residuals are fp32 products
+    q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, 41, k_scale=2.0)
+    off, scale = lc // 2, d ** -0.5
+    print(f"\n  large residuals: {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
+    qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+    o, lse = torch.empty(q.shape, dtype=torch.float32, device=DEV), torch.empty((nq, lq), device=DEV)
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(qd, kd, scale), [(off, lq)], [(0, lc)], qd, kd, vd, o, lse)
+    plain = _large_backward(qd, kd, vd, gd, o, lse, [(off, lq)], [(0, lc)], scale)[0]
+    big = _large_backward(qd, kd, vd, gd * 64, o, lse, [(off, lq)], [(0, lc)], scale)[0]
+    ref = oracle.attn_bwd(to64(q), np.arange(off, off + lq), to64(k), to64(v), np.arange(lc), to64(d_o), scale)
+    e_plain, _ = check("dq", plain.cpu(), ref["dq"], "bf16")
+    e_big, _ = check("dq with residuals everywhere", (big / 64).cpu(), ref["dq"], "bf16")
+    assert float((big / 64 != plain).float().mean()) > 0.5 and e_big <= e_plain
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nq,nkv,lq,lc", [(16, 2, 1000, 1010), (32, 16, 1000, 1010), (16, 16, 100, 1010), (6, 3, 77, 90)])
+def test_f32_grouped_heads_in_both_shapes(nq, nkv, lq, lc, d):
+    # fp32 with several q heads per kv head: dQ in 64-row shared and dK / dV in 16-row split workgroups (two launches), both
+    # shared, the other way round, both split; the halves together and in calls of their own, with the same bits (no sum is
+    # spread over workgroups)
+    w = _custom(f"f32_gqa_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
+    run, inputs, ref = _run_and_compare(w, seed=lq + lc + d)
+    dq = torch.zeros_like(run.dq)
+    for j, ch in enumerate(w.chunks):
+        dk, dv = torch.full_like(run.dk[j], 7.0), torch.full_like(run.dv[j], 7.0)
+        args = (run.desc[j], w.q_segs, ch, run.q, run.k[j], run.v[j], None, run.d_o, run.lse, run.delta)
+        hexi.hexi_attn_bwd_chunk(*args, dq, None, None, flags=hexi.HEXI_SKIP_DKDV)
+        hexi.hexi_attn_bwd_chunk(*args, None, dk, dv, flags=hexi.HEXI_SKIP_DQ)
+        assert torch.equal(dk, run.dk[j]) and torch.equal(dv, run.dv[j])
+    assert torch.equal(dq, run.dq)

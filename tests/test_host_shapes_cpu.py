@@ -81,3 +81,10 @@ def test_no_step_gets_atomics_that_its_128_key_launch_would_not_have(shapes):
             lq, lc = log_int(0, 14), log_int(0, 16)
             steps.append(_step(lq, lc, nq, nkv, rng.choice([64, 128]), rng.choice([0, lc, rng.randrange(lc)])))
     assert all(got["atomic"] <= got["atomic_128"] for got in shapes(steps))
+
+
+def test_the_large_workgroups_tests_reach_them(shapes):
+    from parity_util import LARGE_SHARD as s, LARGE_STEPS
+    steps = [_step(lq, lc, nq, nkv, d, off) for lq, lc, nq, nkv, d in LARGE_STEPS for off in (lc, lc // 2)]
+    steps += [(d, s["nq"], s["nkv"], s["q_segs"], ch, s["kv_of_q"]) for d in (64, 128) for ch in s["chunks"]]
+    assert [(got["fwd_rows"], got["dq_alone"]) for got in shapes(steps)] == [(0, 0)] * len(steps)
