@@ -10,7 +10,7 @@
 // transfers into LDS (16 KB per block and wavefront) hold it while it issues them and while it waits.  With 64 rows per
 // workgroup (forward and dQ) two wavefronts share every streamed block, double-buffered: 1.4 us per block, but chains twice
 // as long.  The large kernels stream an eighth as much per row and stay the better choice once they fill the chip: see the
-// rules in the launchers.  Measured, us per call (head_dim 128, fully visible chunk), large workgroups -> these:
+// rules in hexi_shapes.h.  Measured, us per call (head_dim 128, fully visible chunk), large workgroups -> these:
 //   512 rows x 1024 keys, 24 / 8 heads: forward 32.0 -> 16.3, dQ 47.6 -> 20.3, dK/dV 46.3 -> 21.2;
 //   300 x 700, 4 / 2 heads: 27.5 -> 9.7, 35.3 -> 11.2, 23.9 -> 11.5.
 //
