@@ -407,10 +407,11 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
         if (e != hipSuccess) return e;
     }
     if (a.g.d != 128 && a.g.d != 64) return hipErrorInvalidValue;
-    if (plan.split_keys && a.want_dkdv) {
-        const hipError_t e = hexi_launch_bwd_split_bf16(a, a.want_dq ? dq_rows : 0, runs, shared, s);     // with the dQ, if that is split too
+    if (plan.split_keys && a.want_dkdv) {                  // with the dQ, if that is cut to the same width
+        const bool with_dq = a.want_dq && dq_rows == plan.keys;
+        const hipError_t e = plan.keys == 64 ? hexi_launch_bwd_quad_bf16(a, with_dq, runs, shared, s) : hexi_launch_bwd_split_bf16(a, with_dq, runs, shared, s);
         if (e != hipSuccess) return e;
-        dq_done |= dq_rows > 0;
+        dq_done |= with_dq;
     } else if (grid > 0) {
         if (a.g.d == 128) {
             if (shared) bwd_dkdv_bf16_kernel<128, true><<<grid, 512, 0, s>>>(a, runs, n_kv_tiles, split);
@@ -424,5 +425,6 @@ hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
     if (e != hipSuccess) return e;
     if (dq_done) return hipSuccess;
     runs.n = 0;
-    return dq_rows > 0 ? hexi_launch_bwd_split_bf16(a, dq_rows, runs, false, s) : hexi_launch_bwd_dq_bf16(a, s);
+    if (dq_rows == 64) return hexi_launch_bwd_quad_bf16(a, true, runs, false, s);
+    return dq_rows == 32 ? hexi_launch_bwd_split_bf16(a, true, runs, false, s) : hexi_launch_bwd_dq_bf16(a, s);
 }

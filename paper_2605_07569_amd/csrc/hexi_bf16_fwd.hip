@@ -476,7 +476,7 @@ __global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const in
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
-    if (const int rows = hexi_fwd_split_rows(g); rows > 0) return hexi_launch_fwd_split_bf16(a, rows, s);
+    if (const int rows = hexi_fwd_split_rows(g); rows > 0) return rows == 64 ? hexi_launch_fwd_quad_bf16(a, s) : hexi_launch_fwd_split_bf16(a, s);
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
     // cost of a unit: the key tiles its q tile streams, plus the prologue and epilogue (about six tiles' worth);
     // a unit that sees nothing of the chunk returns at once under HEXI_ACCUMULATE and only writes zeros otherwise

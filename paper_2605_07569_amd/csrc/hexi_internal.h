@@ -136,9 +136,12 @@ hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s);      // dK/dV kernel, then the dQ kernel
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);      // 256-row workgroups
-// the same steps with 32 or 64 (`rows`) stationary rows per workgroup, for launches that do not fill the chip otherwise
-hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, int rows, hipStream_t s);
-hipError_t hexi_launch_bwd_split_bf16(const BwdArgs& a, int dq_rows, const HeadRuns& runs, bool shared, hipStream_t s);
+// the same steps in workgroups of 32 stationary rows (eight wavefronts split the streamed rows) ...
+hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, hipStream_t s);
+hipError_t hexi_launch_bwd_split_bf16(const BwdArgs& a, bool dq, const HeadRuns& runs, bool shared, hipStream_t s);
+// ... and of 64 (four), for launches that do not fill the chip with the large ones
+hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, hipStream_t s);
+hipError_t hexi_launch_bwd_quad_bf16(const BwdArgs& a, bool dq, const HeadRuns& runs, bool shared, hipStream_t s);
 hipError_t hexi_launch_merge(long long n_rows, int nq, int d, float* o_acc, float* lse_acc, const float* o_part,
                              const float* lse_part, void* o_final, int o_final_dtype, hipStream_t s);
 hipError_t hexi_launch_delta(long long lq, int nq, int d, const float* o, const void* d_o, int dtype,

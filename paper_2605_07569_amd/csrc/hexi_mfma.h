@@ -103,6 +103,11 @@ __device__ __forceinline__ void lds_dma4(const void* gptr, uint32_t lds_addr)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(gptr) : "memory");
 }
 
+__device__ __forceinline__ void lds_dma4_base(const void* base, uint32_t byte_off, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(byte_off), "s"(base) : "memory");
+}
+
 // LDS reads issued through inline assembly with a compile-time offset field, for software pipelines whose
 // address registers must stay exactly the ones the kernel computed (the compiler otherwise materialises
 // one address register per buffer).  The compiler does not see these reads: the destination is valid

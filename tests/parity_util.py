@@ -79,3 +79,10 @@ LARGE_STEPS = [(769, 2, 64, 8, 128), (800, 65, 64, 16, 128), (1023, 129, 64, 4, 
 # keys that only the last rows see; a kv head's q heads are not adjacent.
 LARGE_SHARD = dict(nq=128, nkv=8, q_segs=[(300, 400), (900, 1), (1000, 1399)],
                    chunks=[[(0, 180), (290, 110)], [(500, 1), (890, 130)], [(2300, 150)]], kv_of_q=[(5 * h + h // 8) % 8 for h in range(128)])
+
+# Steps that the launch rules send to workgroups of 64 rows or keys: (lq, lc, nq, nkv, d, halves of the step that go there).  Blocks of 32
+# rows and tiles of 64 by one more and one less, fewer rows than a block, runs of heads with and without atomics, chains of one
+# block and of the unrolled loop and its remainder.
+QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 64, 64, 128, "b"), (17, 129, 64, 64, 64, "b"), (65, 33, 64, 64, 64, "b"),
+              (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "fb"), (200, 65, 64, 64, 128, "fb"),
+              (200, 33, 128, 8, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]

@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import LARGE_SHARD, LARGE_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -781,3 +781,45 @@ def test_f32_grouped_heads_in_both_shapes(nq, nkv, lq, lc, d):
         hexi.hexi_attn_bwd_chunk(*args, None, dk, dv, flags=hexi.HEXI_SKIP_DQ)
         assert torch.equal(dk, run.dk[j]) and torch.equal(dv, run.dv[j])
     assert torch.equal(dq, run.dq)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [s[:5] for s in QUAD_STEPS])
+def test_64_wide_workgroup_shapes(lq, lc, nq, nkv, d):
+    # one chunk fully visible and one diagonal in two segments, K scaled by 3 (scores that raise the running maximum, large dS), through
+    # the whole replay: the second chunk merges into the first one's o / lse and adds to its dq
+    w = _custom(f"quad_{nq}_{lq}_{lc}_{d}", "bf16", nq, nkv, d, lc + lq + 7, [(lc, lq // 2), (lc + lq // 2 + 7, lq - lq // 2)],
+                [[(0, lc)], [(lc, lq // 2 + 7), (lc + lq // 2 + 7, lq - lq // 2)]], k_scale=3.0)
+    print(f"\n[{w.name}]", flush=True)
+    inputs = wl.make_inputs(w, lq * 1000 + lc + d)
+    run = replay.ShardRun(w, inputs, DEV)
+    run.step()
+    torch.cuda.synchronize()
+    ref = oracle_full(w, inputs)
+    for name, got, want in (("o", run.o, ref["o"]), ("lse", run.lse, ref["lse"]), ("dq", run.dq, ref["dq"])):
+        check(name, got.cpu(), want, "bf16")
+    for j in range(2):
+        for name, got in (("dk", run.dk[j]), ("dv", run.dv[j])):
+            want = chunk_slices(w, j, ref[name], ref["n_keys"])
+            # P and dS are rounded to bf16, 2^-9 of each product: an element of dv is off by up to 2^-9 sum P |dO| over the rows and heads
+            # that see the key, 2e-2 where that sum is 10; with 16 heads to a group and peaked rows it reaches twice the largest |dv|
+            check(f"{name}[{j}]", got.cpu(), want, "bf16", abs_factor=max(1.0, float(np.max(np.abs(want))) / 5.0))
+
+
+def test_64_wide_workgroups_accumulate():
+    # dk / dv under HEXI_ACCUMULATE (plain stores and atomics): the running value plus the gradient
+    for lq, lc, nq, nkv, d, _ in (s for s in QUAD_STEPS if s[0] in (129, 260)):
+        q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq)
+        qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+        q_segs, kv_segs, scale = [(lc // 2, lq)], [(0, lc)], d ** -0.5
+        o, lse, delta = torch.empty(q.shape, device=DEV), torch.empty((nq, lq), device=DEV), torch.empty((nq, lq), device=DEV)
+        desc = hexi.desc_for(qd, kd, scale)
+        hexi.hexi_attn_fwd_chunk(desc, q_segs, kv_segs, qd, kd, vd, o, lse)
+        outs = []
+        for flags in (0, hexi.HEXI_ACCUMULATE):
+            dq = torch.zeros(q.shape, device=DEV)
+            dk, dv = torch.full(k.shape, 0.5, device=DEV), torch.full(v.shape, -0.25, device=DEV)
+            hexi.hexi_attn_bwd_chunk(desc, q_segs, kv_segs, qd, kd, vd, o, gd, lse, delta, dq, dk, dv, flags=flags | hexi.HEXI_COMPUTE_DELTA)
+            outs.append((dk, dv))
+        # (the same sums, in another order where they are atomic)
+        bound = 1e-5 * float(outs[0][0].abs().max() + outs[0][1].abs().max() + 1.0)
+        assert float((outs[1][0] - outs[0][0] - 0.5).abs().max()) <= bound and float((outs[1][1] - outs[0][1] + 0.25).abs().max()) <= bound

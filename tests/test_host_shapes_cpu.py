@@ -88,3 +88,12 @@ def test_the_large_workgroups_tests_reach_them(shapes):
     steps = [_step(lq, lc, nq, nkv, d, off) for lq, lc, nq, nkv, d in LARGE_STEPS for off in (lc, lc // 2)]
     steps += [(d, s["nq"], s["nkv"], s["q_segs"], ch, s["kv_of_q"]) for d in (64, 128) for ch in s["chunks"]]
     assert [(got["fwd_rows"], got["dq_alone"]) for got in shapes(steps)] == [(0, 0)] * len(steps)
+
+
+def test_the_64_wide_workgroups_tests_reach_them(shapes):
+    from parity_util import QUAD_STEPS
+    steps = [(_step(lq, lc, nq, nkv, d, off), halves) for lq, lc, nq, nkv, d, halves in QUAD_STEPS for off in (lc, lc // 2)]
+    for (step, halves), got in zip(steps, shapes([s for s, _ in steps])):
+        # (dQ workgroups of 64 rows are only ever paired with dK / dV workgroups of 64 keys or of 128)
+        assert "f" not in halves or got["fwd_rows"] == 64, step
+        assert "b" not in halves or (got["dq_rows"] == 64 and got["keys"] < 128), step
