@@ -147,9 +147,13 @@ def _ptr(t):
 
 
 def _stream(stream):
+    """The stream's handle.  Asked of torch's C++ side directly: the Stream object of torch.cuda.current_stream() costs as much as the
+    launch itself."""
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        if not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream)
 
 
@@ -183,11 +187,13 @@ def hexi_shard_mask(q_segs, kv_segs, tile_m=0, tile_n=0, want_pos=True, want_cla
 
 
 def hexi_attn_fwd_chunk(desc, q_segs, kv_segs, q, k, v, o, lse, flags=0, workspace=None, stream=None):
-    qr, _k1 = make_range(q_segs)
-    kr, _k2 = make_range(kv_segs)
+    qr = q_segs if isinstance(q_segs, hexi_range) else make_range(q_segs)[0]
+    kr = kv_segs if isinstance(kv_segs, hexi_range) else make_range(kv_segs)[0]
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().hexi_attn_fwd_chunk(ctypes.byref(desc), ctypes.byref(qr), ctypes.byref(kr), _ptr(q), _ptr(k), _ptr(v),
-                                      _ptr(o), _ptr(lse), flags, _ptr(workspace), ws_bytes, _stream(stream)))
+    rc = (_lib or load()).hexi_attn_fwd_chunk(desc, qr, kr, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), flags,
+                                              _ptr(workspace), ws_bytes, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def hexi_attn_merge_lse(o_acc, lse_acc, o_part, lse_part, o_final=None, stream=None):
@@ -202,12 +208,13 @@ def hexi_attn_merge_lse(o_acc, lse_acc, o_part, lse_part, o_final=None, stream=N
 
 def hexi_attn_bwd_chunk(desc, q_segs, kv_segs, q, k, v, o, d_o, lse, delta, dq_acc, dk, dv, flags=0,
                         workspace=None, stream=None):
-    qr, _k1 = make_range(q_segs)
-    kr, _k2 = make_range(kv_segs)
+    qr = q_segs if isinstance(q_segs, hexi_range) else make_range(q_segs)[0]
+    kr = kv_segs if isinstance(kv_segs, hexi_range) else make_range(kv_segs)[0]
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().hexi_attn_bwd_chunk(ctypes.byref(desc), ctypes.byref(qr), ctypes.byref(kr), _ptr(q), _ptr(k), _ptr(v),
-                                      _ptr(o), _ptr(d_o), _ptr(lse), _ptr(delta), _ptr(dq_acc), _ptr(dk), _ptr(dv),
-                                      flags, _ptr(workspace), ws_bytes, _stream(stream)))
+    rc = (_lib or load()).hexi_attn_bwd_chunk(desc, qr, kr, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(d_o), _ptr(lse), _ptr(delta),
+                                              _ptr(dq_acc), _ptr(dk), _ptr(dv), flags, _ptr(workspace), ws_bytes, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def hexi_workspace_bytes(desc, lq, lc):
