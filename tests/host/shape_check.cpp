@@ -50,8 +50,10 @@ int main()
         BwdPlan dq_alone, dkdv_alone;
         hexi_plan_bwd(g, forced, true, false, &dq_alone);
         hexi_plan_bwd(g, forced, false, true, &dkdv_alone);
-        std::printf("%d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
-                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128);
+        QShare share;
+        const int fwd_rows = hexi_fwd_split_rows(g, &share), fwd_tiles = share.n_units(g.nq), all_tiles = g.nq * ((g.lq + 255) / 256);
+        std::printf("%d %d %d %d %d %d %d %d %d %d\n", fwd_rows, plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
+                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128, fwd_tiles, all_tiles - fwd_tiles);
     }
     return 0;
 }

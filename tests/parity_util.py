@@ -86,3 +86,7 @@ LARGE_SHARD = dict(nq=128, nkv=8, q_segs=[(300, 400), (900, 1), (1000, 1399)],
 QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 64, 64, 128, "b"), (17, 129, 64, 64, 64, "b"), (65, 33, 64, 64, 64, "b"),
               (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "fb"), (200, 65, 64, 64, 128, "fb"),
               (200, 33, 128, 8, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
+
+# Forward steps whose rows are shared by 256-row workgroups (whole rounds of 256 units) and 64-row ones behind them: as many tiles
+# of every head, and one tile more of some heads; last tiles of 1, 188 and 76 rows.
+SHARED_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]

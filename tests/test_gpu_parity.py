@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, SHARED_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -823,3 +823,23 @@ def test_64_wide_workgroups_accumulate():
         # (the same sums, in another order where they are atomic)
         bound = 1e-5 * float(outs[0][0].abs().max() + outs[0][1].abs().max() + 1.0)
         assert float((outs[1][0] - outs[0][0] - 0.5).abs().max()) <= bound and float((outs[1][1] - outs[0][1] + 0.25).abs().max()) <= bound
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", SHARED_STEPS)
+def test_forward_shared_by_large_and_64_row_workgroups(lq, lc, nq, nkv, d):
+    # every row exactly once, first alone, then merged into a running (o, lse)
+    q, _, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
+    qd, kd, vd = (t.to(DEV) for t in (q, k, v))
+    desc, q_segs, kv_segs = hexi.desc_for(qd, kd, d ** -0.5), [(lc, lq)], [(0, lc)]
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc, lc + lq), to64(k), to64(v), np.arange(lc), d ** -0.5)
+    o, lse = torch.full(q.shape, float("nan"), device=DEV), torch.full((nq, lq), float("nan"), device=DEV)
+    hexi.hexi_attn_fwd_chunk(desc, q_segs, kv_segs, qd, kd, vd, o, lse)
+    check("o", o.cpu(), o_ref, "bf16")
+    check("lse", lse.cpu(), lse_ref, "bf16")
+    g = torch.Generator().manual_seed(lq)
+    o0, lse0 = torch.randn(q.shape, generator=g), torch.randn((nq, lq), generator=g)
+    o, lse = o0.to(DEV), lse0.to(DEV)
+    hexi.hexi_attn_fwd_chunk(desc, q_segs, kv_segs, qd, kd, vd, o, lse, flags=hexi.HEXI_ACCUMULATE)
+    o_ref, lse_ref = oracle.merge(to64(o0), to64(lse0), o_ref, lse_ref)
+    check("o merged", o.cpu(), o_ref, "bf16")
+    check("lse merged", lse.cpu(), lse_ref, "bf16")
