@@ -40,13 +40,6 @@ __device__ __forceinline__ bf16x8 lds_tr(uint32_t a, uint32_t b)
 
 // At most N of this wavefront's transfers are still in flight (they complete in order).
 template <int N> __device__ __forceinline__ void wait_transfers() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// This wavefront's LDS reads have returned: the block they came from may be overwritten.
-__device__ __forceinline__ void reads_done()
-{
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // Workgroup barrier behind which LDS holds what the other wavefronts put there before it (after their own waits).
 __device__ __forceinline__ void block_barrier()

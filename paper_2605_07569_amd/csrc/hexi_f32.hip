@@ -12,6 +12,11 @@
 //     (16 of every 128) through a private piece of LDS without any barrier; their partial results are combined through
 //     LDS at the end.  Four times as many workgroups, each on a whole CU, which is what a short shard lacks: 3055 rows
 //     of 6 heads are 288 workgroups of 64 rows on 256 CUs (two rounds, the second one nearly empty) but 1146 of 16 rows.
+//   split, two a CU (TWO, head_dim 64): the same with one tile buffer instead of two, so that 65 KB (backward: 73) of LDS and 128
+//     registers leave room for a second workgroup: 4 wavefronts per SIMD instead of 2 cover each other's LDS reads, vector
+//     work and transfers, where with 2 the matrix pipes idle for a quarter of the time.  us, shared / split / two a CU, all
+//     keys visible: forward of 1500 rows and keys, 24 heads 168 / 181 / 143; backward of 2048, 8 / 8 heads 254 / 302 / 245,
+//     of 1500, 24 / 8 heads 529 / 507 / 411; diagonal: forward of 2048, 24 heads 155 / 179 / 135, backward 666 / 494 / 392.
 // What bounds it: the matrix pipes (256 flop / clk / CU, 157 TFLOP/s; a library product reaches 154).  A 16-byte LDS read
 // per lane feeds four MFMAs of 32 cycles, so LDS needs a quarter of its rate, and the vector work per 16 x 16 block of
 // scores (4 per lane) is ~40 operations against 2048 cycles of MFMA (D = 128).  Measured, executed flops of a launch that
@@ -32,6 +37,7 @@
 // (16 rows, one piece) and the column reads (one row, 16 pieces) then touch all 64 banks once.
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
+#include "hexi_shapes.h"
 
 namespace {
 
@@ -68,7 +74,7 @@ __device__ __forceinline__ float prob(float s, float c_hi, float c_lo, float nl_
     return fast_exp2(fmaf(s, c_hi, nl_hi) + fmaf(max2(s, -3.402823466e38f), c_lo, nl_lo));
 }
 
-template <int D_, bool SPLIT> struct F32Cfg {
+template <int D_, bool SPLIT, bool TWO> struct F32Cfg {
     static constexpr int D = D_;
     static_assert(D == 64 || D == 128, "head_dim 64 or 128");
     static constexpr bool PRIVATE = SPLIT;                 // the streamed rows of a wavefront are its own
@@ -81,9 +87,10 @@ template <int D_, bool SPLIT> struct F32Cfg {
     static constexpr int ROW_BYTES = 4 * D, PIECES = D / 4;
     static constexpr int TILE_BYTES = TK * ROW_BYTES;
     static constexpr int XFERS = TILE_BYTES / 1024 / NW;   // transfers per wavefront and tile (its own rows when split)
-    // Tile buffers: two, or one where two would not fit (128 KB for K and V): a wavefront with rows of its own refills its
-    // part as soon as it is done with it, and the other wavefront of the SIMD covers the wait.
-    static constexpr int NBUF = SPLIT && D == 128 ? 1 : 2;
+    // Tile buffers: two, or one where two would not fit (128 KB for K and V) or would leave no room for a second workgroup on the CU
+    // (TWO): a wavefront with rows of its own refills its part as soon as it is done with it, and the other wavefronts of the SIMD
+    // cover the wait.
+    static constexpr int NBUF = SPLIT && (D == 128 || TWO) ? 1 : 2;
     static constexpr int NG = D / 16;                      // 16-column groups of the head dimension
     static constexpr int NH = D / 64;                      // 64-column halves
     static constexpr int PITCH = D + 4;                    // floats per staged output row
@@ -218,10 +225,10 @@ template <class C> __device__ __forceinline__ void stage_rows(float* stage, cons
                 make_float4(acc[4 * h][r] * w, acc[4 * h + 1][r] * w, acc[4 * h + 2][r] * w, acc[4 * h + 3][r] * w);
 }
 
-template <int D, bool SPLIT>
-__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) fwd_f32_kernel(const FwdArgs a, const int n_q_tiles)
+template <int D, bool SPLIT, bool TWO>
+__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT, TWO>::NW), TWO ? 4 : 1) fwd_f32_kernel(const FwdArgs a, const int n_q_tiles)
 {
-    using C = F32Cfg<D, SPLIT>;
+    using C = F32Cfg<D, SPLIT, TWO>;
     constexpr int NW = C::NW, S = C::S, TK = C::TK, NBLK = C::NBLK;
     const AttnGeom& g = a.g;
     __shared__ __attribute__((aligned(1024))) union {
@@ -328,7 +335,7 @@ __global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) fwd_f32_kernel(co
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) { accs[b] = &acc; ps[b] = &s[b]; }
         pv.run(la, accs, ps);
-        if (C::NBUF == 1 && t + 1 < n_tiles) fetch_tile(t + 1);
+        if (C::NBUF == 1 && t + 1 < n_tiles) { if (TWO) reads_done(); fetch_tile(t + 1); }
     }
 
     // Combine the splits and merge with the running (o, lse): weights per (row, split), then a row-contiguous pass.
@@ -393,10 +400,10 @@ template <class C> struct DqSmem {
     int kpos[2][C::TK];
 };
 
-template <int D, bool SPLIT>
-__device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int q_tile, DqSmem<F32Cfg<D, SPLIT>>& sm)
+template <int D, bool SPLIT, bool TWO>
+__device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int q_tile, DqSmem<F32Cfg<D, SPLIT, TWO>>& sm)
 {
-    using C = F32Cfg<D, SPLIT>;
+    using C = F32Cfg<D, SPLIT, TWO>;
     constexpr int NW = C::NW, S = C::S, TK = C::TK, NBLK = C::NBLK;
     const AttnGeom& g = a.g;
     auto& kpos = sm.kpos;
@@ -471,7 +478,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
             const f32x4* const ps[1] = {&ds};
             kc.run(la, accs, ps);
         }
-        if (C::NBUF == 1 && t + 1 < n_tiles) fetch_tile(t + 1);
+        if (C::NBUF == 1 && t + 1 < n_tiles) { if (TWO) reads_done(); fetch_tile(t + 1); }
     }
     __syncthreads();
     stage_rows<C>(&sm.stage[wave * 16 * C::PITCH], acc, grp, l16, g.scale);
@@ -499,10 +506,10 @@ template <class C> struct DkdvSmem {
     __attribute__((aligned(16))) int qpos[2][C::TK];
 };
 
-template <int D, bool SPLIT>
-__device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, DkdvSmem<F32Cfg<D, SPLIT>>& sm)
+template <int D, bool SPLIT, bool TWO>
+__device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, DkdvSmem<F32Cfg<D, SPLIT, TWO>>& sm)
 {
-    using C = F32Cfg<D, SPLIT>;
+    using C = F32Cfg<D, SPLIT, TWO>;
     constexpr int NW = C::NW, S = C::S, TM = C::TK, NBLK = C::NBLK;
     const AttnGeom& g = a.g;
     constexpr int SET = C::PRIVATE ? 64 : 0;      // row scalars: one set of 64 lanes per wavefront, or one for all
@@ -598,7 +605,7 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const
                 const f32x4* const ps[2] = {&p, &ds};
                 cols.run(la, accs, ps);
             }
-            if (C::NBUF == 1 && fetch_h < g.nq) fetch_tile(buf ^ 1);
+            if (C::NBUF == 1 && fetch_h < g.nq) { if (TWO) reads_done(); fetch_tile(buf ^ 1); }
             buf ^= 1;
             if (++t == n_qtiles) { t = tile0; h = next_head(h); }
         }
@@ -626,36 +633,31 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const
 // side by side, the longest tiles first.  As two launches, each left CUs idle at its end: 2600 keys of 2 kv heads are 324
 // workgroups of equal length, two rounds of 256 CUs with the second one a quarter full.  3055 rows x 12011 keys, 6 / 2 heads,
 // forward + backward: 3.24 -> 2.77 ms.
-template <int D, bool SPLIT>
-__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT>::NW)) bwd_f32_kernel(const BwdArgs a, const unsigned n_dkdv, const int n_q_tiles)
+template <int D, bool SPLIT, bool TWO>
+__global__ void __launch_bounds__((64 * F32Cfg<D, SPLIT, TWO>::NW), TWO ? 4 : 1) bwd_f32_kernel(const BwdArgs a, const unsigned n_dkdv, const int n_q_tiles)
 {
-    using C = F32Cfg<D, SPLIT>;
+    using C = F32Cfg<D, SPLIT, TWO>;
     __shared__ __attribute__((aligned(1024))) union { DkdvSmem<C> dkdv; DqSmem<C> dq; } sm;
     if (blockIdx.x < n_dkdv) {
         const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x / (unsigned)a.g.nkv);
-        dkdv_unit<D, SPLIT>(a, (int)blockIdx.x - tile * a.g.nkv, tile, sm.dkdv);
+        dkdv_unit<D, SPLIT, TWO>(a, (int)blockIdx.x - tile * a.g.nkv, tile, sm.dkdv);
     } else {
         const unsigned unit = blockIdx.x - n_dkdv;
         const int tile = __builtin_amdgcn_readfirstlane(unit / (unsigned)a.g.nq);
-        dq_unit<D, SPLIT>(a, (int)unit - tile * a.g.nq, n_q_tiles - 1 - tile, sm.dq);
+        dq_unit<D, SPLIT, TWO>(a, (int)unit - tile * a.g.nq, n_q_tiles - 1 - tile, sm.dq);
     }
 }
 
-// Which shape: the one with the shorter makespan on 256 CUs when all workgroups are equally long (shared: two share a
-// CU; split: one takes all of it), the split one being a little slower per row (measured on a launch that fills the chip
-// either way, 4096 x 4096 x 16 heads x 128: forward 109 against 120 TFLOP/s, dQ 130 / 132, dK/dV 125 / 132).
-bool f32_split(int n_rows, int n_heads)
+// f(head_dim, split, two) with all three as compile-time constants.
+template <class F> hipError_t with_cfg(int d, F32Shape shape, F f)
 {
-    const long long shared = (long long)((n_rows + 63) / 64) * n_heads, split = (long long)((n_rows + 15) / 16) * n_heads;
-    return 0.25 * (double)((split + 255) / 256) < 0.93 * (double)((shared + 255) / 256);
-}
-
-// f(head_dim, shape) with both as compile-time constants
-template <class F> hipError_t with_cfg(int d, bool split, F f)
-{
-    if (d == 64) { if (split) f(IC<64>{}, std::true_type{}); else f(IC<64>{}, std::false_type{}); }
-    else if (d == 128) { if (split) f(IC<128>{}, std::true_type{}); else f(IC<128>{}, std::false_type{}); }
-    else return hipErrorInvalidValue;
+    using T = std::true_type; using N = std::false_type;
+    const bool split = shape != F32Shape::SHARED;
+    if (d == 128) { if (split) f(IC<128>{}, T{}, N{}); else f(IC<128>{}, N{}, N{}); }
+    else if (d != 64) return hipErrorInvalidValue;
+    else if (shape == F32Shape::SPLIT_TWO) f(IC<64>{}, T{}, T{});
+    else if (split) f(IC<64>{}, T{}, N{});
+    else f(IC<64>{}, N{}, N{});
     return hipGetLastError();
 }
 
@@ -663,29 +665,30 @@ template <class F> hipError_t with_cfg(int d, bool split, F f)
 
 hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s)
 {
-    return with_cfg(a.g.d, f32_split(a.g.lq, a.g.nq), [&](auto d, auto split) {
-        constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(split)::value;
-        using C = F32Cfg<D, SPLIT>;
+    return with_cfg(a.g.d, hexi_f32_fwd_shape(a.g), [&](auto d, auto split, auto two) {
+        constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(split)::value, TWO = decltype(two)::value;
+        using C = F32Cfg<D, SPLIT, TWO>;
         const int n_q_tiles = (a.g.lq + C::ROWS - 1) / C::ROWS;
-        fwd_f32_kernel<D, SPLIT><<<(unsigned)(n_q_tiles * a.g.nq), 64 * C::NW, 0, s>>>(a, n_q_tiles);
+        fwd_f32_kernel<D, SPLIT, TWO><<<(unsigned)(n_q_tiles * a.g.nq), 64 * C::NW, 0, s>>>(a, n_q_tiles);
     });
 }
 
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s)
 {
-    const bool kv_split = f32_split(a.g.lc, a.g.nkv), q_split = f32_split(a.g.lq, a.g.nq);
-    auto launch = [&](bool split, bool dkdv, bool dq) {
-        return with_cfg(a.g.d, split, [&](auto d, auto sp) {
-            constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(sp)::value;
-            using C = F32Cfg<D, SPLIT>;
+    F32Shape kv_shape, q_shape;
+    hexi_f32_bwd_shapes(a.g, a.want_dq, a.want_dkdv, &kv_shape, &q_shape);
+    auto launch = [&](F32Shape shape, bool dkdv, bool dq) {
+        return with_cfg(a.g.d, shape, [&](auto d, auto sp, auto tw) {
+            constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(sp)::value, TWO = decltype(tw)::value;
+            using C = F32Cfg<D, SPLIT, TWO>;
             const int n_q_tiles = (a.g.lq + C::ROWS - 1) / C::ROWS;
             const unsigned n_dkdv = dkdv ? (unsigned)((a.g.lc + C::ROWS - 1) / C::ROWS * a.g.nkv) : 0u;
             const unsigned n_dq = dq ? (unsigned)(n_q_tiles * a.g.nq) : 0u;
-            bwd_f32_kernel<D, SPLIT><<<n_dkdv + n_dq, 64 * C::NW, 0, s>>>(a, n_dkdv, n_q_tiles);
+            bwd_f32_kernel<D, SPLIT, TWO><<<n_dkdv + n_dq, 64 * C::NW, 0, s>>>(a, n_dkdv, n_q_tiles);
         });
     };
-    if (a.want_dkdv && a.want_dq && kv_split == q_split) return launch(kv_split, true, true);
-    hipError_t e = a.want_dkdv ? launch(kv_split, true, false) : hipSuccess;
-    if (e == hipSuccess && a.want_dq) e = launch(q_split, false, true);
+    if (a.want_dkdv && a.want_dq && kv_shape == q_shape) return launch(kv_shape, true, true);
+    hipError_t e = a.want_dkdv ? launch(kv_shape, true, false) : hipSuccess;
+    if (e == hipSuccess && a.want_dq) e = launch(q_shape, false, true);
     return e;
 }

@@ -108,6 +108,14 @@ __device__ __forceinline__ void lds_dma4_base(const void* base, uint32_t byte_of
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(byte_off), "s"(base) : "memory");
 }
 
+// This wavefront's LDS reads have returned: the block they came from may be overwritten.
+__device__ __forceinline__ void reads_done()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // LDS reads issued through inline assembly with a compile-time offset field, for software pipelines whose
 // address registers must stay exactly the ones the kernel computed (the compiler otherwise materialises
 // one address register per buffer).  The compiler does not see these reads: the destination is valid

@@ -304,3 +304,85 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, b
         }
     }
 }
+
+// The fp32 kernels (hexi_f32.hip): 64-row workgroups that share their tiles, or 16-row ones whose wavefronts split the streamed
+// rows, one or (head_dim 64) two of them on a CU.
+enum class F32Shape { SHARED, SPLIT, SPLIT_TWO };
+
+// Shared or split at head_dim 128: the shorter makespan on 256 CUs when all workgroups are equally long (shared: two share a
+// CU; split: one takes all of it), the split one being a little slower per row (measured on a launch that fills the chip
+// either way, 4096 x 4096 x 16 heads x 128: forward 109 against 120 TFLOP/s, dQ 130 / 132, dK/dV 125 / 132).
+inline bool hexi_f32_split(int n_rows, int n_heads)
+{
+    const long long shared = (long long)((n_rows + 63) / 64) * n_heads, split = (long long)((n_rows + 15) / 16) * n_heads;
+    return 0.25 * (double)((split + 255) / 256) < 0.93 * (double)((shared + 255) / 256);
+}
+
+// Keys that a row sees, averaged over 32 rows spread over the shard: the rules below weigh launches, they need no exact count.
+inline double hexi_mean_seen(const AttnGeom& g)
+{
+    long long seen = 0;
+    for (int i = 0; i < 32; ++i) seen += seg_rows_le(g.ks, seg_pos_of_row(g.qs, (int)((2 * i + 1) * (long long)g.lq / 64)));
+    return (double)seen / 32.0;
+}
+
+// Two workgroups on a CU finish more units in a given time (5/6 of the time per unit, measured), but each of them takes longer.
+// So they are taken where the sum of the units, dealt evenly to the CUs, is longer (by 2 %) than the longest unit, which is what the launch waits
+// for otherwise.  us with one / two a CU, and that quotient: backward of 1024 x 1024 keys x 8/2 heads 92 / 96 (0.88), 1500 x 1500 x 8/2
+// 175 / 163 (1.28), 300 x 600 x 16/4 48 / 43 (1.04); diagonal 2048 x 8/2 174 / 187 (0.88), 768 x 8/8 42 / 38 (1.31); forward, diagonal,
+// 4096 x 2 heads 55 / 62 (1.0), 1500 x 6 heads 32 / 28 (1.1).
+inline F32Shape hexi_f32_split_shape(double sum, double longest) { return sum > 262.0 * longest ? F32Shape::SPLIT_TWO : F32Shape::SPLIT; }
+
+// head_dim 64: us of a launch whose units are about equally long (x 1000 streamed rows), besides the launch itself.  Shared: in rounds of
+// 256 workgroups, the first of them 14.5 us longer per 1000 rows of the longest unit; split, two a CU: in rounds of 512, a part of one costs half of the
+// rest of it, and 4.5 us of each are start and combination.  Within 10 % of the measured forward, dK/dV and (x 1.35) dQ
+// for 70 to 4096 streamed rows and 1/4 to 6 shared rounds.  us forward, shared / split / two a CU: 2048 x 70 keys x 16 heads
+// 15 / 42 / 28, x 300 31 / 60 / 41, x 1000 85 / 123 / 92, x 2048 160 / 203 / 163; 1500 x 1500 x 24 168 / 181 / 143, 3000 x 3000 x 24 537 / 623 / 511,
+// 4096 x 4096 x 24 859 / 1106 / 902; 6703 x 4962 x 16, mean 0.63 of the longest, 747 shared, 818 split.  Units less equal than that
+// fill each other's last rounds: split (diagonal 4096 x 24 heads 512 / 602 / 481, 300 x 24 heads 20 / 13 / 11).
+inline bool hexi_f32_shared_64(int n_rows, int n_heads, double mean, double longest, double margin)
+{
+    if (mean <= 0.6 * longest) return false;
+    const long long shared = (long long)((n_rows + 63) / 64) * n_heads, split = (long long)((n_rows + 15) / 16) * n_heads;
+    const double x = mean * 1e-3, r = (double)((shared + 255) / 256), s = 0.5 * ((double)((split + 511) / 512) + (double)split / 512.0);
+    return margin * (3.0 * r + 14.5e-3 * longest + 31.5 * r * x) < s * (4.5 + 17.7 * x);
+}
+
+inline F32Shape hexi_f32_fwd_shape(const AttnGeom& g)
+{
+    if (g.d != 64) return hexi_f32_split(g.lq, g.nq) ? F32Shape::SPLIT : F32Shape::SHARED;
+    const double mean = hexi_mean_seen(g), longest = (double)seg_rows_le(g.ks, seg_pos_of_row(g.qs, g.lq - 1));
+    if (hexi_f32_shared_64(g.lq, g.nq, mean, longest, 0.97)) return F32Shape::SHARED;
+    return hexi_f32_split_shape((double)((g.lq + 15) / 16) * g.nq * mean, longest);
+}
+
+// Backward.  Two split halves, or two shared ones, are one launch and fill each other's rounds.  At head_dim 64 dK/dV is shared where that is
+// expected to be 5 % faster (70 rows x 2740 keys x 12/12 heads: 33 us, with dQ 76, against 60 and 90 as one split launch), dQ where 20 %,
+// which a launch of its own besides dK/dV's has to gain: 2048 rows x 70 keys x 16/4 heads 21 us / 33 split, with dK/dV 186 / 171 as one
+// launch; 2048 x 512 x 16/4 61 / 67, 207 / 176; 3500 x 512 x 16/4 110 / 112, 349 / 288.  As one launch, shared / split / split, two a CU:
+// 4096 x 4096 x 24/8 2781 / 3302 / 2769, 2048 x 2048 x 8/8 254 / 302 / 245, diagonal 249 / 179 / 146.
+// dQ is also split where it fits on the CUs that few long dK/dV units leave idle: 1662 x 141 x 24/3 heads 277 us, dK/dV alone 275; a call
+// for dQ alone has no such units beside it and may be shared where the step's is split.  A dQ unit has three products per
+// block of scores, a dK/dV unit four, and walks the rows of every q head that reads its keys.
+inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv, F32Shape* kv, F32Shape* q)
+{
+    if (g.d != 64) {
+        *kv = hexi_f32_split(g.lc, g.nkv) ? F32Shape::SPLIT : F32Shape::SHARED;
+        *q = hexi_f32_split(g.lq, g.nq) ? F32Shape::SPLIT : F32Shape::SHARED;
+        return;
+    }
+    const double group = (double)g.nq / g.nkv, seen = hexi_mean_seen(g);
+    const double q_longest = (double)seg_rows_le(g.ks, seg_pos_of_row(g.qs, g.lq - 1));
+    const double kv_longest = g.lc > 0 ? group * (double)(g.lq - seg_rows_le(g.qs, seg_pos_of_row(g.ks, 0) - 1)) : 0.0;
+    const double kv_mean = g.lc > 0 ? group * (double)g.lq * seen / (double)g.lc : 0.0;
+    const bool kv_shared = hexi_f32_shared_64(g.lc, g.nkv, kv_mean, kv_longest, 1.05);
+    const double pairs = (double)g.nq * g.lq / 16.0 * seen;
+    const bool beside_dkdv = want_dkdv && !kv_shared && hexi_f32_split_shape(7.0 * pairs, 4.0 * kv_longest) == F32Shape::SPLIT;
+    const bool q_shared = !beside_dkdv && hexi_f32_shared_64(g.lq, g.nq, seen, q_longest, 1.2);
+    const bool split_dq = want_dq && !q_shared, split_dkdv = want_dkdv && !kv_shared;
+    double longest = split_dq ? 3.0 * q_longest : 0.0;
+    if (split_dkdv && 4.0 * kv_longest > longest) longest = 4.0 * kv_longest;
+    const F32Shape split = hexi_f32_split_shape(pairs * ((split_dq ? 3.0 : 0.0) + (split_dkdv ? 4.0 : 0.0)), longest);
+    *kv = kv_shared ? F32Shape::SHARED : split;
+    *q = q_shared ? F32Shape::SHARED : split;
+}

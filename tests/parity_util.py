@@ -87,6 +87,14 @@ QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 6
               (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "fb"), (200, 65, 64, 64, 128, "fb"),
               (200, 33, 128, 8, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
 
+# fp32 steps at head_dim 64, all keys visible (off = lc) or diagonal (off = 0): (lq, lc, nq, nkv, off), shape of the forward, of dQ, of dK/dV
+# and of dQ in a call of its own (0: 64 rows, shared; 1: 16 rows, split; 2: split, two workgroups a CU); rows and keys around the 16-row
+# blocks, the 64-row tiles and the 128-row tiles of the split shapes, chunks shorter than a split tile.
+F32_STEPS = [((33, 16, 2, 1, 16), (1, 1, 1, 1)), ((145, 257, 40, 40, 257), (2, 2, 0, 2)), ((1025, 17, 5, 1, 17), (0, 1, 1, 2)),
+             ((273, 300, 24, 8, 300), (2, 2, 2, 2)), ((1000, 129, 48, 8, 129), (0, 1, 1, 0)), ((1000, 129, 24, 24, 129), (0, 0, 1, 0)), ((1039, 1039, 16, 4, 0), (2, 1, 1, 2)),
+             ((497, 497, 12, 3, 0), (1, 1, 1, 1)), ((65, 1030, 24, 24, 1030), (1, 1, 0, 1)), ((128, 127, 128, 128, 127), (0, 0, 0, 0))]
+
+
 # Forward steps whose rows are shared by 256-row workgroups (whole rounds of 256 units) and 64-row ones behind them: as many tiles
 # of every head, and one tile more of some heads; last tiles of 1, 188 and 76 rows.
 SHARED_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]

@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, SHARED_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, SHARED_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -843,3 +843,37 @@ def test_forward_shared_by_large_and_64_row_workgroups(lq, lc, nq, nkv, d):
     o_ref, lse_ref = oracle.merge(to64(o0), to64(lse0), o_ref, lse_ref)
     check("o merged", o.cpu(), o_ref, "bf16")
     check("lse merged", lse.cpu(), lse_ref, "bf16")
+
+
+@pytest.mark.parametrize("step,shapes", F32_STEPS)
+def test_f32_shapes_at_head_dim_64(step, shapes):
+    # forward alone and merged, backward added to running dq / dk / dv, in every shape the rules deal out (the shapes are asserted on the CPU);
+    # the halves in calls of their own as well: with the same bits, one workgroup a CU or two, unless dQ is split in one of the calls only
+    lq, lc, nq, nkv, off = step
+    d, g = 64, torch.Generator().manual_seed(lq + lc)
+    q, k, v, d_o = (torch.randn(n, h, d, generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
+    scale, pos = d ** -0.5, np.arange(off, off + lq)
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), pos, to64(k), to64(v), np.arange(lc), scale)
+    ref = oracle.attn_bwd(to64(q), pos, to64(k), to64(v), np.arange(lc), to64(d_o), scale)
+    qd, kd, vd, gd = (t.to(DEV) for t in (q, k, v, d_o))
+    desc, args = hexi.desc_for(qd, kd, scale), ([(off, lq)], [(0, lc)], qd, kd, vd)
+    o, lse = torch.full(q.shape, float("nan"), device=DEV), torch.full((nq, lq), float("nan"), device=DEV)
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse)
+    check("o", o.cpu(), o_ref, "f32")
+    check("lse", lse.cpu(), lse_ref, "f32")
+    o0, lse0 = torch.randn(q.shape, generator=g), torch.randn((nq, lq), generator=g)
+    om, lsem = o0.to(DEV), lse0.to(DEV)
+    hexi.hexi_attn_fwd_chunk(desc, *args, om, lsem, flags=hexi.HEXI_ACCUMULATE)
+    om_ref, lsem_ref = oracle.merge(to64(o0), to64(lse0), o_ref, lse_ref)
+    check("o merged", om.cpu(), om_ref, "f32")
+    check("lse merged", lsem.cpu(), lsem_ref, "f32")
+    delta = torch.empty((nq, lq), device=DEV)
+    dq, dk, dv = torch.zeros(q.shape, device=DEV), torch.full(k.shape, 7.0, device=DEV), torch.full(v.shape, 7.0, device=DEV)
+    hexi.hexi_attn_bwd_chunk(desc, *args, o, gd, lse, delta, dq, dk, dv, flags=hexi.HEXI_COMPUTE_DELTA)
+    for name, got in (("dq", dq), ("dk", dk), ("dv", dv)):
+        check(name, got.cpu(), ref[name], "f32")
+    dq2, dk2, dv2 = torch.zeros_like(dq), torch.zeros_like(dk), torch.zeros_like(dv)
+    hexi.hexi_attn_bwd_chunk(desc, *args, None, gd, lse, delta, dq2, None, None, flags=hexi.HEXI_SKIP_DKDV)
+    hexi.hexi_attn_bwd_chunk(desc, *args, None, gd, lse, delta, None, dk2, dv2, flags=hexi.HEXI_SKIP_DQ)
+    check("dq alone", dq2.cpu(), ref["dq"], "f32")
+    assert torch.equal(dk, dk2) and torch.equal(dv, dv2) and ((shapes[1] == 0) != (shapes[3] == 0) or torch.equal(dq, dq2))

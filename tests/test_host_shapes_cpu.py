@@ -26,7 +26,8 @@ def shapes(tmp_path_factory):
             m = " ".join(map(str, more[0])) if more and more[0] else ""
             lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
-        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone", "fwd_tiles", "rest_tiles")
+        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone", "fwd_tiles", "rest_tiles",
+                 "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone")
         return [dict(zip(names, map(int, line.split()))) for line in out if line]
 
     return ask
@@ -106,3 +107,17 @@ def test_whole_rounds_of_large_forward_workgroups_and_the_rest_in_small_ones(sha
     # us measured in 256-row workgroups / shared / in 64-row ones: 228 / 210 / 232, 167 / 135 / 151; unequal units and whole rounds: not shared
     steps = [_step(4096, 4096, 24, 8, 128, 4096), _step(5000, 3000, 16, 4, 128, 3000), _step(10000, 6000, 12, 3, 128, 0), _step(4096, 4096, 32, 8, 128, 4096)]
     assert [got["rest_tiles"] > 0 for got in shapes(steps)] == [True, True, False, False]
+
+
+def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
+    from parity_util import F32_STEPS
+    got = shapes([_step(lq, lc, nq, nkv, 64, off) for (lq, lc, nq, nkv, off), _ in F32_STEPS])
+    assert [(g["f32_fwd"], g["f32_dq"], g["f32_dkdv"], g["f32_dq_alone"]) for g in got] == [s for _, s in F32_STEPS]
+    # us measured, shared / split / two a CU: forward 859 / 1106 / 902, 161 / 199 / 162, 55 / 61 / 50, diagonal 191 / 55 / 62, 155 / 179 / 135
+    steps = [_step(4096, 4096, 24, 8, 64, 4096), _step(2048, 2048, 16, 4, 64, 2048), _step(1024, 1024, 16, 4, 64, 1024), _step(4096, 4096, 2, 2, 64, 0),
+             _step(2048, 2048, 24, 8, 64, 0)]
+    assert [g["f32_fwd"] for g in shapes(steps)] == [0, 0, 2, 1, 2]
+    # backward 2781 / 3302 / 2769, 340 / 90 / 108, 203 / 47 / 50 for split / two a CU; head_dim 128 keeps one workgroup a CU
+    steps = [_step(4096, 4096, 24, 8, 64, 4096), _step(1024, 2048, 4, 1, 64, 2048), _step(512, 512, 8, 2, 64, 512), _step(1000, 1010, 16, 16, 128, 1010),
+             _step(300, 300, 4, 2, 128, 300)]
+    assert [(g["f32_dq"], g["f32_dkdv"]) for g in shapes(steps)] == [(2, 2), (1, 1), (1, 1), (0, 0), (1, 1)]
