@@ -104,52 +104,22 @@ inline bool hexi_q_units(const AttnGeom& g, Units (&u)[3])
     return u[0].n < 1024;
 }
 
-// Which tiles of a forward step in 256-row workgroups these take: all, or whole rounds of 256 units with the rest of the rows in
-// 64-row workgroups behind them, where that is expected to be 3 % faster.  A half-empty last round costs as much as a whole one; 64-row
-// workgroups fill two rounds of a quarter of its length each.  Units have to be of about the same length: unequal ones fill each other's
-// last round already.
-// us: the expected time.
-inline QShare hexi_fwd_share(const AttnGeom& g, const Units (&u)[3], double* us)
-{
-    using namespace hexi_shapes;
-    const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
-    const QShare all = {n_q_tiles, 0};
-    const bool wide = g.d == 128;
-    const double mb = (double)g.lq * g.nq * g.d * 6.0 * 1e-6;      // q read, o written
-    *us = FWD[wide][0].us(u[0], mb);
-    if (u[0].n != (long long)g.nq * n_q_tiles || u[0].longest * (double)u[0].n > 1.1 * u[0].sum) return all;
-    const int n = (int)u[0].n, big = n / 256 * 256;
-    if (big == 0 || big == n || big / g.nq == 0) return all;
-    const double mean = u[0].sum / n, part = (double)big / n;
-    Units first, rest;
-    first.add(mean, big);
-    rest.add(ceil(mean / 2.0), 4LL * (n - big));
-    const double split = FWD[wide][0].us(first, mb * part) + FWD[wide][1].us(rest, mb * (1.0 - part));
-    if (*us <= SMALL_MARGIN * split) return all;
-    *us = split;
-    return {big / g.nq, big % g.nq};
-}
-
 // Rows per forward workgroup of the smaller kernels (32 or 64), or 0 for the 256-row kernel, which is kept unless another is expected
 // to be 8 % faster: of 8000 of the calls 3 are then slower than in 256-row workgroups by more than 3 %, at most 8 % (14 by more than 10 % at
 // a margin of 5 %), and the choice is 0.8 % slower than the best of the three in the mean.  32-row workgroups beyond three rounds stream
 // too much.  Measured, us in 256 / 64 / 32 rows, head_dim 128: 300 rows x 700 keys x 4 heads 28.3 / 13.1 / 9.3; 512 x 1024 x 24 34.1 / 15.7 / 19.7;
 // 1024 x 1024 x 24 37.9 / 28.4 / 28.9; 2048 x 2048 x 24 64.7 / 69.8 / 88.5; head_dim 64: 2048 x 4096 x 24 80.7 / 68.7 / 82.0.
-inline int hexi_fwd_split_rows(const AttnGeom& g, QShare* share)
+inline int hexi_fwd_split_rows(const AttnGeom& g)
 {
     using namespace hexi_shapes;
     Units u[3];
-    *share = {(g.lq + Q_TILE - 1) / Q_TILE, 0};
     if (!hexi_q_units(g, u)) return 0;
     const auto& fit = FWD[g.d == 128];
     const double mb = (double)g.lq * g.nq * g.d * 6.0 * 1e-6;      // q read, o written
-    double t256;
-    *share = hexi_fwd_share(g, u, &t256);
-    const double t64 = fit[1].us(u[1], mb), t32 = u[2].n <= 768 ? fit[2].us(u[2], mb) : INFINITY;
+    const double t256 = fit[0].us(u[0], mb), t64 = fit[1].us(u[1], mb), t32 = u[2].n <= 768 ? fit[2].us(u[2], mb) : INFINITY;
     if (t256 <= 1.08 * (t64 < t32 ? t64 : t32)) return 0;
     return t64 <= t32 ? 64 : 32;
 }
-inline int hexi_fwd_split_rows(const AttnGeom& g) { QShare share; return hexi_fwd_split_rows(g, &share); }
 
 // How a backward step is launched.
 struct BwdPlan {

@@ -2,8 +2,8 @@
 //   head_dim nq nkv forced_run_len  n_q_segs (start len)...  n_kv_segs (start len)...  [kv_of_q ...]
 // and prints: rows per forward workgroup (0: 256), rows per dQ workgroup (0: 256), keys per dK / dV workgroup, q heads per dK / dV
 // workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take; then, for
-// calls for one half alone, the rows per dQ workgroup and the keys per dK / dV workgroup; the forward's 256-row tiles and those left to smaller
-// workgroups; for fp32 inputs the workgroup shape (0 shared, 1 split, 2 split with two on a CU) of the forward, of dQ, of dK / dV and of dQ alone.
+// calls for one half alone, the rows per dQ workgroup and the keys per dK / dV workgroup; for fp32 inputs the workgroup
+// shape (0 shared, 1 split, 2 split with two on a CU) of the forward, of dQ, of dK / dV and of dQ alone.
 #include <cstdio>
 #include <cstring>
 #include <iostream>
@@ -51,13 +51,11 @@ int main()
         BwdPlan dq_alone, dkdv_alone;
         hexi_plan_bwd(g, forced, true, false, &dq_alone);
         hexi_plan_bwd(g, forced, false, true, &dkdv_alone);
-        QShare share;
-        const int fwd_rows = hexi_fwd_split_rows(g, &share), fwd_tiles = share.n_units(g.nq), all_tiles = g.nq * ((g.lq + 255) / 256);
         F32Shape kv32, q32, q32_alone, unused;
         hexi_f32_bwd_shapes(g, true, true, &kv32, &q32);
         hexi_f32_bwd_shapes(g, true, false, &unused, &q32_alone);
-        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", fwd_rows, plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
-                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128, fwd_tiles, all_tiles - fwd_tiles,
+        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
+                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128,
                     (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone);
     }
     return 0;

@@ -95,6 +95,6 @@ F32_STEPS = [((33, 16, 2, 1, 16), (1, 1, 1, 1)), ((145, 257, 40, 40, 257), (2, 2
              ((497, 497, 12, 3, 0), (1, 1, 1, 1)), ((65, 1030, 24, 24, 1030), (1, 1, 0, 1)), ((128, 127, 128, 128, 127), (0, 0, 0, 0))]
 
 
-# Forward steps whose rows are shared by 256-row workgroups (whole rounds of 256 units) and 64-row ones behind them: as many tiles
-# of every head, and one tile more of some heads; last tiles of 1, 188 and 76 rows.
-SHARED_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]
+# Forward steps of one round of 256-row workgroups (256 units of about the same length) and part of a second one; last tiles of 1, 188 and
+# 76 rows.
+PART_ROUND_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]

@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, QUAD_STEPS, SHARED_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, PART_ROUND_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -825,8 +825,8 @@ def test_64_wide_workgroups_accumulate():
         assert float((outs[1][0] - outs[0][0] - 0.5).abs().max()) <= bound and float((outs[1][1] - outs[0][1] + 0.25).abs().max()) <= bound
 
 
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", SHARED_STEPS)
-def test_forward_shared_by_large_and_64_row_workgroups(lq, lc, nq, nkv, d):
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS)
+def test_forward_of_a_round_and_a_part(lq, lc, nq, nkv, d):
     # every row exactly once, first alone, then merged into a running (o, lse)
     q, _, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
     qd, kd, vd = (t.to(DEV) for t in (q, k, v))
@@ -843,6 +843,18 @@ def test_forward_shared_by_large_and_64_row_workgroups(lq, lc, nq, nkv, d):
     o_ref, lse_ref = oracle.merge(to64(o0), to64(lse0), o_ref, lse_ref)
     check("o merged", o.cpu(), o_ref, "bf16")
     check("lse merged", lse.cpu(), lse_ref, "bf16")
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS + [(4096, 4096, 24, 8, 128), (15773, 21188, 9, 3, 64)])
+def test_rows_and_heads_of_a_forward_step_are_summed_alike(lq, lc, nq, nkv, d):
+    # one row and one set of keys, repeated over all rows and heads, all keys visible: results with the same bits everywhere, or a row's
+    # result would depend on its place in the shard and on which heads a device was given
+    g = torch.Generator().manual_seed(lq + nq)
+    q = torch.randn((1, 1, d), generator=g).to(torch.bfloat16).expand(lq, nq, d).contiguous().to(DEV)
+    k, v = (torch.randn((lc, 1, d), generator=g).to(torch.bfloat16).expand(lc, nkv, d).contiguous().to(DEV) for _ in range(2))
+    o, lse = torch.full(q.shape, float("nan"), device=DEV), torch.full((nq, lq), float("nan"), device=DEV)
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(q, k, d ** -0.5), [(lc, lq)], [(0, lc)], q, k, v, o, lse)
+    assert torch.equal(o, o[:1, :1].expand_as(o)) and torch.equal(lse, lse[:1, :1].expand_as(lse))
 
 
 @pytest.mark.parametrize("step,shapes", F32_STEPS)

@@ -26,7 +26,7 @@ def shapes(tmp_path_factory):
             m = " ".join(map(str, more[0])) if more and more[0] else ""
             lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
-        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone", "fwd_tiles", "rest_tiles",
+        names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone",
                  "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone")
         return [dict(zip(names, map(int, line.split()))) for line in out if line]
 
@@ -100,13 +100,10 @@ def test_the_64_wide_workgroups_tests_reach_them(shapes):
         assert "b" not in halves or (got["dq_rows"] == 64 and got["keys"] < 128), step
 
 
-def test_whole_rounds_of_large_forward_workgroups_and_the_rest_in_small_ones(shapes):
-    from parity_util import SHARED_STEPS
-    for (lq, lc, nq, nkv, d), got in zip(SHARED_STEPS, shapes([_step(lq, lc, nq, nkv, d, lc) for lq, lc, nq, nkv, d in SHARED_STEPS])):
-        assert got["fwd_rows"] == 0 and got["fwd_tiles"] == 256 and got["rest_tiles"] == nq * -(-lq // 256) - 256
-    # us measured in 256-row workgroups / shared / in 64-row ones: 228 / 210 / 232, 167 / 135 / 151; unequal units and whole rounds: not shared
-    steps = [_step(4096, 4096, 24, 8, 128, 4096), _step(5000, 3000, 16, 4, 128, 3000), _step(10000, 6000, 12, 3, 128, 0), _step(4096, 4096, 32, 8, 128, 4096)]
-    assert [got["rest_tiles"] > 0 for got in shapes(steps)] == [True, True, False, False]
+def test_a_round_and_a_part_of_large_forward_workgroups(shapes):
+    # 384, 384, 320 and 288 units of 256 rows; us measured in 256 / 64 rows: 226 / 232, 127.5 / 133.1, 167 / 151, 123 / 108
+    steps = [_step(lq, lc, nq, nkv, 128, lc) for lq, lc, nq, nkv in ((4096, 4096, 24, 8), (4096, 2048, 24, 8), (5000, 3000, 16, 4), (9000, 2000, 8, 2))]
+    assert [got["fwd_rows"] for got in shapes(steps)] == [0, 0, 64, 64]
 
 
 def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
