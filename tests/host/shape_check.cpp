@@ -54,8 +54,8 @@ int main()
         F32Shape kv32, q32, q32_alone, unused;
         hexi_f32_bwd_shapes(g, true, true, &kv32, &q32);
         hexi_f32_bwd_shapes(g, true, false, &unused, &q32_alone);
-        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? 32 : 128, plan.run_len, (int)shared,
-                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? 32 : 128,
+        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? plan.keys : 128, plan.run_len, (int)shared,
+                    (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? dkdv_alone.keys : 128,
                     (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone);
     }
     return 0;

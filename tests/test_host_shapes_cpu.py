@@ -58,16 +58,24 @@ def test_forward_takes_the_shape_measured_faster(shapes, lq, lc, nq, nkv, d, off
     assert shapes([_step(lq, lc, nq, nkv, d, off)])[0]["fwd_rows"] == rows
 
 
-@pytest.mark.parametrize("lq,lc,nq,nkv,d,off,dq_alone,keys_alone", [
-    # a step in joint split launches whose halves are slower there by themselves; us of dQ in 256 / 64 rows, of dK / dV in 128 / 32 keys:
-    # 90 / 120; 97 / 134; 155 / 220; 38 / 50
-    (7496, 634, 16, 4, 128, 634, 0, None), (7696, 530, 32, 4, 64, 430, 0, None), (7599, 1171, 24, 8, 64, 0, None, 128),
-    (1016, 390, 64, 8, 64, 390, 0, 128),
-    # 50 / 21, 46 / 22; 35 / 15 (11 in 32 rows), 24 / 11.5: faster alone as well
-    (512, 1024, 24, 8, 128, 1024, 64, 32), (300, 700, 4, 2, 128, 700, 32, 32)])
-def test_a_half_by_itself_is_not_sent_to_a_slower_shape(shapes, lq, lc, nq, nkv, d, off, dq_alone, keys_alone):
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off,keys,dq_alone,keys_alone", [
+    # a step in joint launches of 64 or 32 rows and keys one of whose halves is slower there by itself; us of the step in 128 keys and 256 rows /
+    # in its own shape; of dQ alone in 256 rows / as many as in the step: 290 / 166, 92 / 98; 266 / 204, 92 / 120; 261 / 241, 112 / 127; of dK / dV alone in
+    # 128 keys / as many as in the step: 177 / 180; 60 / 58, 36 / 50
+    (7496, 634, 16, 4, 128, 634, 64, 0, None), (7696, 530, 32, 4, 64, 430, 64, 0, 128), (7599, 1171, 24, 8, 64, 0, 64, 0, None),
+    (1016, 390, 64, 8, 64, 390, 32, 0, 128),
+    # halves that are faster there alone as well: dQ 49 / 17, dK / dV 43 / 27 (64 keys and rows); 36 / 9.4, 23 / 12 (32)
+    (512, 1024, 24, 8, 128, 1024, 64, 64, 64), (300, 700, 4, 2, 128, 700, 32, 32, 32)])
+def test_a_half_by_itself_is_not_sent_to_a_slower_shape(shapes, lq, lc, nq, nkv, d, off, keys, dq_alone, keys_alone):
     got = shapes([_step(lq, lc, nq, nkv, d, off)])[0]
-    assert got["keys"] == 32 and (dq_alone is None or got["dq_alone"] == dq_alone) and (keys_alone is None or got["keys_alone"] == keys_alone)
+    assert got["keys"] == keys and got["dq_alone"] == dq_alone and (keys_alone is None or got["keys_alone"] == keys_alone)
+
+
+def test_64_keys_or_32(shapes):
+    # us measured in 64 / 32 keys and rows: 31.5 / 39.5, 178 / 212, 384 / 459; 18.5 / 12.0, 96 / 58; 64-key workgroups beside 256-row dQ ones, in two launches
+    steps = [_step(512, 1024, 24, 8, 128, 1024), _step(2048, 2048, 24, 8, 128, 2048), _step(4096, 4096, 24, 8, 64, 4096),
+             _step(300, 700, 4, 2, 128, 700), _step(1016, 390, 64, 8, 64, 390), _step(5287, 902, 64, 16, 128, 0), _step(1998, 193, 64, 64, 64, 96)]
+    assert [(got["keys"], got["dq_rows"]) for got in shapes(steps)] == [(64, 64), (64, 64), (64, 64), (32, 32), (32, 32), (64, 0), (64, 0)]
 
 
 def test_no_step_gets_atomics_that_its_128_key_launch_would_not_have(shapes):
@@ -95,9 +103,8 @@ def test_the_64_wide_workgroups_tests_reach_them(shapes):
     from parity_util import QUAD_STEPS
     steps = [(_step(lq, lc, nq, nkv, d, off), halves) for lq, lc, nq, nkv, d, halves in QUAD_STEPS for off in (lc, lc // 2)]
     for (step, halves), got in zip(steps, shapes([s for s, _ in steps])):
-        # (dQ workgroups of 64 rows are only ever paired with dK / dV workgroups of 64 keys or of 128)
         assert "f" not in halves or got["fwd_rows"] == 64, step
-        assert "b" not in halves or (got["dq_rows"] == 64 and got["keys"] < 128), step
+        assert "b" not in halves or (got["dq_rows"] == 64 and got["keys"] == 64), step
 
 
 def test_a_round_and_a_part_of_large_forward_workgroups(shapes):
