@@ -140,10 +140,13 @@ int hexi_attn_merge_lse(int64_t n_rows, int32_t n_q_heads, int32_t head_dim,
  * heads that share a kv head are summed inside one workgroup when the launch is large enough
  * without splitting them (dk/dv are then reproducible run to run); otherwise groups are cut into
  * runs of heads whose contributions are summed with floating-point atomics, whose order (and so
- * the last bits of dk/dv) can vary between runs.  hexi_set_dkdv_run_len() overrides the run length
+ * the last bits of dk/dv) can vary between runs where there are more than two runs to a group (two
+ * under HEXI_ACCUMULATE).  The library cuts so where it expects to gain 15 % or more, or where the
+ * launch fills the chip.  hexi_set_dkdv_run_len() overrides the run length
  * chosen by the library.  HEXI_SKIP_DQ / HEXI_SKIP_DKDV
  * restrict the call to one of the two halves (which may be issued on different streams; a call for
- * both may run them in one launch); both set is HEXI_EINVAL.  A chunk
+ * both may run them in one launch, and may sum in another order than the halves by themselves); both
+ * set is HEXI_EINVAL.  A chunk
  * wholly in the shard's future writes zeros to dk/dv (nothing under HEXI_ACCUMULATE) and leaves
  * dq_acc untouched.  d_o has the dtype and strides of q.
  */

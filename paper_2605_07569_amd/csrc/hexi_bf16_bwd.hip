@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(512) bwd_dkdv_bf16_kernel(const BwdArgs a, con
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s)
 {
     BwdPlan plan;
-    hexi_plan_bwd(a.g, hexi_dkdv_run_len, a.want_dq != 0, a.want_dkdv != 0, &plan);
+    hexi_plan_bwd(a.g, hexi_dkdv_run_len, a.want_dq != 0, a.want_dkdv != 0, a.accumulate != 0, &plan);
     const int dq_rows = plan.dq_rows, n_kv_tiles = plan.n_kv_tiles;
     bool dq_done = !a.want_dq;
     HeadRuns runs;

@@ -9,6 +9,7 @@ constexpr int KV_STREAM_TILE = 64;     // keys per tile that they stream
 constexpr int KV_TILE = 128;           // keys of the large dK / dV workgroups
 constexpr int Q_STREAM_TILE = 64;      // q rows per tile that they stream
 constexpr double SMALL_MARGIN = 1.03;  // the large workgroups are kept unless smaller ones are expected to be faster by this
+constexpr double ORDER_MARGIN = 1.15;  // and sums in a fixed order unless others are (see BwdPlan)
 }  // namespace hexi_shapes
 
 // The units of a launch by the length of their serial chains (key tiles, q tiles, or 32-row blocks per wavefront).
@@ -128,6 +129,11 @@ struct BwdPlan {
     int keys = 32;                // 64 or 32; dQ workgroups of as many rows share the launch
     int run_len = 0;              // q heads per dK / dV workgroup
     int run_len_128 = 0;          // the same if the 128-key workgroups are taken
+    int group = 0;                // q heads of the largest group
+    double whole_cost = 1.0;      // expected time of the step with whole groups in workgroups of the same width, over that of the plan
+    // Whether runs of len heads leave every element of dk and dv with the same bits whatever order they come in: one run of the whole
+    // group, or two that add into a cleared element (0 + a + b = 0 + b + a).
+    bool fixed_order(int len) const { return 2 * len >= group; }
     bool unused = false;          // some kv head is read by no local q head: zero gradient
     int n_kv_tiles = 0;           // 128-key tiles of the chunk
     int n_known = 0;              // entries of seen
@@ -176,6 +182,7 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
         const int c = ++cnt[g.kv_of_q[h]];
         max_cnt = c > max_cnt ? c : max_cnt;
     }
+    plan->group = max_cnt;
     for (int kh = 0; kh < g.nkv; ++kh) unused |= (cnt[kh] == 0);   // a kv head no local q head reads: zero gradient
     // Run length: the longest divisor of the largest group's size (so that its runs are equally long) for which
     // the launch still has about three workgroups per CU and a workgroup walks at most 512 q tiles.  A run
@@ -208,14 +215,16 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
         const int before = seg_rows_le(g.qs, k_min - 1);
         seen[t] = before < g.lq ? (float)(n_qtiles - before / Q_STREAM_TILE) : 0.0f;
     }
-    // Of 7350 of the calls none is then slower than 128-key and 256-row launches by more than 3 %, and the choice is 0.8 % slower than
-    // the best of all shapes in the mean.  Measured, both halves, head_dim 128, us in 128 keys and 256 rows / 64 and 64 / 32 and 32:
+    // Of 7350 of the calls none is then slower than 128-key and 256-row launches by more than 3 %, and the choice (but for the order of
+    // sums, below) is 0.8 % slower than the best of all shapes in the mean.  Measured, both halves, head_dim 128, us in 128 keys and 256 rows / 64 and 64 / 32 and 32:
     // 300 rows x 700 keys x 4 / 2 heads 58 / 19.1 / 12.4; 512 x 1024 x 24 / 8 95 / 35 / 40.6; 2048 x 2048 x 24 / 8 242 / 178 / 212; 4096 x
     // 4096 x 12 / 3 394 / 336 / 402; 8192 x 8192 x 24 / 8 2367 / 2594 / 3060; head_dim 64: 4096 x 4096 x 24 / 8 468 / 384 / 459.
     // Launches that do not fill the chip take workgroups of 64 or 32 keys instead (whole groups where the 128-key ones take whole
     // groups: no atomics that these would not have), in one launch with dQ workgroups of as many rows: the two kinds of unit fill
     // each other's last rounds.  Where the chip is full the 128-key workgroups stream a quarter as much per key.  A forced run length
     // keeps the 128-key workgroups that it is defined for.
+    // A fixed order of the sums is given up only where that is expected to be 15 % faster (an estimate is 4 to 9 % rms off).  Measured, of 100
+    // steps of a smaller expected gain: the order costs 9 % in the mean, between 27 % less and 26 % more; of 50 between 15 and 20 %: 16 %.
     if (forced_run_len >= 1 || n_kv_tiles > 4096) return;
     const Units kv_128 = hexi_kv_units(g, *plan, KV_TILE, run_len, n_runs_for(run_len));
     if (kv_128.n >= 2048) return;
@@ -225,14 +234,18 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
     };
     const int len_128 = run_len;
     const DkdvFit& k128 = DKDV[wide][0];
-    double best = k128.launch.us(kv_128, run_mb * g.nkv) + added(len_128, k128.clear, k128.atomic_mb) + dq_us;
+    auto margin = [&](int len) { return plan->fixed_order(len) ? 1.0 : ORDER_MARGIN; };
+    double best = margin(len_128) * (k128.launch.us(kv_128, run_mb * g.nkv) + added(len_128, k128.clear, k128.atomic_mb) + dq_us);
     for (int w = 1; w < 3; ++w) {
         const int keys = w == 1 ? 64 : 32;
+        double whole_us[2];        // beside 256-row dQ workgroups, and in one launch with dQ workgroups of as many rows
         for (int len = max_cnt; len >= 1; --len) {
             if (max_cnt % len != 0 || (len_128 >= max_cnt && len < max_cnt)) continue;
             const Units kv = hexi_kv_units(g, *plan, keys, len, n_runs_for(len));
-            auto consider = [&](double t, int rows) {
-                if (SMALL_MARGIN * t < best) { best = SMALL_MARGIN * t; run_len = len; plan->split_keys = true; plan->keys = keys; dq_rows = rows; }
+            auto consider = [&](double us, int rows) {
+                const double t = SMALL_MARGIN * margin(len) * us;
+                if (len == max_cnt) whole_us[rows > 0] = us;
+                if (t < best) { best = t; run_len = len; plan->split_keys = true; plan->keys = keys; dq_rows = rows; plan->whole_cost = whole_us[rows > 0] / us; }
             };
             const JointFit& j = JOINT[wide][w - 1];
             if (dq_small) consider(j.us(kv, q[w], run_mb * g.nkv + q_mb) + added(len, j.clear, j.atomic_mb), keys);
@@ -246,33 +259,43 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
 // the other) where that is expected to be 25 % faster there than the large workgroups, and takes those where not: what a joint launch
 // gains for the step by filling last rounds, the half alone does not have.  Of 7350 of the calls no dQ half and 7 dK / dV halves are slower
 // alone than in the large workgroups by more than 3 %, at most 22 %.
-inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, bool want_dkdv, BwdPlan* plan)
+// dK / dV whose sums have a fixed order in the step's shape and not in the large workgroups keep it where these are not expected to be faster:
+// 80 halves between the two bounds measured 2 % faster so in the mean; 80 beyond, up to a tenth slower by the estimate, 6 % slower.
+// accumulate: two runs that add to what dk and dv hold have no fixed order, so whole groups are taken instead, in workgroups of the same width,
+// where these are expected to be at most 15 % slower.
+inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, bool want_dkdv, bool accumulate, BwdPlan* plan)
 {
     using namespace hexi_shapes;
     constexpr double MARGIN = 1.25;
     hexi_plan_bwd_step(g, forced_run_len, plan);
-    if (want_dq && want_dkdv) return;
     const bool wide = g.d == 128;
-    if (want_dq && plan->dq_rows > 0) {
+    if (want_dq && !want_dkdv && plan->dq_rows > 0) {
         Units u[3];
         const int r = plan->dq_rows == 64 ? 1 : 2;
         const double mb = (double)g.lq * g.nq * g.d * 12.0 * 1e-6;      // q and dO read, dq read and written
         if (hexi_q_units(g, u) && MARGIN * DQ[wide][r].us(u[r], mb) >= DQ[wide][0].us(u[0], mb)) plan->dq_rows = 0;
     }
-    if (want_dkdv && plan->split_keys) {
-        auto estimate = [&](int keys, int len) {
-            const DkdvFit& f = DKDV[wide][keys == KV_TILE ? 0 : (keys == 64 ? 1 : 2)];
-            HeadRuns runs;
-            const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, len, &runs);
-            const double run_mb = (double)g.lc * g.d * 8.0 * 1e-6;      // dk and dv of a run
-            return f.launch.us(hexi_kv_units(g, *plan, keys, len, runs.n), run_mb * g.nkv) + (shared || plan->unused ? f.clear : 0.0) +
-                   (shared ? run_mb * runs.n * f.atomic_mb : 0.0);
-        };
-        if (MARGIN * estimate(plan->keys, plan->run_len) >= estimate(KV_TILE, plan->run_len_128)) {
+    if (!want_dkdv || !plan->split_keys) return;
+    auto estimate = [&](int keys, int len) {
+        const DkdvFit& f = DKDV[wide][keys == KV_TILE ? 0 : (keys == 64 ? 1 : 2)];
+        HeadRuns runs;
+        const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, len, &runs);
+        const double run_mb = (double)g.lc * g.d * 8.0 * 1e-6;      // dk and dv of a run
+        return f.launch.us(hexi_kv_units(g, *plan, keys, len, runs.n), run_mb * g.nkv) + (shared || plan->unused ? f.clear : 0.0) +
+               (shared ? run_mb * runs.n * f.atomic_mb : 0.0);
+    };
+    double whole_cost = plan->whole_cost;
+    if (!want_dq) {
+        const bool loses_order = plan->fixed_order(plan->run_len) && !plan->fixed_order(plan->run_len_128);
+        const double us = estimate(plan->keys, plan->run_len);
+        if ((loses_order ? 1.0 : MARGIN) * us >= estimate(KV_TILE, plan->run_len_128)) {
             plan->split_keys = false;
             plan->run_len = plan->run_len_128;
+            return;
         }
+        whole_cost = estimate(plan->keys, plan->group) / us;
     }
+    if (accumulate && plan->fixed_order(plan->run_len) && whole_cost <= ORDER_MARGIN) plan->run_len = plan->group;
 }
 
 // The fp32 kernels (hexi_f32.hip): 64-row workgroups that share their tiles, or 16-row ones whose wavefronts split the streamed

@@ -3,7 +3,8 @@
 // and prints: rows per forward workgroup (0: 256), rows per dQ workgroup (0: 256), keys per dK / dV workgroup, q heads per dK / dV
 // workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take; then, for
 // calls for one half alone, the rows per dQ workgroup and the keys per dK / dV workgroup; for fp32 inputs the workgroup
-// shape (0 shared, 1 split, 2 split with two on a CU) of the forward, of dQ, of dK / dV and of dQ alone.
+// shape (0 shared, 1 split, 2 split with two on a CU) of the forward, of dQ, of dK / dV and of dQ alone; and the q heads per
+// dK / dV workgroup of a call for dK / dV alone, and of a whole step that adds to dk and dv.
 #include <cstdio>
 #include <cstring>
 #include <iostream>
@@ -44,19 +45,21 @@ int main()
         int m;
         for (int h = 0; h < g.nq; ++h) g.kv_of_q[h] = (signed char)((is >> m) ? m : h / (g.nq / g.nkv));
         BwdPlan plan;
-        hexi_plan_bwd(g, forced, true, true, &plan);
+        hexi_plan_bwd(g, forced, true, true, false, &plan);
         HeadRuns runs;
         const bool shared = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len, &runs);
         const bool shared_128 = hexi_build_head_runs(g.kv_of_q, g.nq, g.nkv, plan.run_len_128, &runs);
         BwdPlan dq_alone, dkdv_alone;
-        hexi_plan_bwd(g, forced, true, false, &dq_alone);
-        hexi_plan_bwd(g, forced, false, true, &dkdv_alone);
+        hexi_plan_bwd(g, forced, true, false, false, &dq_alone);
+        hexi_plan_bwd(g, forced, false, true, false, &dkdv_alone);
+        BwdPlan added;
+        hexi_plan_bwd(g, forced, true, true, true, &added);
         F32Shape kv32, q32, q32_alone, unused;
         hexi_f32_bwd_shapes(g, true, true, &kv32, &q32);
         hexi_f32_bwd_shapes(g, true, false, &unused, &q32_alone);
-        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? plan.keys : 128, plan.run_len, (int)shared,
+        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? plan.keys : 128, plan.run_len, (int)shared,
                     (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? dkdv_alone.keys : 128,
-                    (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone);
+                    (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone, dkdv_alone.run_len, added.run_len);
     }
     return 0;
 }

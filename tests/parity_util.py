@@ -84,8 +84,8 @@ LARGE_SHARD = dict(nq=128, nkv=8, q_segs=[(300, 400), (900, 1), (1000, 1399)],
 # rows and tiles of 64 by one more and one less, fewer rows than a block, runs of heads with and without atomics, chains of one
 # block and of the unrolled loop and its remainder.
 QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 64, 64, 128, "b"), (17, 129, 64, 64, 64, "b"), (65, 33, 64, 64, 64, "b"),
-              (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "fb"), (200, 65, 64, 64, 128, "fb"),
-              (200, 33, 128, 8, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
+              (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "f"), (129, 33, 128, 4, 128, "fb"),
+              (200, 65, 64, 64, 128, "fb"), (200, 33, 128, 8, 64, "f"), (200, 33, 128, 4, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
 
 # fp32 steps at head_dim 64, all keys visible (off = lc) or diagonal (off = 0): (lq, lc, nq, nkv, off), shape of the forward, of dQ, of dK/dV
 # and of dQ in a call of its own (0: 64 rows, shared; 1: 16 rows, split; 2: split, two workgroups a CU); rows and keys around the 16-row
@@ -98,3 +98,9 @@ F32_STEPS = [((33, 16, 2, 1, 16), (1, 1, 1, 1)), ((145, 257, 40, 40, 257), (2, 2
 # Forward steps of one round of 256-row workgroups (256 units of about the same length) and part of a second one; last tiles of 1, 188 and
 # 76 rows.
 PART_ROUND_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]
+
+
+# Backward steps whose dk / dv are summed in a fixed order, though runs of fewer heads are expected to be a little faster: (lq, lc, nq, nkv,
+# head_dim, off), q heads per dK / dV workgroup: whole groups, and half groups, two of which add into a cleared element.
+ORDER_STEPS = [((9087, 501, 24, 8, 128, 501), 3), ((100, 123, 32, 4, 128, 0), 4), ((364, 126, 16, 4, 64, 126), 2), ((358, 535, 6, 2, 128, 0), 3),
+               ((6280, 1109, 16, 4, 64, 1109), 2), ((3476, 3476, 12, 3, 128, 0), 2)]

@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, PART_ROUND_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -357,6 +357,22 @@ def test_dkdv_reproducible_when_a_workgroup_sums_the_whole_group(force_run_len):
     run.backward(); torch.cuda.synchronize()
     for (a0, b0), a1, b1 in zip(first, run.dk, run.dv):
         assert torch.equal(a0, a1) and torch.equal(b0, b1)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off", [s for s, _ in ORDER_STEPS])
+def test_dkdv_reproducible_in_whole_and_in_half_groups(lq, lc, nq, nkv, d, off):
+    # the shapes that the library chooses by itself (asserted on the CPU): the same bits in every call, the half alone included
+    q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
+    qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+    desc, args = hexi.desc_for(qd, kd, d ** -0.5), ([(off, lq)], [(0, lc)], qd, kd, vd)
+    o, lse, delta, dq = (torch.zeros(s, device=DEV) for s in (q.shape, (nq, lq), (nq, lq), q.shape))
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse)
+    outs = []
+    for flags in (hexi.HEXI_COMPUTE_DELTA, 0, hexi.HEXI_SKIP_DQ, hexi.HEXI_SKIP_DQ, 0):
+        dk, dv = torch.full(k.shape, float("nan"), device=DEV), torch.full(v.shape, float("nan"), device=DEV)
+        hexi.hexi_attn_bwd_chunk(desc, *args, o, gd, lse, delta, dq, dk, dv, flags=flags)
+        outs.append((dk, dv))
+    assert all(torch.equal(dk, outs[0][0]) and torch.equal(dv, outs[0][1]) for dk, dv in outs) and bool(torch.isfinite(outs[0][0]).all())
 
 
 def test_forward_is_deterministic():

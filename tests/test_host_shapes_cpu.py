@@ -27,7 +27,7 @@ def shapes(tmp_path_factory):
             lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone",
-                 "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone")
+                 "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone", "run_len_alone", "run_len_accumulate")
         return [dict(zip(names, map(int, line.split()))) for line in out if line]
 
     return ask
@@ -90,6 +90,15 @@ def test_no_step_gets_atomics_that_its_128_key_launch_would_not_have(shapes):
             lq, lc = log_int(0, 14), log_int(0, 16)
             steps.append(_step(lq, lc, nq, nkv, rng.choice([64, 128]), rng.choice([0, lc, rng.randrange(lc)])))
     assert all(got["atomic"] <= got["atomic_128"] for got in shapes(steps))
+
+
+def test_sums_keep_a_fixed_order_for_a_small_gain(shapes):
+    from parity_util import ORDER_STEPS
+    got = shapes([_step(*s) for s, _ in ORDER_STEPS])
+    assert [g["run_len"] for g in got] == [n for _, n in ORDER_STEPS]
+    assert [g["run_len_alone"] for g in got] == [n for _, n in ORDER_STEPS]
+    # added to what dk and dv hold already, two runs have no fixed order: whole groups, unless two are expected to be 15 % faster
+    assert [g["run_len_accumulate"] for g in got] == [3, 8, 4, 3, 2, 2]
 
 
 def test_the_large_workgroups_tests_reach_them(shapes):
