@@ -87,6 +87,19 @@ QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 6
               (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "f"), (129, 33, 128, 4, 128, "fb"),
               (200, 65, 64, 64, 128, "fb"), (200, 33, 128, 8, 64, "f"), (200, 33, 128, 4, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
 
+# Single steps of the 64-row forward kernel and of dQ in 64-row workgroups in a call of its own, all keys visible or half of them (off = lc / 2).
+QUAD_FWD_STEPS = [(130, 1000, 64, 16, 128), (520, 600, 64, 16, 64)]
+QUAD_DQ_STEPS = [(130, 700, 64, 16, 128), (260, 700, 64, 16, 64)]
+
+# A step whose dK / dV are cut into workgroups of 64 keys beside dQ in 256-row ones: (lq, lc, nq, nkv, head_dim, off), with one head to a group and,
+# with atomics, three.
+WIDE_DQ_STEPS = [(1998, 193, 64, 64, 64, 96), (2938, 83, 96, 32, 128, 83)]
+
+# A shard of three segments whose steps all go to workgroups of 64 rows and keys: chunks with holes, wholly and partly visible; a kv
+# head's q heads are not adjacent.
+QUAD_SHARD = dict(nq=64, nkv=16, q_segs=[(1000, 180), (1230, 1), (1451, 210)], chunks=[[(0, 200), (500, 400)], [(200, 255), (1100, 346)], [(900, 200), (1460, 401)]],
+                  kv_of_q=[(5 * h) % 16 for h in range(64)])
+
 # fp32 steps at head_dim 64, all keys visible (off = lc) or diagonal (off = 0): (lq, lc, nq, nkv, off), shape of the forward, of dQ, of dK/dV
 # and of dQ in a call of its own (0: 64 rows, shared; 1: 16 rows, split; 2: split, two workgroups a CU); rows and keys around the 16-row
 # blocks, the 64-row tiles and the 128-row tiles of the split shapes, chunks shorter than a split tile.

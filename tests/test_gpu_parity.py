@@ -12,7 +12,8 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_STEPS, check, chunk_slices, oracle_full, to64
+from parity_util import (F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
+                         WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -247,7 +248,8 @@ def test_strided_inputs_and_accumulate_flags(run_len, force_run_len):
 def test_dq_residuals_of_large_ds(d):
     # The dQ kernels add the rounding residuals of a 32-key block's dS when some |dS| >= 2.  With dO scaled by 64 (exact
     # in bf16; every gradient is linear in dO) nearly every block takes that path -- masked and unmasked tiles, ragged
-    # tails -- here in the kernel for small launches; test_large_workgroups_residuals has the 256-row one -- and dq / 64 must still match the oracle, more closely than without the scaling
+    # tails -- here in the 32-row kernel; test_64_row_dq_residuals and
+    # test_large_workgroups_residuals have the others -- and dq / 64 must still match the oracle, more closely than without the scaling
     # (dS carried to fp32 accuracy instead of bf16); dk and dv, which have no such path, must come out as exactly 64 x
     # their unscaled values.
     w = _custom(f"residual_{d}", "bf16", 4, 2, d, 1500, [(60, 200), (700, 777)], [[(0, 333)], [(333, 617), (950, 27)], [(977, 523)]],
@@ -473,7 +475,8 @@ def test_measured_compute_rate_feeds_the_scheduler():
 @pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 1, 1, 1), (2, 2, 15, 17), (3, 1, 16, 128), (2, 1, 17, 129), (2, 1, 129, 15), (4, 2, 300, 257), (16, 16, 1000, 1010)])
 def test_f32_workgroup_shapes(nq, nkv, lq, lc, d):
     # lengths at the edges of the fp32 kernels' 16-row blocks and 128-row (split) / 32-row (shared) tiles; the last size
-    # is dealt to the shared shape (256 workgroups of 64 rows), the others to the split one.  The second chunk is diagonal.
+    # is dealt to the shared shape (256 workgroups of 64 rows) at head_dim 128 and to two split workgroups a CU at 64, the others to the
+    # split one.  The second chunk is diagonal.
     w = _custom(f"f32_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
     run, inputs, ref = _run_and_compare(w, seed=lq * 1000 + lc + d)
     # dk / dv under HEXI_ACCUMULATE: the running value plus the gradient; dq_acc adds up over calls
@@ -489,7 +492,7 @@ def test_f32_workgroup_shapes(nq, nkv, lq, lc, d):
 @pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 2, 31, 33), (3, 1, 32, 64), (2, 1, 95, 257), (24, 8, 500, 1000), (8, 1, 600, 600)])
 def test_bf16_split_workgroup_shapes(nq, nkv, lq, lc, d):
     # lengths around the 32-row blocks of the kernels for small launches, fewer and more of them than a workgroup has
-    # wavefronts; the fourth size takes the 64-row workgroups of the forward and dQ kernels, the last one cuts its group of
+    # wavefronts; at head_dim 128 the fourth size takes 64-row workgroups instead, the last one cuts its group of
     # heads into runs that add their dk / dv.  The second chunk is diagonal and in two segments.
     w = _custom(f"split_{nq}_{lq}_{lc}_{d}", "bf16", nq, nkv, d, lc + lq + 7, [(lc, lq // 2), (lc + lq // 2 + 7, lq - lq // 2)],
                 [[(0, lc)], [(lc, lq // 2 + 7), (lc + lq // 2 + 7, lq - lq // 2)]])
@@ -531,7 +534,8 @@ def _exact_ds_case(lq, lc, nq, nkv, d, seed):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("lq,lc,nq,nkv", [(1, 1, 1, 1), (40, 100, 2, 1), (300, 700, 4, 2), (512, 1000, 24, 8), (300, 2100, 128, 8),
-                                          (1024, 320, 64, 64), (1024, 385, 64, 4)])      # the last two: 256-row workgroups
+                                          (1024, 320, 64, 64), (1024, 385, 64, 4),      # 256-row workgroups
+                                          (130, 700, 64, 16), (260, 700, 64, 16)])      # 64-row ones: both at head_dim 128, the last at 64
 def test_large_ds_reaches_dq_unrounded(lq, lc, nq, nkv, d):
     # a dS of 24 significant bits must come out of the dQ kernels bit for bit (a residual rounded to bf16 loses up to
     # 2^-18 of it)
@@ -584,7 +588,7 @@ def _infinite_lse_case(dtype, lq, lc, nq, nkv, d, dead):
 
 
 @pytest.mark.parametrize("dead", [-float("inf"), float("inf")])
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (512, 1000, 24, 8, 128), (512, 1000, 24, 8, 64)])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (512, 1000, 24, 8, 128), (512, 1000, 24, 8, 64)] + QUAD_DQ_STEPS)
 def test_bf16_dq_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
     # a row switched off through its LSE contributes nothing, whether or not it sees keys
     (q, k, v, d_o, lse, delta), qs, ks, scale, ref = _infinite_lse_case("bf16", lq, lc, nq, nkv, d, dead)
@@ -703,9 +707,19 @@ def test_large_workgroups_segments_strides_and_head_map(d, run_len, force_run_le
     # strided q / dO and k / v, three-segment shard, chunks with holes and diagonal parts, accumulated o / lse / dq, dk / dv
     # under HEXI_ACCUMULATE; dK / dV in the launcher's shape and in 128-key workgroups walking whole groups or runs with a remainder
     force_run_len(run_len)
-    s = LARGE_SHARD
+    _segments_strides_and_head_map(LARGE_SHARD, d, run_len, together=False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("together", [False, True])
+def test_64_wide_workgroups_segments_strides_and_head_map(d, together):
+    # the same in workgroups of 64 rows and keys, the halves of a backward step in one launch too
+    _segments_strides_and_head_map(QUAD_SHARD, d, 0, together)
+
+
+def _segments_strides_and_head_map(s, d, run_len, together):
     nq, nkv, q_segs, kv_of_q, scale = s["nq"], s["nkv"], s["q_segs"], s["kv_of_q"], d ** -0.5
-    print(f"\n  large shard: d={d} run_len={run_len}", flush=True)
+    print(f"\n  shard of {nq}/{nkv} heads: d={d} run_len={run_len} together={together}", flush=True)
     g = torch.Generator().manual_seed(d + run_len)
     rnd = lambda *x: torch.randn(x, generator=g).to(torch.bfloat16)
     q_pos = np.concatenate([np.arange(a, a + n) for a, n in q_segs])
@@ -727,6 +741,10 @@ def test_large_workgroups_segments_strides_and_head_map(d, run_len, force_run_le
         hexi.hexi_attn_fwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], o, lse, flags=hexi.HEXI_ACCUMULATE)
     dk, dv = [torch.full(t.shape, 0.5, device=DEV) for t in ks], [torch.full(t.shape, -0.25, device=DEV) for t in ks]
     for j, ch in enumerate(s["chunks"]):
+        if together:
+            hexi.hexi_attn_bwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], o, gd, lse, delta, dq, dk[j], dv[j],
+                                     flags=hexi.HEXI_ACCUMULATE | (hexi.HEXI_COMPUTE_DELTA if j == 0 else 0))
+            continue
         hexi.hexi_attn_bwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], o, gd, lse, delta, dq, None, None,
                                  flags=hexi.HEXI_SKIP_DKDV | (hexi.HEXI_COMPUTE_DELTA if j == 0 else 0))
         hexi.hexi_attn_bwd_chunk(desc[j], q_segs, ch, qd, kd[j], vd[j], None, gd, lse, delta, None, dk[j], dv[j],
@@ -741,10 +759,11 @@ def test_large_workgroups_segments_strides_and_head_map(d, run_len, force_run_le
         check(name, got, want, "bf16", abs_factor=max(1.0, float(np.max(np.abs(want))) / 8))
 
 
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(1024, 320, 64, 64, 128), (1024, 385, 64, 4, 64)])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(1024, 320, 64, 64, 128), (1024, 385, 64, 4, 64)] + QUAD_FWD_STEPS)
 def test_large_workgroups_softmax_fallback(lq, lc, nq, nkv, d):
     # The 256-row forward kernel fixes each row's softmax reference at its first key tile and repeats the workgroup with the
-    # exact online softmax when a row's sum leaves [2^-60, 2^60].  Every second kv head scales the keys beyond the first
+    # exact online softmax when a row's sum leaves [2^-60, 2^60]; the 64-row one (the last two sizes) raises its reference as it goes, and the parts
+    # of its four wavefronts differ by such factors when they are combined.  Every second kv head scales the keys beyond the first
     # tile so that later scores exceed the first tile's maximum by far more than 2^100; the others do the reverse.
     q, _, k, v = _large_step_inputs(lq, lc, nq, nkv, d, 99)
     q = (q.float() * 3).to(torch.bfloat16)
@@ -767,6 +786,16 @@ def test_large_workgroups_softmax_fallback(lq, lc, nq, nkv, d):
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", [(1024, 320, 64, 64, 128), (1024, 385, 64, 4, 64)])
 def test_large_workgroups_residuals(lq, lc, nq, nkv, d):
     # test_dq_residuals_of_large_ds in the 256-row dQ kernel, whose residuals are fp32 products
+    _dq_residuals(lq, lc, nq, nkv, d)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", QUAD_DQ_STEPS)
+def test_64_row_dq_residuals(lq, lc, nq, nkv, d):
+    # the same in the 64-row one, whose residuals are two more bf16 operands on the fragments of the product before
+    _dq_residuals(lq, lc, nq, nkv, d)
+
+
+def _dq_residuals(lq, lc, nq, nkv, d):
     q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, 41, k_scale=2.0)
     off, scale = lc // 2, d ** -0.5
     print(f"\n  large residuals: {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
@@ -784,8 +813,9 @@ def test_large_workgroups_residuals(lq, lc, nq, nkv, d):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nkv,lq,lc", [(16, 2, 1000, 1010), (32, 16, 1000, 1010), (16, 16, 100, 1010), (6, 3, 77, 90)])
 def test_f32_grouped_heads_in_both_shapes(nq, nkv, lq, lc, d):
-    # fp32 with several q heads per kv head: dQ in 64-row shared and dK / dV in 16-row split workgroups (two launches), both
-    # shared, the other way round, both split; the halves together and in calls of their own, with the same bits (no sum is
+    # fp32 with several q heads per kv head: at head_dim 128 dQ in 64-row shared and dK / dV in 16-row split workgroups (two launches), both
+    # shared, the other way round, both split; at 64 split, two of them a CU in the second size, and dK / dV shared in the first chunk of the third
+    # (test_f32_shapes_at_head_dim_64 has the others).  The halves together and in calls of their own, with the same bits (no sum is
     # spread over workgroups)
     w = _custom(f"f32_gqa_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
     run, inputs, ref = _run_and_compare(w, seed=lq + lc + d)
@@ -839,6 +869,22 @@ def test_64_wide_workgroups_accumulate():
         # (the same sums, in another order where they are atomic)
         bound = 1e-5 * float(outs[0][0].abs().max() + outs[0][1].abs().max() + 1.0)
         assert float((outs[1][0] - outs[0][0] - 0.5).abs().max()) <= bound and float((outs[1][1] - outs[0][1] + 0.25).abs().max()) <= bound
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off", WIDE_DQ_STEPS)
+def test_64_key_workgroups_beside_256_row_dq(lq, lc, nq, nkv, d, off):
+    print(f"\n  64 keys, 256 rows: {lq} x {lc} x {nq}/{nkv} x {d} at {off}", flush=True)
+    q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
+    qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+    desc, args = hexi.desc_for(qd, kd, d ** -0.5), ([(off, lq)], [(0, lc)], qd, kd, vd)
+    o, lse, delta, dq = torch.empty(q.shape, device=DEV), torch.empty((nq, lq), device=DEV), torch.empty((nq, lq), device=DEV), torch.zeros(q.shape, device=DEV)
+    dk, dv = torch.full(k.shape, 7.0, device=DEV), torch.full(v.shape, 7.0, device=DEV)
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse)
+    hexi.hexi_attn_bwd_chunk(desc, *args, o, gd, lse, delta, dq, dk, dv, flags=hexi.HEXI_COMPUTE_DELTA)
+    ref = oracle.attn_bwd(to64(q), np.arange(off, off + lq), to64(k), to64(v), np.arange(lc), to64(d_o), d ** -0.5)
+    check("dq", dq.cpu(), ref["dq"], "bf16")
+    for name, got in (("dk", dk), ("dv", dv)):      # (the bound on a single element as in test_large_workgroups_boundary_sizes)
+        check(name, got.cpu(), ref[name], "bf16", abs_factor=max(1.0, float(np.max(np.abs(ref[name]))) / 8))
 
 
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS)

@@ -116,6 +116,15 @@ def test_the_64_wide_workgroups_tests_reach_them(shapes):
         assert "b" not in halves or (got["dq_rows"] == 64 and got["keys"] == 64), step
 
 
+def test_the_single_steps_of_64_wide_workgroups_reach_them(shapes):
+    from parity_util import QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD as s, WIDE_DQ_STEPS
+    assert [got["fwd_rows"] for got in shapes([_step(*x, off) for x in QUAD_FWD_STEPS for off in (x[1], x[1] // 2)])] == [64] * 4
+    assert [got["dq_alone"] for got in shapes([_step(*x, off) for x in QUAD_DQ_STEPS for off in (x[1], x[1] // 2)])] == [64] * 4
+    assert [(got["dq_rows"], got["keys"], got["atomic"]) for got in shapes([_step(*x) for x in WIDE_DQ_STEPS])] == [(0, 64, 0), (0, 64, 1)]
+    for got in shapes([(d, s["nq"], s["nkv"], s["q_segs"], ch, s["kv_of_q"]) for d in (64, 128) for ch in s["chunks"]]):
+        assert (got["fwd_rows"], got["dq_rows"], got["keys"], got["keys_alone"]) == (64, 64, 64, 64)
+
+
 def test_a_round_and_a_part_of_large_forward_workgroups(shapes):
     # 384, 384, 320 and 288 units of 256 rows; us measured in 256 / 64 rows: 226 / 232, 127.5 / 133.1, 167 / 151, 123 / 108
     steps = [_step(lq, lc, nq, nkv, 128, lc) for lq, lc, nq, nkv in ((4096, 4096, 24, 8), (4096, 2048, 24, 8), (5000, 3000, 16, 4), (9000, 2000, 8, 2))]
