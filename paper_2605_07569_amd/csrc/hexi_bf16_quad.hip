@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 2 : 1) fwd_quad_bf16_kernel(con
         constexpr bool STEADY = decltype(steadyc)::value;
         constexpr uint32_t here = buf * 2 * C::TILE_BYTES, there = (buf ^ 1) * 2 * C::TILE_BYTES;
         constexpr int N = C::NDB * 2, SLOTS = 2 * C::NKS;  // MFMAs of a row block in the second product, of both in the scores
-        constexpr int LEAD = D == 128 ? 4 : 4, EARLY = 12;       // pairs of probabilities before the first MFMA, before the second product
+        constexpr int LEAD = 4, EARLY = 12;                // pairs of probabilities before the first MFMA, before the second product
         const bool next = STEADY || b + NW < n_blocks, next2 = STEADY || b + 2 * NW < n_blocks;
         const int b2 = b + 2 * NW;
         const uint16_t *k2 = k + (long long)(b2 * TB) * g.kv_stride_tok, *v2 = v + (long long)(b2 * TB) * g.kv_stride_tok;
@@ -460,6 +460,8 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     const float c_log2 = g.scale * LOG2E;
 #pragma unroll
     for (int r = 0; r < 2; ++r) neg_l[r] = neg_l[r] == -INFINITY ? -INFINITY : -neg_l[r] * LOG2E;       // a row whose LSE is infinite has P = 0
+    // The compiler waits here for everything in flight, not for these loads alone: it does not see the transfers behind them.  So the first
+    // K and V have landed too before the barrier, and the wait in front of that finds nothing left to wait for.
     asm volatile("" ::"v"(neg_l[0]), "v"(neg_l[1]), "v"(delta[0]), "v"(delta[1]));
     f32x16 dq[2][C::NDB];
 #pragma unroll
@@ -492,6 +494,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     if (sp + NW < n_blocks) { fetch_v(sp + NW, 1); fetch_k(sp + NW, 1); }
 
     constexpr int N = 2 * C::NDB;                          // MFMAs of a row block in the third product
+    static_assert(N == C::NKS, "one transposed read per MFMA");
     constexpr int AHEAD = 3;
     bf16x8 x[C::NKS];
     f32x16 nd[2];                                          // -Delta of the lane's rows, which dP is accumulated on
@@ -559,7 +562,7 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
             dp[1] = mfma32(x[ks], gf[1][ks], ks == 0 ? nd[1] : dp[1]);
             __builtin_amdgcn_sched_barrier(0);
             for (int i = ks * 8 / C::NKS; i < (ks + 1) * 8 / C::NKS; ++i) ds2(0, i);
-            if (ks * N / C::NKS < N) read(ks * N / C::NKS);
+            read(ks);
             __builtin_amdgcn_sched_barrier(0);
         }
         mask(0);

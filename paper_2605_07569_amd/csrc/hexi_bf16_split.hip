@@ -304,10 +304,12 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int
     for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
-    if (asked) wait_transfers<2 * C::XFERS>();             // Q, dO, LSE and Delta have landed
+    if (asked) wait_transfers<2 * C::XFERS>();             // Q and dO have landed
     else wait_transfers<0>();
     const float neg_l = lse == -INFINITY ? -INFINITY : -lse * LOG2E;       // a row whose LSE is infinite has P = 0
-    asm volatile("" ::"v"(neg_l), "v"(delta));             // (no wait for these inside the loop)
+    // No wait for these inside the loop.  (The compiler waits here for everything in flight, the first K and V included: it does not see
+    // the transfers issued behind these two loads.)
+    asm volatile("" ::"v"(neg_l), "v"(delta));
     block_barrier();
     bf16x8 qf[C::NKS], gf[C::NKS];
 #pragma unroll

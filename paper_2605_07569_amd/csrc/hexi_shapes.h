@@ -1,4 +1,4 @@
-// Which workgroup shapes a bf16 ring step is launched with, from its sizes: the rules of the launchers, host code alone.
+// Which workgroup shapes a ring step is launched with, from its sizes: the rules of the bf16 and fp32 launchers, host code alone.
 #pragma once
 #include <cmath>
 #include "hexi_internal.h"
