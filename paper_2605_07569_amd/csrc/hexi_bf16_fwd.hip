@@ -72,7 +72,7 @@ template <int D> struct FwdSmem {
 };
 
 template <int D>
-__global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const int n_q_tiles, const XcdSplit split)
+__global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const int n_q_tiles, const QShare share, const XcdSplit split)
 {
     using C = FwdCfg<D>;
     constexpr int NKS = C::NKS, NDB = C::NDB, K_ROW_BYTES = C::K_ROW_BYTES, V_ROW_BYTES = C::V_ROW_BYTES;
@@ -99,8 +99,9 @@ __global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const in
         unit = split.start[xcd] + slot;
         if (unit >= split.start[xcd + 1]) return;
     }
-    const int h = unit / n_q_tiles;
-    const int q_tile = n_q_tiles - 1 - (unit - h * n_q_tiles);
+    int h, p;
+    share.unit(unit, &h, &p);
+    const int q_tile = n_q_tiles - 1 - p;
     const int kvh = g.kv_of_q[h];
     const int row0 = q_tile * WG_ROWS;
     const int grow0 = row0 + GROUP_ROWS * grp;
@@ -476,7 +477,8 @@ __global__ void __launch_bounds__(512) fwd_bf16_kernel(const FwdArgs a, const in
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s)
 {
     const AttnGeom& g = a.g;
-    if (const int rows = hexi_fwd_split_rows(g); rows > 0) return rows == 64 ? hexi_launch_fwd_quad_bf16(a, s) : hexi_launch_fwd_split_bf16(a, s);
+    QShare share;
+    if (const int rows = hexi_fwd_split_rows(g, &share); rows > 0) return rows == 64 ? hexi_launch_fwd_quad_bf16(a, {}, s) : hexi_launch_fwd_split_bf16(a, s);
     const int n_q_tiles = (g.lq + WG_ROWS - 1) / WG_ROWS;
     // cost of a unit: the key tiles its q tile streams, plus the prologue and epilogue (about six tiles' worth);
     // a unit that sees nothing of the chunk returns at once under HEXI_ACCUMULATE and only writes zeros otherwise
@@ -489,10 +491,13 @@ hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s)
         cost[p] = nt > 0 ? (float)nt + 6.0f : (a.accumulate ? 0.25f : 2.0f);
     }
     unsigned grid = 0;
-    const XcdSplit split = hexi_split_units(g.nq * n_q_tiles, [&](int u) { const int p = u % n_q_tiles; return cost[p < n_known ? p : n_known - 1]; }, &grid);
-    if (grid == 0) return hipSuccess;
-    if (g.d == 128) fwd_bf16_kernel<128><<<grid, 512, 0, s>>>(a, n_q_tiles, split);
-    else if (g.d == 64) fwd_bf16_kernel<64><<<grid, 512, 0, s>>>(a, n_q_tiles, split);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    const XcdSplit split = hexi_split_units(share.n_units(g.nq), [&](int u) { int h, p; share.unit(u, &h, &p); return cost[p < n_known ? p : n_known - 1]; }, &grid);
+    if (grid > 0) {
+        if (g.d == 128) fwd_bf16_kernel<128><<<grid, 512, 0, s>>>(a, n_q_tiles, share, split);
+        else if (g.d == 64) fwd_bf16_kernel<64><<<grid, 512, 0, s>>>(a, n_q_tiles, share, split);
+        else return hipErrorInvalidValue;
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || share.tiles >= n_q_tiles) return e;
+    return hexi_launch_fwd_quad_bf16(a, rest_of(share, n_q_tiles), s);      // the first rows of every head
 }

@@ -63,7 +63,7 @@ __device__ __forceinline__ float add_rounded(uint32_t p, float sum)
 }
 
 template <int D>
-__global__ void __launch_bounds__(256, D == 64 ? 2 : 1) fwd_quad_bf16_kernel(const FwdArgs a, const int n_q_tiles)
+__global__ void __launch_bounds__(256, D == 64 ? 2 : 1) fwd_quad_bf16_kernel(const FwdArgs a, const QuadRest rest)
 {
     using C = QuadCfg<D>;
     const AttnGeom& g = a.g;
@@ -78,7 +78,9 @@ __global__ void __launch_bounds__(256, D == 64 ? 2 : 1) fwd_quad_bf16_kernel(con
 
     // heads of a q tile side by side, the longest (last) q tiles first
     const int h = blockIdx.x;
-    const int row0 = (n_q_tiles - 1 - (int)blockIdx.y) * ROWS;
+    const int q_tile = rest.tiles - 1 - (int)blockIdx.y;
+    if (!rest.has(h, q_tile)) return;
+    const int row0 = q_tile * ROWS;
     const int kvh = arg_byte(g.kv_of_q, h);
     const uint16_t* k = static_cast<const uint16_t*>(a.k) + (long long)kvh * g.kv_stride_head;
     const uint16_t* v = static_cast<const uint16_t*>(a.v) + (long long)kvh * g.kv_stride_head;
@@ -987,12 +989,12 @@ __global__ void __launch_bounds__(256, 1) bwd_quad_bf16_kernel(const BwdArgs a, 
 
 }  // namespace
 
-hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, hipStream_t s)
+hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, QuadRest rest, hipStream_t s)
 {
-    const int n_q_tiles = (a.g.lq + ROWS - 1) / ROWS;
-    const dim3 grid((unsigned)a.g.nq, (unsigned)n_q_tiles);
-    if (a.g.d == 128) fwd_quad_bf16_kernel<128><<<grid, 256, 0, s>>>(a, n_q_tiles);
-    else if (a.g.d == 64) fwd_quad_bf16_kernel<64><<<grid, 256, 0, s>>>(a, n_q_tiles);
+    if (rest.tiles == 0) rest.tiles = (a.g.lq + ROWS - 1) / ROWS;
+    const dim3 grid((unsigned)a.g.nq, (unsigned)rest.tiles);
+    if (a.g.d == 128) fwd_quad_bf16_kernel<128><<<grid, 256, 0, s>>>(a, rest);
+    else if (a.g.d == 64) fwd_quad_bf16_kernel<64><<<grid, 256, 0, s>>>(a, rest);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -62,6 +62,32 @@ struct BwdArgs {
     int want_dq, want_dkdv;   // which halves of the backward step to run
 };
 
+// Which 256-row q tiles a launch of large workgroups takes: the last `tiles` of every head, one more of the first `extra` heads.  Its
+// units are numbered head by head, a head's last tile first.
+struct QShare {
+    int tiles, extra;
+    __host__ __device__ int n_units(int nq) const { return nq * tiles + extra; }
+    __host__ __device__ void unit(int u, int* h, int* p) const     // p: tiles from the end of the shard
+    {
+        const int first = extra * (tiles + 1), n = u < first ? tiles + 1 : tiles;
+        const int v = u < first ? u : u - first;
+        *h = v / n + (u < first ? 0 : extra);
+        *p = v - v / n * n;
+    }
+};
+// The 64-row tiles that are left of it: the first `tiles` of every head (0: all of the shard), four fewer of the first `less_heads` heads.
+struct QuadRest {
+    int tiles = 0, less_heads = 0;
+    __host__ __device__ bool has(int h, int tile) const { return h >= less_heads || tile < tiles - 4; }
+};
+__host__ __device__ inline QuadRest rest_of(const QShare& share, int n_q_tiles)
+{
+    QuadRest rest;
+    rest.tiles = 4 * (n_q_tiles - share.tiles);
+    rest.less_heads = share.extra;
+    return rest;
+}
+
 // Work split over the 8 XCDs of the chip.  Workgroup ids are dealt round-robin to the XCDs (id % 8) and every XCD
 // starts its workgroups in id order, so workgroup `id` takes unit start[id % 8] + id / 8 of a launch whose units are
 // numbered so that neighbours share their streamed operands (same head, adjacent tiles): every XCD works on a
@@ -140,7 +166,7 @@ hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);      // 256
 hipError_t hexi_launch_fwd_split_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_split_bf16(const BwdArgs& a, bool dq, const HeadRuns& runs, bool shared, hipStream_t s);
 // ... and of 64 (four), for launches that do not fill the chip with the large ones
-hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, hipStream_t s);
+hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, QuadRest rest, hipStream_t s);
 hipError_t hexi_launch_bwd_quad_bf16(const BwdArgs& a, bool dq, const HeadRuns& runs, bool shared, hipStream_t s);
 hipError_t hexi_launch_merge(long long n_rows, int nq, int d, float* o_acc, float* lse_acc, const float* o_part,
                              const float* lse_part, void* o_final, int o_final_dtype, hipStream_t s);

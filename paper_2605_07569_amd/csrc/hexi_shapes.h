@@ -105,21 +105,54 @@ inline bool hexi_q_units(const AttnGeom& g, Units (&u)[3])
     return u[0].n < 1024;
 }
 
+// Which tiles of a forward step are given to 256-row workgroups where it is shared between these and 64-row ones in a second launch: as many as
+// fill whole rounds of 256 units; the rest of the rows has to fit one round of 64-row workgroups.  All of them: not to be shared.  A nearly
+// empty last round costs as much as a whole one, a round of 64-row workgroups a quarter of that and a launch.  Units have to be of about
+// the same length: unequal ones fill each other's last round already.  us: the expected time.
+inline QShare hexi_fwd_share(const AttnGeom& g, const Units (&u)[3], double* us)
+{
+    using namespace hexi_shapes;
+    const int n_q_tiles = (g.lq + Q_TILE - 1) / Q_TILE;
+    const QShare all = {n_q_tiles, 0};
+    if (g.d != 128) return all;            // head_dim 64: 64-row workgroups alone are the better choice wherever sharing would be one
+    if (u[0].n != (long long)g.nq * n_q_tiles || u[0].longest * (double)u[0].n > 1.1 * u[0].sum) return all;
+    const double mb = (double)g.lq * g.nq * g.d * 6.0 * 1e-6;      // q read, o written
+    const int n = (int)u[0].n, big = n / 256 * 256, small = n - big;
+    if (small == 0 || 4 * small > 256 || big / g.nq == 0) return all;
+    const double mean = u[0].sum / n, part = (double)big / n;
+    Units first, rest;
+    first.add(mean, big);
+    rest.add(ceil(mean / 2.0), 4LL * small);
+    *us = FWD[1][0].us(first, mb * part) + FWD[1][1].us(rest, mb * (1.0 - part));
+    return {big / g.nq, big % g.nq};
+}
+
 // Rows per forward workgroup of the smaller kernels (32 or 64), or 0 for the 256-row kernel, which is kept unless another is expected
 // to be 8 % faster: of 8000 of the calls 3 are then slower than in 256-row workgroups by more than 3 %, at most 8 % (14 by more than 10 % at
 // a margin of 5 %), and the choice is 0.8 % slower than the best of the three in the mean.  32-row workgroups beyond three rounds stream
 // too much.  Measured, us in 256 / 64 / 32 rows, head_dim 128: 300 rows x 700 keys x 4 heads 28.3 / 13.1 / 9.3; 512 x 1024 x 24 34.1 / 15.7 / 19.7;
 // 1024 x 1024 x 24 37.9 / 28.4 / 28.9; 2048 x 2048 x 24 64.7 / 69.8 / 88.5; head_dim 64: 2048 x 4096 x 24 80.7 / 68.7 / 82.0.
-inline int hexi_fwd_split_rows(const AttnGeom& g)
+// share: the 256-row workgroups' part of a step for which 0 is returned.  It is shared with 64-row ones where that is expected to be 10 % faster,
+// more than the estimates are off.  Whole passes of four visible steps, merged inside or by a launch of their own, us in one kernel / shared, units left
+// over a round: 5612 x 24 heads 2172 / 1891 (16), 11725 x 12 4193 / 3635 (40), 6128 x 24 2254 / 2001 (64), 4862 x 16 1019 / 912 (48), 4184 x 16 917 / 912 (16),
+// 5714 x 12 1187 / 1193 (20, the least of ten).  Left out: more than a round of 64-row workgroups, 5705 x 16 1425 / 1486 (112), 7769 x 12 1858 / 1956
+// (116), eight steps of 4096 x 24 1144 / 1169 (128), though 7321 x 12 1652 / 1555 (92).
+inline int hexi_fwd_split_rows(const AttnGeom& g, QShare* share)
 {
     using namespace hexi_shapes;
+    constexpr double SHARE_MARGIN = 1.1;
     Units u[3];
+    *share = {(g.lq + Q_TILE - 1) / Q_TILE, 0};
     if (!hexi_q_units(g, u)) return 0;
     const auto& fit = FWD[g.d == 128];
     const double mb = (double)g.lq * g.nq * g.d * 6.0 * 1e-6;      // q read, o written
     const double t256 = fit[0].us(u[0], mb), t64 = fit[1].us(u[1], mb), t32 = u[2].n <= 768 ? fit[2].us(u[2], mb) : INFINITY;
-    if (t256 <= 1.08 * (t64 < t32 ? t64 : t32)) return 0;
-    return t64 <= t32 ? 64 : 32;
+    const double small = t64 < t32 ? t64 : t32;
+    const bool large = t256 <= 1.08 * small;
+    double shared = INFINITY;
+    const QShare part = hexi_fwd_share(g, u, &shared);
+    if ((large ? t256 : small) > SHARE_MARGIN * shared) { *share = part; return 0; }
+    return large ? 0 : (t64 <= t32 ? 64 : 32);
 }
 
 // How a backward step is launched.

@@ -4,7 +4,8 @@
 // workgroup, whether dk / dv are summed with atomics, and that of the 128-key launch the step would otherwise take; then, for
 // calls for one half alone, the rows per dQ workgroup and the keys per dK / dV workgroup; for fp32 inputs the workgroup
 // shape (0 shared, 1 split, 2 split with two on a CU) of the forward, of dQ, of dK / dV and of dQ alone; and the q heads per
-// dK / dV workgroup of a call for dK / dV alone, and of a whole step that adds to dk and dv.
+// dK / dV workgroup of a call for dK / dV alone, and of a whole step that adds to dk and dv; the
+// forward's 256-row tiles and those left to 64-row workgroups in a launch behind it.
 #include <cstdio>
 #include <cstring>
 #include <iostream>
@@ -54,12 +55,14 @@ int main()
         hexi_plan_bwd(g, forced, false, true, false, &dkdv_alone);
         BwdPlan added;
         hexi_plan_bwd(g, forced, true, true, true, &added);
+        QShare share;
+        const int fwd_rows = hexi_fwd_split_rows(g, &share), n_q_tiles = (g.lq + 255) / 256, fwd_tiles = share.n_units(g.nq);
         F32Shape kv32, q32, q32_alone, unused;
         hexi_f32_bwd_shapes(g, true, true, &kv32, &q32);
         hexi_f32_bwd_shapes(g, true, false, &unused, &q32_alone);
-        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", hexi_fwd_split_rows(g), plan.dq_rows, plan.split_keys ? plan.keys : 128, plan.run_len, (int)shared,
+        std::printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", fwd_rows, plan.dq_rows, plan.split_keys ? plan.keys : 128, plan.run_len, (int)shared,
                     (int)shared_128, dq_alone.dq_rows, dkdv_alone.split_keys ? dkdv_alone.keys : 128,
-                    (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone, dkdv_alone.run_len, added.run_len);
+                    (int)hexi_f32_fwd_shape(g), (int)q32, (int)kv32, (int)q32_alone, dkdv_alone.run_len, added.run_len, fwd_tiles, g.nq * n_q_tiles - fwd_tiles);
     }
     return 0;
 }

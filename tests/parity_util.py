@@ -113,6 +113,11 @@ F32_STEPS = [((33, 16, 2, 1, 16), (1, 1, 1, 1)), ((145, 257, 40, 40, 257), (2, 2
 PART_ROUND_STEPS = [(1025, 200, 64, 8, 128), (700, 200, 100, 20, 128), (1100, 257, 60, 60, 128)]
 
 
+# Forward steps shared between whole rounds of 256-row workgroups and 64-row ones for the rest of the rows, (lq, lc, nq, nkv, head_dim, off): tiles
+# of every head and of some, last tiles of 152, 213, 5 and 162 rows, the first rows without the last keys.
+SHARED_STEPS = [(2712, 392, 24, 3, 128, 392), (5589, 388, 12, 3, 128, 388), (11269, 397, 6, 3, 128, 397), (4258, 420, 16, 8, 128, 399)]
+SHARED_SHARD = dict(nq=24, nkv=3, d=128, q_segs=[(500, 1000), (1600, 1), (1650, 1711)], kv_segs=[(0, 300), (480, 120)])
+
 # Backward steps whose dk / dv are summed in a fixed order, though runs of fewer heads are expected to be a little faster: (lq, lc, nq, nkv,
 # head_dim, off), q heads per dK / dV workgroup: whole groups, and half groups, two of which add into a cleared element.
 ORDER_STEPS = [((9087, 501, 24, 8, 128, 501), 3), ((100, 123, 32, 4, 128, 0), 4), ((364, 126, 16, 4, 64, 126), 2), ((358, 535, 6, 2, 128, 0), 3),

@@ -13,7 +13,7 @@ import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
 from parity_util import (F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
-                         WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
+                         SHARED_SHARD, SHARED_STEPS, WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -887,13 +887,14 @@ def test_64_key_workgroups_beside_256_row_dq(lq, lc, nq, nkv, d, off):
         check(name, got.cpu(), ref[name], "bf16", abs_factor=max(1.0, float(np.max(np.abs(ref[name]))) / 8))
 
 
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS)
-def test_forward_of_a_round_and_a_part(lq, lc, nq, nkv, d):
+def _forward_alone_and_merged(q_segs, kv_segs, lq, lc, nq, nkv, d):
     # every row exactly once, first alone, then merged into a running (o, lse)
+    print(f"\n  forward: {q_segs} x {kv_segs} x {nq}/{nkv} x {d}", flush=True)
     q, _, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
     qd, kd, vd = (t.to(DEV) for t in (q, k, v))
-    desc, q_segs, kv_segs = hexi.desc_for(qd, kd, d ** -0.5), [(lc, lq)], [(0, lc)]
-    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc, lc + lq), to64(k), to64(v), np.arange(lc), d ** -0.5)
+    desc = hexi.desc_for(qd, kd, d ** -0.5)
+    q_pos, kv_pos = (np.concatenate([np.arange(a, a + n) for a, n in segs]) for segs in (q_segs, kv_segs))
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), q_pos, to64(k), to64(v), kv_pos, d ** -0.5)
     o, lse = torch.full(q.shape, float("nan"), device=DEV), torch.full((nq, lq), float("nan"), device=DEV)
     hexi.hexi_attn_fwd_chunk(desc, q_segs, kv_segs, qd, kd, vd, o, lse)
     check("o", o.cpu(), o_ref, "bf16")
@@ -907,10 +908,25 @@ def test_forward_of_a_round_and_a_part(lq, lc, nq, nkv, d):
     check("lse merged", lse.cpu(), lse_ref, "bf16")
 
 
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS)
+def test_forward_of_a_round_and_a_part(lq, lc, nq, nkv, d):
+    _forward_alone_and_merged([(lc, lq)], [(0, lc)], lq, lc, nq, nkv, d)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off", SHARED_STEPS)
+def test_forward_shared_by_large_and_64_row_workgroups(lq, lc, nq, nkv, d, off):
+    _forward_alone_and_merged([(off, lq)], [(0, lc)], lq, lc, nq, nkv, d)
+
+
+def test_forward_shared_by_large_and_64_row_workgroups_in_segments():
+    w = SHARED_SHARD
+    _forward_alone_and_merged(w["q_segs"], w["kv_segs"], sum(n for _, n in w["q_segs"]), sum(n for _, n in w["kv_segs"]), w["nq"], w["nkv"], w["d"])
+
+
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", PART_ROUND_STEPS + [(4096, 4096, 24, 8, 128), (15773, 21188, 9, 3, 64)])
 def test_rows_and_heads_of_a_forward_step_are_summed_alike(lq, lc, nq, nkv, d):
-    # one row and one set of keys, repeated over all rows and heads, all keys visible: results with the same bits everywhere, or a row's
-    # result would depend on its place in the shard and on which heads a device was given
+    # one row and one set of keys, repeated over all rows and heads, all keys visible: results with the same bits everywhere, as all rows of such a
+    # step go to one kernel (whose rest over whole rounds of workgroups is too large for a second one)
     g = torch.Generator().manual_seed(lq + nq)
     q = torch.randn((1, 1, d), generator=g).to(torch.bfloat16).expand(lq, nq, d).contiguous().to(DEV)
     k, v = (torch.randn((lc, 1, d), generator=g).to(torch.bfloat16).expand(lc, nkv, d).contiguous().to(DEV) for _ in range(2))

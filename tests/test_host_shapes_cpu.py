@@ -7,16 +7,21 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def shapes(tmp_path_factory):
+def _compile(tmp_path_factory, name):
     hipcc = "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
-    exe = str(tmp_path_factory.mktemp("shapes") / "shape_check")
+    exe = str(tmp_path_factory.mktemp("shapes") / name)
     subprocess.check_call([hipcc, "-O1", "-std=c++17", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
                            "-I", os.path.join(ROOT, "include"),
                            "-I", os.path.join(ROOT, "paper_2605_07569_amd", "csrc"),
-                           os.path.join(ROOT, "tests", "host", "shape_check.cpp"), "-o", exe])
+                           os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe])
+    return exe
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    exe = _compile(tmp_path_factory, "shape_check")
 
     def ask(steps):
         """steps: (head_dim, nq, nkv, q_segs, kv_segs[, kv_of_q[, forced run length]]) -> dicts"""
@@ -27,7 +32,7 @@ def shapes(tmp_path_factory):
             lines.append(f"{d} {nq} {nkv} {more[1] if len(more) > 1 else 0} {segs(qs)} {segs(ks)} {m}")
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         names = ("fwd_rows", "dq_rows", "keys", "run_len", "atomic", "atomic_128", "dq_alone", "keys_alone",
-                 "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone", "run_len_alone", "run_len_accumulate")
+                 "f32_fwd", "f32_dq", "f32_dkdv", "f32_dq_alone", "run_len_alone", "run_len_accumulate", "fwd_tiles", "rest_tiles")
         return [dict(zip(names, map(int, line.split()))) for line in out if line]
 
     return ask
@@ -126,9 +131,37 @@ def test_the_single_steps_of_64_wide_workgroups_reach_them(shapes):
 
 
 def test_a_round_and_a_part_of_large_forward_workgroups(shapes):
-    # 384, 384, 320 and 288 units of 256 rows; us measured in 256 / 64 rows: 226 / 232, 127.5 / 133.1, 167 / 151, 123 / 108
-    steps = [_step(lq, lc, nq, nkv, 128, lc) for lq, lc, nq, nkv in ((4096, 4096, 24, 8), (4096, 2048, 24, 8), (5000, 3000, 16, 4), (9000, 2000, 8, 2))]
-    assert [got["fwd_rows"] for got in shapes(steps)] == [0, 0, 64, 64]
+    # more than 64 units over whole rounds: one kernel for all rows.  384, 384, 380 units of 256 rows; us measured in 256 / 64 rows: 226 / 232, 127.5 /
+    # 133.1; whole passes of eight such steps, some of 2048 visible keys, in 256 rows / shared 1144 / 1169; of four 1425 / 1486, 1858 / 1956
+    steps = [_step(4096, 4096, 24, 8, 128, 4096), _step(4096, 2048, 24, 8, 128, 2048), _step(5705, 5705, 16, 4, 128, 5705), _step(7769, 7769, 12, 4, 128, 7769)]
+    zigzag = lambda r: [(2048 * r, 2048), (2048 * (15 - r), 2048)]
+    steps += [(128, 24, 8, zigzag(5), zigzag(j)) for j in range(8)]
+    got = shapes(steps)
+    assert [g["fwd_rows"] for g in got] == [0] * len(steps) and not any(g["rest_tiles"] for g in got)
+    # head_dim 64, and rows with so few keys that a second launch takes what it saves
+    from parity_util import PART_ROUND_STEPS
+    got = shapes([_step(9000, 9000, 8, 2, 64, 9000)] + [_step(*s, s[1]) for s in PART_ROUND_STEPS])
+    assert not any(g["rest_tiles"] for g in got)
+
+
+def test_whole_rounds_of_large_forward_workgroups_and_the_rest_in_small_ones(shapes):
+    from parity_util import SHARED_SHARD as w, SHARED_STEPS
+    got = shapes([_step(*s) for s in SHARED_STEPS] + [(w["d"], w["nq"], w["nkv"], w["q_segs"], w["kv_segs"])])
+    assert [(g["fwd_rows"], g["fwd_tiles"], g["rest_tiles"]) for g in got] == [(0, 256, 8), (0, 256, 8), (0, 256, 14), (0, 256, 16), (0, 256, 8)]
+    # us of whole passes measured in one kernel / shared: 2172 / 1891, 4193 / 3635, 2254 / 2001, 1019 / 912, 3250 / 2947
+    steps = [_step(lq, lq, nq, nkv, 128, lq) for lq, nq, nkv in ((5612, 24, 3), (11725, 12, 4), (6128, 24, 8), (4862, 16, 2), (6325, 32, 8))]
+    assert [g["rest_tiles"] for g in shapes(steps)] == [16, 40, 64, 48, 32]
+
+
+def test_a_shared_forward_step_covers_every_row_once(tmp_path_factory):
+    import random
+    exe, rng, lines = _compile(tmp_path_factory, "share_check"), random.Random(5), []
+    for _ in range(3000):
+        nq, n_q_tiles = rng.randint(1, 128), rng.randint(1, 40)
+        if nq * n_q_tiles > nq:
+            lines.append(f"{nq} {n_q_tiles} {rng.choice([nq, nq * n_q_tiles - 1, rng.randint(nq, nq * n_q_tiles - 1)])}")
+    out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split()
+    assert len(out) == len(lines) and set(out) == {"0"}
 
 
 def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
