@@ -11,7 +11,7 @@
 // out in one sequence: the scores of the next block beside the probabilities of this one (forward), the second half of a product
 // beside the P and dS of the first (backward), the transfers of the block after the next one by one behind MFMAs, scalar work and the
 // first fragments of the next block behind the last ones.
-// What bounds it: MFMAs are 1024 of about 1800 clocks of a forward step, 1536 of 2450 (dQ), 2048 of 3450 (dK / dV; head_dim 128); the
+// What bounds it: MFMAs are 1024 of 1860 clocks of a forward step, 1536 of 2420 (dQ), 2048 of 3420 (dK / dV; head_dim 128, counted); the
 // rest is vector work that does not fit beside them (about 600), transfers (about 300) and the waits at a step's ends; short chains
 // add 2.5 to 3.5 us to start and 2 to 4 to finish.  Where the chip is full it is power (1.6 to 1.8 GHz), and the large workgroups, which move
 // less through LDS per MFMA, are the better choice.  Measured, us per call, the smaller of the 64-row split and the 256-row workgroups
