@@ -366,9 +366,9 @@ inline F32Shape hexi_f32_split_shape(double sum, double longest) { return sum > 
 // 15 / 42 / 28, x 300 31 / 60 / 41, x 1000 85 / 123 / 92, x 2048 160 / 203 / 163; 1500 x 1500 x 24 168 / 181 / 143, 3000 x 3000 x 24 537 / 623 / 511,
 // 4096 x 4096 x 24 859 / 1106 / 902; 6703 x 4962 x 16, mean 0.63 of the longest, 747 shared, 818 split.  Units less equal than that
 // fill each other's last rounds: split (diagonal 4096 x 24 heads 512 / 602 / 481, 300 x 24 heads 20 / 13 / 11).
-inline bool hexi_f32_shared_64(int n_rows, int n_heads, double mean, double longest, double margin)
+inline bool hexi_f32_shared_64(int n_rows, int n_heads, double mean, double longest, double margin, double start = 0.0)
 {
-    if (mean <= 0.6 * longest) return false;
+    if (mean + start <= 0.6 * (longest + start)) return false;
     const long long shared = (long long)((n_rows + 63) / 64) * n_heads, split = (long long)((n_rows + 15) / 16) * n_heads;
     const double x = mean * 1e-3, r = (double)((shared + 255) / 256), s = 0.5 * ((double)((split + 511) / 512) + (double)split / 512.0);
     return margin * (3.0 * r + 14.5e-3 * longest + 31.5 * r * x) < s * (4.5 + 17.7 * x);
@@ -390,6 +390,10 @@ inline F32Shape hexi_f32_fwd_shape(const AttnGeom& g)
 // dQ is also split where it fits on the CUs that few long dK/dV units leave idle: 1662 x 141 x 24/3 heads 277 us, dK/dV alone 275; a call
 // for dQ alone has no such units beside it and may be shared where the step's is split.  A dQ unit has three products per
 // block of scores, a dK/dV unit four, and walks the rows of every q head that reads its keys.
+// Keys that no row sees are units too, of a start and an end: where there are such keys these count like 500 rows in the comparison of unit lengths
+// and in the sum (fitted to 3400 calls; 400 and 800 give the same choices but for a few), and dQ units of up to 400 keys join shared dK/dV ones
+// in their launch: 209 rows x 2390 keys x 4/4 heads, the first 209 seen, 26 us, 35 as two launches.  us shared / split / two a CU, dK/dV alone: 117 x 4743 keys x 16/16
+// heads, the first 117 keys seen, 32 / 174 / 114; 53 x 3065 x 64/16, 1608 seen, 64 / 261 / 162.
 inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv, F32Shape* kv, F32Shape* q)
 {
     if (g.d != 64) {
@@ -401,14 +405,16 @@ inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv,
     const double q_longest = (double)seg_rows_le(g.ks, seg_pos_of_row(g.qs, g.lq - 1));
     const double kv_longest = g.lc > 0 ? group * (double)(g.lq - seg_rows_le(g.qs, seg_pos_of_row(g.ks, 0) - 1)) : 0.0;
     const double kv_mean = g.lc > 0 ? group * (double)g.lq * seen / (double)g.lc : 0.0;
-    const bool kv_shared = hexi_f32_shared_64(g.lc, g.nkv, kv_mean, kv_longest, 1.05);
-    const double pairs = (double)g.nq * g.lq / 16.0 * seen;
-    const bool beside_dkdv = want_dkdv && !kv_shared && hexi_f32_split_shape(7.0 * pairs, 4.0 * kv_longest) == F32Shape::SPLIT;
-    const bool q_shared = !beside_dkdv && hexi_f32_shared_64(g.lq, g.nq, seen, q_longest, 1.2);
+    const double start = q_longest < (double)g.lc ? 500.0 : 0.0;
+    const bool kv_shared = hexi_f32_shared_64(g.lc, g.nkv, kv_mean, kv_longest, 1.05, start);
+    const double pairs = (double)g.nq * g.lq / 16.0 * seen, starts = (double)((g.lc + 15) / 16) * g.nkv * start;
+    const bool beside_dkdv = want_dkdv && !kv_shared && hexi_f32_split_shape(7.0 * pairs + 4.0 * starts, 4.0 * (kv_longest + start)) == F32Shape::SPLIT;
+    const bool beside_shared = want_dq && want_dkdv && kv_shared && start > 0.0 && q_longest <= 400.0;
+    const bool q_shared = beside_shared || (!beside_dkdv && hexi_f32_shared_64(g.lq, g.nq, seen, q_longest, 1.2));
     const bool split_dq = want_dq && !q_shared, split_dkdv = want_dkdv && !kv_shared;
     double longest = split_dq ? 3.0 * q_longest : 0.0;
-    if (split_dkdv && 4.0 * kv_longest > longest) longest = 4.0 * kv_longest;
-    const F32Shape split = hexi_f32_split_shape(pairs * ((split_dq ? 3.0 : 0.0) + (split_dkdv ? 4.0 : 0.0)), longest);
+    if (split_dkdv && 4.0 * (kv_longest + start) > longest) longest = 4.0 * (kv_longest + start);
+    const F32Shape split = hexi_f32_split_shape(pairs * ((split_dq ? 3.0 : 0.0) + (split_dkdv ? 4.0 : 0.0)) + (split_dkdv ? 4.0 * starts : 0.0), longest);
     *kv = kv_shared ? F32Shape::SHARED : split;
     *q = q_shared ? F32Shape::SHARED : split;
 }

@@ -105,7 +105,8 @@ QUAD_SHARD = dict(nq=64, nkv=16, q_segs=[(1000, 180), (1230, 1), (1451, 210)], c
 # blocks, the 64-row tiles and the 128-row tiles of the split shapes, chunks shorter than a split tile.
 F32_STEPS = [((33, 16, 2, 1, 16), (1, 1, 1, 1)), ((145, 257, 40, 40, 257), (2, 2, 0, 2)), ((1025, 17, 5, 1, 17), (0, 1, 1, 2)),
              ((273, 300, 24, 8, 300), (2, 2, 2, 2)), ((1000, 129, 48, 8, 129), (0, 1, 1, 0)), ((1000, 129, 24, 24, 129), (0, 0, 1, 0)), ((1039, 1039, 16, 4, 0), (2, 1, 1, 2)),
-             ((497, 497, 12, 3, 0), (1, 1, 1, 1)), ((65, 1030, 24, 24, 1030), (1, 1, 0, 1)), ((128, 127, 128, 128, 127), (0, 0, 0, 0))]
+             ((497, 497, 12, 3, 0), (1, 1, 1, 1)), ((65, 1030, 24, 24, 1030), (1, 1, 0, 1)), ((128, 127, 128, 128, 127), (0, 0, 0, 0)),
+             ((77, 1020, 16, 16, 0), (1, 0, 0, 1)), ((53, 865, 64, 16, 455), (1, 1, 0, 1))]      # (the last two: most keys are seen by no row)
 
 
 # Forward steps of one round of 256-row workgroups (256 units of about the same length) and part of a second one; last tiles of 1, 188 and

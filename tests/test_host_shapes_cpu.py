@@ -172,6 +172,10 @@ def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
     steps = [_step(4096, 4096, 24, 8, 64, 4096), _step(2048, 2048, 16, 4, 64, 2048), _step(1024, 1024, 16, 4, 64, 1024), _step(4096, 4096, 2, 2, 64, 0),
              _step(2048, 2048, 24, 8, 64, 0)]
     assert [g["f32_fwd"] for g in shapes(steps)] == [0, 0, 2, 1, 2]
+    # keys that no row sees are units as well; us of the whole backward shared / split / two a CU 34 / 174 / 114; 26 / 24 / 19 (35 as two launches);
+    # dQ split beside shared dK / dV 93, as one launch 148 / 285 / 182
+    steps = [_step(lq, lc, nq, nkv, 64, off) for lq, lc, nq, nkv, off in ((117, 4743, 16, 16, 0), (209, 2390, 4, 4, 0), (53, 3065, 64, 16, 1555))]
+    assert [(min(g["f32_dq"], 1), g["f32_dkdv"]) for g in shapes(steps)] == [(0, 0), (0, 0), (1, 0)]
     # backward 2781 / 3302 / 2769, 340 / 90 / 108, 203 / 47 / 50 for split / two a CU; head_dim 128 keeps one workgroup a CU
     steps = [_step(4096, 4096, 24, 8, 64, 4096), _step(1024, 2048, 4, 1, 64, 2048), _step(512, 512, 8, 2, 64, 512), _step(1000, 1010, 16, 16, 128, 1010),
              _step(300, 300, 4, 2, 128, 300)]
