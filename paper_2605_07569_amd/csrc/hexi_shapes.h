@@ -167,6 +167,7 @@ struct BwdPlan {
     // Whether runs of len heads leave every element of dk and dv with the same bits whatever order they come in: one run of the whole
     // group, or two that add into a cleared element (0 + a + b = 0 + b + a).
     bool fixed_order(int len) const { return 2 * len >= group; }
+    bool small = false;           // not large enough for the 128-key workgroups as a matter of course
     bool unused = false;          // some kv head is read by no local q head: zero gradient
     int n_kv_tiles = 0;           // 128-key tiles of the chunk
     int n_known = 0;              // entries of seen
@@ -261,6 +262,7 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
     if (forced_run_len >= 1 || n_kv_tiles > 4096) return;
     const Units kv_128 = hexi_kv_units(g, *plan, KV_TILE, run_len, n_runs_for(run_len));
     if (kv_128.n >= 2048) return;
+    plan->small = true;
     const double run_mb = (double)g.lc * g.d * 8.0 * 1e-6;      // dk and dv of a run
     auto added = [&](int len, double clear, double atomic_mb) {
         return (len < max_cnt || unused ? clear : 0.0) + (len < max_cnt ? run_mb * n_runs_for(len) * atomic_mb : 0.0);
@@ -288,27 +290,31 @@ inline void hexi_plan_bwd_step(const AttnGeom& g, int forced_run_len, BwdPlan* p
     }
 }
 
-// The shapes of a call for both halves or for one of them.  One by itself keeps the step's shape (and so the bits that it gives with
-// the other) where that is expected to be 25 % faster there than the large workgroups, and takes those where not: what a joint launch
-// gains for the step by filling last rounds, the half alone does not have.  Of 7350 of the calls no dQ half and 7 dK / dV halves are slower
-// alone than in the large workgroups by more than 3 %, at most 22 %.
-// dK / dV whose sums have a fixed order in the step's shape and not in the large workgroups keep it where these are not expected to be faster:
-// 80 halves between the two bounds measured 2 % faster so in the mean; 80 beyond, up to a tenth slower by the estimate, 6 % slower.
+// The shapes of a call for both halves or for one of them.  One by itself keeps the step's shape (and so the bits that it gives with the other)
+// unless another is expected to be faster: what a joint launch gains for the step by filling last rounds, and what it chooses for the other half's
+// sake, the half alone does not have.  Margins: dQ 15 %, also for the 256-row workgroups where the step has others; dK / dV, whose bits depend on
+// more than the width, 3 %, fixed orders of sums counting as in the step.  Of 9828 random calls for dQ alone 2.6 % are then slower than with the kernels
+// before by more than 10 %, of 13400 for dK / dV alone 0.9 % (6.5 and 8.5 % where a half took the step's shape or the large workgroups and nothing
+// else), and they take 0.81 and 0.92 of the time in the mean (0.84 and 0.97).  us in 256 / 64 / 32 rows, dQ alone: 8245 x 74 keys x 2 heads
+// x 64 21.9 / 11.4 / 11.1, 582 x 9338 x 8 x 128 236 / 65.9 / 39.0; dK / dV alone in 128 / 64 / 32 keys, the best run lengths: 3078 x 283 x 16 / 4 x 64
+// 75.7 / 44.2 / 25.4, 1016 x 390 x 64 / 8 x 64 36.2 / 31.4 / 29.5.
 // accumulate: two runs that add to what dk and dv hold have no fixed order, so whole groups are taken instead, in workgroups of the same width,
 // where these are expected to be at most 15 % slower.
 inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, bool want_dkdv, bool accumulate, BwdPlan* plan)
 {
     using namespace hexi_shapes;
-    constexpr double MARGIN = 1.25;
+    constexpr double MARGIN = 1.15;
     hexi_plan_bwd_step(g, forced_run_len, plan);
     const bool wide = g.d == 128;
-    if (want_dq && !want_dkdv && plan->dq_rows > 0) {
-        Units u[3];
-        const int r = plan->dq_rows == 64 ? 1 : 2;
+    Units u[3];
+    if (!want_dkdv && hexi_q_units(g, u)) {
         const double mb = (double)g.lq * g.nq * g.d * 12.0 * 1e-6;      // q and dO read, dq read and written
-        if (hexi_q_units(g, u) && MARGIN * DQ[wide][r].us(u[r], mb) >= DQ[wide][0].us(u[0], mb)) plan->dq_rows = 0;
+        const double us[3] = {DQ[wide][0].us(u[0], mb), DQ[wide][1].us(u[1], mb), DQ[wide][2].us(u[2], mb)};
+        const double small_us = us[1] < us[2] ? us[1] : us[2];
+        if (us[0] <= MARGIN * small_us) plan->dq_rows = 0;
+        else if (plan->dq_rows == 0 || us[plan->dq_rows == 64 ? 1 : 2] > MARGIN * small_us) plan->dq_rows = us[1] <= us[2] ? 64 : 32;
     }
-    if (!want_dkdv || !plan->split_keys) return;
+    if (!want_dkdv || forced_run_len >= 1 || plan->n_kv_tiles > 4096) return;
     auto estimate = [&](int keys, int len) {
         const DkdvFit& f = DKDV[wide][keys == KV_TILE ? 0 : (keys == 64 ? 1 : 2)];
         HeadRuns runs;
@@ -318,17 +324,25 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, b
                (shared ? run_mb * runs.n * f.atomic_mb : 0.0);
     };
     double whole_cost = plan->whole_cost;
-    if (!want_dq) {
-        const bool loses_order = plan->fixed_order(plan->run_len) && !plan->fixed_order(plan->run_len_128);
-        const double us = estimate(plan->keys, plan->run_len);
-        if ((loses_order ? 1.0 : MARGIN) * us >= estimate(KV_TILE, plan->run_len_128)) {
-            plan->split_keys = false;
-            plan->run_len = plan->run_len_128;
-            return;
+    if (!want_dq && plan->small) {
+        auto priced = [&](int keys, int len) { return (plan->fixed_order(len) ? 1.0 : ORDER_MARGIN) * estimate(keys, len); };
+        const double step_us = priced(plan->split_keys ? plan->keys : KV_TILE, plan->run_len);
+        double best = priced(KV_TILE, plan->run_len_128);
+        int best_keys = KV_TILE, best_len = plan->run_len_128;
+        for (int keys = 64; keys >= 32; keys /= 2)
+            for (int len = plan->group; len >= 1; --len) {
+                if (plan->group % len != 0 || (plan->run_len_128 >= plan->group && len < plan->group)) continue;
+                const double t = priced(keys, len);
+                if (t < best) { best = t; best_keys = keys; best_len = len; }
+            }
+        if (step_us > SMALL_MARGIN * best) {
+            plan->split_keys = best_keys != KV_TILE;
+            plan->keys = plan->split_keys ? best_keys : 32;
+            plan->run_len = best_len;
         }
-        whole_cost = estimate(plan->keys, plan->group) / us;
+        if (plan->split_keys) whole_cost = estimate(plan->keys, plan->group) / estimate(plan->keys, plan->run_len);
     }
-    if (accumulate && plan->fixed_order(plan->run_len) && whole_cost <= ORDER_MARGIN) plan->run_len = plan->group;
+    if (accumulate && plan->split_keys && plan->fixed_order(plan->run_len) && whole_cost <= ORDER_MARGIN) plan->run_len = plan->group;
 }
 
 // The fp32 kernels (hexi_f32.hip): 64-row workgroups that share their tiles, or 16-row ones whose wavefronts split the streamed

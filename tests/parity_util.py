@@ -87,9 +87,10 @@ QUAD_STEPS = [(33, 65, 64, 64, 128, "b"), (33, 65, 64, 64, 64, "b"), (17, 129, 6
               (130, 700, 64, 16, 128, "fb"), (130, 1000, 64, 16, 128, "fb"), (129, 33, 128, 8, 128, "f"), (129, 33, 128, 4, 128, "fb"),
               (200, 65, 64, 64, 128, "fb"), (200, 33, 128, 8, 64, "f"), (200, 33, 128, 4, 64, "fb"), (260, 700, 64, 16, 64, "b"), (257, 65, 64, 64, 64, "fb"), (520, 600, 64, 16, 64, "fb")]
 
-# Single steps of the 64-row forward kernel and of dQ in 64-row workgroups in a call of its own, all keys visible or half of them (off = lc / 2).
+# Single steps of the 64-row forward kernel, all keys visible or half of them at the start (off = lc / 2), and of dQ in 64-row workgroups in a call
+# of its own (off = lc / 2).
 QUAD_FWD_STEPS = [(130, 1000, 64, 16, 128), (520, 600, 64, 16, 64)]
-QUAD_DQ_STEPS = [(130, 700, 64, 16, 128), (260, 700, 64, 16, 64)]
+QUAD_DQ_STEPS = [(130, 700, 64, 16, 128), (315, 132, 32, 32, 64)]
 
 # A step whose dK / dV are cut into workgroups of 64 keys beside dQ in 256-row ones: (lq, lc, nq, nkv, head_dim, off), with one head to a group and,
 # with atomics, three.
@@ -120,6 +121,7 @@ SHARED_STEPS = [(2712, 392, 24, 3, 128, 392), (5589, 388, 12, 3, 128, 388), (112
 SHARED_SHARD = dict(nq=24, nkv=3, d=128, q_segs=[(500, 1000), (1600, 1), (1650, 1711)], kv_segs=[(0, 300), (480, 120)])
 
 # Backward steps whose dk / dv are summed in a fixed order, though runs of fewer heads are expected to be a little faster: (lq, lc, nq, nkv,
-# head_dim, off), q heads per dK / dV workgroup: whole groups, and half groups, two of which add into a cleared element.
-ORDER_STEPS = [((9087, 501, 24, 8, 128, 501), 3), ((100, 123, 32, 4, 128, 0), 4), ((364, 126, 16, 4, 64, 126), 2), ((358, 535, 6, 2, 128, 0), 3),
-               ((6280, 1109, 16, 4, 64, 1109), 2), ((3476, 3476, 12, 3, 128, 0), 2)]
+# head_dim, off), q heads per dK / dV workgroup in the step, and in a call for dK / dV alone: whole groups, and half groups, two of which add into
+# a cleared element; the last two have more than two runs where dK / dV alone is expected to gain 15 %.
+ORDER_STEPS = [((100, 123, 32, 4, 128, 0), 4, 4), ((364, 126, 16, 4, 64, 126), 2, 2), ((358, 535, 6, 2, 128, 0), 3, 3), ((3476, 3476, 12, 3, 128, 0), 2, 2),
+               ((9087, 501, 24, 8, 128, 501), 3, 1), ((6280, 1109, 16, 4, 64, 1109), 2, 1)]
