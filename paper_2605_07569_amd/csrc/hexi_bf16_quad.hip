@@ -1003,7 +1003,8 @@ hipError_t hexi_launch_fwd_quad_bf16(const FwdArgs& a, QuadRest rest, hipStream_
 hipError_t hexi_launch_bwd_quad_bf16(const BwdArgs& a, bool dq, const HeadRuns& runs, bool shared, hipStream_t s)
 {
     const int n_q_tiles = dq ? (a.g.lq + ROWS - 1) / ROWS : 0;
-    const unsigned n_dkdv = (unsigned)((a.g.lc + ROWS - 1) / ROWS) * (unsigned)runs.n;
+    const int n_keys = shared ? hexi_keys_seen(a.g) : a.g.lc;
+    const unsigned n_dkdv = (unsigned)((n_keys + ROWS - 1) / ROWS) * (unsigned)runs.n;
     const unsigned grid = n_dkdv + (unsigned)n_q_tiles * (unsigned)a.g.nq;
     if (grid == 0) return hipSuccess;
     if (a.g.d == 128) {

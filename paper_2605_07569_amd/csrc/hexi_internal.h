@@ -46,6 +46,9 @@ struct AttnGeom {
     signed char kv_of_q[HEXI_MAX_HEADS];
 };
 
+// Keys that some row sees: the first so many of the chunk.
+inline int hexi_keys_seen(const AttnGeom& g) { return seg_rows_le(g.ks, seg_pos_of_row(g.qs, g.lq - 1)); }
+
 struct FwdArgs {
     AttnGeom g;
     const void *q, *k, *v;

@@ -125,3 +125,9 @@ SHARED_SHARD = dict(nq=24, nkv=3, d=128, q_segs=[(500, 1000), (1600, 1), (1650, 
 # a cleared element; the last two have more than two runs where dK / dV alone is expected to gain 15 %.
 ORDER_STEPS = [((100, 123, 32, 4, 128, 0), 4, 4), ((364, 126, 16, 4, 64, 126), 2, 2), ((358, 535, 6, 2, 128, 0), 3, 3), ((3476, 3476, 12, 3, 128, 0), 2, 2),
                ((9087, 501, 24, 8, 128, 501), 3, 1), ((6280, 1109, 16, 4, 64, 1109), 2, 1)]
+
+# Backward steps of 32-key and 64-key workgroups that add with atomics, in chunks whose last keys no row sees: (head_dim, nq, nkv, q_segs, kv_segs),
+# keys per workgroup, keys seen (one less, as many and one more than whole workgroups).
+UNSEEN_STEPS = [((128, 8, 1, [(0, 127)], [(0, 197)]), 32, 127), ((128, 8, 1, [(0, 128)], [(0, 428)]), 32, 128), ((64, 32, 4, [(0, 129)], [(0, 199)]), 32, 129),
+                ((64, 8, 1, [(100, 60), (400, 90)], [(0, 150), (480, 200)]), 32, 160), ((128, 64, 8, [(0, 895)], [(0, 965)]), 64, 895),
+                ((64, 64, 8, [(0, 1024)], [(0, 1094)]), 64, 1024), ((128, 64, 8, [(0, 1025)], [(0, 1095)]), 64, 1025)]

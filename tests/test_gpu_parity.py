@@ -13,7 +13,7 @@ import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
 from parity_util import (F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
-                         SHARED_SHARD, SHARED_STEPS, WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
+                         SHARED_SHARD, SHARED_STEPS, UNSEEN_STEPS, WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -874,6 +874,31 @@ def test_64_wide_workgroups_accumulate():
         # (the same sums, in another order where they are atomic)
         bound = 1e-5 * float(outs[0][0].abs().max() + outs[0][1].abs().max() + 1.0)
         assert float((outs[1][0] - outs[0][0] - 0.5).abs().max()) <= bound and float((outs[1][1] - outs[0][1] + 0.25).abs().max()) <= bound
+
+
+@pytest.mark.parametrize("step,keys,seen", UNSEEN_STEPS)
+def test_atomic_sums_of_a_chunk_with_keys_that_no_row_sees(step, keys, seen):
+    # zeros where nothing is seen, over NaN and over what is to be added to
+    d, nq, nkv, q_segs, kv_segs = step
+    print(f"\n  {keys} keys, {step}, {seen} seen", flush=True)
+    lq, lc = sum(n for _, n in q_segs), sum(n for _, n in kv_segs)
+    q_pos, k_pos = (np.concatenate([np.arange(a, a + n) for a, n in segs]) for segs in (q_segs, kv_segs))
+    assert int(np.sum(k_pos <= q_pos[-1])) == seen
+    q, d_o, k, v = _large_step_inputs(lq, lc, nq, nkv, d, lq + lc)
+    qd, gd, kd, vd = (t.to(DEV) for t in (q, d_o, k, v))
+    desc, args = hexi.desc_for(qd, kd, d ** -0.5), (q_segs, kv_segs, qd, kd, vd)
+    o, lse, delta, dq = (torch.zeros(s, device=DEV) for s in (q.shape, (nq, lq), (nq, lq), q.shape))
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse)
+    ref = oracle.attn_bwd(to64(q), q_pos, to64(k), to64(v), k_pos, to64(d_o), d ** -0.5)
+    for flags, fill in ((0, float("nan")), (hexi.HEXI_ACCUMULATE, 0.5)):
+        dq.zero_()
+        dk, dv = torch.full(k.shape, fill, device=DEV), torch.full(v.shape, fill, device=DEV)
+        hexi.hexi_attn_bwd_chunk(desc, *args, o, gd, lse, delta, dq, dk, dv, flags=flags | hexi.HEXI_COMPUTE_DELTA)
+        held = fill if flags else 0.0
+        check("dq", dq.cpu(), ref["dq"], "bf16")
+        for name, got in (("dk", dk), ("dv", dv)):      # (the bound on a single element as in test_large_workgroups_boundary_sizes)
+            assert bool((got[seen:] == held).all())
+            check(name, got.cpu() - held, ref[name], "bf16", abs_factor=max(1.0, float(np.max(np.abs(ref[name]))) / 8))
 
 
 @pytest.mark.parametrize("lq,lc,nq,nkv,d,off", WIDE_DQ_STEPS)

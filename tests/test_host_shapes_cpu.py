@@ -107,6 +107,11 @@ def test_sums_keep_a_fixed_order_for_a_small_gain(shapes):
     assert [g["run_len_accumulate"] for g in got] == [8, 4, 3, 2, 3, 2]
 
 
+def test_the_unseen_keys_tests_reach_atomics(shapes):
+    from parity_util import UNSEEN_STEPS
+    assert [(g["keys"], g["atomic"]) for g in shapes([s for s, *_ in UNSEEN_STEPS])] == [(keys, 1) for _, keys, _ in UNSEEN_STEPS]
+
+
 def test_the_large_workgroups_tests_reach_them(shapes):
     from parity_util import LARGE_SHARD as s, LARGE_STEPS
     steps = [_step(lq, lc, nq, nkv, d, off) for lq, lc, nq, nkv, d in LARGE_STEPS for off in (lc, lc // 2)]
