@@ -10,14 +10,14 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhexi_attn.so")
 PROBE_LIB = os.path.join(HERE, "libhexi_probe.so")      # the benchmark's measurement aid (include/hexi_probe.h)
 EXPORT_MAP = os.path.join(CSRC, "hexi_exports.map")     # only hexi_* symbols leave the libraries
-SOURCES = ["hexi_api.hip", "hexi_sched.cpp", "hexi_misc.hip", "hexi_a2a.hip", "hexi_f32.hip", "hexi_bf16_fwd.hip", "hexi_bf16_bwd.hip", "hexi_bf16_bwd_dq.hip", "hexi_bf16_split.hip", "hexi_bf16_quad.hip"]
+SOURCES = ["hexi_api.hip", "hexi_sched.cpp", "hexi_misc.hip", "hexi_a2a.hip", "hexi_f32.hip", "hexi_f32_bf16x3.hip", "hexi_bf16_fwd.hip", "hexi_bf16_bwd.hip", "hexi_bf16_bwd_dq.hip", "hexi_bf16_split.hip", "hexi_bf16_quad.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-munsafe-fp-atomics", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Wno-inline-asm",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 # One wavefront per SIMD with 512 registers: results of MFMAs in ordinary registers (what is kept in the accumulation ones is said in
 # the source), or every score would be copied before the vector unit can read it.
-FILE_FLAGS = {"hexi_bf16_quad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"hexi_f32_bf16x3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "hexi_bf16_quad.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _hipcc():

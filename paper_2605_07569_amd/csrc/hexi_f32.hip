@@ -38,11 +38,9 @@
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 #include "hexi_shapes.h"
+#include "hexi_f32_common.h"
 
 namespace {
-
-constexpr float LOG2E_HI = 1.44269502162933349609f;      // log2(e) rounded to fp32, and the rest
-constexpr float LOG2E_LO = 1.92596299112661746887e-8f;
 
 __device__ __forceinline__ f32x4 mfma16_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -57,14 +55,6 @@ __device__ __forceinline__ float sum_over_groups(float x)
     const unsigned xi = __float_as_uint(x);
     const auto r = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
     return sum_across_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
-
-// -LSE * log2(e) as two floats.  A row whose LSE is infinite (one that sees nothing anywhere, or that is switched off) has P = 0.
-__device__ __forceinline__ void neg_lse_log2(float l, float& hi, float& lo)
-{
-    const bool live = fabsf(l) != INFINITY;
-    hi = live ? -l * LOG2E_HI : -INFINITY;
-    lo = live ? fmaf(-l, LOG2E_HI, -hi) - l * LOG2E_LO : 0.f;
 }
 
 // P of a score: 2^(s (c_hi + c_lo) + nl_hi + nl_lo).  The low product takes a finite score: one that overflowed to -inf has
@@ -166,13 +156,17 @@ __device__ __forceinline__ f32x4 lds_f4(const unsigned char* p) { return *reinte
 // out[m = streamed row][n = stationary row] = sum over the head dimension: A from LDS (row reads), B in registers.
 // The reads of a step are issued before the MFMAs of the step before it (4 NT MFMAs = 128 NT cycles ahead); left to
 // itself the compiler issues them a few dozen cycles before their use.  The summation order over the head dimension is
-// the same in all three kernels: the rounding errors of a score and of the LSE it went into then cancel in P (with two
-// interleaved chains in the forward kernel only, the errors of dq, dk, dv on sharply peaked rows were 1.5 times as large).
+// the same in all three kernels: the rounding errors of a score and of the LSE it went into then cancel in P.  At head_dim 128, where the LSE may
+// come from the split-operand forward instead (hexi_f32_bf16x3.hip), four chains, one per MFMA of a group, halve the error of one and more
+// than make up for what no longer cancels: errors of dq, dk, dv, K scaled by 3, 777 x 1000 x 8/2 heads, one chain in all kernels 1, that forward
+// with one chain here 1.5, 1.5, 1.7, with four 0.79, 0.78, 0.81 (times: backward 123 / 125 us).
 template <class C, int NT> __device__ __forceinline__ void score_block(f32x4 (&out)[NT], const unsigned char* const (&tile)[NT], const LaneAddr<C>& la, const f32x4* const (&frag)[NT])
 {
-    f32x4 x[2][NT];
+    constexpr int CH = C::D == 128 ? 4 : 1;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 x[2][NT], sum[CH][NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) { x[0][t] = lds_f4(tile[t] + la.row[0]); out[t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int t = 0; t < NT; ++t) x[0][t] = lds_f4(tile[t] + la.row[0]);
 #pragma unroll
     for (int G = 0; G < C::NG; ++G) {
         if (G + 1 < C::NG) {
@@ -183,8 +177,13 @@ template <class C, int NT> __device__ __forceinline__ void score_block(f32x4 (&o
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) out[t] = mfma16_f32(x[G & 1][t][j], frag[t][G][j], out[t]);
+            for (int t = 0; t < NT; ++t) sum[j % CH][t] = mfma16_f32(x[G & 1][t][j], frag[t][G][j], G == 0 && j < CH ? zero : sum[j % CH][t]);
         __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if constexpr (CH == 4) out[t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
+        else out[t] = sum[0][t];
     }
 }
 
@@ -665,6 +664,7 @@ template <class F> hipError_t with_cfg(int d, F32Shape shape, F f)
 
 hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s)
 {
+    if (const F32x3Fwd plan = hexi_f32x3_fwd(a.g); plan.use) return hexi_launch_fwd_f32x3(a, plan, s);
     return with_cfg(a.g.d, hexi_f32_fwd_shape(a.g), [&](auto d, auto split, auto two) {
         constexpr int D = decltype(d)::value; constexpr bool SPLIT = decltype(split)::value, TWO = decltype(two)::value;
         using C = F32Cfg<D, SPLIT, TWO>;
@@ -675,6 +675,7 @@ hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s)
 
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s)
 {
+    if (const F32x3Bwd plan = hexi_f32x3_bwd(a.g); plan.use) return hexi_launch_bwd_f32x3(a, plan, s);
     F32Shape kv_shape, q_shape;
     hexi_f32_bwd_shapes(a.g, a.want_dq, a.want_dkdv, &kv_shape, &q_shape);
     auto launch = [&](F32Shape shape, bool dkdv, bool dq) {

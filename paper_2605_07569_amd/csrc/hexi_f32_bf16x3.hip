@@ -1,0 +1,754 @@
+// fp32 attention with its products on the bf16 matrix instructions: every fp32 operand is cut into three bf16 values whose sum it is exactly (24 bits
+// in 8 + 8 + 8), and of the nine products of two cut operands the six that reach above 2^-24 of their product are added up in fp32.  A bf16
+// product is exact in fp32, v_mfma_f32_32x32x16_bf16 keeps denormals and its sums are rounded without bias (0.41 ulp rms over random
+// operands, v_mfma_f32_16x16x4_f32 0.54), so the results are no further from fp64 than those of the fp32 instruction (hexi_f32.hip), which rounds
+// more often: relative errors of o, dq, dk, dv at 4096 rows x 4096 keys x 16/4 heads x 128 1.2e-6, 1.4e-6, 2.4e-6, 2.4e-6 with it alone, 5e-7,
+// 7e-7, 5e-7, 5e-7 here; over 37 shapes of 256 to 6000 rows and keys, K scaled by 1 and by 3, no output is further off than before.
+// Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: the forward and dQ, 64 rows at a time, execute 1.1 PFLOP/s in
+// bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
+// the same box); dK / dV, with four splits of streamed operands for two, 0.9.  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here:
+// forward 1130 / 765, dQ 1551 / 1100, dK / dV 2360 / 1950; 4096 diagonal x 8 heads x 64, forward and backward: 180 / 119, 530 / 455.
+//
+// Shape.  Cutting costs 5.5 vector operations per element, and a vector operation beside a saturated matrix pipe takes 6 cycles (10 for the packing
+// ones) next to 32x32x16 and 8.5 (13) next to 16x16x32; v_dot2_f32_bf16, which would subtract a packed value in one operation, waits for the
+// matrix pipe (37 cycles).  So the 32x32x16 form throughout, operands cut once where they can be: a workgroup's 32 or 64 stationary rows (q rows, or
+// keys for dK / dV) are cut at its start and their operands kept in LDS; 4 wavefronts, one per SIMD with its 512 registers, split the
+// streamed rows in blocks of 32, each through a slot of its own without any barrier, and combine their results through LDS at the end.  Per
+// block the rows arrive twice: by transfers into the slot for the scores, and as columns straight into registers for the accumulation
+// (a column of 32 rows is what neighbouring lanes read together; rows of 64 lanes read directly cost a cycle per lane, 64 instead of 16).  The
+// cutting of a step stands between the matrix instructions of the step before.  8 wavefronts, two per SIMD, with 16x16x32 products: 926 us forward;
+// 64 rows against 32: 757 / 930.
+//
+// Values: no finite value becomes infinite in the cut; a value below 2^-110 loses its last bits (2^-133 is the smallest bf16).  An infinite one has
+// no rest (inf - inf): scores then count their upper product alone, infinite values of V, dO or dS give NaN where they give infinities in hexi_f32.hip.
+#include "hexi_internal.h"
+#include "hexi_mfma.h"
+#include "hexi_shapes.h"
+#include "hexi_f32_common.h"
+
+namespace {
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// scale * log2(e) as two floats, the lower one positive: s * lo then has the sign of s, and a score of -inf gives 2^-inf without further care.
+struct Log2Scale {
+    float hi, lo;
+    __device__ __forceinline__ explicit Log2Scale(float scale)
+    {
+        hi = scale * LOG2E_HI;
+        lo = fmaf(scale, LOG2E_HI, -hi) + scale * LOG2E_LO;
+        if (lo <= 0.f) {
+            hi = __uint_as_float(__float_as_uint(hi) - 1u);
+            lo = fmaf(scale, LOG2E_HI, -hi) + scale * LOG2E_LO;
+        }
+        lo = fmaxf(lo, 1.17549435e-38f);
+    }
+};
+
+template <int D_, int NB_> struct X3Cfg {
+    static constexpr int D = D_;
+    static_assert(D == 64 || D == 128, "head_dim 64 or 128");
+    static constexpr int NW = 4;                       // wavefronts, one per SIMD, which split the streamed rows
+    static constexpr int NB = NB_, ROWS = 32 * NB;     // stationary rows of a workgroup: 32 or 64
+    static constexpr int BLK = 32;                     // streamed rows of a block
+    static constexpr int NK = D / 16;                  // contraction steps of a score
+    static constexpr int NJ = D / 32;                  // columns of a lane in an accumulation, and accumulators of 32 columns
+    static constexpr int ROW_BYTES = 4 * D, BLOCK_BYTES = BLK * ROW_BYTES;
+    static constexpr int XFERS = BLOCK_BYTES / 1024;   // transfers of a block into LDS
+    static constexpr int PIECES = NK * NB * 3 * 1024;  // bytes of a stationary tensor's operands in LDS
+    static constexpr int PITCH = D + 4;                // floats per staged output row
+    static constexpr int STAGE_FLOATS = NW * ROWS * PITCH;
+};
+
+// The three bf16 operands of eight values: x = h + m + l exactly.  h holds the upper 16 bits of x (cut, so that no finite x becomes infinite), m
+// the rounded rest, l what is left of it.
+struct Split3 { bf16x8 h, m, l; };
+__device__ __forceinline__ unsigned pack_rounded(float a, float b)
+{
+    const bf16x2 t = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(unsigned, t);
+}
+__device__ __forceinline__ Split3 split8(float x0, float x1, float x2, float x3, float x4, float x5, float x6, float x7)
+{
+    const float x[8] = {x0, x1, x2, x3, x4, x5, x6, x7};
+    u32x4 h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+        h[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+        a -= __uint_as_float(__float_as_uint(a) & 0xffff0000u);
+        b -= __uint_as_float(__float_as_uint(b) & 0xffff0000u);
+        m[i] = pack_rounded(a, b);
+        a -= __uint_as_float(m[i] << 16);
+        b -= __uint_as_float(m[i] & 0xffff0000u);
+        l[i] = pack_rounded(a, b);
+    }
+    return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+__device__ __forceinline__ Split3 split8(const f32x4& a, const f32x4& b) { return split8(a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]); }
+
+// Operands of a stationary tensor in LDS: step ks, row block n, piece p at ((NB ks + n) 3 + p) KB, a lane's 16 bytes at 16 lane.
+template <class C> __device__ __forceinline__ void put_stationary(unsigned char* lds, const float* src, long long stride_tok, int row0, int total, int wave, int lane)
+{
+#pragma unroll
+    for (int i = 0; i < C::NK * C::NB / C::NW; ++i) {
+        const int c = wave + C::NW * i, ks = c / C::NB, row = row0 + 32 * (c % C::NB) + (lane & 31);
+        const float* p = src + (long long)(row < total ? row : total - 1) * stride_tok + 16 * ks + 8 * (lane >> 5);
+        const Split3 s = split8(*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 4));
+        unsigned char* d = lds + c * 3072 + 16 * lane;
+        *reinterpret_cast<bf16x8*>(d) = s.h;
+        *reinterpret_cast<bf16x8*>(d + 1024) = s.m;
+        *reinterpret_cast<bf16x8*>(d + 2048) = s.l;
+    }
+}
+
+// A block of 32 streamed rows on its way to the scores: transfers into the wavefront's own piece of LDS, the 16-byte pieces of a row permuted by
+// piece ^ (row & 15), so that the reads of 16 rows' pieces meet all banks once.
+template <class C> struct RowBlock {
+    uint32_t slot, src[C::XFERS], rd[4];
+    __device__ __forceinline__ static int row_of(int i, int lane) { return (1024 * i + 16 * lane) / C::ROW_BYTES; }
+    __device__ __forceinline__ RowBlock(const unsigned char* lds, int lane, long long stride_tok)
+    {
+        slot = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+#pragma unroll
+        for (int i = 0; i < C::XFERS; ++i) {
+            const int r = row_of(i, lane), p = (1024 * i + 16 * lane) % C::ROW_BYTES / 16;
+            src[i] = 4u * (uint32_t)(r * (int)stride_tok) + 16u * (uint32_t)(p ^ (r & 15));
+        }
+        // piece 4 ks + 2 hh + i of row l: steps ks and ks + 4 are 256 bytes apart
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) rd[ks] = (uint32_t)((lane & 31) * C::ROW_BYTES + 16 * ((4 * ks + 2 * (lane >> 5)) ^ (lane & 15)));
+    }
+    // rows past `total` re-read the last one
+    __device__ __forceinline__ void request(const float* base, long long stride_tok, int row0, int total, int lane) const
+    {
+        const float* b = base + (long long)row0 * stride_tok;
+        if (row0 + C::BLK <= total) {
+#pragma unroll
+            for (int i = 0; i < C::XFERS; ++i) lds_dma16_base(b, src[i], slot + 1024 * i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < C::XFERS; ++i) {
+                uint32_t o = src[i];
+                const int r = row_of(i, lane);
+                if (row0 + r >= total) o -= 4u * (uint32_t)((row0 + r - (total - 1)) * (int)stride_tok);
+                lds_dma16_base(b, o, slot + 1024 * i);
+            }
+        }
+    }
+    // columns 16 ks + 8 hh .. + 7 of row l
+    __device__ __forceinline__ void read(f32x4 (&x)[2], const unsigned char* lds, int ks) const
+    {
+        x[0] = *reinterpret_cast<const f32x4*>(lds + rd[ks & 3] + 256 * (ks >> 2));
+        x[1] = *reinterpret_cast<const f32x4*>(lds + (rd[ks & 3] ^ 16u) + 256 * (ks >> 2));
+    }
+};
+template <int YOUNGER> __device__ __forceinline__ void landed()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(YOUNGER) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// 32 streamed rows as the other operand of an accumulation over them: lane (hh, c) holds columns NJ c .. of rows 16 u + 8 (e / 4) + 4 hh + e % 4.
+template <class C> struct ColBlock {
+    typedef float vec __attribute__((ext_vector_type(C::NJ)));
+    vec x[2][8];
+    __device__ __forceinline__ void load(const float* src, long long stride_tok, int row0, int total, int hh, int c)
+    {
+        const char* base = reinterpret_cast<const char*>(src + (long long)row0 * stride_tok);
+        const uint32_t step = 4u * (uint32_t)stride_tok;
+        const uint32_t lane_off = 4u * (uint32_t)(C::NJ * c);
+        if (row0 + C::BLK <= total) {
+            const uint32_t off = 4u * step * (uint32_t)hh + lane_off;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[u][e] = *reinterpret_cast<const vec*>(base + (size_t)((16 * u + 8 * (e / 4) + e % 4) * step) + off);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int r = 16 * u + 8 * (e / 4) + 4 * hh + e % 4, rc = row0 + r < total ? r : total - 1 - row0;
+                    x[u][e] = *reinterpret_cast<const vec*>(base + ((uint32_t)rc * step + lane_off));
+                }
+        }
+    }
+    __device__ __forceinline__ Split3 split(int u, int j) const { return split8(x[u][0][j], x[u][1][j], x[u][2][j], x[u][3][j], x[u][4][j], x[u][5][j], x[u][6][j], x[u][7][j]); }
+};
+
+__device__ __forceinline__ float probability(float s, const Log2Scale& c, float nl_hi, float nl_lo) { return fast_exp2(fmaf(s, c.hi, nl_hi) + fmaf(s, c.lo, nl_lo)); }
+
+// one MFMA, then vector work of the next step in its shadow
+template <int N, int V, int DS> __device__ __forceinline__ void interleave()
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        HEXI_SCHED_MFMA(1);
+        HEXI_SCHED_VALU(V);
+        if (DS) HEXI_SCHED_DSREAD(DS);
+    }
+}
+
+// s[n], register 4 b + t: streamed row 8 b + 4 hh + t times stationary row 32 n + l.
+template <class C> __device__ __forceinline__ void scores(f32x16 (&s)[C::NB], const RowBlock<C>& rows, const unsigned char* slot, const unsigned char* stat)
+{
+    constexpr int NB = C::NB;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 lo[NB];
+    f32x4 raw[2];
+    bf16x8 b[2][NB][3];
+    auto read_stat = [&](int ks) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[ks & 1][n][p] = *reinterpret_cast<const bf16x8*>(stat + (NB * ks + n) * 3072 + 1024 * p);
+    };
+    rows.read(raw, slot, 0);
+    read_stat(0);
+    Split3 t = split8(raw[0], raw[1]);
+    rows.read(raw, slot, 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < C::NK; ++ks) {
+        Split3 next = t;
+        if (ks + 1 < C::NK) {
+            read_stat(ks + 1);
+            next = split8(raw[0], raw[1]);
+            if (ks + 2 < C::NK) rows.read(raw, slot, ks + 2);
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const bf16x8 (&q)[3] = b[ks & 1][n];
+            s[n] = mfma32(t.h, q[0], ks == 0 ? zero : s[n]);
+            lo[n] = mfma32(t.h, q[1], ks == 0 ? zero : lo[n]);
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) lo[n] = mfma32(t.h, b[ks & 1][n][2], lo[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) lo[n] = mfma32(t.m, b[ks & 1][n][0], lo[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) lo[n] = mfma32(t.m, b[ks & 1][n][1], lo[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) lo[n] = mfma32(t.l, b[ks & 1][n][0], lo[n]);
+        interleave<6 * NB, 8 / NB, 1>();
+        __builtin_amdgcn_sched_barrier(0);
+        t = next;
+    }
+    // an infinite operand has no rest, nor has a product that overflows: NaN and infinity become finite there, and the sum of the upper pieces decides
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[n][r] += __builtin_amdgcn_fmed3f(lo[n][r], -3.4e38f, 3.4e38f);
+}
+
+// acc[n][j], register 4 b + t: column NJ (8 b + 4 hh + t) + j of stationary row 32 n + l; p[n]: probabilities or dS as scores() leaves its results.
+// APART: the block's sum by itself, then added, for the long chains of dK / dV: one rounding of the running value in 32 rows instead of 12 (the backward
+// 4 % slower; dv of 3643 rows of 4 heads 1.1 times as far from fp64 as with hexi_f32.hip without it, 0.43 times with it).
+template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB])
+{
+    constexpr int NB = C::NB;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    Split3 po[2][NB];
+    auto split_p = [&](int u) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+            po[u][n] = split8(p[n][8 * u], p[n][8 * u + 1], p[n][8 * u + 2], p[n][8 * u + 3], p[n][8 * u + 4], p[n][8 * u + 5], p[n][8 * u + 6], p[n][8 * u + 7]);
+    };
+    split_p(0);
+    if (APART) split_p(1);
+    Split3 t = v.split(0, 0);
+    f32x16 sum[NB];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < 2 * C::NJ; ++st) {
+        const int u = APART ? st % 2 : st / C::NJ, j = APART ? st / 2 : st % C::NJ, st1 = st + 1;
+        Split3 next = t;
+        if (st1 < 2 * C::NJ) next = v.split(APART ? st1 % 2 : st1 / C::NJ, APART ? st1 / 2 : st1 % C::NJ);
+        f32x16* to[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) to[n] = APART ? &sum[n] : &acc[n][j];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.l, po[u][n].h, APART && u == 0 ? zero : *to[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.h, po[u][n].l, *to[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.m, po[u][n].m, *to[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.m, po[u][n].h, *to[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.h, po[u][n].m, *to[n]);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) *to[n] = mfma32(t.h, po[u][n].h, *to[n]);
+        interleave<6 * NB, 8 / NB, 0>();
+        __builtin_amdgcn_sched_barrier(0);
+        t = next;
+        if (APART && u == 1) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc[n][j] += sum[n];
+        }
+        if (!APART && j == C::NJ - 1 && u == 0) { split_p(1); __builtin_amdgcn_sched_barrier(0); }
+    }
+}
+
+template <class C> __device__ __forceinline__ void zero_acc(f32x16 (&acc)[C::NB][C::NJ])
+{
+#pragma unroll
+    for (int n = 0; n < C::NB; ++n)
+#pragma unroll
+        for (int i = 0; i < C::NJ; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[n][i][r] = 0.f;
+}
+
+// The wavefront's ROWS x D block, times w, as rows of a staging area.
+template <class C> __device__ __forceinline__ void stage_rows(float* stage, const f32x16 (&acc)[C::NB][C::NJ], int lane, float w)
+{
+    const int hh = lane >> 5;
+#pragma unroll
+    for (int n = 0; n < C::NB; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            typename ColBlock<C>::vec x;
+#pragma unroll
+            for (int j = 0; j < C::NJ; ++j) x[j] = acc[n][j][r] * w;
+            *reinterpret_cast<typename ColBlock<C>::vec*>(&stage[(32 * n + (lane & 31)) * C::PITCH + C::NJ * (8 * (r / 4) + 4 * hh + r % 4)]) = x;
+        }
+}
+
+template <class C> union X3FwdSmem {
+    struct { unsigned char q[C::PIECES], rows[C::NW][C::BLOCK_BYTES]; } t;
+    struct { float stage[C::STAGE_FLOATS], m[C::NW * C::ROWS], l[C::NW * C::ROWS], w[C::NW * C::ROWS], wa[C::ROWS]; } e;
+};
+
+// One thread per row of a workgroup whose streamed rows were split S ways: the weights of the splits (references, in units of log2, at
+// ref_of[split * ROWS + row], sums at l_of) and of the running o, and the row's new LSE.
+template <int ROWS, int S> __device__ __forceinline__ void combine_rows(const FwdArgs& a, int h, int row0, int tid, const float* ref_of, const float* l_of, float* w_of, float* wa_of)
+{
+    float m = -INFINITY, l = 0.f, e[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) m = l_of[s * ROWS + tid] == 0.f ? m : fmaxf(m, ref_of[s * ROWS + tid]);      // (a split that saw nothing of the row has no reference)
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        e[s] = l_of[s * ROWS + tid] == 0.f ? 0.f : fast_exp2(ref_of[s * ROWS + tid] - m);
+        l += e[s] * l_of[s * ROWS + tid];
+    }
+    // the sum is up to 2^8 times that of an exact maximum, and its logarithm would lose those bits: in fp64, over the mantissa alone
+    float lse_part = -INFINITY;
+    if (l > 0.f) {
+        int ex;
+        const float f = __builtin_frexpf(l, &ex);
+        lse_part = (float)(((double)m + (double)ex) * 0.6931471805599453 + (double)logf(f));
+    }
+    float wb = l > 0.f ? 1.0f / l : 0.f, wa = 0.f, lse_new = lse_part;
+    const int row = row0 + tid;
+    if (row < a.g.lq) {
+        float* lp = a.lse + (long long)h * a.g.lq + row;
+        if (a.accumulate) {
+            const float la_old = *lp;
+            const float mm = fmaxf(la_old, lse_part);
+            if (mm == -INFINITY) { wb = 0.f; lse_new = -INFINITY; }
+            else {
+                const float ea = expf(la_old - mm), eb = expf(lse_part - mm), inv = 1.0f / (ea + eb);
+                wa = ea * inv;
+                wb *= eb * inv;
+                lse_new = mm + logf(ea + eb);
+            }
+        }
+        *lp = lse_new;
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) w_of[s * ROWS + tid] = e[s] * wb;
+    wa_of[tid] = wa;
+}
+
+template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int h, const int row0, X3FwdSmem<X3Cfg<D, NB>>& sm)
+{
+    using C = X3Cfg<D, NB>;
+    constexpr int NW = C::NW, ROWS = C::ROWS;
+    const AttnGeom& g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = lane >> 5, l32 = lane & 31;
+    const int kvh = g.kv_of_q[h];
+    const int last_row = (row0 + ROWS < g.lq ? row0 + ROWS : g.lq) - 1;
+    const int n_vis = seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row));      // visible columns form the prefix [0, n_vis)
+    const int n_full = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0));         // columns that every row sees
+    if (n_vis == 0 && a.accumulate) return;                                   // merging an empty partial is the identity
+    const int n_blocks = (n_vis + C::BLK - 1) / C::BLK;
+    int vis[NB];                                                              // columns that rows 32 n + l see
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int row = row0 + 32 * n + l32;
+        vis[n] = row < g.lq ? seg_rows_le(g.ks, seg_pos_of_row(g.qs, row)) : 0;
+    }
+    const float* k = static_cast<const float*>(a.k) + (long long)kvh * g.kv_stride_head;
+    const float* v = static_cast<const float*>(a.v) + (long long)kvh * g.kv_stride_head;
+    unsigned char* const slot = sm.t.rows[wave];
+    const RowBlock<C> rows(slot, lane, g.kv_stride_tok);
+    int b = wave;
+    if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
+    put_stationary<C>(sm.t.q, static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, row0, g.lq, wave, lane);
+    __syncthreads();
+    const unsigned char* stat = sm.t.q + 16 * lane;
+
+    f32x16 acc[NB][C::NJ];
+    zero_acc<C>(acc);
+    const Log2Scale c(g.scale);
+    const float slack = 8.0f / c.hi;
+    // a row's reference, in units of log2, is raised when a score exceeds it by more than 8 of them
+    float ref[NB], limit[NB], l_run[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) { ref[n] = 0.f; limit[n] = -INFINITY; l_run[n] = 0.f; }
+
+    for (; b < n_blocks; b += NW) {
+        f32x16 s[NB];
+        ColBlock<C> vc;
+        landed<0>();
+        vc.load(v, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
+        __builtin_amdgcn_sched_barrier(0);
+        scores<C>(s, rows, slot, stat);
+        reads_done();
+        if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        if (C::BLK * b + C::BLK > n_full) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = -INFINITY;
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            float mx = max3(s[n][0], s[n][1], s[n][2]);
+#pragma unroll
+            for (int r = 3; r < 15; r += 2) mx = max3(mx, s[n][r], s[n][r + 1]);
+            mx = max2(mx, s[n][15]);
+            if (__any(mx > limit[n])) {
+                const float top = max_across_halves(mx);
+                if (top > limit[n]) {
+                    const float to = top * c.hi, alpha = limit[n] == -INFINITY ? 0.f : fast_exp2(ref[n] - to);
+                    ref[n] = to;
+                    limit[n] = top + slack;
+                    l_run[n] *= alpha;
+#pragma unroll
+                    for (int i = 0; i < C::NJ; ++i) acc[n][i] *= alpha;
+                }
+            }
+            float part[4];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s[n][r] = fast_exp2(fmaf(s[n][r], c.lo, fmaf(s[n][r], c.hi, -ref[n])));
+                part[r & 3] = r < 4 ? s[n][r] : part[r & 3] + s[n][r];
+            }
+            l_run[n] += (part[0] + part[1]) + (part[2] + part[3]);
+        }
+        accumulate<C, false>(acc, vc, s);
+    }
+
+    // Combine the splits and merge with the running (o, lse): weights per (row, split), then a row-contiguous pass.
+#pragma unroll
+    for (int n = 0; n < NB; ++n) l_run[n] = sum_across_halves(l_run[n]);
+    __syncthreads();              // the operands are free
+    stage_rows<C>(&sm.e.stage[wave * ROWS * C::PITCH], acc, lane, 1.0f);
+    if (hh == 0) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            sm.e.m[wave * ROWS + 32 * n + l32] = ref[n];
+            sm.e.l[wave * ROWS + 32 * n + l32] = l_run[n];
+        }
+    }
+    __syncthreads();
+    if (tid < ROWS) combine_rows<ROWS, NW>(a, h, row0, tid, sm.e.m, sm.e.l, sm.e.w, sm.e.wa);
+    __syncthreads();
+    for (int i = tid; i < ROWS * D / 4; i += 64 * NW) {
+        const int r = i / (D / 4), c = 4 * (i % (D / 4));
+        if (row0 + r >= g.lq) continue;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NW; ++s) x += sm.e.w[s * ROWS + r] * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
+        f32x4* op = reinterpret_cast<f32x4*>(a.o + ((long long)(row0 + r) * g.nq + h) * D + c);
+        if (a.accumulate) x += sm.e.wa[r] * *op;
+        *op = x;
+    }
+}
+
+// Which rows a launch takes in units of 64 and of 32 rows: the last `n64` 64-row tiles (heads side by side, the longest first), the tiles before
+// them as two 32-row units each.
+template <int D>
+__global__ void __launch_bounds__(256, 1) fwd_f32x3_kernel(const FwdArgs a, const unsigned n64, const int n_tiles)
+{
+    __shared__ __attribute__((aligned(1024))) union { X3FwdSmem<X3Cfg<D, 2>> two; X3FwdSmem<X3Cfg<D, 1>> one; } sm;
+    const unsigned nq = a.g.nq;
+    if (blockIdx.x < n64) {
+        const int tile = n_tiles - 1 - (int)(blockIdx.x / nq);
+        fwd_unit<D, 2>(a, blockIdx.x % nq, 64 * tile, sm.two);
+    } else {
+        const unsigned u = blockIdx.x - n64, t = n64 + u / 2;
+        const int row0 = 64 * (n_tiles - 1 - (int)(t / nq)) + 32 * (1 - (int)(u & 1));
+        if (row0 < a.g.lq) fwd_unit<D, 1>(a, t % nq, row0, sm.one);
+    }
+}
+
+template <class C> union X3BwdTiles {
+    struct { unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES]; };
+    float stage[C::STAGE_FLOATS];
+};
+// and the row scalars of each wavefront's block (dK / dV): -LSE log2(e) in two floats, Delta
+template <class C> struct X3BwdSmem { X3BwdTiles<C> u; };
+template <class C> struct X3KvSmem { X3BwdTiles<C> u; float scalars[C::NW][3][32]; };
+
+// dQ: S^T = K Q^T and dP^T = V dO^T per block, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
+template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int row0, X3BwdSmem<X3Cfg<D, NB>>& sm)
+{
+    using C = X3Cfg<D, NB>;
+    constexpr int NW = C::NW, ROWS = C::ROWS;
+    const AttnGeom& g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = lane >> 5, l32 = lane & 31;
+    const int kvh = g.kv_of_q[h];
+    const int last_row = (row0 + ROWS < g.lq ? row0 + ROWS : g.lq) - 1;
+    const int n_vis = seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row));
+    const int n_full = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0));
+    if (n_vis == 0) return;                               // dq_acc unchanged
+    const int n_blocks = (n_vis + C::BLK - 1) / C::BLK;
+    const Log2Scale c(g.scale);
+    int vis[NB];
+    float nl_hi[NB], nl_lo[NB], delta[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int row = row0 + 32 * n + l32, row_c = row < g.lq ? row : g.lq - 1;
+        vis[n] = row < g.lq ? seg_rows_le(g.ks, seg_pos_of_row(g.qs, row)) : 0;
+        neg_lse_log2(a.lse[(long long)h * g.lq + row_c], nl_hi[n], nl_lo[n]);
+        delta[n] = a.delta[(long long)h * g.lq + row_c];
+    }
+    const float* k = static_cast<const float*>(a.k) + (long long)kvh * g.kv_stride_head;
+    const float* v = static_cast<const float*>(a.v) + (long long)kvh * g.kv_stride_head;
+    unsigned char* const slot = sm.u.rows[wave];
+    const RowBlock<C> rows(slot, lane, g.kv_stride_tok);
+    int b = wave;
+    if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
+    const long long q_off = (long long)h * g.q_stride_head;
+    put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
+    put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
+    __syncthreads();
+    const unsigned char *q_stat = sm.u.t[0] + 16 * lane, *g_stat = sm.u.t[1] + 16 * lane;
+
+    f32x16 acc[NB][C::NJ];
+    zero_acc<C>(acc);
+    for (; b < n_blocks; b += NW) {
+        f32x16 s[NB], dp[NB];
+        ColBlock<C> kc;
+        landed<0>();
+        scores<C>(s, rows, slot, q_stat);
+        reads_done();
+        rows.request(v, g.kv_stride_tok, C::BLK * b, g.lc, lane);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[n][r] = probability(s[n][r], c, nl_hi[n], nl_lo[n]);
+        landed<0>();
+        kc.load(k, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
+        __builtin_amdgcn_sched_barrier(0);
+        scores<C>(dp, rows, slot, g_stat);
+        reads_done();
+        if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[n][r] *= dp[n][r] - delta[n];
+        if (C::BLK * b + C::BLK > n_full) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = 0.f;
+        }
+        accumulate<C, false>(acc, kc, s);
+    }
+    __syncthreads();
+    stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
+    __syncthreads();
+    // Added with atomics, consecutive lanes on consecutive floats: chunks of one shard may be in flight on several streams.
+    // One addition per element and call, so calls in stream order still have a fixed order.
+    for (int i = tid; i < ROWS * D; i += 64 * NW) {
+        const int r = i / D, c = i % D;
+        if (row0 + r >= g.lq) continue;
+        float x = sm.u.stage[r * C::PITCH + c];
+#pragma unroll
+        for (int s = 1; s < NW; ++s) x += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
+        global_atomic_add(a.dq + ((long long)(row0 + r) * g.nq + h) * D + c, x);
+    }
+}
+
+// dK / dV: the stationary rows are keys, the streamed rows q rows of every q head that reads the kv head, one head after the other:
+// S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.
+template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, X3KvSmem<X3Cfg<D, NB>>& sm)
+{
+    using C = X3Cfg<D, NB>;
+    constexpr int NW = C::NW, ROWS = C::ROWS, BLK = C::BLK;
+    const AttnGeom& g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = lane >> 5, l32 = lane & 31;
+    const int col0 = kv_tile * ROWS;
+    const int last_col = (col0 + ROWS < g.lc ? col0 + ROWS : g.lc) - 1;
+    const int row_first = seg_rows_le(g.qs, seg_pos_of_row(g.ks, col0) - 1);         // rows before it see nothing of the tile
+    const int row_full = seg_rows_le(g.qs, seg_pos_of_row(g.ks, last_col) - 1);      // rows from it on see all of it
+    const bool key_ragged = col0 + ROWS > g.lc;
+    int first[NB];                                        // the first row that sees keys 32 n + l
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int col = col0 + 32 * n + l32;
+        first[n] = col < g.lc ? seg_rows_le(g.qs, seg_pos_of_row(g.ks, col) - 1) : 0x7fffffff;
+    }
+    const int block0 = row_first / BLK, n_blocks = (g.lq + BLK - 1) / BLK, per_head = row_first < g.lq ? n_blocks - block0 : 0;
+    const Log2Scale c(g.scale);
+    auto next_head = [&](int h) { for (++h; h < g.nq && g.kv_of_q[h] != kvh; ++h) {} return h; };
+
+    f32x16 dk[NB][C::NJ], dv[NB][C::NJ];
+    zero_acc<C>(dk);
+    zero_acc<C>(dv);
+    if (per_head > 0) {
+        // this wavefront's next block: number b of head h; the blocks of all heads in one sequence are dealt to the wavefronts in turn
+        int h = next_head(-1), b = block0 + wave;
+        auto settle = [&]() { while (b >= n_blocks && h < g.nq) { b -= per_head; h = next_head(h); } };
+        settle();
+        unsigned char* const slot = sm.u.rows[wave];
+        const RowBlock<C> rows(slot, lane, g.q_stride_tok);
+        auto request_q = [&]() { rows.request(static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, BLK * b, g.lq, lane); };
+        if (h < g.nq) request_q();
+        const long long k_off = (long long)kvh * g.kv_stride_head;
+        put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.k) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
+        put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.v) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
+        __syncthreads();
+        const unsigned char *k_stat = sm.u.t[0] + 16 * lane, *v_stat = sm.u.t[1] + 16 * lane;
+        while (h < g.nq) {
+            const long long off = (long long)h * g.q_stride_head;
+            const int r0 = BLK * b;
+            f32x16 p[NB], ds[NB];
+            const long long ri = (long long)h * g.lq + (r0 + l32 < g.lq ? r0 + l32 : g.lq - 1);
+            const float lse = a.lse[ri], delta = a.delta[ri];
+            landed<0>();
+            scores<C>(p, rows, slot, k_stat);
+            reads_done();
+            rows.request(static_cast<const float*>(a.d_o) + off, g.q_stride_tok, r0, g.lq, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                float nl_hi, nl_lo;
+                neg_lse_log2(lse, nl_hi, nl_lo);
+                float (&sc)[3][32] = sm.scalars[wave];      // (both half-waves write the same)
+                sc[0][l32] = nl_hi;
+                sc[1][l32] = nl_lo;
+                sc[2][l32] = delta;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            const float (&sc)[3][32] = sm.scalars[wave];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 nl_hi = *reinterpret_cast<const f32x4*>(&sc[0][8 * q + 4 * hh]), nl_lo = *reinterpret_cast<const f32x4*>(&sc[1][8 * q + 4 * hh]);
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) p[n][4 * q + t] = probability(p[n][4 * q + t], c, nl_hi[t], nl_lo[t]);
+            }
+            if (r0 < row_full || key_ragged || r0 + BLK > g.lq) {
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = r0 + 8 * (r / 4) + 4 * hh + r % 4;
+                        if (row < first[n] || row >= g.lq) p[n][r] = 0.f;
+                    }
+            }
+            landed<0>();
+            ColBlock<C> gc;
+            gc.load(static_cast<const float*>(a.d_o) + off, g.q_stride_tok, r0, g.lq, hh, l32);
+            __builtin_amdgcn_sched_barrier(0);
+            scores<C>(ds, rows, slot, v_stat);
+            reads_done();
+            ColBlock<C> qc;
+            qc.load(static_cast<const float*>(a.q) + off, g.q_stride_tok, r0, g.lq, hh, l32);
+            b += NW;
+            settle();
+            if (h < g.nq) request_q();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 dl = *reinterpret_cast<const f32x4*>(&sc[2][8 * q + 4 * hh]);
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) ds[n][4 * q + t] = p[n][4 * q + t] * (ds[n][4 * q + t] - dl[t]);
+            }
+            accumulate<C, true>(dv, gc, p);
+            accumulate<C, true>(dk, qc, ds);
+        }
+    }
+    auto write_out = [&](float* out, const f32x16 (&acc)[NB][C::NJ], float w) {
+        __syncthreads();
+        stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, w);
+        __syncthreads();
+        for (int i = tid; i < ROWS * D / 4; i += 64 * NW) {
+            const int r = i / (D / 4), c = 4 * (i % (D / 4));
+            if (col0 + r >= g.lc) continue;
+            f32x4 x = *reinterpret_cast<const f32x4*>(&sm.u.stage[r * C::PITCH + c]);
+#pragma unroll
+            for (int s = 1; s < NW; ++s) x += *reinterpret_cast<const f32x4*>(&sm.u.stage[(s * ROWS + r) * C::PITCH + c]);
+            f32x4* op = reinterpret_cast<f32x4*>(out + ((long long)(col0 + r) * g.nkv + kvh) * D + c);
+            if (a.accumulate) x += *op;
+            *op = x;
+        }
+    };
+    write_out(a.dv, dv, 1.0f);
+    write_out(a.dk, dk, g.scale);
+}
+
+// The backward step in one launch: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first), the others dQ units of 64 and of 32 rows.
+template <int D, int KB>
+__global__ void __launch_bounds__(256, 1) bwd_f32x3_kernel(const BwdArgs a, const unsigned n_dkdv, const unsigned n64, const int n_tiles)
+{
+    __shared__ __attribute__((aligned(1024))) union { X3KvSmem<X3Cfg<D, KB>> kv; X3BwdSmem<X3Cfg<D, 2>> two; X3BwdSmem<X3Cfg<D, 1>> one; } sm;
+    const unsigned nq = a.g.nq;
+    if (blockIdx.x < n_dkdv) {
+        const unsigned tile = blockIdx.x / (unsigned)a.g.nkv;
+        dkdv_unit<D, KB>(a, (int)(blockIdx.x - tile * a.g.nkv), (int)tile, sm.kv);
+    } else if (blockIdx.x < n_dkdv + n64) {
+        const unsigned u = blockIdx.x - n_dkdv;
+        dq_unit<D, 2>(a, u % nq, 64 * (n_tiles - 1 - (int)(u / nq)), sm.two);
+    } else {
+        const unsigned u = blockIdx.x - n_dkdv - n64, t = n64 + u / 2;
+        const int row0 = 64 * (n_tiles - 1 - (int)(t / nq)) + 32 * (1 - (int)(u & 1));
+        if (row0 < a.g.lq) dq_unit<D, 1>(a, t % nq, row0, sm.one);
+    }
+}
+
+}  // namespace
+
+hipError_t hexi_launch_fwd_f32x3(const FwdArgs& a, const F32x3Fwd& plan, hipStream_t s)
+{
+    const int n_tiles = (a.g.lq + 63) / 64;
+    const unsigned n64 = (unsigned)plan.n64, grid = n64 + 2u * ((unsigned)(n_tiles * a.g.nq) - n64);
+    if (a.g.d == 128) fwd_f32x3_kernel<128><<<grid, 256, 0, s>>>(a, n64, n_tiles);
+    else if (a.g.d == 64) fwd_f32x3_kernel<64><<<grid, 256, 0, s>>>(a, n64, n_tiles);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t hexi_launch_bwd_f32x3(const BwdArgs& a, const F32x3Bwd& plan, hipStream_t s)
+{
+    const int n_tiles = (a.g.lq + 63) / 64, keys = 32 * plan.key_blocks;
+    const unsigned tiles = a.want_dq ? (unsigned)(n_tiles * a.g.nq) : 0u, n64 = plan.rows64 ? tiles : 0u;
+    const unsigned n_dkdv = a.want_dkdv ? (unsigned)((a.g.lc + keys - 1) / keys * a.g.nkv) : 0u, grid = n_dkdv + n64 + 2u * (tiles - n64);
+    if (a.g.d == 128 && plan.key_blocks == 1) bwd_f32x3_kernel<128, 1><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
+    else if (a.g.d == 64 && plan.key_blocks == 1) bwd_f32x3_kernel<64, 1><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
+    else if (a.g.d == 64) bwd_f32x3_kernel<64, 2><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}

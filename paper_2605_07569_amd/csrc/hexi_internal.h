@@ -162,6 +162,10 @@ extern int hexi_dkdv_run_len;
 // Launchers (each returns a hipError_t from the launch).
 hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s);
+struct F32x3Fwd;
+struct F32x3Bwd;
+hipError_t hexi_launch_fwd_f32x3(const FwdArgs& a, const F32x3Fwd& plan, hipStream_t s);      // products as bf16 matrix instructions on split operands
+hipError_t hexi_launch_bwd_f32x3(const BwdArgs& a, const F32x3Bwd& plan, hipStream_t s);
 hipError_t hexi_launch_fwd_bf16(const FwdArgs& a, hipStream_t s);
 hipError_t hexi_launch_bwd_bf16(const BwdArgs& a, hipStream_t s);      // dK/dV kernel, then the dQ kernel
 hipError_t hexi_launch_bwd_dq_bf16(const BwdArgs& a, hipStream_t s);      // 256-row workgroups

@@ -432,3 +432,99 @@ inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv,
     *kv = kv_shared ? F32Shape::SHARED : split;
     *q = q_shared ? F32Shape::SHARED : split;
 }
+
+// Split-operand fp32 kernels (hexi_f32_bf16x3.hip), 32 or 64 stationary rows to a workgroup, one workgroup on a CU: taken where they are expected to
+// be 5 % faster than the kernels above.  Their matrix work takes under half of the time, but their units are two and four times as long as
+// the 16-row ones, so a launch with few units is better off with those.  us: a launch, a unit, and 1000 streamed rows of its chain,
+// fitted to 300 random calls of 60 to 7000 rows and keys and 1 to 32 heads (90 % of them within 12 %; the 16-row fit stands for all shapes of
+// those kernels, 90 % within 25 %).  Over these calls, geometric mean of the time before / after at head_dim 128: forward 1.24 (taken by 55 % of them),
+// whole backward 1.05 (19 %); at 64 2 % take them.  us before / after, all keys visible: 4096 x 4096 x 16/4 heads x 128
+// forward 1130 / 765, backward 3630 / 3050; 3056 x 3000 x 6/2 x 128 310 / 217, 880 / 770; the other way round
+// 100 x 4000 x 8/2 x 128 forward 79 / 100, dQ 107 / 149, 777 x 1000 x 8/2 x 128 dK / dV 118 / 170.
+struct F32Fit { double launch, unit, per_k; };
+struct F32x3Fwd { bool use = false; int n64 = 0; };                                     // the last n64 64-row tiles (of all heads) as such, the others as two units
+struct F32x3Bwd { bool use = false; int key_blocks = 1; bool rows64 = false; };         // keys of a dK / dV unit / 32, dQ units of 64 rows
+
+inline double hexi_f32_launch_us(const F32Fit& f, long long n, double mean, double longest)
+{
+    const double rounds = (double)((n + 255) / 256);
+    double chain = longest;
+    if (n > 256) chain = mean >= 0.9 * longest ? rounds * mean : std::fmax(longest, mean * (double)n / 256.0 + 0.5 * longest);
+    return f.launch + f.unit * rounds + 1e-3 * f.per_k * chain;
+}
+
+inline F32x3Fwd hexi_f32x3_fwd_by_itself(const AttnGeom& g)
+{
+    const bool wide = g.d == 128;
+    const F32Fit r16 = wide ? F32Fit{6.6, 1.5, 19.3} : F32Fit{6.4, 0.5, 9.9}, r32 = wide ? F32Fit{2.0, 7.2, 23.6} : F32Fit{2.8, 4.7, 14.6},
+                 r64 = wide ? F32Fit{0.5, 11.2, 35.2} : F32Fit{2.4, 6.9, 20.2};
+    const double mean = hexi_mean_seen(g), longest = (double)hexi_keys_seen(g);
+    auto units = [&](int rows) { return (long long)((g.lq + rows - 1) / rows) * g.nq; };
+    const long long tiles = units(64), rest = tiles % 256;
+    const double us32 = hexi_f32_launch_us(r32, units(32), mean, longest), us64 = hexi_f32_launch_us(r64, tiles, mean, longest);
+    F32x3Fwd plan;
+    double us = us32;
+    if (us64 < us) { us = us64; plan.n64 = (int)tiles; }
+    if (tiles > 256 && rest > 0 && rest <= 128 && mean >= 0.9 * longest) {      // whole rounds of 64-row units, a last one of 32-row units
+        const double mixed = hexi_f32_launch_us(r64, tiles - rest, mean, longest) + r32.unit + 1e-3 * r32.per_k * mean;
+        if (mixed < us) { us = mixed; plan.n64 = (int)(tiles - rest); }
+    }
+    plan.use = 1.05 * us + 2.0 < hexi_f32_launch_us(r16, units(16), mean, longest);
+    return plan;
+}
+
+// A step's halves are one launch whose units fill each other's rounds.  A call for one half takes the kernel, and so has the bits, of the whole step.
+inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g)
+{
+    struct Part { long long n; double mean, longest; F32Fit f; };
+    const bool wide = g.d == 128;
+    const double group = (double)g.nq / g.nkv, q_mean = hexi_mean_seen(g), q_longest = (double)hexi_keys_seen(g);
+    const double kv_longest = group * (double)(g.lq - seg_rows_le(g.qs, seg_pos_of_row(g.ks, 0) - 1)), kv_mean = group * (double)g.lq * q_mean / (double)g.lc;
+    auto q_part = [&](int rows, F32Fit f) { return Part{(long long)((g.lq + rows - 1) / rows) * g.nq, q_mean, q_longest, f}; };
+    auto kv_part = [&](int keys, F32Fit f) { return Part{(long long)((g.lc + keys - 1) / keys) * g.nkv, kv_mean, kv_longest, f}; };
+    const Part q16 = q_part(16, wide ? F32Fit{7.2, 3.0, 25.5} : F32Fit{6.7, 1.0, 12.6}), kv16 = kv_part(16, wide ? F32Fit{7.2, 6.0, 33.5} : F32Fit{6.7, 2.9, 18.2});
+    const Part q32 = q_part(32, wide ? F32Fit{3.5, 9.0, 35.3} : F32Fit{3.0, 5.2, 20.3}), q64 = q_part(64, wide ? F32Fit{3.5, 13.0, 55.0} : F32Fit{3.0, 8.2, 30.7});
+    const Part kv32 = kv_part(32, wide ? F32Fit{3.5, 8.0, 54.0} : F32Fit{3.0, 6.3, 31.5}), kv64 = kv_part(64, F32Fit{3.0, 11.2, 50.0});
+    // (the 16-row kernels' units fill each other's rounds better, two of them on a CU at head_dim 64)
+    auto us = [](const Part* kv, const Part* q, double tail) {
+        double sum = 0.0, longest = 0.0, launch = 0.0;
+        long long n = 0;
+        for (const Part* p : {kv, q}) {
+            if (!p) continue;
+            sum += (double)p->n * (p->f.unit + 1e-3 * p->f.per_k * p->mean);
+            longest = std::fmax(longest, p->f.unit + 1e-3 * p->f.per_k * p->longest);
+            launch = p->f.launch;
+            n += p->n;
+        }
+        return launch + (n <= 256 ? longest : std::fmax(longest, sum / 256.0 + tail * longest));
+    };
+    F32x3Bwd plan;
+    const Part *kv = &kv32, *q = &q32;
+    double best = us(kv, q, 0.35);
+    auto consider = [&](const Part* k2, const Part* q2) {
+        const double t = us(k2, q2, 0.35);
+        if (t < best) { best = t; kv = k2; q = q2; }
+    };
+    consider(&kv32, &q64);
+    if (!wide) consider(&kv64, &q64);
+    plan.key_blocks = kv == &kv64 ? 2 : 1;
+    plan.rows64 = q == &q64;
+    plan.use = (wide ? 1.1 : 1.15) * best < us(&kv16, &q16, wide ? 0.1 : 0.0);
+    return plan;
+}
+
+// At head_dim 64 a step takes them forward and backward or not at all: the score of the 16-row backward is one chain of sums there (four have no
+// room in its 128 registers), whose rounding errors cancel in P with those of a forward of the same chain alone.  Measured with the
+// split-operand forward before it, K scaled by 3: errors of dq, dk, dv 1.6, 1.5, 1.6 times as large (310 x 1040 x 16/2 heads).
+inline F32x3Fwd hexi_f32x3_fwd(const AttnGeom& g)
+{
+    F32x3Fwd plan = hexi_f32x3_fwd_by_itself(g);
+    if (plan.use && g.d != 128) plan.use = hexi_f32x3_bwd_by_itself(g).use;
+    return plan;
+}
+inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g)
+{
+    F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g);
+    if (plan.use && g.d != 128) plan.use = hexi_f32x3_fwd_by_itself(g).use;
+    return plan;
+}

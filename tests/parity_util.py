@@ -131,3 +131,17 @@ ORDER_STEPS = [((100, 123, 32, 4, 128, 0), 4, 4), ((364, 126, 16, 4, 64, 126), 2
 UNSEEN_STEPS = [((128, 8, 1, [(0, 127)], [(0, 197)]), 32, 127), ((128, 8, 1, [(0, 128)], [(0, 428)]), 32, 128), ((64, 32, 4, [(0, 129)], [(0, 199)]), 32, 129),
                 ((64, 8, 1, [(100, 60), (400, 90)], [(0, 150), (480, 200)]), 32, 160), ((128, 64, 8, [(0, 895)], [(0, 965)]), 64, 895),
                 ((64, 64, 8, [(0, 1024)], [(0, 1094)]), 64, 1024), ((128, 64, 8, [(0, 1025)], [(0, 1095)]), 64, 1025)]
+
+
+# fp32 steps of the split-operand kernels: (lq, lc, nq, nkv, head_dim), all keys visible, then what the rules deal out: the forward's tiles (32: all
+# as 32-row units, 64: all as 64-row ones, 96: both, 0: another kernel), keys of a dK / dV unit (0: another kernel), rows of a dQ unit.
+F32X3_STEPS = [((87, 185, 48, 16, 128), (32, 32, 32)), ((172, 196, 48, 16, 128), (64, 32, 64)), ((726, 224, 24, 24, 128), (96, 32, 64)),
+               ((88, 448, 96, 24, 128), (64, 32, 32)), ((497, 161, 16, 4, 128), (32, 0, 0)), ((529, 231, 24, 24, 128), (64, 0, 0)),
+               ((651, 577, 8, 8, 64), (32, 32, 64)), ((91, 611, 48, 16, 64), (32, 64, 64)), ((113, 814, 96, 24, 64), (64, 64, 64)),
+               ((693, 755, 24, 24, 64), (96, 64, 64)), ((1393, 203, 24, 24, 64), (0, 0, 0))]
+
+
+def f32x3_diagonal(lq, lc):
+    """The shard's own keys after a chunk of lc, in two segments with a gap, the first keys of which are not the shard's."""
+    a = lq // 2
+    return [(lc, a), (lc + a + 7, lq - a)], [(lc, a + 7), (lc + a + 7, lq - a)]

@@ -12,8 +12,8 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import (F32_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
-                         SHARED_SHARD, SHARED_STEPS, UNSEEN_STEPS, WIDE_DQ_STEPS, check, chunk_slices, oracle_full, to64)
+from parity_util import (F32_STEPS, F32X3_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
+                         SHARED_SHARD, SHARED_STEPS, UNSEEN_STEPS, WIDE_DQ_STEPS, check, chunk_slices, f32x3_diagonal, oracle_full, to64)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -997,3 +997,53 @@ def test_f32_shapes_at_head_dim_64(step, shapes):
     hexi.hexi_attn_bwd_chunk(desc, *args, None, gd, lse, delta, None, dk2, dv2, flags=hexi.HEXI_SKIP_DQ)
     check("dq alone", dq2.cpu(), ref["dq"], "f32")
     assert torch.equal(dk, dk2) and torch.equal(dv, dv2) and ((shapes[1] == 0) != (shapes[3] == 0) or torch.equal(dq, dq2))
+
+
+@pytest.mark.parametrize("step,_", F32X3_STEPS)
+def test_f32_split_operand_shapes(step, _):
+    # the kernels that cut fp32 operands into three bf16 ones, in every shape the rules deal out (asserted on the CPU): one chunk fully visible and
+    # a diagonal one in two segments that merges into its o / lse, K scaled by 3; strided tensors with the same bits; dk / dv under
+    # HEXI_ACCUMULATE; the halves in calls of their own with the same bits
+    lq, lc, nq, nkv, d = step
+    q_segs, own = f32x3_diagonal(lq, lc)
+    w = _custom(f"f32x3_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, own[-1][0] + own[-1][1], q_segs, [[(0, lc)], own], k_scale=3.0)
+    run, inputs, ref = _run_and_compare(w, seed=lq + lc + d)
+    wide = lambda t: torch.cat([t, torch.zeros_like(t[:, :1])], 1)[:, :t.shape[1]]
+    for j, ch in enumerate(w.chunks):
+        dk, dv, dq = torch.full_like(run.dk[j], 0.5), torch.full_like(run.dv[j], -0.25), torch.zeros_like(run.dq)
+        args = (run.desc[j], w.q_segs, ch, run.q, run.k[j], run.v[j], None, run.d_o, run.lse, run.delta)
+        hexi.hexi_attn_bwd_chunk(*args, dq, dk, dv, flags=hexi.HEXI_ACCUMULATE)
+        check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "f32")
+        check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "f32")
+        dq2, dk2, dv2 = torch.zeros_like(dq), torch.full_like(dk, 7.0), torch.full_like(dv, 7.0)
+        hexi.hexi_attn_bwd_chunk(*args, dq2, None, None, flags=hexi.HEXI_SKIP_DKDV)
+        q, d_o, k, v = wide(run.q), wide(run.d_o), wide(run.k[j]), wide(run.v[j])
+        desc = hexi.desc_for(q, k, w.scale)
+        hexi.hexi_attn_bwd_chunk(desc, w.q_segs, ch, q, k, v, None, d_o, run.lse, run.delta, None, dk2, dv2, flags=hexi.HEXI_SKIP_DQ)
+        assert torch.equal(dk2, run.dk[j]) and torch.equal(dv2, run.dv[j]) and torch.equal(dq2, dq)
+    o, lse = torch.full_like(run.o, float("nan")), torch.full_like(run.lse, float("nan"))
+    for j, ch in enumerate(w.chunks):
+        k, v = wide(run.k[j]), wide(run.v[j])
+        hexi.hexi_attn_fwd_chunk(hexi.desc_for(wide(run.q), k, w.scale), w.q_segs, ch, wide(run.q), k, v, o, lse, flags=hexi.HEXI_ACCUMULATE if j else 0)
+    assert torch.equal(o, run.o) and torch.equal(lse, run.lse)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(172, 196, 48, 16, 128), (651, 577, 8, 8, 64)])
+def test_f32_split_operands_at_the_ends_of_the_range(lq, lc, nq, nkv, d):
+    # q near the largest fp32 value (cut, not rounded: no piece is infinite), columns of v of 1e33 and 1e-30, scores whose upper product is -inf
+    g = torch.Generator().manual_seed(lq)
+    q, k, v, d_o = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
+    v[..., 0] *= 1e33
+    v[..., 1] *= 1e-30
+    k[:, :, 0] = 0.0
+    q[..., 0] = 3.4e38
+    k[3::7, :, 0] = -1e20
+    qs, ks = [(lc, lq)], [(0, lc)]
+    t = {n: x.to(DEV) for n, x in dict(q=q, k=k, v=v).items()}
+    o, lse = torch.empty((lq, nq, d), device=DEV), torch.empty((nq, lq), device=DEV)
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(t["q"], t["k"], 0.1), qs, ks, t["q"], t["k"], t["v"], o, lse)
+    keep = torch.tensor([j for j in range(lc) if j % 7 != 3])
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc, lc + lq), to64(k[keep]), to64(v[keep]), keep.numpy(), float(np.float32(0.1)))
+    check("lse", lse.cpu(), lse_ref, "f32")
+    for col, unit in ((0, 1e33), (1, 1e-30), (slice(2, None), 1.0)):
+        check(f"o[{col}]", (o.cpu().double() / unit)[..., col].float(), o_ref[..., col] / unit, "f32")

@@ -186,3 +186,28 @@ def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
     steps = [_step(4096, 4096, 24, 8, 64, 4096), _step(1024, 2048, 4, 1, 64, 2048), _step(512, 512, 8, 2, 64, 512), _step(1000, 1010, 16, 16, 128, 1010),
              _step(300, 300, 4, 2, 128, 300)]
     assert [(g["f32_dq"], g["f32_dkdv"]) for g in shapes(steps)] == [(2, 2), (1, 1), (1, 1), (0, 0), (1, 1)]
+
+
+def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(tmp_path_factory):
+    from parity_util import F32X3_STEPS, f32x3_diagonal
+    exe = _compile(tmp_path_factory, "f32x3_check")
+
+    def ask(steps):
+        segs = lambda x: f"{len(x)} " + " ".join(f"{s} {n}" for s, n in x)
+        lines = [f"{nq} {nkv} {d} {segs(qs)} {segs(ks)}" for d, nq, nkv, qs, ks in steps]
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
+        got = []
+        for line in filter(None, out):
+            use, n64, tiles, bwd, keys, rows64 = map(int, line.split())
+            got.append(((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0, (64 if rows64 else 32) if bwd else 0))
+        return got
+
+    assert ask([_step(lq, lc, nq, nkv, d, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS]) == [s for _, s in F32X3_STEPS]
+    # masked blocks: diagonal chunks as well, forward and backward, with units of 32 and of 64
+    diagonal = ask([(d, nq, nkv) + f32x3_diagonal(lq, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS])
+    assert [diagonal[i] for i in (2, 4, 5, 10)] == [(0, 32, 64), (32, 0, 0), (64, 32, 64), (64, 64, 64)]
+    # us measured before / with the split-operand kernels: forward 1130 / 765, 310 / 217, 180 / 119; backward 3630 / 3050, 880 / 770, 530 / 455; and 79 / 100,
+    # 17 / 23 forward, 124 / 178, 43 / 48 backward
+    taken = ask([_step(4096, 4096, 16, 4, 128, 4096), _step(3056, 3000, 6, 2, 128, 3000), _step(4096, 4096, 8, 8, 64, 0),
+                 _step(100, 4000, 8, 2, 128, 4000), _step(777, 1000, 8, 2, 128, 600), _step(1024, 1024, 4, 4, 64, 1024)])
+    assert [t[0] for t in taken] == [64, 96, 64, 0, 32, 0] and [t[1] > 0 for t in taken] == [True, True, True, False, False, False]
