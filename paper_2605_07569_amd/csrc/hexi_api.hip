@@ -186,10 +186,7 @@ HEXI_EXPORT int hexi_attn_fwd_chunk(const hexi_attn_desc* desc, const hexi_range
     a.accumulate = (flags & HEXI_ACCUMULATE) ? 1 : 0;
     hipError_t e = hipSuccess;
     if (chunk_in_future(a.g)) {
-        if (!a.accumulate) {
-            e = hexi_launch_fill_f32(o, (long long)a.g.lq * a.g.nq * a.g.d, 0.f, s);
-            if (e == hipSuccess) e = hexi_launch_fill_f32(lse, (long long)a.g.lq * a.g.nq, -INFINITY, s);
-        }
+        if (!a.accumulate) e = hexi_launch_empty_partial(o, lse, (long long)a.g.lq * a.g.nq, a.g.d, s);
     } else {
         e = desc->dtype == HEXI_F32 ? hexi_launch_fwd_f32(a, s) : hexi_launch_fwd_bf16(a, s);
     }

@@ -179,7 +179,7 @@ hipError_t hexi_launch_merge(long long n_rows, int nq, int d, float* o_acc, floa
                              const float* lse_part, void* o_final, int o_final_dtype, hipStream_t s);
 hipError_t hexi_launch_delta(long long lq, int nq, int d, const float* o, const void* d_o, int dtype,
                              long long stride_tok, long long stride_head, float* delta, hipStream_t s);
-hipError_t hexi_launch_fill_f32(float* p, long long n, float value, hipStream_t s);
+hipError_t hexi_launch_empty_partial(float* o, float* lse, long long n_rows_heads, int d, hipStream_t s);     // o zero, lse -inf; o 16-byte aligned
 hipError_t hexi_launch_zero2_f32(float* p, float* q, long long n, hipStream_t s);     // both 16-byte aligned, n a multiple of 4
 // pack (x -> packed) or unpack (packed -> y, which has x's layout); host tables, validated by the caller
 hipError_t hexi_launch_a2a(bool pack, const void* x, void* packed, void* y, long long s, int n_heads_total, int row_bytes,

@@ -1,4 +1,4 @@
-// HBM-bound elementwise kernels: two-term log-sum-exp merge, Delta = rowsum(dO * O), fill.
+// HBM-bound elementwise kernels: two-term log-sum-exp merge, Delta = rowsum(dO * O), fills.
 #include "hexi_internal.h"
 #include <hip/hip_bf16.h>
 #include <type_traits>
@@ -26,11 +26,18 @@ __global__ void __launch_bounds__(256) merge_kernel(long long n_vec, int nq, int
     const float a = lse_acc[li], b = lse_part[li];
     const float m = fmaxf(a, b);
     typedef float nt_f32x4 __attribute__((ext_vector_type(4)));
+    // A partial that saw nothing of the row is the identity: o_acc and lse_acc stay, and o_part need not be read.  Half of the rows in most steps of a
+    // zigzag ring, all of them where the chunk lies in the future: 4096 rows x 24 heads x 128, us per merge before / now: no such row 26.4 / 26.4, half
+    // of them 26.0 / 16.0, all 25.4 / 6.3.
+    const bool identity = b == -INFINITY && m != -INFINITY;
+    if (OUT_MODE == 0 && identity) return;
     const nt_f32x4 oa_v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_acc) + idx);
     float4 oa = make_float4(oa_v[0], oa_v[1], oa_v[2], oa_v[3]);
     float4 r;
     if (m == -INFINITY) {
         r = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else if (identity) {
+        r = oa;
     } else {
         const nt_f32x4 ob_v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_part) + idx);
         const float4 ob = make_float4(ob_v[0], ob_v[1], ob_v[2], ob_v[3]);
@@ -39,7 +46,7 @@ __global__ void __launch_bounds__(256) merge_kernel(long long n_vec, int nq, int
         const float wa = ea * inv, wb = eb * inv;
         r = make_float4(wa * oa.x + wb * ob.x, wa * oa.y + wb * ob.y, wa * oa.z + wb * ob.z, wa * oa.w + wb * ob.w);
     }
-    { const nt_f32x4 r_v = {r.x, r.y, r.z, r.w}; __builtin_nontemporal_store(r_v, reinterpret_cast<nt_f32x4*>(o_acc) + idx); }
+    if (!identity) { const nt_f32x4 r_v = {r.x, r.y, r.z, r.w}; __builtin_nontemporal_store(r_v, reinterpret_cast<nt_f32x4*>(o_acc) + idx); }
     // m + log(e_a + e_b), as merge_lse_kernel forms it
     if (WITH_LSE && c4 == 0) lse_acc[li] = (m == -INFINITY) ? -INFINITY : m + logf(expf(a - m) + expf(b - m));
     if (OUT_MODE == 1) reinterpret_cast<float4*>(o_final)[idx] = r;
@@ -138,26 +145,6 @@ hipError_t hexi_launch_delta(long long lq, int nq, int d, const float* o, const 
 
 namespace {
 
-__global__ void __launch_bounds__(256) fill_kernel(float* __restrict__ p, long long n, float value)
-{
-    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long stride = (long long)gridDim.x * 256;
-    for (; i < n; i += stride) p[i] = value;
-}
-
-}  // namespace
-
-hipError_t hexi_launch_fill_f32(float* p, long long n, float value, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    long long blocks = (n + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    fill_kernel<<<(unsigned)blocks, 256, 0, s>>>(p, n, value);
-    return hipGetLastError();
-}
-
-namespace {
-
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // Two buffers of n4 16-byte pieces set to zero in one launch (dk and dv of a chunk): 4 pieces per thread.
@@ -170,7 +157,30 @@ __global__ void __launch_bounds__(256) zero2_kernel(f32x4_t* __restrict__ p, f32
         if (i + 256 * u < n4) out[i + 256 * u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
+// The forward partial of a chunk that no row sees, in one launch: o (n4 16-byte pieces) zero by the first `o_blocks` workgroups, the n_lse values of lse
+// -inf by the others.  4096 rows x 24 heads x 128: 16.3 us as two launches of 4-byte stores, 8.3 us.
+__global__ void __launch_bounds__(256) empty_partial_kernel(f32x4_t* __restrict__ o, long long n4, unsigned o_blocks, float* __restrict__ lse, long long n_lse)
+{
+    if (blockIdx.x < o_blocks) {
+        const long long i = (long long)blockIdx.x * 1024 + threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + 256 * u < n4) o[i + 256 * u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    } else {
+        const long long i = (long long)(blockIdx.x - o_blocks) * 256 + threadIdx.x;
+        if (i < n_lse) lse[i] = -INFINITY;
+    }
+}
+
 }  // namespace
+
+hipError_t hexi_launch_empty_partial(float* o, float* lse, long long n_rows_heads, int d, hipStream_t s)
+{
+    const long long n4 = n_rows_heads * (d / 4);
+    const unsigned o_blocks = (unsigned)((n4 + 1023) / 1024), lse_blocks = (unsigned)((n_rows_heads + 255) / 256);
+    empty_partial_kernel<<<o_blocks + lse_blocks, 256, 0, s>>>(reinterpret_cast<f32x4_t*>(o), n4, o_blocks, lse, n_rows_heads);
+    return hipGetLastError();
+}
 
 hipError_t hexi_launch_zero2_f32(float* p, float* q, long long n, hipStream_t s)
 {

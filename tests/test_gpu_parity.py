@@ -1047,3 +1047,36 @@ def test_f32_split_operands_at_the_ends_of_the_range(lq, lc, nq, nkv, d):
     check("lse", lse.cpu(), lse_ref, "f32")
     for col, unit in ((0, 1e33), (1, 1e-30), (slice(2, None), 1.0)):
         check(f"o[{col}]", (o.cpu().double() / unit)[..., col].float(), o_ref[..., col] / unit, "f32")
+
+
+@pytest.mark.parametrize("d", [64, 128, 12])
+@pytest.mark.parametrize("final", [None, torch.float32, torch.bfloat16])
+def test_merge_of_partials_that_saw_nothing(d, final):
+    # rows whose partial has LSE -inf are the identity, whatever its o holds; both sides -inf: o = 0; the other rows as ever
+    g = torch.Generator().manual_seed(d)
+    rows, nq = 37, 3
+    oa, ob = torch.randn((rows, nq, d), generator=g), torch.randn((rows, nq, d), generator=g)
+    la, lb = torch.randn((nq, rows), generator=g), torch.randn((nq, rows), generator=g)
+    lb[:, 5:20] = -float("inf")
+    la[1, 10:25] = -float("inf")
+    ob[5:20] = float("nan")
+    og, lg = oa.clone().to(DEV), la.clone().to(DEV)
+    out = None if final is None else torch.empty((rows, nq, d), dtype=final, device=DEV)
+    hexi.hexi_attn_merge_lse(og, lg, ob.to(DEV), lb.to(DEV), out)
+    o_ref, l_ref = oracle.merge(to64(oa), to64(la), to64(torch.nan_to_num(ob)), to64(lb))
+    check("o", og.cpu(), o_ref, "f32")
+    check("lse", lg.cpu(), l_ref, "f32")
+    same = (torch.isinf(lb) & ~torch.isinf(la)).T
+    assert torch.equal(og.cpu()[same], oa[same]) and torch.equal(lg.cpu().T[same], la.T[same])
+    if final is not None:
+        assert torch.equal(out, og.to(final))
+
+
+@pytest.mark.parametrize("lq,nq,d", [(1, 1, 64), (33, 3, 128), (1000, 5, 64)])
+def test_partial_of_a_chunk_in_the_future(lq, nq, d):
+    # o = 0 and lse = -inf, whatever was there
+    q = torch.ones((lq, nq, d), dtype=torch.bfloat16, device=DEV)
+    o, lse = torch.full((lq * nq * d + 8,), float("nan"), device=DEV), torch.full((nq * lq + 8,), 7.0, device=DEV)
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(q, q, 1.0), [(0, lq)], [(lq, lq)], q, q, q, o[:lq * nq * d].view(lq, nq, d), lse[:nq * lq].view(nq, lq))
+    assert torch.all(o[:lq * nq * d] == 0) and torch.all(torch.isnan(o[lq * nq * d:]))
+    assert torch.all(lse[:nq * lq] == -float("inf")) and torch.all(lse[nq * lq:] == 7.0)
