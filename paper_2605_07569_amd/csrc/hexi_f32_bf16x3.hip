@@ -16,7 +16,7 @@
 // streamed rows in blocks of 32, each through a slot of its own without any barrier, and combine their results through LDS at the end.  Per
 // block the rows arrive twice: by transfers into the slot for the scores, and as columns straight into registers for the accumulation
 // (a column of 32 rows is what neighbouring lanes read together; rows of 64 lanes read directly cost a cycle per lane, 64 instead of 16).  The
-// cutting of a step stands between the matrix instructions of the step before.  8 wavefronts, two per SIMD, with 16x16x32 products: 926 us forward;
+// cutting of a step stands between the matrix instructions of the step before, and a slot is asked for again before the products of the last step (dQ 1 to 3 %).  8 wavefronts, two per SIMD, with 16x16x32 products: 926 us forward;
 // 64 rows against 32: 757 / 930.
 //
 // Values: no finite value becomes infinite in the cut; a value below 2^-110 loses its last bits (2^-133 is the smallest bf16).  An infinite one has
@@ -191,8 +191,9 @@ template <int N, int V, int DS> __device__ __forceinline__ void interleave()
     }
 }
 
-// s[n], register 4 b + t: streamed row 8 b + 4 hh + t times stationary row 32 n + l.
-template <class C> __device__ __forceinline__ void scores(f32x16 (&s)[C::NB], const RowBlock<C>& rows, const unsigned char* slot, const unsigned char* stat)
+// s[n], register 4 b + t: streamed row 8 b + 4 hh + t times stationary row 32 n + l; slot_free() once the block has been read, before the products of the
+// last step.
+template <class C, class F> __device__ __forceinline__ void scores(f32x16 (&s)[C::NB], const RowBlock<C>& rows, const unsigned char* slot, const unsigned char* stat, F&& slot_free)
 {
     constexpr int NB = C::NB;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -217,6 +218,10 @@ template <class C> __device__ __forceinline__ void scores(f32x16 (&s)[C::NB], co
             read_stat(ks + 1);
             next = split8(raw[0], raw[1]);
             if (ks + 2 < C::NK) rows.read(raw, slot, ks + 2);
+        } else {
+            reads_done();
+            slot_free();
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
@@ -408,9 +413,7 @@ template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs&
         landed<0>();
         vc.load(v, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
         __builtin_amdgcn_sched_barrier(0);
-        scores<C>(s, rows, slot, stat);
-        reads_done();
-        if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane);
+        scores<C>(s, rows, slot, stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
         __builtin_amdgcn_sched_barrier(0);
         if (C::BLK * b + C::BLK > n_full) {
 #pragma unroll
@@ -542,9 +545,7 @@ template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& 
         f32x16 s[NB], dp[NB];
         ColBlock<C> kc;
         landed<0>();
-        scores<C>(s, rows, slot, q_stat);
-        reads_done();
-        rows.request(v, g.kv_stride_tok, C::BLK * b, g.lc, lane);
+        scores<C>(s, rows, slot, q_stat, [&]() { rows.request(v, g.kv_stride_tok, C::BLK * b, g.lc, lane); });
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int n = 0; n < NB; ++n)
@@ -553,9 +554,7 @@ template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& 
         landed<0>();
         kc.load(k, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
         __builtin_amdgcn_sched_barrier(0);
-        scores<C>(dp, rows, slot, g_stat);
-        reads_done();
-        if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane);
+        scores<C>(dp, rows, slot, g_stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int n = 0; n < NB; ++n)
@@ -634,9 +633,7 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
             const long long ri = (long long)h * g.lq + (r0 + l32 < g.lq ? r0 + l32 : g.lq - 1);
             const float lse = a.lse[ri], delta = a.delta[ri];
             landed<0>();
-            scores<C>(p, rows, slot, k_stat);
-            reads_done();
-            rows.request(static_cast<const float*>(a.d_o) + off, g.q_stride_tok, r0, g.lq, lane);
+            scores<C>(p, rows, slot, k_stat, [&]() { rows.request(static_cast<const float*>(a.d_o) + off, g.q_stride_tok, r0, g.lq, lane); });
             __builtin_amdgcn_sched_barrier(0);
             {
                 float nl_hi, nl_lo;
@@ -671,13 +668,11 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
             ColBlock<C> gc;
             gc.load(static_cast<const float*>(a.d_o) + off, g.q_stride_tok, r0, g.lq, hh, l32);
             __builtin_amdgcn_sched_barrier(0);
-            scores<C>(ds, rows, slot, v_stat);
-            reads_done();
-            ColBlock<C> qc;
-            qc.load(static_cast<const float*>(a.q) + off, g.q_stride_tok, r0, g.lq, hh, l32);
             b += NW;
             settle();
-            if (h < g.nq) request_q();
+            scores<C>(ds, rows, slot, v_stat, [&]() { if (h < g.nq) request_q(); });
+            ColBlock<C> qc;
+            qc.load(static_cast<const float*>(a.q) + off, g.q_stride_tok, r0, g.lq, hh, l32);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
