@@ -7,7 +7,7 @@
 // Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: the forward and dQ, 64 rows at a time, execute 1.1 PFLOP/s in
 // bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
 // the same box); dK / dV, with four splits of streamed operands for two, 0.9.  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here:
-// forward 1130 / 765, dQ 1551 / 1100, dK / dV 2360 / 1950; 4096 diagonal x 8 heads x 64, forward and backward: 180 / 119, 530 / 455.
+// forward 1163 / 770, dQ 1554 / 1096, dK / dV 2366 / 1938; 4096 diagonal x 8 heads x 64, forward and backward: 164 / 113, 493 / 394.
 //
 // Shape.  Cutting costs 5.5 vector operations per element, and a vector operation beside a saturated matrix pipe takes 6 cycles (10 for the packing
 // ones) next to 32x32x16 and 8.5 (13) next to 16x16x32; v_dot2_f32_bf16, which would subtract a packed value in one operation, waits for the
@@ -585,8 +585,10 @@ template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& 
 }
 
 // dK / dV: the stationary rows are keys, the streamed rows q rows of every q head that reads the kv head, one head after the other:
-// S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.
-template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, X3KvSmem<X3Cfg<D, NB>>& sm)
+// S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.  With two runs a unit takes the first or the second half of those heads and adds its result
+// to zeros: 0 + a + b = 0 + b + a, so the order of the two does not show.
+template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, const int run, const int runs,
+                                                                        X3KvSmem<X3Cfg<D, NB>>& sm)
 {
     using C = X3Cfg<D, NB>;
     constexpr int NW = C::NW, ROWS = C::ROWS, BLK = C::BLK;
@@ -609,24 +611,34 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
     const Log2Scale c(g.scale);
     auto next_head = [&](int h) { for (++h; h < g.nq && g.kv_of_q[h] != kvh; ++h) {} return h; };
 
+    // the heads of this run: `left` of them from h on
+    int h = next_head(-1), left = 0;
+    for (int i = h; i < g.nq; i = next_head(i)) ++left;
+    if (runs == 2) {
+        const int half = (left + 1) / 2;
+        for (int i = 0; i < (run ? half : 0); ++i) h = next_head(h);
+        left = run ? left - half : half;
+        if (left == 0 || per_head == 0) return;           // (the zeros are there)
+    }
+
     f32x16 dk[NB][C::NJ], dv[NB][C::NJ];
     zero_acc<C>(dk);
     zero_acc<C>(dv);
     if (per_head > 0) {
         // this wavefront's next block: number b of head h; the blocks of all heads in one sequence are dealt to the wavefronts in turn
-        int h = next_head(-1), b = block0 + wave;
-        auto settle = [&]() { while (b >= n_blocks && h < g.nq) { b -= per_head; h = next_head(h); } };
+        int b = block0 + wave;
+        auto settle = [&]() { while (b >= n_blocks && left > 0) { b -= per_head; h = next_head(h); --left; } };
         settle();
         unsigned char* const slot = sm.u.rows[wave];
         const RowBlock<C> rows(slot, lane, g.q_stride_tok);
         auto request_q = [&]() { rows.request(static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, BLK * b, g.lq, lane); };
-        if (h < g.nq) request_q();
+        if (left > 0) request_q();
         const long long k_off = (long long)kvh * g.kv_stride_head;
         put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.k) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
         put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.v) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
         __syncthreads();
         const unsigned char *k_stat = sm.u.t[0] + 16 * lane, *v_stat = sm.u.t[1] + 16 * lane;
-        while (h < g.nq) {
+        while (left > 0) {
             const long long off = (long long)h * g.q_stride_head;
             const int r0 = BLK * b;
             f32x16 p[NB], ds[NB];
@@ -670,7 +682,7 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
             __builtin_amdgcn_sched_barrier(0);
             b += NW;
             settle();
-            scores<C>(ds, rows, slot, v_stat, [&]() { if (h < g.nq) request_q(); });
+            scores<C>(ds, rows, slot, v_stat, [&]() { if (left > 0) request_q(); });
             ColBlock<C> qc;
             qc.load(static_cast<const float*>(a.q) + off, g.q_stride_tok, r0, g.lq, hh, l32);
             __builtin_amdgcn_sched_barrier(0);
@@ -690,6 +702,17 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
         __syncthreads();
         stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, w);
         __syncthreads();
+        if (runs == 2) {           // consecutive lanes on consecutive floats
+            for (int i = tid; i < ROWS * D; i += 64 * NW) {
+                const int r = i / D, c = i % D;
+                if (col0 + r >= g.lc) continue;
+                float x = sm.u.stage[r * C::PITCH + c];
+#pragma unroll
+                for (int s = 1; s < NW; ++s) x += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
+                global_atomic_add(out + ((long long)(col0 + r) * g.nkv + kvh) * D + c, x);
+            }
+            return;
+        }
         for (int i = tid; i < ROWS * D / 4; i += 64 * NW) {
             const int r = i / (D / 4), c = 4 * (i % (D / 4));
             if (col0 + r >= g.lc) continue;
@@ -705,15 +728,16 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
     write_out(a.dk, dk, g.scale);
 }
 
-// The backward step in one launch: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first), the others dQ units of 64 and of 32 rows.
+// The backward step in one launch: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first, and of two runs the
+// one with more heads before the other: 703 us where two runs a tile side by side take 840, 3056 x 3000 x 6/2 heads), the others dQ units of 64 and of 32 rows.
 template <int D, int KB>
-__global__ void __launch_bounds__(256, 1) bwd_f32x3_kernel(const BwdArgs a, const unsigned n_dkdv, const unsigned n64, const int n_tiles)
+__global__ void __launch_bounds__(256, 1) bwd_f32x3_kernel(const BwdArgs a, const unsigned n_dkdv, const unsigned runs, const unsigned n64, const int n_tiles)
 {
     __shared__ __attribute__((aligned(1024))) union { X3KvSmem<X3Cfg<D, KB>> kv; X3BwdSmem<X3Cfg<D, 2>> two; X3BwdSmem<X3Cfg<D, 1>> one; } sm;
     const unsigned nq = a.g.nq;
     if (blockIdx.x < n_dkdv) {
-        const unsigned tile = blockIdx.x / (unsigned)a.g.nkv;
-        dkdv_unit<D, KB>(a, (int)(blockIdx.x - tile * a.g.nkv), (int)tile, sm.kv);
+        const unsigned per_run = n_dkdv / runs, run = blockIdx.x / per_run, u = blockIdx.x - run * per_run, tile = u / (unsigned)a.g.nkv;
+        dkdv_unit<D, KB>(a, (int)(u - tile * a.g.nkv), (int)tile, (int)run, (int)runs, sm.kv);
     } else if (blockIdx.x < n_dkdv + n64) {
         const unsigned u = blockIdx.x - n_dkdv;
         dq_unit<D, 2>(a, u % nq, 64 * (n_tiles - 1 - (int)(u / nq)), sm.two);
@@ -740,10 +764,15 @@ hipError_t hexi_launch_bwd_f32x3(const BwdArgs& a, const F32x3Bwd& plan, hipStre
 {
     const int n_tiles = (a.g.lq + 63) / 64, keys = 32 * plan.key_blocks;
     const unsigned tiles = a.want_dq ? (unsigned)(n_tiles * a.g.nq) : 0u, n64 = plan.rows64 ? tiles : 0u;
-    const unsigned n_dkdv = a.want_dkdv ? (unsigned)((a.g.lc + keys - 1) / keys * a.g.nkv) : 0u, grid = n_dkdv + n64 + 2u * (tiles - n64);
-    if (a.g.d == 128 && plan.key_blocks == 1) bwd_f32x3_kernel<128, 1><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
-    else if (a.g.d == 64 && plan.key_blocks == 1) bwd_f32x3_kernel<64, 1><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
-    else if (a.g.d == 64) bwd_f32x3_kernel<64, 2><<<grid, 256, 0, s>>>(a, n_dkdv, n64, n_tiles);
+    const unsigned runs = (unsigned)plan.runs, n_dkdv = a.want_dkdv ? (unsigned)((a.g.lc + keys - 1) / keys * a.g.nkv) * runs : 0u;
+    const unsigned grid = n_dkdv + n64 + 2u * (tiles - n64);
+    if (runs == 2 && a.want_dkdv) {
+        const hipError_t e = hexi_launch_zero2_f32(a.dk, a.dv, (long long)a.g.lc * a.g.nkv * a.g.d, s);
+        if (e != hipSuccess) return e;
+    }
+    if (a.g.d == 128 && plan.key_blocks == 1) bwd_f32x3_kernel<128, 1><<<grid, 256, 0, s>>>(a, n_dkdv, runs, n64, n_tiles);
+    else if (a.g.d == 64 && plan.key_blocks == 1) bwd_f32x3_kernel<64, 1><<<grid, 256, 0, s>>>(a, n_dkdv, runs, n64, n_tiles);
+    else if (a.g.d == 64) bwd_f32x3_kernel<64, 2><<<grid, 256, 0, s>>>(a, n_dkdv, runs, n64, n_tiles);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

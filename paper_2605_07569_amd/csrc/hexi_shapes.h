@@ -437,19 +437,19 @@ inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv,
 // be 5 % faster than the kernels above.  Their matrix work takes under half of the time, but their units are two and four times as long as
 // the 16-row ones, so a launch with few units is better off with those.  us: a launch, a unit, and 1000 streamed rows of its chain,
 // fitted to 300 random calls of 60 to 7000 rows and keys and 1 to 32 heads (90 % of them within 12 %; the 16-row fit stands for all shapes of
-// those kernels, 90 % within 25 %).  Over these calls, geometric mean of the time before / after at head_dim 128: forward 1.24 (taken by 55 % of them),
-// whole backward 1.05 (19 %); at 64 2 % take them.  us before / after, all keys visible: 4096 x 4096 x 16/4 heads x 128
-// forward 1130 / 765, backward 3630 / 3050; 3056 x 3000 x 6/2 x 128 310 / 217, 880 / 770; the other way round
-// 100 x 4000 x 8/2 x 128 forward 79 / 100, dQ 107 / 149, 777 x 1000 x 8/2 x 128 dK / dV 118 / 170.
+// those kernels, 90 % within 25 %).  Over 320 other random calls, geometric mean of the time before / after at head_dim 128: forward 1.19, whole
+// backward 1.11, under HEXI_ACCUMULATE 1.05; at 64, where few take them, 1.04, 1.02, 1.02.  us before / after, all keys visible: 4096 x 4096 x 16/4
+// heads x 128 forward 1163 / 770, backward 3641 / 3021; 3056 x 3000 x 6/2 x 128 295 / 213, 863 / 725; the other way round
+// 100 x 4000 x 8/2 x 128 forward 79 / 100, dQ 107 / 149, 777 x 1000 x 8/2 x 128 dK / dV with heads in one run 118 / 170.
 struct F32Fit { double launch, unit, per_k; };
 struct F32x3Fwd { bool use = false; int n64 = 0; };                                     // the last n64 64-row tiles (of all heads) as such, the others as two units
-struct F32x3Bwd { bool use = false; int key_blocks = 1; bool rows64 = false; };         // keys of a dK / dV unit / 32, dQ units of 64 rows
+struct F32x3Bwd { bool use = false; int key_blocks = 1, runs = 1; bool rows64 = false; }; // keys of a dK / dV unit / 32, parts of a head group, dQ units of 64 rows
 
-inline double hexi_f32_launch_us(const F32Fit& f, long long n, double mean, double longest)
+inline double hexi_f32_launch_us(const F32Fit& f, long long n, double mean, double longest, double tail = 0.5)
 {
     const double rounds = (double)((n + 255) / 256);
     double chain = longest;
-    if (n > 256) chain = mean >= 0.9 * longest ? rounds * mean : std::fmax(longest, mean * (double)n / 256.0 + 0.5 * longest);
+    if (n > 256) chain = mean >= 0.9 * longest ? rounds * mean : std::fmax(longest, mean * (double)n / 256.0 + tail * longest);
     return f.launch + f.unit * rounds + 1e-3 * f.per_k * chain;
 }
 
@@ -469,12 +469,16 @@ inline F32x3Fwd hexi_f32x3_fwd_by_itself(const AttnGeom& g)
         const double mixed = hexi_f32_launch_us(r64, tiles - rest, mean, longest) + r32.unit + 1e-3 * r32.per_k * mean;
         if (mixed < us) { us = mixed; plan.n64 = (int)(tiles - rest); }
     }
-    plan.use = 1.05 * us + 2.0 < hexi_f32_launch_us(r16, units(16), mean, longest);
+    plan.use = 1.05 * us + 2.0 < hexi_f32_launch_us(r16, units(16), mean, longest, 0.2);
     return plan;
 }
 
 // A step's halves are one launch whose units fill each other's rounds.  A call for one half takes the kernel, and so has the bits, of the whole step.
-inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g)
+// A few long dK / dV units are what such a launch waits for: the heads of a group may be dealt to two of them, which add to cleared elements (not
+// where dk and dv hold a running value, whose sum would show the order: the margin is wider there, 1.1 lost up to 9 % in some of the calls).
+// 128 columns, one run / two: 6000 x 800 x 8/1 heads 1888 / 1294 us, 3056 x 3000 x 6/2 703 / 701, 2048 x 2048 x 16/4 737 / 743; 16-row kernels / two
+// runs: 1500 x 2500 x 8/2 496 / 380, 777 x 1000 x 8/2 123 / 108.
+inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate)
 {
     struct Part { long long n; double mean, longest; F32Fit f; };
     const bool wide = g.d == 128;
@@ -484,6 +488,10 @@ inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g)
     auto kv_part = [&](int keys, F32Fit f) { return Part{(long long)((g.lc + keys - 1) / keys) * g.nkv, kv_mean, kv_longest, f}; };
     const Part q16 = q_part(16, wide ? F32Fit{7.2, 3.0, 25.5} : F32Fit{6.7, 1.0, 12.6}), kv16 = kv_part(16, wide ? F32Fit{7.2, 6.0, 33.5} : F32Fit{6.7, 2.9, 18.2});
     const Part q32 = q_part(32, wide ? F32Fit{3.5, 9.0, 35.3} : F32Fit{3.0, 5.2, 20.3}), q64 = q_part(64, wide ? F32Fit{3.5, 13.0, 55.0} : F32Fit{3.0, 8.2, 30.7});
+    auto halves = [&](Part p) {        // two runs: twice the units, of the longer half at most; the clearing launch
+        const double longer = std::ceil(0.5 * group) / group;
+        return Part{2 * p.n, 0.5 * p.mean, longer * p.longest, F32Fit{p.f.launch + 5.0, p.f.unit, p.f.per_k}};
+    };
     const Part kv32 = kv_part(32, wide ? F32Fit{3.5, 8.0, 54.0} : F32Fit{3.0, 6.3, 31.5}), kv64 = kv_part(64, F32Fit{3.0, 11.2, 50.0});
     // (the 16-row kernels' units fill each other's rounds better, two of them on a CU at head_dim 64)
     auto us = [](const Part* kv, const Part* q, double tail) {
@@ -493,7 +501,7 @@ inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g)
             if (!p) continue;
             sum += (double)p->n * (p->f.unit + 1e-3 * p->f.per_k * p->mean);
             longest = std::fmax(longest, p->f.unit + 1e-3 * p->f.per_k * p->longest);
-            launch = p->f.launch;
+            launch = std::fmax(launch, p->f.launch);
             n += p->n;
         }
         return launch + (n <= 256 ? longest : std::fmax(longest, sum / 256.0 + tail * longest));
@@ -507,24 +515,37 @@ inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g)
     };
     consider(&kv32, &q64);
     if (!wide) consider(&kv64, &q64);
-    plan.key_blocks = kv == &kv64 ? 2 : 1;
+    const Part kv32_2 = halves(kv32), kv64_2 = halves(kv64);
+    if (!accumulate && group >= 2.0) {
+        best /= 1.03;                  // (a fixed cost of atomics that the fits do not hold)
+        consider(&kv32_2, &q32);
+        consider(&kv32_2, &q64);
+        if (!wide) consider(&kv64_2, &q64);
+        if (kv != &kv32_2 && kv != &kv64_2) best *= 1.03;
+    }
+    plan.runs = kv == &kv32_2 || kv == &kv64_2 ? 2 : 1;
+    plan.key_blocks = kv == &kv64 || kv == &kv64_2 ? 2 : 1;
     plan.rows64 = q == &q64;
-    plan.use = (wide ? 1.1 : 1.15) * best < us(&kv16, &q16, wide ? 0.1 : 0.0);
+    plan.use = (!wide ? 1.15 : accumulate ? 1.25 : 1.1) * best < us(&kv16, &q16, wide ? 0.1 : 0.0);
     return plan;
 }
 
 // At head_dim 64 a step takes them forward and backward or not at all: the score of the 16-row backward is one chain of sums there (four have no
 // room in its 128 registers), whose rounding errors cancel in P with those of a forward of the same chain alone.  Measured with the
 // split-operand forward before it, K scaled by 3: errors of dq, dk, dv 1.6, 1.5, 1.6 times as large (310 x 1040 x 16/2 heads).
+inline bool hexi_f32x3_at_64(const AttnGeom& g)
+{
+    return hexi_f32x3_fwd_by_itself(g).use && hexi_f32x3_bwd_by_itself(g, false).use && hexi_f32x3_bwd_by_itself(g, true).use;
+}
 inline F32x3Fwd hexi_f32x3_fwd(const AttnGeom& g)
 {
     F32x3Fwd plan = hexi_f32x3_fwd_by_itself(g);
-    if (plan.use && g.d != 128) plan.use = hexi_f32x3_bwd_by_itself(g).use;
+    if (plan.use && g.d != 128) plan.use = hexi_f32x3_at_64(g);
     return plan;
 }
-inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g)
+inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate)
 {
-    F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g);
-    if (plan.use && g.d != 128) plan.use = hexi_f32x3_fwd_by_itself(g).use;
+    F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g, accumulate);
+    if (plan.use && g.d != 128) plan.use = hexi_f32x3_at_64(g);
     return plan;
 }

@@ -134,11 +134,13 @@ UNSEEN_STEPS = [((128, 8, 1, [(0, 127)], [(0, 197)]), 32, 127), ((128, 8, 1, [(0
 
 
 # fp32 steps of the split-operand kernels: (lq, lc, nq, nkv, head_dim), all keys visible, then what the rules deal out: the forward's tiles (32: all
-# as 32-row units, 64: all as 64-row ones, 96: both, 0: another kernel), keys of a dK / dV unit (0: another kernel), rows of a dQ unit.
-F32X3_STEPS = [((87, 185, 48, 16, 128), (32, 32, 32)), ((172, 196, 48, 16, 128), (64, 32, 64)), ((726, 224, 24, 24, 128), (96, 32, 64)),
-               ((88, 448, 96, 24, 128), (64, 32, 32)), ((497, 161, 16, 4, 128), (32, 0, 0)), ((529, 231, 24, 24, 128), (64, 0, 0)),
-               ((651, 577, 8, 8, 64), (32, 32, 64)), ((91, 611, 48, 16, 64), (32, 64, 64)), ((113, 814, 96, 24, 64), (64, 64, 64)),
-               ((693, 755, 24, 24, 64), (96, 64, 64)), ((1393, 203, 24, 24, 64), (0, 0, 0))]
+# as 32-row units, 64: all as 64-row ones, 96: both, 0: another kernel), keys of a dK / dV unit (0: another kernel), rows of a dQ unit,
+# units that the heads of a group are dealt to.
+F32X3_STEPS = [((1079, 162, 4, 1, 128), (32, 32, 32, 2)), ((868, 112, 16, 8, 128), (64, 32, 64, 2)), ((691, 119, 32, 8, 128), (96, 32, 64, 2)),
+               ((516, 93, 24, 8, 128), (64, 0, 0, 0)), ((523, 882, 9, 3, 128), (32, 32, 64, 2)), ((172, 196, 48, 16, 128), (64, 32, 64, 1)),
+               ((726, 224, 24, 24, 128), (96, 32, 64, 1)), ((327, 161, 4, 1, 128), (0, 32, 32, 2)), ((625, 231, 24, 24, 128), (64, 32, 64, 1)),
+               ((651, 577, 8, 8, 64), (32, 32, 64, 1)), ((91, 611, 48, 16, 64), (32, 64, 64, 1)), ((113, 814, 96, 24, 64), (64, 64, 64, 1)),
+               ((693, 755, 24, 24, 64), (96, 64, 64, 1)), ((1196, 203, 32, 32, 64), (0, 0, 0, 0))]
 
 
 def f32x3_diagonal(lq, lc):

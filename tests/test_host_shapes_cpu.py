@@ -198,16 +198,17 @@ def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(tmp_path_fa
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         got = []
         for line in filter(None, out):
-            use, n64, tiles, bwd, keys, rows64 = map(int, line.split())
-            got.append(((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0, (64 if rows64 else 32) if bwd else 0))
+            use, n64, tiles, bwd, keys, rows64, runs = map(int, line.split())
+            got.append(((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0, (64 if rows64 else 32) if bwd else 0,
+                        runs if bwd else 0))
         return got
 
     assert ask([_step(lq, lc, nq, nkv, d, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS]) == [s for _, s in F32X3_STEPS]
     # masked blocks: diagonal chunks as well, forward and backward, with units of 32 and of 64
     diagonal = ask([(d, nq, nkv) + f32x3_diagonal(lq, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS])
-    assert [diagonal[i] for i in (2, 4, 5, 10)] == [(0, 32, 64), (32, 0, 0), (64, 32, 64), (64, 64, 64)]
-    # us measured before / with the split-operand kernels: forward 1130 / 765, 310 / 217, 180 / 119; backward 3630 / 3050, 880 / 770, 530 / 455; and 79 / 100,
-    # 17 / 23 forward, 124 / 178, 43 / 48 backward
+    assert [diagonal[i] for i in (0, 7, 8, 13)] == [(0, 32, 32, 2), (0, 32, 32, 2), (64, 32, 64, 1), (64, 64, 64, 1)]
+    # us measured before / with the split-operand kernels: forward 1163 / 770, 295 / 213, 164 / 113; backward 3641 / 3021, 863 / 725, 493 / 394; 79 / 100
+    # forward of 100 rows; 17 / 23 and 43 / 48 of 1024 at head_dim 64
     taken = ask([_step(4096, 4096, 16, 4, 128, 4096), _step(3056, 3000, 6, 2, 128, 3000), _step(4096, 4096, 8, 8, 64, 0),
-                 _step(100, 4000, 8, 2, 128, 4000), _step(777, 1000, 8, 2, 128, 600), _step(1024, 1024, 4, 4, 64, 1024)])
-    assert [t[0] for t in taken] == [64, 96, 64, 0, 32, 0] and [t[1] > 0 for t in taken] == [True, True, True, False, False, False]
+                 _step(100, 4000, 8, 2, 128, 4000), _step(1024, 1024, 4, 4, 64, 1024)])
+    assert [t[0] for t in taken] == [64, 96, 64, 0, 0] and [t[1] > 0 for t in taken] == [True, True, True, False, False]
