@@ -20,7 +20,8 @@
 // 64 rows against 32: 757 / 930.
 //
 // Values: no finite value becomes infinite in the cut; a value below 2^-110 loses its last bits (2^-133 is the smallest bf16).  An infinite one has
-// no rest (inf - inf): scores then count their upper product alone, infinite values of V, dO or dS give NaN where they give infinities in hexi_f32.hip.
+// no rest (inf - inf): scores then count their upper product alone, the forward looks an output that came out as NaN up in V, infinite values of dO or dS give NaN where
+// some give infinities in hexi_f32.hip.
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 #include "hexi_shapes.h"
@@ -368,6 +369,20 @@ template <int ROWS, int S> __device__ __forceinline__ void combine_rows(const Fw
     wa_of[tid] = wa;
 }
 
+// An output that came out as NaN although its weights are good: an infinite value of V has NaN for the rests of its cut.  What positive weights make of the
+// n values that the row sees in this column of V.
+__device__ __noinline__ float sum_with_infinities(const float* v, const long long stride, const int n)
+{
+    bool up = false, down = false, nan = false;
+    for (int j = 0; j < n; ++j) {
+        const float x = v[j * stride];
+        up |= x == INFINITY;
+        down |= x == -INFINITY;
+        nan |= x != x;
+    }
+    return nan || up == down ? NAN : up ? INFINITY : -INFINITY;
+}
+
 template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int h, const int row0, X3FwdSmem<X3Cfg<D, NB>>& sm)
 {
     using C = X3Cfg<D, NB>;
@@ -469,8 +484,19 @@ template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs&
         const int r = i / (D / 4), c = 4 * (i % (D / 4));
         if (row0 + r >= g.lq) continue;
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        float w_sum = 0.f;
 #pragma unroll
-        for (int s = 0; s < NW; ++s) x += sm.e.w[s * ROWS + r] * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
+        for (int s = 0; s < NW; ++s) {
+            const float ws = sm.e.w[s * ROWS + r];
+            x += ws * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
+            w_sum += ws;
+        }
+        if (__builtin_expect(w_sum > 0.f && (x[0] != x[0] || x[1] != x[1] || x[2] != x[2] || x[3] != x[3]), 0)) {
+            const int seen = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0 + r));
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x[e] != x[e]) x[e] = sum_with_infinities(v + c + e, g.kv_stride_tok, seen);
+        }
         f32x4* op = reinterpret_cast<f32x4*>(a.o + ((long long)(row0 + r) * g.nq + h) * D + c);
         if (a.accumulate) x += sm.e.wa[r] * *op;
         *op = x;

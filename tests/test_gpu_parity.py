@@ -1050,6 +1050,25 @@ def test_f32_split_operands_at_the_ends_of_the_range(lq, lc, nq, nkv, d):
         check(f"o[{col}]", (o.cpu().double() / unit)[..., col].float(), o_ref[..., col] / unit, "f32")
 
 
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(691, 119, 32, 8, 128), (651, 577, 8, 8, 64)])
+def test_f32_split_operands_with_infinite_values(lq, lc, nq, nkv, d):
+    # infinite values of v, whose rests after the cut are NaN: columns of one sign, of both and with a NaN, the others untouched; q with a NaN in one row
+    g = torch.Generator().manual_seed(lc)
+    q, k, v = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv)))
+    inf, nan = float("inf"), float("nan")
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc, lc + lq), to64(k), to64(v), np.arange(lc), float(np.float32(0.1)))
+    v[5, :, 0], v[lc - 1, :, 1], v[5, :, 2], v[40, :, 2], v[9, :, 3] = inf, -inf, inf, -inf, nan
+    q[7] = nan
+    t = {n: x.to(DEV) for n, x in dict(q=q, k=k, v=v).items()}
+    o, lse = torch.empty((lq, nq, d), device=DEV), torch.empty((nq, lq), device=DEV)
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(t["q"], t["k"], 0.1), [(lc, lq)], [(0, lc)], t["q"], t["k"], t["v"], o, lse)
+    rows = [r for r in range(lq) if r != 7]
+    check("o", o.cpu()[rows][..., 4:], o_ref[rows][..., 4:], "f32")
+    check("lse", lse.cpu()[:, rows], lse_ref[:, rows], "f32")
+    o = o.cpu()
+    assert (o[rows][..., 0] == inf).all() and (o[rows][..., 1] == -inf).all() and o[rows][..., 2:4].isnan().all() and o[7].isnan().all()
+
+
 @pytest.mark.parametrize("d", [64, 128, 12])
 @pytest.mark.parametrize("final", [None, torch.float32, torch.bfloat16])
 def test_merge_of_partials_that_saw_nothing(d, final):
