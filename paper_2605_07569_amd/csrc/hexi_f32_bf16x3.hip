@@ -6,7 +6,7 @@
 // 7e-7, 5e-7, 5e-7 here; over 37 shapes of 256 to 6000 rows and keys, K scaled by 1 and by 3, no output is further off than before.
 // Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: the forward and dQ, 64 rows at a time, execute 1.1 PFLOP/s in
 // bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
-// the same box); dK / dV, with four splits of streamed operands for two, 0.9.  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here:
+// the same card); dK / dV, with four splits of streamed operands for two, 0.9.  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here:
 // forward 1163 / 770, dQ 1554 / 1096, dK / dV 2366 / 1938; 4096 diagonal x 8 heads x 64, forward and backward: 164 / 113, 493 / 394.
 //
 // Shape.  Cutting costs 5.5 vector operations per element, and a vector operation beside a saturated matrix pipe takes 6 cycles (10 for the packing
