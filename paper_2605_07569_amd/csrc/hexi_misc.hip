@@ -26,27 +26,25 @@ __global__ void __launch_bounds__(256) merge_kernel(long long n_vec, int nq, int
     const float a = lse_acc[li], b = lse_part[li];
     const float m = fmaxf(a, b);
     typedef float nt_f32x4 __attribute__((ext_vector_type(4)));
-    // A partial that saw nothing of the row is the identity: o_acc and lse_acc stay, and o_part need not be read.  Half of the rows in most steps of a
-    // zigzag ring, all of them where the chunk lies in the future: 4096 rows x 24 heads x 128, us per merge before / now: no such row 26.4 / 26.4, half
-    // of them 26.0 / 16.0, all 25.4 / 6.3.
-    const bool identity = b == -INFINITY && m != -INFINITY;
-    if (OUT_MODE == 0 && identity) return;
-    const nt_f32x4 oa_v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_acc) + idx);
-    float4 oa = make_float4(oa_v[0], oa_v[1], oa_v[2], oa_v[3]);
-    float4 r;
-    if (m == -INFINITY) {
-        r = make_float4(0.f, 0.f, 0.f, 0.f);
-    } else if (identity) {
-        r = oa;
-    } else {
-        const nt_f32x4 ob_v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_part) + idx);
-        const float4 ob = make_float4(ob_v[0], ob_v[1], ob_v[2], ob_v[3]);
+    // A partial that saw nothing of the row has weight 0: o_acc and lse_acc stay, and o_acc need not be read or written.  o_part is read all the same: its
+    // LSE is -inf also where the row's sum is NaN (a NaN key, a score that overflowed to +inf), and then 0 x NaN has to reach o.  Half of the rows in
+    // most steps of a zigzag ring see nothing, all of them where the chunk lies in the future: 4096 rows x 24 heads x 128, us per merge, every row merged /
+    // as here: no such row 27.7 / 27.5, half of them 27.8 / 20.4, all 27.7 / 12.2 (17.8 and 6.2 if o_part were not read either).
+    const bool weightless = b == -INFINITY && fabsf(m) != INFINITY;
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    bool stays = false;
+    if (m != -INFINITY) {
+        const nt_f32x4 ob = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_part) + idx);
+        stays = weightless && fabsf(ob[0]) < INFINITY && fabsf(ob[1]) < INFINITY && fabsf(ob[2]) < INFINITY && fabsf(ob[3]) < INFINITY;
+        if (OUT_MODE == 0 && stays) return;
+        const nt_f32x4 oa = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(o_acc) + idx);
         const float ea = expf(a - m), eb = expf(b - m);
         const float inv = 1.0f / (ea + eb);
         const float wa = ea * inv, wb = eb * inv;
-        r = make_float4(wa * oa.x + wb * ob.x, wa * oa.y + wb * ob.y, wa * oa.z + wb * ob.z, wa * oa.w + wb * ob.w);
+        r = stays ? make_float4(oa[0], oa[1], oa[2], oa[3])
+                  : make_float4(wa * oa[0] + wb * ob[0], wa * oa[1] + wb * ob[1], wa * oa[2] + wb * ob[2], wa * oa[3] + wb * ob[3]);
     }
-    if (!identity) { const nt_f32x4 r_v = {r.x, r.y, r.z, r.w}; __builtin_nontemporal_store(r_v, reinterpret_cast<nt_f32x4*>(o_acc) + idx); }
+    if (!stays) { const nt_f32x4 r_v = {r.x, r.y, r.z, r.w}; __builtin_nontemporal_store(r_v, reinterpret_cast<nt_f32x4*>(o_acc) + idx); }
     // m + log(e_a + e_b), as merge_lse_kernel forms it
     if (WITH_LSE && c4 == 0) lse_acc[li] = (m == -INFINITY) ? -INFINITY : m + logf(expf(a - m) + expf(b - m));
     if (OUT_MODE == 1) reinterpret_cast<float4*>(o_final)[idx] = r;

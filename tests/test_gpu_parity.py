@@ -1072,24 +1072,65 @@ def test_f32_split_operands_with_infinite_values(lq, lc, nq, nkv, d):
 @pytest.mark.parametrize("d", [64, 128, 12])
 @pytest.mark.parametrize("final", [None, torch.float32, torch.bfloat16])
 def test_merge_of_partials_that_saw_nothing(d, final):
-    # rows whose partial has LSE -inf are the identity, whatever its o holds; both sides -inf: o = 0; the other rows as ever
+    # rows whose partial has LSE -inf are the identity, whatever finite values its o holds; both sides -inf: o = 0; the other rows as ever
     g = torch.Generator().manual_seed(d)
     rows, nq = 37, 3
     oa, ob = torch.randn((rows, nq, d), generator=g), torch.randn((rows, nq, d), generator=g)
     la, lb = torch.randn((nq, rows), generator=g), torch.randn((nq, rows), generator=g)
     lb[:, 5:20] = -float("inf")
     la[1, 10:25] = -float("inf")
-    ob[5:20] = float("nan")
+    ob[5:20] = 3e38
     og, lg = oa.clone().to(DEV), la.clone().to(DEV)
     out = None if final is None else torch.empty((rows, nq, d), dtype=final, device=DEV)
     hexi.hexi_attn_merge_lse(og, lg, ob.to(DEV), lb.to(DEV), out)
-    o_ref, l_ref = oracle.merge(to64(oa), to64(la), to64(torch.nan_to_num(ob)), to64(lb))
+    o_ref, l_ref = oracle.merge(to64(oa), to64(la), to64(ob), to64(lb))
     check("o", og.cpu(), o_ref, "f32")
     check("lse", lg.cpu(), l_ref, "f32")
     same = (torch.isinf(lb) & ~torch.isinf(la)).T
     assert torch.equal(og.cpu()[same], oa[same]) and torch.equal(lg.cpu().T[same], la.T[same])
     if final is not None:
         assert torch.equal(out, og.to(final))
+
+
+@pytest.mark.parametrize("d", [64, 128, 12])
+@pytest.mark.parametrize("final", [None, torch.float32, torch.bfloat16])
+def test_merge_keeps_what_is_not_finite_in_a_weightless_partial(d, final):
+    # a partial whose sum is NaN has LSE -inf as well (0 x NaN and 0 x inf are NaN); the other columns of its rows and both rows' LSE stay; a running LSE of
+    # +inf leaves no weights at all
+    g = torch.Generator().manual_seed(d + 1)
+    rows, nq = 37, 3
+    oa, ob, la = torch.randn((rows, nq, d), generator=g), torch.randn((rows, nq, d), generator=g), torch.randn((nq, rows), generator=g)
+    lb = torch.full((nq, rows), -float("inf"))
+    ob[3, :, :], ob[8, 1, d - 1], ob[9, 2, 0], la[0, 30] = float("nan"), float("nan"), float("inf"), float("inf")
+    og, lg = oa.clone().to(DEV), la.clone().to(DEV)
+    out = None if final is None else torch.empty((rows, nq, d), dtype=final, device=DEV)
+    hexi.hexi_attn_merge_lse(og, lg, ob.to(DEV), lb.to(DEV), out)
+    want, lse = oa + 0.0 * ob, la.clone()
+    want[30, 0], lse[0, 30] = float("nan"), float("nan")
+    assert torch.equal(torch.isnan(og.cpu()), torch.isnan(want)) and torch.equal(og.cpu().nan_to_num(), want.nan_to_num())
+    assert torch.equal(lg.cpu().isnan(), lse.isnan()) and torch.equal(lg.cpu().nan_to_num(), lse.nan_to_num())
+    if final is not None:
+        assert torch.equal(out.isnan(), og.isnan()) and torch.equal(out.nan_to_num(), og.to(final).nan_to_num())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("chunk", [0, 2])
+def test_a_poisoned_chunk_is_not_left_out_of_an_unfused_replay(dtype, chunk):
+    # NaN in one key, and finite q and k whose score overflows to +inf: the rows that see them are NaN in o, with the merges apart as with the fused ones
+    w = _custom(f"poison_{dtype}", dtype, 4, 2, 128, 1200, [(700, 500)], [[(300 * j, 300)] for j in range(4)])
+    inputs = wl.make_inputs(w, 5)
+    inputs["k"][300 * chunk + 17, 0] = float("nan")
+    inputs["k"][300 * chunk + 100, 1, 0] = 3e38
+    inputs["q"][:, 2:, 0] = 0.0
+    inputs["q"][::5, 2, 0] = 100.0
+    got = []
+    for fused in (True, False):
+        run = replay.ShardRun(w, inputs, DEV, fused_merge=fused)
+        run.forward()
+        got.append(run.o.cpu())
+    sees = (torch.arange(700, 1200) >= 300 * chunk + 100)
+    assert all(o[sees][:, :2].isnan().all() and o[sees][::5, 2].isnan().all() and not o[:, 3].isnan().any() for o in got)
+    assert torch.equal(got[0].isnan(), got[1].isnan())
 
 
 @pytest.mark.parametrize("lq,nq,d", [(1, 1, 64), (33, 3, 128), (1000, 5, 64)])
