@@ -24,7 +24,7 @@ __global__ void __launch_bounds__((64 * rows16::F32Cfg<D, SPLIT, TWO>::NW), TWO 
     __shared__ __attribute__((aligned(1024))) union { rows16::DkdvSmem<C> dkdv; rows16::DqSmem<C> dq; } sm;
     if (blockIdx.x < n_dkdv) {
         const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x / (unsigned)a.g.nkv);
-        rows16::dkdv_unit<C>(a, (int)blockIdx.x - tile * a.g.nkv, tile, sm.dkdv);
+        rows16::dkdv_unit<C>(a, (int)blockIdx.x - tile * a.g.nkv, tile, sm.dkdv, 0, a.g.nq, false);
     } else {
         const unsigned unit = blockIdx.x - n_dkdv;
         const int tile = __builtin_amdgcn_readfirstlane(unit / (unsigned)a.g.nq);

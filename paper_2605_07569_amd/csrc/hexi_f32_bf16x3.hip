@@ -19,13 +19,16 @@
 // cutting of a step stands between the matrix instructions of the step before, and a slot is asked for again before the products of the last step (dQ 1 to 3 %).  8 wavefronts, two per SIMD, with 16x16x32 products: 926 us forward;
 // 64 rows against 32: 757 / 930.
 //
-// Values: no finite value becomes infinite in the cut; a value below 2^-110 loses its last bits (2^-133 is the smallest bf16).  An infinite one has
-// no rest (inf - inf): scores then count their upper product alone, the forward looks an output that came out as NaN up in V, infinite values of dO or dS give NaN where
-// some give infinities in hexi_f32.hip.
+// Values.  A cut loses bits of a value below 2^-110 (2^-133 is the smallest bf16: up to 2^-134 of it), an infinite one has no rest (inf - inf), and the
+// probabilities of the forward, up to 2^8 here, may overflow in a sum that would not.  A unit therefore looks its operands and results over
+// (largest(), stationary_range(), too_small_or_not_finite()) and, where the cut may show in a result, hands its rows to the units on the fp32 instruction
+// (hexi_f32_units.h) before anything is written: values, infinities and NaN come out as there.  For the results that are kept it costs one v_maximum3_f32
+// for two values of the columns and of dS: forward launches 1 us of 127, backward ones 13 of 701 (3056 rows x 12 011 keys x 6/2 heads x 128).
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 #include "hexi_shapes.h"
 #include "hexi_f32_common.h"
+#include "hexi_f32_units.h"
 
 namespace {
 
@@ -88,6 +91,56 @@ __device__ __forceinline__ Split3 split8(float x0, float x1, float x2, float x3,
 }
 __device__ __forceinline__ Split3 split8(const f32x4& a, const f32x4& b) { return split8(a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]); }
 
+// max(m, |a|, |b|), NaN if one of them is
+__device__ __forceinline__ float largest(float m, float a, float b) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), m); }
+// over the lanes of the wavefront
+__device__ __forceinline__ float largest_of_wave(float x)
+{
+#pragma unroll
+    for (int i = 32; i > 0; i /= 2) x = __builtin_elementwise_maximum(x, __shfl_xor(x, i, 64));
+    return x;
+}
+
+// The largest of the wavefronts' values, which they have put into a row of `top`.
+template <int NW> __device__ __forceinline__ float largest_of_workgroup(const float (&top)[NW])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m = __builtin_elementwise_maximum(m, top[w]);
+    return m;
+}
+
+// What a unit's results depend on besides the products themselves.  Stationary values are to be zero or within [2^-100, 2^60): their cuts lose
+// nothing, and what the cuts of streamed values lose moves a score (in units of log2, scale below 2^20) by 2^-127 2^60 2^21 at most.  Then a sum of n products p v is off by
+// n 2^-134 (max p + max v) besides its roundings, and p itself, a dS, by 2^-127 max s with s the stationary values of dP: nothing that 24 bits of
+// the result show if it is zero or not below 2^24 times that.
+constexpr float SMALLEST = 7.88860905e-31f;                            // 2^-100
+constexpr float CUT_LOSS = 7.70371978e-34f, SCORE_LOSS = 9.86076132e-32f;      // 2^24 2^-134, 2^24 2^-127
+__device__ __forceinline__ unsigned too_small(float largest_value) { return (unsigned)(largest_value > 0.f) & (unsigned)(largest_value < SMALLEST); }
+__device__ __forceinline__ unsigned too_small_or_not_finite(float x, float least)
+{
+    const float m = __builtin_fabsf(x);
+    return (unsigned)!(m < INFINITY) | ((unsigned)(m > 0.f) & (unsigned)!(m >= least));
+}
+// Whether any thread of the workgroup finds its values so; votes: a word of LDS for each wavefront.
+template <int NW> __device__ __forceinline__ bool any_of_workgroup(unsigned x, unsigned* votes, int tid)
+{
+    const unsigned any = __any(x != 0u);
+    if ((tid & 63) == 0) votes[tid >> 6] = any;
+    __syncthreads();
+    unsigned sum = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sum |= votes[w];
+    return sum != 0u;
+}
+
+// The thread's number once more, by a name that the compiler cannot see through: what the end of a unit computes from it is not kept over the loop.
+__device__ __forceinline__ int fresh(int tid)
+{
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 // Operands of a stationary tensor in LDS: step ks, row block n, piece p at ((NB ks + n) 3 + p) KB, a lane's 16 bytes at 16 lane.
 template <class C> __device__ __forceinline__ void put_stationary(unsigned char* lds, const float* src, long long stride_tok, int row0, int total, int wave, int lane)
 {
@@ -101,6 +154,24 @@ template <class C> __device__ __forceinline__ void put_stationary(unsigned char*
         *reinterpret_cast<bf16x8*>(d + 1024) = s.m;
         *reinterpret_cast<bf16x8*>(d + 2048) = s.l;
     }
+}
+
+// The upper pieces that put_stationary() left there: sets `odd` where a value is out of range, and returns a bound of the thread's share of them.
+template <class C> __device__ __forceinline__ float stationary_range(const unsigned char* lds, int wave, int lane, unsigned& odd)
+{
+    unsigned low = 0xffffu, high = 0u;                    // smallest nonzero one (less one), largest: upper 16 bits, without sign
+#pragma unroll
+    for (int i = 0; i < C::NK * C::NB / C::NW; ++i) {
+        const u32x4 h = *reinterpret_cast<const u32x4*>(lds + (wave + C::NW * i) * 3072 + 16 * lane);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const unsigned u = (e & 1 ? h[e / 2] >> 16 : h[e / 2]) & 0x7fffu;
+            low = min(low, (u - 1u) & 0xffffu);
+            high = max(high, u);
+        }
+    }
+    odd |= low < 0x0d80u - 1u || high >= 0x5d80u;         // 2^-100, 2^60
+    return __uint_as_float((high + 1u) << 16);
 }
 
 // A block of 32 streamed rows on its way to the scores: transfers into the wavefront's own piece of LDS, the 16-byte pieces of a row permuted by
@@ -176,7 +247,12 @@ template <class C> struct ColBlock {
                 }
         }
     }
-    __device__ __forceinline__ Split3 split(int u, int j) const { return split8(x[u][0][j], x[u][1][j], x[u][2][j], x[u][3][j], x[u][4][j], x[u][5][j], x[u][6][j], x[u][7][j]); }
+    __device__ __forceinline__ Split3 split(int u, int j, float& top) const      // top: their largest magnitude so far
+    {
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) top = largest(top, x[u][e][j], x[u][e + 1][j]);
+        return split8(x[u][0][j], x[u][1][j], x[u][2][j], x[u][3][j], x[u][4][j], x[u][5][j], x[u][6][j], x[u][7][j]);
+    }
 };
 
 __device__ __forceinline__ float probability(float s, const Log2Scale& c, float nl_hi, float nl_lo) { return fast_exp2(fmaf(s, c.hi, nl_hi) + fmaf(s, c.lo, nl_lo)); }
@@ -242,17 +318,14 @@ template <class C, class F> __device__ __forceinline__ void scores(f32x16 (&s)[C
         __builtin_amdgcn_sched_barrier(0);
         t = next;
     }
-    // an infinite operand has no rest, nor has a product that overflows: NaN and infinity become finite there, and the sum of the upper pieces decides
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[n][r] += __builtin_amdgcn_fmed3f(lo[n][r], -3.4e38f, 3.4e38f);
+    for (int n = 0; n < NB; ++n) s[n] += lo[n];
 }
 
 // acc[n][j], register 4 b + t: column NJ (8 b + 4 hh + t) + j of stationary row 32 n + l; p[n]: probabilities or dS as scores() leaves its results.
 // APART: the block's sum by itself, then added, for the long chains of dK / dV: one rounding of the running value in 32 rows instead of 12 (the backward
 // 4 % slower; dv of 3643 rows of 4 heads 1.1 times as far from fp64 as with hexi_f32.hip without it, 0.43 times with it).
-template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB])
+template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB], float& top)
 {
     constexpr int NB = C::NB;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -264,14 +337,14 @@ template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16
     };
     split_p(0);
     if (APART) split_p(1);
-    Split3 t = v.split(0, 0);
+    Split3 t = v.split(0, 0, top);
     f32x16 sum[NB];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int st = 0; st < 2 * C::NJ; ++st) {
         const int u = APART ? st % 2 : st / C::NJ, j = APART ? st / 2 : st % C::NJ, st1 = st + 1;
         Split3 next = t;
-        if (st1 < 2 * C::NJ) next = v.split(APART ? st1 % 2 : st1 / C::NJ, APART ? st1 / 2 : st1 % C::NJ);
+        if (st1 < 2 * C::NJ) next = v.split(APART ? st1 % 2 : st1 / C::NJ, APART ? st1 / 2 : st1 % C::NJ, top);
         f32x16* to[NB];
 #pragma unroll
         for (int n = 0; n < NB; ++n) to[n] = APART ? &sum[n] : &acc[n][j];
@@ -325,12 +398,12 @@ template <class C> __device__ __forceinline__ void stage_rows(float* stage, cons
 
 template <class C> union X3FwdSmem {
     struct { unsigned char q[C::PIECES], rows[C::NW][C::BLOCK_BYTES]; } t;
-    struct { float stage[C::STAGE_FLOATS], m[C::NW * C::ROWS], l[C::NW * C::ROWS], w[C::NW * C::ROWS], wa[C::ROWS]; } e;
+    struct { float stage[C::STAGE_FLOATS], m[C::NW * C::ROWS], l[C::NW * C::ROWS], w[C::NW * C::ROWS], wa[C::ROWS], top[C::NW]; unsigned votes[C::NW]; } e;
 };
 
 // One thread per row of a workgroup whose streamed rows were split S ways: the weights of the splits (references, in units of log2, at
-// ref_of[split * ROWS + row], sums at l_of) and of the running o, and the row's new LSE.
-template <int ROWS, int S> __device__ __forceinline__ void combine_rows(const FwdArgs& a, int h, int row0, int tid, const float* ref_of, const float* l_of, float* w_of, float* wa_of)
+// ref_of[split * ROWS + row], sums at l_of) and of the running o; returns the row's new LSE.
+template <int ROWS, int S> __device__ __forceinline__ float combine_rows(const FwdArgs& a, int h, int row0, int tid, const float* ref_of, const float* l_of, float* w_of, float* wa_of)
 {
     float m = -INFINITY, l = 0.f, e[S];
 #pragma unroll
@@ -350,9 +423,8 @@ template <int ROWS, int S> __device__ __forceinline__ void combine_rows(const Fw
     float wb = l > 0.f ? 1.0f / l : 0.f, wa = 0.f, lse_new = lse_part;
     const int row = row0 + tid;
     if (row < a.g.lq) {
-        float* lp = a.lse + (long long)h * a.g.lq + row;
         if (a.accumulate) {
-            const float la_old = *lp;
+            const float la_old = a.lse[(long long)h * a.g.lq + row];
             const float mm = fmaxf(la_old, lse_part);
             if (mm == -INFINITY) { wb = 0.f; lse_new = -INFINITY; }
             else {
@@ -362,40 +434,26 @@ template <int ROWS, int S> __device__ __forceinline__ void combine_rows(const Fw
                 lse_new = mm + logf(ea + eb);
             }
         }
-        *lp = lse_new;
     }
 #pragma unroll
     for (int s = 0; s < S; ++s) w_of[s * ROWS + tid] = e[s] * wb;
     wa_of[tid] = wa;
+    return lse_new;
 }
 
-// An output that came out as NaN although its weights are good: an infinite value of V has NaN for the rests of its cut.  What positive weights make of the
-// n values that the row sees in this column of V.
-__device__ __noinline__ float sum_with_infinities(const float* v, const long long stride, const int n)
-{
-    bool up = false, down = false, nan = false;
-    for (int j = 0; j < n; ++j) {
-        const float x = v[j * stride];
-        up |= x == INFINITY;
-        down |= x == -INFINITY;
-        nan |= x != x;
-    }
-    return nan || up == down ? NAN : up ? INFINITY : -INFINITY;
-}
-
-template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs& a, const int h, const int row0, X3FwdSmem<X3Cfg<D, NB>>& sm)
+// False, with nothing written, where the results are left to the units on the fp32 instruction.
+template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs& a, const int h, const int row0, X3FwdSmem<X3Cfg<D, NB>>& sm)
 {
     using C = X3Cfg<D, NB>;
     constexpr int NW = C::NW, ROWS = C::ROWS;
     const AttnGeom& g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hh = lane >> 5, l32 = lane & 31;
     const int kvh = g.kv_of_q[h];
     const int last_row = (row0 + ROWS < g.lq ? row0 + ROWS : g.lq) - 1;
     const int n_vis = seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row));      // visible columns form the prefix [0, n_vis)
     const int n_full = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0));         // columns that every row sees
-    if (n_vis == 0 && a.accumulate) return;                                   // merging an empty partial is the identity
+    if (n_vis == 0 && a.accumulate) return true;                              // merging an empty partial is the identity
     const int n_blocks = (n_vis + C::BLK - 1) / C::BLK;
     int vis[NB];                                                              // columns that rows 32 n + l see
 #pragma unroll
@@ -409,13 +467,14 @@ template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs&
     const RowBlock<C> rows(slot, lane, g.kv_stride_tok);
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
+    const Log2Scale c(g.scale);
+    float top = 0.f;
     put_stationary<C>(sm.t.q, static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
     const unsigned char* stat = sm.t.q + 16 * lane;
 
     f32x16 acc[NB][C::NJ];
     zero_acc<C>(acc);
-    const Log2Scale c(g.scale);
     const float slack = 8.0f / c.hi;
     // a row's reference, in units of log2, is raised when a score exceeds it by more than 8 of them
     float ref[NB], limit[NB], l_run[NB];
@@ -462,12 +521,18 @@ template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs&
             }
             l_run[n] += (part[0] + part[1]) + (part[2] + part[3]);
         }
-        accumulate<C, false>(acc, vc, s);
+        accumulate<C, false>(acc, vc, s, top);
     }
 
     // Combine the splits and merge with the running (o, lse): weights per (row, split), then a row-contiguous pass.
+    unsigned odd = g.scale >= 1048576.f;
+    stationary_range<C>(sm.t.q, wave, lane, odd);
 #pragma unroll
-    for (int n = 0; n < NB; ++n) l_run[n] = sum_across_halves(l_run[n]);
+    for (int n = 0; n < NB; ++n) {
+        l_run[n] = sum_across_halves(l_run[n]);
+        odd |= (unsigned)!(l_run[n] < INFINITY);
+    }
+    top = largest_of_wave(top);
     __syncthreads();              // the operands are free
     stage_rows<C>(&sm.e.stage[wave * ROWS * C::PITCH], acc, lane, 1.0f);
     if (hh == 0) {
@@ -477,71 +542,81 @@ template <int D, int NB> __device__ __forceinline__ void fwd_unit(const FwdArgs&
             sm.e.l[wave * ROWS + 32 * n + l32] = l_run[n];
         }
     }
+    const int tid = fresh(threadIdx.x);
+    if (lane == 0) sm.e.top[wave] = top;
     __syncthreads();
-    if (tid < ROWS) combine_rows<ROWS, NW>(a, h, row0, tid, sm.e.m, sm.e.l, sm.e.w, sm.e.wa);
+    float lse_new = 0.f;
+    if (tid < ROWS) lse_new = combine_rows<ROWS, NW>(a, h, row0, tid, sm.e.m, sm.e.l, sm.e.w, sm.e.wa);
     __syncthreads();
-    for (int i = tid; i < ROWS * D / 4; i += 64 * NW) {
-        const int r = i / (D / 4), c = 4 * (i % (D / 4));
-        if (row0 + r >= g.lq) continue;
+    top = largest_of_workgroup(sm.e.top);
+    odd |= too_small(top);
+    const float least = CUT_LOSS * (float)n_vis * (256.f + top);      // (the probabilities' largest is 2^8)
+    constexpr int PARTS = ROWS * D / 4 / (64 * NW);
+    f32x4 out[PARTS];
+#pragma unroll
+    for (int u = 0; u < PARTS; ++u) {
+        const int i = tid + 64 * NW * u, r = i / (D / 4), c = 4 * (i % (D / 4));
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
-        float w_sum = 0.f;
 #pragma unroll
-        for (int s = 0; s < NW; ++s) {
-            const float ws = sm.e.w[s * ROWS + r];
-            x += ws * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
-            w_sum += ws;
-        }
-        if (__builtin_expect(w_sum > 0.f && (x[0] != x[0] || x[1] != x[1] || x[2] != x[2] || x[3] != x[3]), 0)) {
-            const int seen = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0 + r));
+        for (int s = 0; s < NW; ++s) x += sm.e.w[s * ROWS + r] * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (x[e] != x[e]) x[e] = sum_with_infinities(v + c + e, g.kv_stride_tok, seen);
-        }
-        f32x4* op = reinterpret_cast<f32x4*>(a.o + ((long long)(row0 + r) * g.nq + h) * D + c);
-        if (a.accumulate) x += sm.e.wa[r] * *op;
-        *op = x;
+        for (int e = 0; e < 4; ++e) odd |= (unsigned)(row0 + r < g.lq) & too_small_or_not_finite(x[e], least);
+        out[u] = x;
+        __builtin_amdgcn_sched_barrier(0);
     }
+    if (any_of_workgroup<NW>(odd, sm.e.votes, tid)) return false;
+    if (tid < ROWS && row0 + tid < g.lq) a.lse[(long long)h * g.lq + row0 + tid] = lse_new;
+#pragma unroll
+    for (int u = 0; u < PARTS; ++u) {
+        const int i = tid + 64 * NW * u, r = i / (D / 4), c = 4 * (i % (D / 4));
+        if (row0 + r >= g.lq) continue;
+        f32x4* op = reinterpret_cast<f32x4*>(a.o + ((long long)(row0 + r) * g.nq + h) * D + c);
+        if (a.accumulate) out[u] += sm.e.wa[r] * *op;
+        *op = out[u];
+    }
+    return true;
 }
+
+// The units on the fp32 instruction as 256 threads run them, 16 rows one after another; four chains for a score, as the other pass may have been cut
+template <int D> using Rows16 = rows16::F32Cfg<D, true, false, 4, 4, true>;
 
 // Which rows a launch takes in units of 64 and of 32 rows: the last `n64` 64-row tiles (heads side by side, the longest first), the tiles before
 // them as two 32-row units each.
 template <int D>
 __global__ void __launch_bounds__(256, 1) fwd_f32x3_kernel(const FwdArgs a, const unsigned n64, const int n_tiles)
 {
-    __shared__ __attribute__((aligned(1024))) union { X3FwdSmem<X3Cfg<D, 2>> two; X3FwdSmem<X3Cfg<D, 1>> one; } sm;
-    const unsigned nq = a.g.nq;
-    if (blockIdx.x < n64) {
-        const int tile = n_tiles - 1 - (int)(blockIdx.x / nq);
-        fwd_unit<D, 2>(a, blockIdx.x % nq, 64 * tile, sm.two);
-    } else {
-        const unsigned u = blockIdx.x - n64, t = n64 + u / 2;
-        const int row0 = 64 * (n_tiles - 1 - (int)(t / nq)) + 32 * (1 - (int)(u & 1));
-        if (row0 < a.g.lq) fwd_unit<D, 1>(a, t % nq, row0, sm.one);
+    __shared__ __attribute__((aligned(1024))) union { X3FwdSmem<X3Cfg<D, 2>> two; X3FwdSmem<X3Cfg<D, 1>> one; rows16::FwdSmem<Rows16<D>> rows; } sm;
+    const unsigned nq = a.g.nq, u = blockIdx.x - n64, t = blockIdx.x < n64 ? blockIdx.x : n64 + u / 2;
+    const int h = (int)(t % nq), tile0 = 64 * (n_tiles - 1 - (int)(t / nq)), row0 = blockIdx.x < n64 ? tile0 : tile0 + 32 * (1 - (int)(u & 1));
+    if (row0 >= a.g.lq || (blockIdx.x < n64 ? fwd_unit<D, 2>(a, h, row0, sm.two) : fwd_unit<D, 1>(a, h, row0, sm.one))) return;
+    const int end = row0 + (blockIdx.x < n64 ? 64 : 32);
+    for (int row = row0; row < end && row < a.g.lq; row += 16) {
+        __syncthreads();
+        rows16::fwd_unit<Rows16<D>>(a, h, row / 16, sm.rows);
     }
 }
 
 template <class C> union X3BwdTiles {
     struct { unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES]; };
-    float stage[C::STAGE_FLOATS];
+    struct { float stage[C::STAGE_FLOATS], top[4][C::NW]; unsigned votes[C::NW]; };
 };
 // and the row scalars of each wavefront's block (dK / dV): -LSE log2(e) in two floats, Delta
 template <class C> struct X3BwdSmem { X3BwdTiles<C> u; };
 template <class C> struct X3KvSmem { X3BwdTiles<C> u; float scalars[C::NW][3][32]; };
 
 // dQ: S^T = K Q^T and dP^T = V dO^T per block, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
-template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& a, const int h, const int row0, X3BwdSmem<X3Cfg<D, NB>>& sm)
+template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& a, const int h, const int row0, X3BwdSmem<X3Cfg<D, NB>>& sm)
 {
     using C = X3Cfg<D, NB>;
     constexpr int NW = C::NW, ROWS = C::ROWS;
     const AttnGeom& g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hh = lane >> 5, l32 = lane & 31;
     const int kvh = g.kv_of_q[h];
     const int last_row = (row0 + ROWS < g.lq ? row0 + ROWS : g.lq) - 1;
     const int n_vis = seg_rows_le(g.ks, seg_pos_of_row(g.qs, last_row));
     const int n_full = seg_rows_le(g.ks, seg_pos_of_row(g.qs, row0));
-    if (n_vis == 0) return;                               // dq_acc unchanged
+    if (n_vis == 0) return true;                          // dq_acc unchanged
     const int n_blocks = (n_vis + C::BLK - 1) / C::BLK;
     const Log2Scale c(g.scale);
     int vis[NB];
@@ -560,6 +635,7 @@ template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& 
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
     const long long q_off = (long long)h * g.q_stride_head;
+    float ds_top = 0.f, top = 0.f;
     put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
@@ -593,34 +669,59 @@ template <int D, int NB> __device__ __forceinline__ void dq_unit(const BwdArgs& 
                 for (int r = 0; r < 16; ++r)
                     if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = 0.f;
         }
-        accumulate<C, false>(acc, kc, s);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, s[n][r], s[n][r + 1]);
+        accumulate<C, false>(acc, kc, s, top);
     }
+    unsigned odd = g.scale >= 1048576.f;
+    stationary_range<C>(sm.u.t[0], wave, lane, odd);
+    float g_top = largest_of_wave(stationary_range<C>(sm.u.t[1], wave, lane, odd));
+    top = largest_of_wave(top);
+    ds_top = largest_of_wave(ds_top);
     __syncthreads();
     stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
+    const int tid = fresh(threadIdx.x);
+    if (lane == 0) { sm.u.top[0][wave] = top; sm.u.top[1][wave] = g_top; sm.u.top[2][wave] = ds_top; }
     __syncthreads();
-    // Added with atomics, consecutive lanes on consecutive floats: chunks of one shard may be in flight on several streams.
-    // One addition per element and call, so calls in stream order still have a fixed order.
-    for (int i = tid; i < ROWS * D; i += 64 * NW) {
-        const int r = i / D, c = i % D;
-        if (row0 + r >= g.lq) continue;
-        float x = sm.u.stage[r * C::PITCH + c];
+    top = largest_of_workgroup(sm.u.top[0]);
+    g_top = largest_of_workgroup(sm.u.top[1]);
+    ds_top = largest_of_workgroup(sm.u.top[2]);
+    odd |= too_small(ds_top) | too_small(top);
+    const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top + top) + SCORE_LOSS * g_top * top);
+    constexpr int PARTS = ROWS * D / (64 * NW);
+    float out[PARTS];             // consecutive lanes on consecutive floats
 #pragma unroll
-        for (int s = 1; s < NW; ++s) x += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
-        global_atomic_add(a.dq + ((long long)(row0 + r) * g.nq + h) * D + c, x);
+    for (int u = 0; u < PARTS; ++u) {
+        const int i = tid + 64 * NW * u, r = i / D, c = i % D;
+        out[u] = sm.u.stage[r * C::PITCH + c];
+#pragma unroll
+        for (int s = 1; s < NW; ++s) out[u] += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
+        odd |= (unsigned)(row0 + r < g.lq) & too_small_or_not_finite(out[u], least);
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
+    if (any_of_workgroup<NW>(odd, sm.u.votes, tid)) return false;
+    // Added with atomics: chunks of one shard may be in flight on several streams.
+    // One addition per element and call, so calls in stream order still have a fixed order.
+#pragma unroll
+    for (int u = 0; u < PARTS; ++u) {
+        const int i = tid + 64 * NW * u, r = i / D, c = i % D;
+        if (row0 + r < g.lq) global_atomic_add(a.dq + ((long long)(row0 + r) * g.nq + h) * D + c, out[u]);
+    }
+    return true;
 }
 
 // dK / dV: the stationary rows are keys, the streamed rows q rows of every q head that reads the kv head, one head after the other:
 // S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.  With two runs a unit takes the first or the second half of those heads and adds its result
 // to zeros: 0 + a + b = 0 + b + a, so the order of the two does not show.
-template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, const int run, const int runs,
+template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, const int h_first, const int h_end, const bool atomic,
                                                                         X3KvSmem<X3Cfg<D, NB>>& sm)
 {
     using C = X3Cfg<D, NB>;
     constexpr int NW = C::NW, ROWS = C::ROWS, BLK = C::BLK;
     const AttnGeom& g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hh = lane >> 5, l32 = lane & 31;
     const int col0 = kv_tile * ROWS;
     const int last_col = (col0 + ROWS < g.lc ? col0 + ROWS : g.lc) - 1;
@@ -635,21 +736,18 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
     }
     const int block0 = row_first / BLK, n_blocks = (g.lq + BLK - 1) / BLK, per_head = row_first < g.lq ? n_blocks - block0 : 0;
     const Log2Scale c(g.scale);
-    auto next_head = [&](int h) { for (++h; h < g.nq && g.kv_of_q[h] != kvh; ++h) {} return h; };
+    auto next_head = [&](int h) { for (++h; h < h_end && g.kv_of_q[h] != kvh; ++h) {} return h; };
 
-    // the heads of this run: `left` of them from h on
-    int h = next_head(-1), left = 0;
-    for (int i = h; i < g.nq; i = next_head(i)) ++left;
-    if (runs == 2) {
-        const int half = (left + 1) / 2;
-        for (int i = 0; i < (run ? half : 0); ++i) h = next_head(h);
-        left = run ? left - half : half;
-        if (left == 0 || per_head == 0) return;           // (the zeros are there)
-    }
+    int h = next_head(h_first - 1), left = 0;             // `left` heads from h on
+    for (int i = h; i < h_end; i = next_head(i)) ++left;
+    if (atomic && (left == 0 || per_head == 0)) return true;      // (the zeros are there)
+    const float n_rows = (float)left * (float)(g.lq - row_first);
 
     f32x16 dk[NB][C::NJ], dv[NB][C::NJ];
     zero_acc<C>(dk);
     zero_acc<C>(dv);
+    float ds_top = 0.f, q_top = 0.f, g_top = 0.f, v_top = 0.f;
+    unsigned odd = g.scale >= 1048576.f;
     if (per_head > 0) {
         // this wavefront's next block: number b of head h; the blocks of all heads in one sequence are dealt to the wavefronts in turn
         int b = block0 + wave;
@@ -720,38 +818,70 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
 #pragma unroll
                     for (int t = 0; t < 4; ++t) ds[n][4 * q + t] = p[n][4 * q + t] * (ds[n][4 * q + t] - dl[t]);
             }
-            accumulate<C, true>(dv, gc, p);
-            accumulate<C, true>(dk, qc, ds);
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, ds[n][r], ds[n][r + 1]);
+            accumulate<C, true>(dv, gc, p, g_top);
+            accumulate<C, true>(dk, qc, ds, q_top);
         }
+        stationary_range<C>(sm.u.t[0], wave, lane, odd);
+        v_top = largest_of_wave(stationary_range<C>(sm.u.t[1], wave, lane, odd));
     }
-    auto write_out = [&](float* out, const f32x16 (&acc)[NB][C::NJ], float w) {
+    q_top = largest_of_wave(q_top);
+    g_top = largest_of_wave(g_top);
+    ds_top = largest_of_wave(ds_top);
+    // consecutive lanes on consecutive floats where they are added with atomics, on consecutive 16 bytes where they are stored
+    constexpr int PARTS = ROWS * D / (64 * NW);
+    const int tid = fresh(threadIdx.x);
+    auto float_of = [&](int u) { return atomic ? tid + 64 * NW * u : 4 * tid + 256 * NW * (u / 4) + u % 4; };
+    auto gather = [&](float (&out)[PARTS], const f32x16 (&acc)[NB][C::NJ], float w) {
         __syncthreads();
         stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, w);
+        if (lane == 0) { sm.u.top[0][wave] = q_top; sm.u.top[1][wave] = g_top; sm.u.top[2][wave] = v_top; sm.u.top[3][wave] = ds_top; }
         __syncthreads();
-        if (runs == 2) {           // consecutive lanes on consecutive floats
-            for (int i = tid; i < ROWS * D; i += 64 * NW) {
-                const int r = i / D, c = i % D;
-                if (col0 + r >= g.lc) continue;
-                float x = sm.u.stage[r * C::PITCH + c];
 #pragma unroll
-                for (int s = 1; s < NW; ++s) x += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
-                global_atomic_add(out + ((long long)(col0 + r) * g.nkv + kvh) * D + c, x);
-            }
-            return;
-        }
-        for (int i = tid; i < ROWS * D / 4; i += 64 * NW) {
-            const int r = i / (D / 4), c = 4 * (i % (D / 4));
-            if (col0 + r >= g.lc) continue;
-            f32x4 x = *reinterpret_cast<const f32x4*>(&sm.u.stage[r * C::PITCH + c]);
+        for (int u = 0; u < PARTS; ++u) {
+            const int i = float_of(u), at = i / D * C::PITCH + i % D;
+            out[u] = sm.u.stage[at];
 #pragma unroll
-            for (int s = 1; s < NW; ++s) x += *reinterpret_cast<const f32x4*>(&sm.u.stage[(s * ROWS + r) * C::PITCH + c]);
-            f32x4* op = reinterpret_cast<f32x4*>(out + ((long long)(col0 + r) * g.nkv + kvh) * D + c);
-            if (a.accumulate) x += *op;
-            *op = x;
+            for (int s = 1; s < NW; ++s) out[u] += sm.u.stage[s * ROWS * C::PITCH + at];
+            if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    write_out(a.dv, dv, 1.0f);
-    write_out(a.dk, dk, g.scale);
+    float out_v[PARTS], out_k[PARTS];
+    gather(out_v, dv, 1.0f);
+    gather(out_k, dk, g.scale);
+    const float q_all = largest_of_workgroup(sm.u.top[0]), g_all = largest_of_workgroup(sm.u.top[1]), v_all = largest_of_workgroup(sm.u.top[2]),
+                ds_all = largest_of_workgroup(sm.u.top[3]);
+    odd |= too_small(ds_all) | too_small(q_all) | too_small(g_all);
+    const float least_v = n_rows * CUT_LOSS * (2.f + g_all), least_k = g.scale * n_rows * (CUT_LOSS * (ds_all + q_all) + SCORE_LOSS * v_all * q_all);
+#pragma unroll
+    for (int u = 0; u < PARTS; ++u)
+        odd |= (unsigned)(col0 + float_of(u) / D < g.lc) & (too_small_or_not_finite(out_v[u], least_v) | too_small_or_not_finite(out_k[u], least_k));
+    if (any_of_workgroup<NW>(odd, sm.u.votes, tid)) return false;
+    auto write_out = [&](float* to, const float (&out)[PARTS]) {
+#pragma unroll
+        for (int u = 0; u < PARTS; u += 4) {
+            if (atomic) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = float_of(u + e), r = i / D;
+                    if (col0 + r < g.lc) global_atomic_add(to + ((long long)(col0 + r) * g.nkv + kvh) * D + i % D, out[u + e]);
+                }
+            } else {
+                const int i = float_of(u), r = i / D;
+                if (col0 + r >= g.lc) continue;
+                f32x4 x = {out[u], out[u + 1], out[u + 2], out[u + 3]};
+                f32x4* op = reinterpret_cast<f32x4*>(to + ((long long)(col0 + r) * g.nkv + kvh) * D + i % D);
+                if (a.accumulate) x += *op;
+                *op = x;
+            }
+        }
+    };
+    write_out(a.dv, out_v);
+    write_out(a.dk, out_k);
+    return true;
 }
 
 // The backward step in one launch: workgroups [0, n_dkdv) are dK / dV units (the longer ones, first, and of two runs the
@@ -759,18 +889,34 @@ template <int D, int NB> __device__ __forceinline__ void dkdv_unit(const BwdArgs
 template <int D, int KB>
 __global__ void __launch_bounds__(256, 1) bwd_f32x3_kernel(const BwdArgs a, const unsigned n_dkdv, const unsigned runs, const unsigned n64, const int n_tiles)
 {
-    __shared__ __attribute__((aligned(1024))) union { X3KvSmem<X3Cfg<D, KB>> kv; X3BwdSmem<X3Cfg<D, 2>> two; X3BwdSmem<X3Cfg<D, 1>> one; } sm;
+    __shared__ __attribute__((aligned(1024))) union { X3KvSmem<X3Cfg<D, KB>> kv; X3BwdSmem<X3Cfg<D, 2>> two; X3BwdSmem<X3Cfg<D, 1>> one;
+                                                      rows16::DkdvSmem<Rows16<D>> kv_rows; rows16::DqSmem<Rows16<D>> q_rows; } sm;
     const unsigned nq = a.g.nq;
     if (blockIdx.x < n_dkdv) {
         const unsigned per_run = n_dkdv / runs, run = blockIdx.x / per_run, u = blockIdx.x - run * per_run, tile = u / (unsigned)a.g.nkv;
-        dkdv_unit<D, KB>(a, (int)(u - tile * a.g.nkv), (int)tile, (int)run, (int)runs, sm.kv);
-    } else if (blockIdx.x < n_dkdv + n64) {
-        const unsigned u = blockIdx.x - n_dkdv;
-        dq_unit<D, 2>(a, u % nq, 64 * (n_tiles - 1 - (int)(u / nq)), sm.two);
+        const int kvh = (int)(u - tile * a.g.nkv), key0 = 32 * KB * (int)tile;
+        const bool atomic = runs == 2;
+        int first = 0, end = a.g.nq;
+        if (atomic) {             // the first half of the heads that read kvh, or the rest
+            int n = 0, half = 0;
+            for (int h = 0; h < end; ++h) n += a.g.kv_of_q[h] == kvh;
+            for (n = (n + 1) / 2; n > 0; ++half) n -= a.g.kv_of_q[half] == kvh;
+            (run ? first : end) = half;
+        }
+        if (dkdv_unit<D, KB>(a, kvh, (int)tile, first, end, atomic, sm.kv)) return;
+        for (int key = key0; key < key0 + 32 * KB && key < a.g.lc; key += 16) {
+            __syncthreads();
+            rows16::dkdv_unit<Rows16<D>>(a, kvh, key / 16, sm.kv_rows, first, end, atomic);
+        }
     } else {
-        const unsigned u = blockIdx.x - n_dkdv - n64, t = n64 + u / 2;
-        const int row0 = 64 * (n_tiles - 1 - (int)(t / nq)) + 32 * (1 - (int)(u & 1));
-        if (row0 < a.g.lq) dq_unit<D, 1>(a, t % nq, row0, sm.one);
+        const unsigned w = blockIdx.x - n_dkdv, u = w - n64, t = w < n64 ? w : n64 + u / 2;
+        const int h = (int)(t % nq), tile0 = 64 * (n_tiles - 1 - (int)(t / nq)), row0 = w < n64 ? tile0 : tile0 + 32 * (1 - (int)(u & 1));
+        if (row0 >= a.g.lq || (w < n64 ? dq_unit<D, 2>(a, h, row0, sm.two) : dq_unit<D, 1>(a, h, row0, sm.one))) return;
+        const int end = row0 + (w < n64 ? 64 : 32);
+        for (int row = row0; row < end && row < a.g.lq; row += 16) {
+            __syncthreads();
+            rows16::dq_unit<Rows16<D>>(a, h, row / 16, sm.q_rows);
+        }
     }
 }
 

@@ -64,8 +64,9 @@ __device__ __forceinline__ float prob(float s, float c_hi, float c_lo, float nl_
     return fast_exp2(fmaf(s, c_hi, nl_hi) + fmaf(max2(s, -3.402823466e38f), c_lo, nl_lo));
 }
 
-template <int D_, bool SPLIT_, bool TWO_, int NW_ = SPLIT_ ? 8 : 4> struct F32Cfg {
-    static constexpr int D = D_;
+template <int D_, bool SPLIT_, bool TWO_, int NW_ = SPLIT_ ? 8 : 4, int CHAINS_ = D_ == 128 ? 4 : 1, bool CLEAR_ = false> struct F32Cfg {
+    static constexpr int D = D_, CHAINS = CHAINS_;           // chains of sums of a score: 1 or 4
+    static constexpr bool CLEAR = CLEAR_;                  // rows past the end are zeros (SPLIT): no 0 x inf of theirs where the last row is infinite
     static constexpr bool SPLIT = SPLIT_, TWO = TWO_;
     static_assert(D == 64 || D == 128, "head_dim 64 or 128");
     static constexpr bool PRIVATE = SPLIT;                 // the streamed rows of a wavefront are its own
@@ -131,6 +132,18 @@ template <class C> __device__ __forceinline__ void tile_landed()
     if (!C::PRIVATE) __syncthreads();
 }
 
+// Of the wavefront's own 16 rows of a tile, which start at row `row0` of `total`, those past the end become zeros.
+template <class C> __device__ __forceinline__ void clear_past_end(unsigned char* rows, int row0, int total, int lane)
+{
+    static_assert(C::SPLIT && C::NBLK == 1, "a wavefront's rows are its own");
+    if (row0 + 16 <= total) return;
+#pragma unroll
+    for (int i = 0; i < 16 * C::ROW_BYTES / 1024; ++i) {
+        const int off = 1024 * i + 16 * lane;
+        if (row0 + off / C::ROW_BYTES >= total) *reinterpret_cast<f32x4*>(rows + off) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
 // Row fragments of a stationary tensor: lane (g, l) holds columns 16 G + 4 g .. + 3 of its row in frag[G].
 template <int NG> __device__ __forceinline__ void load_rows(f32x4 (&frag)[NG], const float* p, int g)
 {
@@ -163,7 +176,7 @@ __device__ __forceinline__ f32x4 lds_f4(const unsigned char* p) { return *reinte
 // with one chain here 1.5, 1.5, 1.7, with four 0.79, 0.78, 0.81 (times: backward 123 / 125 us).
 template <class C, int NT> __device__ __forceinline__ void score_block(f32x4 (&out)[NT], const unsigned char* const (&tile)[NT], const LaneAddr<C>& la, const f32x4* const (&frag)[NT])
 {
-    constexpr int CH = C::D == 128 ? 4 : 1;
+    constexpr int CH = C::CHAINS;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     f32x4 x[2][NT], sum[CH][NT];
 #pragma unroll
@@ -285,6 +298,7 @@ template <class C> __device__ __forceinline__ void fwd_unit(const FwdArgs& a, co
         const int buf = t & 1;
         const unsigned char* kt = &sm.t.k[buf % C::NBUF][sp * NBLK * 16 * C::ROW_BYTES];
         const unsigned char* vt = &sm.t.v[buf % C::NBUF][sp * NBLK * 16 * C::ROW_BYTES];
+        if constexpr (C::CLEAR) clear_past_end<C>(&sm.t.v[buf % C::NBUF][16 * wave * C::ROW_BYTES], t * TK + 16 * wave, g.lc, lane);
         f32x4 s[NBLK];
         {
             const unsigned char* tiles[NBLK];
@@ -457,6 +471,7 @@ template <class C> __device__ __forceinline__ void dq_unit(const BwdArgs& a, con
         for (int b = 0; b < NBLK; ++b) {
             const unsigned char* kt = &sm.t.k[buf % C::NBUF][(sp * NBLK + b) * 16 * C::ROW_BYTES];
             const unsigned char* vt = &sm.t.v[buf % C::NBUF][(sp * NBLK + b) * 16 * C::ROW_BYTES];
+            if constexpr (C::CLEAR) clear_past_end<C>(&sm.t.k[buf % C::NBUF][16 * wave * C::ROW_BYTES], t * TK + 16 * wave, g.lc, lane);
             f32x4 sd[2];       // S^T and dP^T of the block: register r is key 4 grp + r
             const unsigned char* const tiles[2] = {kt, vt};
             const f32x4* const frags[2] = {qf, gf};
@@ -495,7 +510,8 @@ template <class C> __device__ __forceinline__ void dq_unit(const BwdArgs& a, con
 }
 
 // dK / dV: the stationary rows are keys, the streamed rows q rows (of every q head that reads the kv head, one head
-// after the other): S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.
+// after the other): S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.  Of those q heads the ones in [h_first, h_end); `atomic`: the result is
+// added to dk and dv with atomics.
 template <class C> struct DkdvSmem {
     union {
         struct { unsigned char q[C::NBUF][C::TILE_BYTES], g[C::NBUF][C::TILE_BYTES]; } t;
@@ -505,7 +521,7 @@ template <class C> struct DkdvSmem {
     __attribute__((aligned(16))) int qpos[2][C::TK];
 };
 
-template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, DkdvSmem<C>& sm)
+template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, const int kvh, const int kv_tile, DkdvSmem<C>& sm, const int h_first, const int h_end, const bool atomic)
 {
     constexpr int D = C::D, NW = C::NW, S = C::S, TM = C::TK, NBLK = C::NBLK;
     constexpr bool SPLIT = C::SPLIT, TWO = C::TWO;
@@ -537,8 +553,8 @@ template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, c
     const LaneAddr<C> la(grp, l16);
     const TileFetch<C> fetch(wave, lane, g.q_stride_tok);
     const uint32_t lds_q = (uint32_t)(uintptr_t)(&sm.t.q[0][0]), lds_g = (uint32_t)(uintptr_t)(&sm.t.g[0][0]);
-    auto next_head = [&](int h) { for (++h; h < g.nq && g.kv_of_q[h] != kvh; ++h) {} return h; };
-    int fetch_h = next_head(-1), fetch_t = tile0;
+    auto next_head = [&](int h) { for (++h; h < h_end && g.kv_of_q[h] != kvh; ++h) {} return h; };
+    int fetch_h = next_head(h_first - 1), fetch_t = tile0;
     const int pos_slot = C::PRIVATE ? (lane < 16 ? 16 * wave + lane : TM) : tid;
     auto fetch_tile = [&](int buf) {
         const long long off = (long long)fetch_h * g.q_stride_head;
@@ -560,10 +576,10 @@ template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, c
     for (int i = 0; i < 4 * C::NH; ++i) { dk[i] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[i] = dk[i]; }
     if (per_head > 0) {
         int buf = 0, t = tile0;
-        if (fetch_h < g.nq) fetch_tile(0);
-        for (int h = next_head(-1); h < g.nq;) {
+        if (fetch_h < h_end) fetch_tile(0);
+        for (int h = next_head(h_first - 1); h < h_end;) {
             tile_landed<C>();
-            if (C::NBUF == 2 && fetch_h < g.nq) fetch_tile(buf ^ 1);
+            if (C::NBUF == 2 && fetch_h < h_end) fetch_tile(buf ^ 1);
             // (the last tile may hold padding rows, whose position is -1)
             const bool masked = t * TM < row_full || key_ragged || t == n_qtiles - 1;
 #pragma unroll
@@ -572,6 +588,10 @@ template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, c
                 if (SPLIT && (t * TM + 16 * blk >= g.lq || t * TM + 16 * blk + 16 <= row_first)) continue;      // rows that see nothing
                 const unsigned char* qt = &sm.t.q[buf % C::NBUF][blk * 16 * C::ROW_BYTES];
                 const unsigned char* gt = &sm.t.g[buf % C::NBUF][blk * 16 * C::ROW_BYTES];
+                if constexpr (C::CLEAR) {
+                    clear_past_end<C>(&sm.t.q[buf % C::NBUF][16 * wave * C::ROW_BYTES], t * TM + 16 * wave, g.lq, lane);
+                    clear_past_end<C>(&sm.t.g[buf % C::NBUF][16 * wave * C::ROW_BYTES], t * TM + 16 * wave, g.lq, lane);
+                }
                 f32x4 sd[2];       // S and dP of the block: register r is row 4 grp + r
                 const unsigned char* const tiles[2] = {qt, gt};
                 const f32x4* const frags[2] = {kf, vf};
@@ -603,7 +623,7 @@ template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, c
                 const f32x4* const ps[2] = {&p, &ds};
                 cols.run(la, accs, ps);
             }
-            if (C::NBUF == 1 && fetch_h < g.nq) { if (TWO) reads_done(); fetch_tile(buf ^ 1); }
+            if (C::NBUF == 1 && fetch_h < h_end) { if (TWO) reads_done(); fetch_tile(buf ^ 1); }
             buf ^= 1;
             if (++t == n_qtiles) { t = tile0; h = next_head(h); }
         }
@@ -619,6 +639,11 @@ template <class C> __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, c
 #pragma unroll
             for (int s = 1; s < S; ++s) x += *reinterpret_cast<const f32x4*>(&sm.stage[(s * C::ROWS + r) * C::PITCH + c]);
             f32x4* op = reinterpret_cast<f32x4*>(out + ((long long)(col0 + r) * g.nkv + kvh) * D + c);
+            if (atomic) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) global_atomic_add(reinterpret_cast<float*>(op) + e, x[e]);
+                continue;
+            }
             if (a.accumulate) x += *op;
             *op = x;
         }

@@ -1069,6 +1069,123 @@ def test_f32_split_operands_with_infinite_values(lq, lc, nq, nkv, d):
     assert (o[rows][..., 0] == inf).all() and (o[rows][..., 1] == -inf).all() and o[rows][..., 2:4].isnan().all() and o[7].isnan().all()
 
 
+def _f32_step(q, k, v, d_o, off, scale, merged=False):
+    """o, lse, dq, dk, dv of one fp32 step, rows from `off` against keys from 0; merged: o / lse into an empty running result, dk / dv added to zeros."""
+    lq, lc = q.shape[0], k.shape[0]
+    t = [x.to(DEV) for x in (q, k, v, d_o)]
+    desc, args, add = hexi.desc_for(t[0], t[1], scale), ([(off, lq)], [(0, lc)], *t[:3]), hexi.HEXI_ACCUMULATE if merged else 0
+    o, lse, delta, dq = torch.zeros_like(t[0]), torch.full((q.shape[1], lq), -float("inf"), device=DEV), torch.empty((q.shape[1], lq), device=DEV), torch.zeros_like(t[0])
+    dk, dv = torch.zeros_like(t[1]), torch.zeros_like(t[1])
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse, flags=add)
+    hexi.hexi_attn_bwd_chunk(desc, *args, o, t[3], lse, delta, dq, dk, dv, flags=hexi.HEXI_COMPUTE_DELTA | add)
+    return [x.cpu() for x in (o, lse, dq, dk, dv)]
+
+
+# (the kernels that cut operands, forward and backward: with heads in two runs, with 64-row units, at head_dim 64 with 32 and 64 keys)
+F32X3_VALUE_STEPS = [(523, 882, 9, 3, 128), (172, 196, 48, 16, 128), (651, 577, 8, 8, 64), (693, 755, 24, 24, 64)]
+F32X3_MASKED_STEPS = [(568, 167, 8, 2, 128), (625, 231, 24, 24, 128), (635, 1158, 24, 24, 64)]      # (rows from the middle of the keys)
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_VALUE_STEPS)
+@pytest.mark.parametrize("units", [dict(v=1e-36), dict(d_o=1e-36), dict(d_o=1e-32), dict(q=1e36, k=1e-36), dict(q=1e-36, k=1e36), dict(v=1e-25, d_o=1e-10),
+                                   dict(q=1e-36, k=1e36, d_o=1e-30, v=1e30)], ids=str)
+def test_f32_keeps_its_range_where_operands_are_cut(lq, lc, nq, nkv, d, units):
+    # operands with magnitudes near the ends of fp32's range: every output keeps its relative accuracy
+    g = torch.Generator().manual_seed(lq)
+    x = {n: torch.randn((rows, h, d), generator=g) for n, rows, h in (("q", lq, nq), ("k", lc, nkv), ("v", lc, nkv), ("d_o", lq, nq))}
+    for name, unit in units.items():
+        x[name] *= unit
+    u = {n: units.get(n, 1.0) for n in x}
+    scale = float(np.float32(0.1))
+    got = _f32_step(*x.values(), lc, scale)
+    in_units = {n: to64(x[n]) / u[n] for n in x}
+    qk = u["q"] * u["k"]
+    ref = oracle.attn_bwd(in_units["q"], np.arange(lc, lc + lq), in_units["k"], in_units["v"], np.arange(lc), in_units["d_o"], scale * qk)
+    o_ref, lse_ref = oracle.attn_fwd(in_units["q"], np.arange(lc, lc + lq), in_units["k"], in_units["v"], np.arange(lc), scale * qk)
+    g_v = u["v"] * u["d_o"]
+    for name, t, want, unit in (("o", got[0], o_ref, u["v"]), ("lse", got[1], lse_ref, 1.0), ("dq", got[2], ref["dq"], g_v * qk / u["q"]),
+                                ("dk", got[3], ref["dk"], g_v * qk / u["k"]), ("dv", got[4], ref["dv"], u["d_o"])):
+        if unit > (1e-33 if name in ("dq", "dk") else 1e-37):      # (dS, and below 1e-38 everything, has fewer than 24 bits in fp32)
+            check(name, t.double() / unit, want, "f32")
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_VALUE_STEPS)
+def test_f32_large_values_whose_weighted_sum_is_finite(lq, lc, nq, nkv, d):
+    # positive values of v up to 1e37, scores that rise after the first keys: the sum of v with weights of at most 1 is finite
+    g = torch.Generator().manual_seed(lq)
+    q, k, v = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv)))
+    k[:128] *= 0.02
+    v = 2.0 + torch.tanh(v)
+    scale = float(np.float32(1.2 * d ** -0.5))
+    o, lse = torch.empty((lq, nq, d), device=DEV), torch.empty((nq, lq), device=DEV)
+    t = [x.to(DEV) for x in (q, k, v * 3e36)]
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(t[0], t[1], scale), [(lc, lq)], [(0, lc)], *t, o, lse)
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(lc, lc + lq), to64(k), to64(v * 3e36) / 3e36, np.arange(lc), scale)
+    check("o", o.cpu().double() / 3e36, o_ref, "f32")
+    check("lse", lse.cpu(), lse_ref, "f32")
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_VALUE_STEPS)
+def test_f32_nan_with_a_payload_in_its_lower_bits(lq, lc, nq, nkv, d):
+    # cut to its upper 16 bits it is an infinity, here one whose scores are -inf: the rows that see it are NaN all the same
+    g = torch.Generator().manual_seed(lc)
+    q, k, v, d_o = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
+    q[..., 0] = -q[..., 0].abs() - 0.1
+    k[lc - 7, 0, 0] = torch.tensor(0x7f800001, dtype=torch.int32).view(torch.float32)
+    o, lse, dq, dk, dv = _f32_step(q, k, v, d_o, lc, 0.1)
+    group = nq // nkv
+    assert o[:, :group].isnan().all() and not o[:, group:].isnan().any()
+    assert dq[:, :group].isnan().all() and dk[:, 0].isnan().all() and not dq[:, group:].isnan().any() and not dk[:, 1:].isnan().any()
+
+
+@pytest.mark.parametrize("merged", [False, True])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,off", [s + (s[1],) for s in F32X3_VALUE_STEPS] + [s + (s[1] // 2,) for s in F32X3_MASKED_STEPS])
+def test_f32_infinite_gradients_of_the_output(lq, lc, nq, nkv, d, off, merged):
+    # one infinite dO: dv of the keys that its row sees is infinite in that column, and dk has the signs of P x v x q there; nothing else is touched
+    g = torch.Generator().manual_seed(lc + 1)
+    q, k, v, d_o = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
+    row, head, col = 61, nkv - 1, 5
+    t = [x.to(DEV) for x in (q, k, v, d_o)]
+    desc, args = hexi.desc_for(t[0], t[1], 0.1), ([(off, lq)], [(0, lc)], *t[:3])
+    o, lse, delta = torch.zeros_like(t[0]), torch.full((nq, lq), -float("inf"), device=DEV), torch.empty((nq, lq), device=DEV)
+    hexi.hexi_attn_fwd_chunk(desc, *args, o, lse)
+    run = lambda: [torch.zeros_like(t[0]), torch.zeros_like(t[1]), torch.zeros_like(t[1])]
+    want, got = run(), run()
+    flags = hexi.HEXI_ACCUMULATE if merged else 0
+    hexi.hexi_attn_bwd_chunk(desc, *args, o, t[3], lse, delta, *want, flags=flags | hexi.HEXI_COMPUTE_DELTA)
+    t[3][row, head * (nq // nkv), col] = float("inf")
+    hexi.hexi_attn_bwd_chunk(desc, *args, None, t[3], lse, delta, *got, flags=flags)
+    (dq, dk, dv), (_, dk0, dv0) = [x.cpu() for x in got], [x.cpu() for x in want]
+    seen = off + row + 1
+    h = head * (nq // nkv)
+    assert (dv[:seen, head, col] == float("inf")).all() and (dk[:seen, head] == float("inf") * torch.sign(v[:seen, head, col, None] * q[row, h])).all()
+    rest = lambda x: torch.cat([x[seen + 127:, head].flatten(), x[:, :head].flatten()])      # (0 x inf: keys just behind the row's may be NaN)
+    for name, x, x0 in (("dk", dk, dk0), ("dv", dv, dv0)):
+        check(name, rest(x), rest(x0), "f32")
+    others = torch.ones((lq, nq), dtype=torch.bool)
+    others[row - row % 16:row - row % 16 + 16, h] = False
+    check("dq", dq[others], want[0].cpu()[others], "f32")
+
+
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_MASKED_STEPS)
+def test_f32_infinite_value_at_a_key_that_some_rows_do_not_see(lq, lc, nq, nkv, d):
+    # rows of blocks before the key are as if it were not there, rows that see it are infinite in its column
+    g = torch.Generator().manual_seed(lc + 2)
+    q, k, v, d_o = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
+    off, key, col = lc // 2, lc // 2 + 83, 9
+    o_ref, lse_ref = oracle.attn_fwd(to64(q), np.arange(off, off + lq), to64(k), to64(v), np.arange(lc), float(np.float32(0.1)))
+    v[key, 0, col] = float("inf")
+    o, lse, *_ = _f32_step(q, k, v, d_o, off, 0.1)
+    group = nq // nkv
+    assert (o[83:, :group, col] == float("inf")).all()
+    check("lse", lse, lse_ref, "f32")
+    before = 16 * max(b for b in range(6) if off + 16 * b <= key // 16 * 16)      # (0 x inf: a 16-row block that sees other keys of the key's block is NaN)
+    assert before >= 64
+    check("o of the rows before", o[:before], o_ref[:before], "f32")
+    others = [j for j in range(d) if j != col]
+    check("other columns", o[:, :, others], o_ref[:, :, others], "f32")
+
+
 @pytest.mark.parametrize("d", [64, 128, 12])
 @pytest.mark.parametrize("final", [None, torch.float32, torch.bfloat16])
 def test_merge_of_partials_that_saw_nothing(d, final):
