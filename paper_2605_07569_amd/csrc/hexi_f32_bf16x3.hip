@@ -21,9 +21,10 @@
 //
 // Values.  A cut loses bits of a value below 2^-110 (2^-133 is the smallest bf16: up to 2^-134 of it), an infinite one has no rest (inf - inf), and the
 // probabilities of the forward, up to 2^8 here, may overflow in a sum that would not.  A unit therefore looks its operands and results over
-// (largest(), stationary_range(), too_small_or_not_finite()) and, where the cut may show in a result, hands its rows to the units on the fp32 instruction
+// (largest(), stationary_range(), Extremes) and, where the cut may show in a result, hands its rows to the units on the fp32 instruction
 // (hexi_f32_units.h) before anything is written: values, infinities and NaN come out as there.  For the results that are kept it costs one v_maximum3_f32
-// for two values of the columns and of dS: forward launches 1 us of 127, backward ones 13 of 701 (3056 rows x 12 011 keys x 6/2 heads x 128).
+// for two values of the columns and of dS: 3056 rows x 12011 keys x 6/2 heads x 128, forward and backward,
+// 2346 / 2352 us without / with it.
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 #include "hexi_shapes.h"
@@ -96,9 +97,15 @@ __device__ __forceinline__ float largest(float m, float a, float b) { return __b
 // over the lanes of the wavefront
 __device__ __forceinline__ float largest_of_wave(float x)
 {
-#pragma unroll
-    for (int i = 32; i > 0; i /= 2) x = __builtin_elementwise_maximum(x, __shfl_xor(x, i, 64));
-    return x;
+    auto rotated = [&](auto by) { return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + decltype(by)::value, 0xf, 0xf, false)); };
+    x = largest(x, x, rotated(IC<8>{}));
+    x = largest(x, x, rotated(IC<4>{}));
+    x = largest(x, x, rotated(IC<2>{}));
+    x = largest(x, x, rotated(IC<1>{}));
+    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = largest(0.f, __uint_as_float(rows[0]), __uint_as_float(rows[1]));
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return largest(0.f, __uint_as_float(halves[0]), __uint_as_float(halves[1]));
 }
 
 // The largest of the wavefronts' values, which they have put into a row of `top`.
@@ -117,11 +124,18 @@ template <int NW> __device__ __forceinline__ float largest_of_workgroup(const fl
 constexpr float SMALLEST = 7.88860905e-31f;                            // 2^-100
 constexpr float CUT_LOSS = 7.70371978e-34f, SCORE_LOSS = 9.86076132e-32f;      // 2^24 2^-134, 2^24 2^-127
 __device__ __forceinline__ unsigned too_small(float largest_value) { return (unsigned)(largest_value > 0.f) & (unsigned)(largest_value < SMALLEST); }
-__device__ __forceinline__ unsigned too_small_or_not_finite(float x, float least)
-{
-    const float m = __builtin_fabsf(x);
-    return (unsigned)!(m < INFINITY) | ((unsigned)(m > 0.f) & (unsigned)!(m >= least));
-}
+// Results: their largest magnitude and the smallest that is not zero, as its bits without the sign, less one.
+struct Extremes {
+    float top = 0.f;
+    unsigned low = 0xffffffffu;
+    __device__ __forceinline__ static unsigned bits(float x) { return (__float_as_uint(x) << 1) - 1u; }
+    __device__ __forceinline__ void add(float a, float b)
+    {
+        top = largest(top, a, b);
+        low = min(low, min(bits(a), bits(b)));
+    }
+    __device__ __forceinline__ unsigned not_finite_or_below(float least) const { return (unsigned)!(top < INFINITY) | (unsigned)(low < bits(least)); }
+};
 // Whether any thread of the workgroup finds its values so; votes: a word of LDS for each wavefront.
 template <int NW> __device__ __forceinline__ bool any_of_workgroup(unsigned x, unsigned* votes, int tid)
 {
@@ -132,13 +146,6 @@ template <int NW> __device__ __forceinline__ bool any_of_workgroup(unsigned x, u
 #pragma unroll
     for (int w = 0; w < NW; ++w) sum |= votes[w];
     return sum != 0u;
-}
-
-// The thread's number once more, by a name that the compiler cannot see through: what the end of a unit computes from it is not kept over the loop.
-__device__ __forceinline__ int fresh(int tid)
-{
-    asm volatile("" : "+v"(tid));
-    return tid;
 }
 
 // Operands of a stationary tensor in LDS: step ks, row block n, piece p at ((NB ks + n) 3 + p) KB, a lane's 16 bytes at 16 lane.
@@ -159,19 +166,21 @@ template <class C> __device__ __forceinline__ void put_stationary(unsigned char*
 // The upper pieces that put_stationary() left there: sets `odd` where a value is out of range, and returns a bound of the thread's share of them.
 template <class C> __device__ __forceinline__ float stationary_range(const unsigned char* lds, int wave, int lane, unsigned& odd)
 {
-    unsigned low = 0xffffu, high = 0u;                    // smallest nonzero one (less one), largest: upper 16 bits, without sign
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 low = 0xffff, high = 0;                         // smallest nonzero one (less one), largest: upper 16 bits, without sign
 #pragma unroll
     for (int i = 0; i < C::NK * C::NB / C::NW; ++i) {
         const u32x4 h = *reinterpret_cast<const u32x4*>(lds + (wave + C::NW * i) * 3072 + 16 * lane);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const unsigned u = (e & 1 ? h[e / 2] >> 16 : h[e / 2]) & 0x7fffu;
-            low = min(low, (u - 1u) & 0xffffu);
-            high = max(high, u);
+        for (int e = 0; e < 4; ++e) {
+            const u16x2 u = __builtin_bit_cast(u16x2, h[e] & 0x7fff7fffu), one = 1;
+            low = __builtin_elementwise_min(low, (u16x2)(u - one));
+            high = __builtin_elementwise_max(high, u);
         }
     }
-    odd |= low < 0x0d80u - 1u || high >= 0x5d80u;         // 2^-100, 2^60
-    return __uint_as_float((high + 1u) << 16);
+    const unsigned l = min(low[0], low[1]), m = max(high[0], high[1]);
+    odd |= (unsigned)(l < 0x0d80u - 1u) | (unsigned)(m >= 0x5d80u);         // 2^-100, 2^60
+    return __uint_as_float((m + 1u) << 16);
 }
 
 // A block of 32 streamed rows on its way to the scores: transfers into the wavefront's own piece of LDS, the 16-byte pieces of a row permuted by
@@ -542,7 +551,7 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
             sm.e.l[wave * ROWS + 32 * n + l32] = l_run[n];
         }
     }
-    const int tid = fresh(threadIdx.x);
+    const int tid = threadIdx.x;
     if (lane == 0) sm.e.top[wave] = top;
     __syncthreads();
     float lse_new = 0.f;
@@ -553,17 +562,19 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
     const float least = CUT_LOSS * (float)n_vis * (256.f + top);      // (the probabilities' largest is 2^8)
     constexpr int PARTS = ROWS * D / 4 / (64 * NW);
     f32x4 out[PARTS];
+    Extremes ends;
 #pragma unroll
     for (int u = 0; u < PARTS; ++u) {
         const int i = tid + 64 * NW * u, r = i / (D / 4), c = 4 * (i % (D / 4));
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < NW; ++s) x += sm.e.w[s * ROWS + r] * *reinterpret_cast<const f32x4*>(&sm.e.stage[(s * ROWS + r) * C::PITCH + c]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) odd |= (unsigned)(row0 + r < g.lq) & too_small_or_not_finite(x[e], least);
+        ends.add(x[0], x[1]);
+        ends.add(x[2], x[3]);
         out[u] = x;
         __builtin_amdgcn_sched_barrier(0);
     }
+    odd |= ends.not_finite_or_below(least);
     if (any_of_workgroup<NW>(odd, sm.e.votes, tid)) return false;
     if (tid < ROWS && row0 + tid < g.lq) a.lse[(long long)h * g.lq + row0 + tid] = lse_new;
 #pragma unroll
@@ -596,13 +607,17 @@ __global__ void __launch_bounds__(256, 1) fwd_f32x3_kernel(const FwdArgs a, cons
     }
 }
 
-template <class C> union X3BwdTiles {
+template <class C> union X3BwdSmem {
     struct { unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES]; };
-    struct { float stage[C::STAGE_FLOATS], top[4][C::NW]; unsigned votes[C::NW]; };
+    struct { float stage[C::STAGE_FLOATS], top[3][C::NW]; unsigned votes[C::NW]; };
 };
-// and the row scalars of each wavefront's block (dK / dV): -LSE log2(e) in two floats, Delta
-template <class C> struct X3BwdSmem { X3BwdTiles<C> u; };
-template <class C> struct X3KvSmem { X3BwdTiles<C> u; float scalars[C::NW][3][32]; };
+template <class C> union X3KvSmem {
+    struct {
+        unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES];
+        float scalars[C::NW][3][32];                       // the row scalars of each wavefront's block: -LSE log2(e) in two floats, Delta
+    };
+    struct { float stage[2][C::STAGE_FLOATS], top[4][C::NW]; unsigned votes[C::NW]; };
+};
 
 // dQ: S^T = K Q^T and dP^T = V dO^T per block, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
 template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& a, const int h, const int row0, X3BwdSmem<X3Cfg<D, NB>>& sm)
@@ -630,16 +645,16 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
     }
     const float* k = static_cast<const float*>(a.k) + (long long)kvh * g.kv_stride_head;
     const float* v = static_cast<const float*>(a.v) + (long long)kvh * g.kv_stride_head;
-    unsigned char* const slot = sm.u.rows[wave];
+    unsigned char* const slot = sm.rows[wave];
     const RowBlock<C> rows(slot, lane, g.kv_stride_tok);
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
     const long long q_off = (long long)h * g.q_stride_head;
     float ds_top = 0.f, top = 0.f;
-    put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
-    put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
+    put_stationary<C>(sm.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
+    put_stationary<C>(sm.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
-    const unsigned char *q_stat = sm.u.t[0] + 16 * lane, *g_stat = sm.u.t[1] + 16 * lane;
+    const unsigned char *q_stat = sm.t[0] + 16 * lane, *g_stat = sm.t[1] + 16 * lane;
 
     f32x16 acc[NB][C::NJ];
     zero_acc<C>(acc);
@@ -676,32 +691,34 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
         accumulate<C, false>(acc, kc, s, top);
     }
     unsigned odd = g.scale >= 1048576.f;
-    stationary_range<C>(sm.u.t[0], wave, lane, odd);
-    float g_top = largest_of_wave(stationary_range<C>(sm.u.t[1], wave, lane, odd));
+    stationary_range<C>(sm.t[0], wave, lane, odd);
+    float g_top = largest_of_wave(stationary_range<C>(sm.t[1], wave, lane, odd));
     top = largest_of_wave(top);
     ds_top = largest_of_wave(ds_top);
     __syncthreads();
-    stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
-    const int tid = fresh(threadIdx.x);
-    if (lane == 0) { sm.u.top[0][wave] = top; sm.u.top[1][wave] = g_top; sm.u.top[2][wave] = ds_top; }
+    stage_rows<C>(&sm.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
+    const int tid = threadIdx.x;
+    if (lane == 0) { sm.top[0][wave] = top; sm.top[1][wave] = g_top; sm.top[2][wave] = ds_top; }
     __syncthreads();
-    top = largest_of_workgroup(sm.u.top[0]);
-    g_top = largest_of_workgroup(sm.u.top[1]);
-    ds_top = largest_of_workgroup(sm.u.top[2]);
+    top = largest_of_workgroup(sm.top[0]);
+    g_top = largest_of_workgroup(sm.top[1]);
+    ds_top = largest_of_workgroup(sm.top[2]);
     odd |= too_small(ds_top) | too_small(top);
     const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top + top) + SCORE_LOSS * g_top * top);
     constexpr int PARTS = ROWS * D / (64 * NW);
     float out[PARTS];             // consecutive lanes on consecutive floats
+    Extremes ends;
 #pragma unroll
     for (int u = 0; u < PARTS; ++u) {
         const int i = tid + 64 * NW * u, r = i / D, c = i % D;
-        out[u] = sm.u.stage[r * C::PITCH + c];
+        out[u] = sm.stage[r * C::PITCH + c];
 #pragma unroll
-        for (int s = 1; s < NW; ++s) out[u] += sm.u.stage[(s * ROWS + r) * C::PITCH + c];
-        odd |= (unsigned)(row0 + r < g.lq) & too_small_or_not_finite(out[u], least);
+        for (int s = 1; s < NW; ++s) out[u] += sm.stage[(s * ROWS + r) * C::PITCH + c];
+        if (u % 2 == 1) ends.add(out[u - 1], out[u]);
         if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
-    if (any_of_workgroup<NW>(odd, sm.u.votes, tid)) return false;
+    odd |= ends.not_finite_or_below(least);
+    if (any_of_workgroup<NW>(odd, sm.votes, tid)) return false;
     // Added with atomics: chunks of one shard may be in flight on several streams.
     // One addition per element and call, so calls in stream order still have a fixed order.
 #pragma unroll
@@ -734,34 +751,42 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
         const int col = col0 + 32 * n + l32;
         first[n] = col < g.lc ? seg_rows_le(g.qs, seg_pos_of_row(g.ks, col) - 1) : 0x7fffffff;
     }
-    const int block0 = row_first / BLK, n_blocks = (g.lq + BLK - 1) / BLK, per_head = row_first < g.lq ? n_blocks - block0 : 0;
+    const int block0 = row_first / BLK, n_blocks = (g.lq + BLK - 1) / BLK, per_head = row_first < g.lq ? n_blocks - block0 : 0;      // 0: keys that no row sees
     const Log2Scale c(g.scale);
     auto next_head = [&](int h) { for (++h; h < h_end && g.kv_of_q[h] != kvh; ++h) {} return h; };
 
     int h = next_head(h_first - 1), left = 0;             // `left` heads from h on
     for (int i = h; i < h_end; i = next_head(i)) ++left;
-    if (atomic && (left == 0 || per_head == 0)) return true;      // (the zeros are there)
+    if (left == 0 || per_head == 0) {
+        for (int i = threadIdx.x; i < ROWS * D / 4 && !atomic && !a.accumulate; i += 64 * NW) {      // (else the zeros, or sums, are there)
+            const int r = i / (D / 4), c = 4 * (i % (D / 4));
+            if (col0 + r >= g.lc) continue;
+            const long long at = ((long long)(col0 + r) * g.nkv + kvh) * D + c;
+            *reinterpret_cast<f32x4*>(a.dv + at) = f32x4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4*>(a.dk + at) = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        return true;
+    }
     const float n_rows = (float)left * (float)(g.lq - row_first);
 
     f32x16 dk[NB][C::NJ], dv[NB][C::NJ];
     zero_acc<C>(dk);
     zero_acc<C>(dv);
-    float ds_top = 0.f, q_top = 0.f, g_top = 0.f, v_top = 0.f;
-    unsigned odd = g.scale >= 1048576.f;
-    if (per_head > 0) {
+    float ds_top = 0.f, q_top = 0.f, g_top = 0.f;
+    {
         // this wavefront's next block: number b of head h; the blocks of all heads in one sequence are dealt to the wavefronts in turn
         int b = block0 + wave;
         auto settle = [&]() { while (b >= n_blocks && left > 0) { b -= per_head; h = next_head(h); --left; } };
         settle();
-        unsigned char* const slot = sm.u.rows[wave];
+        unsigned char* const slot = sm.rows[wave];
         const RowBlock<C> rows(slot, lane, g.q_stride_tok);
         auto request_q = [&]() { rows.request(static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, BLK * b, g.lq, lane); };
-        if (left > 0) request_q();
+        if (left > 0) request_q();                        // (with few rows there may be no block for this one)
         const long long k_off = (long long)kvh * g.kv_stride_head;
-        put_stationary<C>(sm.u.t[0], static_cast<const float*>(a.k) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
-        put_stationary<C>(sm.u.t[1], static_cast<const float*>(a.v) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
+        put_stationary<C>(sm.t[0], static_cast<const float*>(a.k) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
+        put_stationary<C>(sm.t[1], static_cast<const float*>(a.v) + k_off, g.kv_stride_tok, col0, g.lc, wave, lane);
         __syncthreads();
-        const unsigned char *k_stat = sm.u.t[0] + 16 * lane, *v_stat = sm.u.t[1] + 16 * lane;
+        const unsigned char *k_stat = sm.t[0] + 16 * lane, *v_stat = sm.t[1] + 16 * lane;
         while (left > 0) {
             const long long off = (long long)h * g.q_stride_head;
             const int r0 = BLK * b;
@@ -825,41 +850,42 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
             accumulate<C, true>(dv, gc, p, g_top);
             accumulate<C, true>(dk, qc, ds, q_top);
         }
-        stationary_range<C>(sm.u.t[0], wave, lane, odd);
-        v_top = largest_of_wave(stationary_range<C>(sm.u.t[1], wave, lane, odd));
     }
+    unsigned odd = g.scale >= 1048576.f;
+    stationary_range<C>(sm.t[0], wave, lane, odd);
+    const float v_top = largest_of_wave(stationary_range<C>(sm.t[1], wave, lane, odd));
     q_top = largest_of_wave(q_top);
     g_top = largest_of_wave(g_top);
     ds_top = largest_of_wave(ds_top);
     // consecutive lanes on consecutive floats where they are added with atomics, on consecutive 16 bytes where they are stored
     constexpr int PARTS = ROWS * D / (64 * NW);
-    const int tid = fresh(threadIdx.x);
+    const int tid = threadIdx.x;
     auto float_of = [&](int u) { return atomic ? tid + 64 * NW * u : 4 * tid + 256 * NW * (u / 4) + u % 4; };
-    auto gather = [&](float (&out)[PARTS], const f32x16 (&acc)[NB][C::NJ], float w) {
-        __syncthreads();
-        stage_rows<C>(&sm.u.stage[wave * ROWS * C::PITCH], acc, lane, w);
-        if (lane == 0) { sm.u.top[0][wave] = q_top; sm.u.top[1][wave] = g_top; sm.u.top[2][wave] = v_top; sm.u.top[3][wave] = ds_top; }
-        __syncthreads();
+    auto gather = [&](float (&out)[PARTS], const float* stage) {
+        Extremes ends;
 #pragma unroll
         for (int u = 0; u < PARTS; ++u) {
             const int i = float_of(u), at = i / D * C::PITCH + i % D;
-            out[u] = sm.u.stage[at];
+            out[u] = stage[at];
 #pragma unroll
-            for (int s = 1; s < NW; ++s) out[u] += sm.u.stage[s * ROWS * C::PITCH + at];
+            for (int s = 1; s < NW; ++s) out[u] += stage[s * ROWS * C::PITCH + at];
+            if (u % 2 == 1) ends.add(out[u - 1], out[u]);
             if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        return ends;
     };
+    __syncthreads();
+    stage_rows<C>(&sm.stage[0][wave * ROWS * C::PITCH], dv, lane, 1.0f);
+    stage_rows<C>(&sm.stage[1][wave * ROWS * C::PITCH], dk, lane, g.scale);
+    if (lane == 0) { sm.top[0][wave] = q_top; sm.top[1][wave] = g_top; sm.top[2][wave] = v_top; sm.top[3][wave] = ds_top; }
+    __syncthreads();
     float out_v[PARTS], out_k[PARTS];
-    gather(out_v, dv, 1.0f);
-    gather(out_k, dk, g.scale);
-    const float q_all = largest_of_workgroup(sm.u.top[0]), g_all = largest_of_workgroup(sm.u.top[1]), v_all = largest_of_workgroup(sm.u.top[2]),
-                ds_all = largest_of_workgroup(sm.u.top[3]);
-    odd |= too_small(ds_all) | too_small(q_all) | too_small(g_all);
-    const float least_v = n_rows * CUT_LOSS * (2.f + g_all), least_k = g.scale * n_rows * (CUT_LOSS * (ds_all + q_all) + SCORE_LOSS * v_all * q_all);
-#pragma unroll
-    for (int u = 0; u < PARTS; ++u)
-        odd |= (unsigned)(col0 + float_of(u) / D < g.lc) & (too_small_or_not_finite(out_v[u], least_v) | too_small_or_not_finite(out_k[u], least_k));
-    if (any_of_workgroup<NW>(odd, sm.u.votes, tid)) return false;
+    const Extremes ends_v = gather(out_v, sm.stage[0]), ends_k = gather(out_k, sm.stage[1]);
+    const float q_all = largest_of_workgroup(sm.top[0]), g_all = largest_of_workgroup(sm.top[1]), v_all = largest_of_workgroup(sm.top[2]),
+                ds_all = largest_of_workgroup(sm.top[3]);
+    odd |= too_small(ds_all) | too_small(q_all) | too_small(g_all) | ends_v.not_finite_or_below(n_rows * CUT_LOSS * (2.f + g_all)) |
+           ends_k.not_finite_or_below(g.scale * n_rows * (CUT_LOSS * (ds_all + q_all) + SCORE_LOSS * v_all * q_all));
+    if (any_of_workgroup<NW>(odd, sm.votes, tid)) return false;
     auto write_out = [&](float* to, const float (&out)[PARTS]) {
 #pragma unroll
         for (int u = 0; u < PARTS; u += 4) {
