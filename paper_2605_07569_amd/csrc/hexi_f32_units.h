@@ -64,7 +64,7 @@ __device__ __forceinline__ float prob(float s, float c_hi, float c_lo, float nl_
     return fast_exp2(fmaf(s, c_hi, nl_hi) + fmaf(max2(s, -3.402823466e38f), c_lo, nl_lo));
 }
 
-template <int D_, bool SPLIT_, bool TWO_, int NW_ = SPLIT_ ? 8 : 4, int CHAINS_ = D_ == 128 ? 4 : 1, bool CLEAR_ = false> struct F32Cfg {
+template <int D_, bool SPLIT_, bool TWO_, int NW_ = SPLIT_ ? 8 : 4, int CHAINS_ = 1, bool CLEAR_ = false> struct F32Cfg {
     static constexpr int D = D_, CHAINS = CHAINS_;           // chains of sums of a score: 1 or 4
     static constexpr bool CLEAR = CLEAR_;                  // rows past the end are zeros (SPLIT): no 0 x inf of theirs where the last row is infinite
     static constexpr bool SPLIT = SPLIT_, TWO = TWO_;
@@ -171,9 +171,11 @@ __device__ __forceinline__ f32x4 lds_f4(const unsigned char* p) { return *reinte
 // The reads of a step are issued before the MFMAs of the step before it (4 NT MFMAs = 128 NT cycles ahead); left to
 // itself the compiler issues them a few dozen cycles before their use.  The summation order over the head dimension is
 // the same in all three kernels: the rounding errors of a score and of the LSE it went into then cancel in P.  At head_dim 128, where the LSE may
-// come from the split-operand forward instead (hexi_f32_bf16x3.hip), four chains, one per MFMA of a group, halve the error of one and more
-// than make up for what no longer cancels: errors of dq, dk, dv, K scaled by 3, 777 x 1000 x 8/2 heads, one chain in all kernels 1, that forward
-// with one chain here 1.5, 1.5, 1.7, with four 0.79, 0.78, 0.81 (times: backward 123 / 125 us).
+// come from the split-operand forward instead (hexi_f32_bf16x3.hip), or go to its backward, four chains, one per MFMA of a group, halve the error of
+// one and more than make up for what no longer cancels: errors of dq, dk, dv, K scaled by 3, 777 x 1000 x 8/2 heads, one chain in all kernels 1, that
+// forward with one chain here 1.5, 1.5, 1.7, with four 0.79, 0.78, 0.81.  Steps that take no kernel of that file keep the one chain
+// (hexi_f32_chains(); a backward of 1264 x 108 x 48/24 heads 182 us, with four, and one
+// shared workgroup on a CU, 200).
 template <class C, int NT> __device__ __forceinline__ void score_block(f32x4 (&out)[NT], const unsigned char* const (&tile)[NT], const LaneAddr<C>& la, const f32x4* const (&frag)[NT])
 {
     constexpr int CH = C::CHAINS;

@@ -549,3 +549,10 @@ inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate)
     if (plan.use && g.d != 128) plan.use = hexi_f32x3_at_64(g);
     return plan;
 }
+
+// Chains of sums of a score in the 16-row kernels (hexi_f32_units.h): four at head_dim 128 where any part of the step, forward or backward, may take the
+// split-operand kernels.
+inline int hexi_f32_chains(const AttnGeom& g)
+{
+    return g.d == 128 && (hexi_f32x3_fwd(g).use || hexi_f32x3_bwd(g, false).use || hexi_f32x3_bwd(g, true).use) ? 4 : 1;
+}

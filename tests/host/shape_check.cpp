@@ -13,23 +13,7 @@
 #include <string>
 #include "hexi_internal.h"
 #include "hexi_shapes.h"
-
-static SegTable read_segs(std::istringstream& is)
-{
-    SegTable t;
-    std::memset(&t, 0, sizeof(t));
-    is >> t.n;
-    int rows = 0;
-    for (int s = 0; s < t.n; ++s) {
-        int len;
-        is >> t.start[s] >> len;
-        t.row0[s] = rows;
-        rows += len;
-    }
-    for (int s = t.n; s <= HEXI_MAX_SEGS; ++s) t.row0[s] = rows;
-    t.total = rows;
-    return t;
-}
+#include "read_segs.h"
 
 int main()
 {

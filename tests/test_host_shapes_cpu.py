@@ -188,21 +188,35 @@ def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
     assert [(g["f32_dq"], g["f32_dkdv"]) for g in shapes(steps)] == [(2, 2), (1, 1), (1, 1), (0, 0), (1, 1)]
 
 
-def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(tmp_path_factory):
-    from parity_util import F32X3_STEPS, f32x3_diagonal
+@pytest.fixture(scope="module")
+def split_operand_shapes(tmp_path_factory):
     exe = _compile(tmp_path_factory, "f32x3_check")
 
-    def ask(steps):
+    def ask(steps, accumulate=False, chains=False):
         segs = lambda x: f"{len(x)} " + " ".join(f"{s} {n}" for s, n in x)
         lines = [f"{nq} {nkv} {d} {segs(qs)} {segs(ks)}" for d, nq, nkv, qs, ks in steps]
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         got = []
         for line in filter(None, out):
-            use, n64, tiles, bwd, keys, rows64, runs = map(int, line.split())
-            got.append(((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0, (64 if rows64 else 32) if bwd else 0,
-                        runs if bwd else 0))
+            use, n64, tiles, *bwds, n_chains = map(int, line.split())
+            bwd, keys, rows64, runs = bwds[4:] if accumulate else bwds[:4]
+            got.append(n_chains if chains else ((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0,
+                                                (64 if rows64 else 32) if bwd else 0, runs if bwd else 0))
         return got
 
+    return ask
+
+
+def test_scores_are_summed_in_one_chain_unless_a_part_of_the_step_is_cut(split_operand_shapes):
+    # us of a backward with one chain / four: 664 / 729, 182 / 200; forward, backward or a backward under HEXI_ACCUMULATE cut: four
+    steps = [_step(*s) for s in ((5761, 130, 32, 16, 128, 130), (1264, 108, 48, 24, 128, 0), (300, 300, 4, 2, 128, 300), (1079, 162, 4, 1, 128, 162),
+                                 (516, 93, 24, 8, 128, 93), (327, 161, 4, 1, 128, 161), (4096, 4096, 16, 4, 128, 4096), (4096, 4096, 24, 8, 64, 4096))]
+    assert split_operand_shapes(steps, chains=True) == [1, 1, 1, 4, 4, 4, 4, 1]
+
+
+def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(split_operand_shapes):
+    from parity_util import F32X3_STEPS, f32x3_diagonal
+    ask = split_operand_shapes
     assert ask([_step(lq, lc, nq, nkv, d, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS]) == [s for _, s in F32X3_STEPS]
     # masked blocks: diagonal chunks as well, forward and backward, with units of 32 and of 64
     diagonal = ask([(d, nq, nkv) + f32x3_diagonal(lq, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS])
