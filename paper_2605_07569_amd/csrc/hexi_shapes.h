@@ -473,7 +473,7 @@ inline F32x3Fwd hexi_f32x3_fwd_by_itself(const AttnGeom& g)
     return plan;
 }
 
-// A step's halves are one launch whose units fill each other's rounds.  A call for one half takes the kernel, and so has the bits, of the whole step.
+// A step's halves are one launch whose units fill each other's rounds.
 // A few long dK / dV units are what such a launch waits for: the heads of a group may be dealt to two of them, which add to cleared elements (not
 // where dk and dv hold a running value, whose sum would show the order: the margin is wider there, 1.1 lost up to 9 % in some of the calls).
 // 128 columns, one run / two: 6000 x 800 x 8/1 heads 1888 / 1294 us, 3056 x 3000 x 6/2 703 / 701, 2048 x 2048 x 16/4 737 / 743; 16-row kernels / two
@@ -543,10 +543,46 @@ inline F32x3Fwd hexi_f32x3_fwd(const AttnGeom& g)
     if (plan.use && g.d != 128) plan.use = hexi_f32x3_at_64(g);
     return plan;
 }
-inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate)
+// A half of a backward step by itself at head_dim 128: us expected with the 16-row kernels (in the shape hexi_f32_split() says) and with the plan's units.
+// Fitted to 260 random halves, 90 % of each kind within 10 % (split dK / dV 20 %).
+struct F32Half { double us16, us; };
+inline F32Half hexi_f32x3_dq_alone(const AttnGeom& g, const F32x3Bwd& plan)
+{
+    const double mean = hexi_mean_seen(g), longest = (double)hexi_keys_seen(g);
+    auto us = [&](int rows, F32Fit f, double tail) { return hexi_f32_launch_us(f, (long long)((g.lq + rows - 1) / rows) * g.nq, mean, longest, tail); };
+    return {hexi_f32_split(g.lq, g.nq) ? us(16, {2.7, 6.9, 25.0}, 0.29) : us(64, {7.7, 7.2, 98.7}, 0.27),
+            plan.rows64 ? us(64, {0.0, 16.3, 52.1}, 0.3) : us(32, {1.8, 9.7, 35.9}, 0.37)};
+}
+inline F32Half hexi_f32x3_dkdv_alone(const AttnGeom& g, const F32x3Bwd& plan)
+{
+    const double group = (double)g.nq / g.nkv, longer = std::ceil(0.5 * group) / group;
+    const int seen = hexi_keys_seen(g);
+    const double longest = group * (double)(g.lq - seg_rows_le(g.qs, seg_pos_of_row(g.ks, 0) - 1)), mean = group * (double)g.lq * hexi_mean_seen(g) / seen;
+    // unseen: us of a round of units of keys that no row sees
+    auto us = [&](int keys, int runs, F32Fit f, double tail, double unseen) {
+        const long long n = (long long)((seen + keys - 1) / keys) * g.nkv * runs, all = (long long)((g.lc + keys - 1) / keys) * g.nkv * runs;
+        return hexi_f32_launch_us(f, n, mean / runs, runs == 2 ? longer * longest : longest, tail) + unseen * (double)(all - n) / 256.0;
+    };
+    return {hexi_f32_split(g.lc, g.nkv) ? us(16, 1, {2.3, 14.1, 33.1}, 0.26, 13.0) : us(64, 1, {12.5, 7.6, 139.5}, 0.17, 3.9),
+            plan.runs == 2 ? us(32, 2, {0.0, 21.3, 54.9}, 0.24, 4.6) : us(32, 1, {0.1, 19.7, 53.8}, 0.3, 1.9)};
+}
+
+// At head_dim 128 a half in a call of its own has rounds to itself, and takes the units of the whole step only where those are expected 5 % faster
+// than the 16-row ones by themselves (us, 16-row / the whole step's: dQ of 329 rows x 1509 keys x 24 heads 92 / 126, of 124 x 1387 x 32 46 / 58, dK / dV of
+// 93 x 2465 x 24/24 with half of the keys seen 66 / 97).  A whole step wants the sum of its halves not 15 % slower: 135 x 4439 keys x 24/24, four
+// blocks of rows to a dK / dV unit, 318 / 496.
+inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate, bool want_dq = true, bool want_dkdv = true)
 {
     F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g, accumulate);
-    if (plan.use && g.d != 128) plan.use = hexi_f32x3_at_64(g);
+    if (!plan.use) return plan;
+    if (g.d != 128) {
+        plan.use = hexi_f32x3_at_64(g);
+        return plan;
+    }
+    const F32Half q = hexi_f32x3_dq_alone(g, plan), kv = hexi_f32x3_dkdv_alone(g, plan);
+    plan.use = 0.85 * (q.us + kv.us) < q.us16 + kv.us16;
+    if (!want_dkdv) plan.use = plan.use && 1.05 * q.us < q.us16;
+    if (!want_dq) plan.use = plan.use && 1.05 * kv.us < kv.us16;
     return plan;
 }
 

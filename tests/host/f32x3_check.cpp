@@ -1,7 +1,8 @@
 // Host-side view of the launch rules of the split-operand fp32 kernels (csrc/hexi_shapes.h).  Reads one step per line from stdin: nq nkv
 // head_dim, then the shard's and the chunk's segments as in shape_check.cpp, and prints whether the forward takes them, its 64-row tiles taken as such
 // and all of them; for the backward, and again for one under HEXI_ACCUMULATE, whether it does, keys of a dK / dV unit, whether its dQ units have 64
-// rows, and the units that the heads of a group are dealt to; then the chains of a score in the other kernels.
+// rows, and the units that the heads of a group are dealt to; then the chains of a score in the other kernels; and for a call for dQ alone whether it
+// takes them and in 64 rows, for dK / dV alone and under HEXI_ACCUMULATE whether and in how many units a group.
 #include <cstdio>
 #include <cstring>
 #include <iostream>
@@ -29,6 +30,7 @@ int main()
             const F32x3Bwd b = hexi_f32x3_bwd(g, accumulate);
             std::printf(" %d %d %d %d", b.use, 32 * b.key_blocks, b.rows64, b.runs);
         }
-        std::printf(" %d\n", hexi_f32_chains(g));
+        const F32x3Bwd q = hexi_f32x3_bwd(g, false, true, false), kv = hexi_f32x3_bwd(g, false, false, true), added = hexi_f32x3_bwd(g, true, false, true);
+        std::printf(" %d %d %d %d %d %d %d\n", hexi_f32_chains(g), q.use, q.rows64, kv.use, kv.runs, added.use, added.runs);
     }
 }

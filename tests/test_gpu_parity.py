@@ -1003,7 +1003,7 @@ def test_f32_shapes_at_head_dim_64(step, shapes):
 def test_f32_split_operand_shapes(step, _):
     # the kernels that cut fp32 operands into three bf16 ones, in every shape the rules deal out (asserted on the CPU): one chunk fully visible and
     # a diagonal one in two segments that merges into its o / lse, K scaled by 3; strided tensors with the same bits; dk / dv under
-    # HEXI_ACCUMULATE; the halves in calls of their own with the same bits
+    # HEXI_ACCUMULATE; the halves in calls of their own, which may take other kernels
     lq, lc, nq, nkv, d = step
     q_segs, own = f32x3_diagonal(lq, lc)
     w = _custom(f"f32x3_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, own[-1][0] + own[-1][1], q_segs, [[(0, lc)], own], k_scale=3.0)
@@ -1015,13 +1015,20 @@ def test_f32_split_operand_shapes(step, _):
         hexi.hexi_attn_bwd_chunk(*args, dq, dk, dv, flags=hexi.HEXI_ACCUMULATE)
         check("dk acc", dk.cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]) + 0.5, "f32")
         check("dv acc", dv.cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]) - 0.25, "f32")
-        dq, dq2, dk2, dv2 = torch.zeros_like(dq), torch.zeros_like(dq), torch.full_like(dk, 7.0), torch.full_like(dv, 7.0)
-        hexi.hexi_attn_bwd_chunk(*args, dq, dk, dv)  # whole: heads in two runs are a rule of calls that write dk / dv
-        hexi.hexi_attn_bwd_chunk(*args, dq2, None, None, flags=hexi.HEXI_SKIP_DKDV)
         q, d_o, k, v = wide(run.q), wide(run.d_o), wide(run.k[j]), wide(run.v[j])
-        desc = hexi.desc_for(q, k, w.scale)
-        hexi.hexi_attn_bwd_chunk(desc, w.q_segs, ch, q, k, v, None, d_o, run.lse, run.delta, None, dk2, dv2, flags=hexi.HEXI_SKIP_DQ)
-        assert torch.equal(dk2, run.dk[j]) and torch.equal(dv2, run.dv[j]) and torch.equal(dk, dk2) and torch.equal(dv, dv2) and torch.equal(dq2, dq)
+        wide_args = (hexi.desc_for(q, k, w.scale), w.q_segs, ch, q, k, v, None, d_o, run.lse, run.delta)
+        out = []
+        for a in (args, wide_args):
+            dq, dk, dv = torch.zeros_like(dq), torch.full_like(dk, 7.0), torch.full_like(dv, 7.0)
+            dq_half, dk_half, dv_half = torch.zeros_like(dq), torch.full_like(dk, 7.0), torch.full_like(dv, 7.0)
+            hexi.hexi_attn_bwd_chunk(*a, dq, dk, dv)
+            hexi.hexi_attn_bwd_chunk(*a, dq_half, None, None, flags=hexi.HEXI_SKIP_DKDV)
+            hexi.hexi_attn_bwd_chunk(*a, None, dk_half, dv_half, flags=hexi.HEXI_SKIP_DQ)
+            out.append((dq, dk, dv, dq_half, dk_half, dv_half))
+        assert all(torch.equal(x, y) for x, y in zip(*out)) and torch.equal(out[0][1], run.dk[j]) and torch.equal(out[0][2], run.dv[j])
+        check("dk alone", out[0][4].cpu(), chunk_slices(w, j, ref["dk"], ref["n_keys"]), "f32")
+        check("dv alone", out[0][5].cpu(), chunk_slices(w, j, ref["dv"], ref["n_keys"]), "f32")
+        check("dq alone", out[0][3].cpu(), to64(out[0][0].cpu()), "f32")
     o, lse = torch.full_like(run.o, float("nan")), torch.full_like(run.lse, float("nan"))
     for j, ch in enumerate(w.chunks):
         k, v = wide(run.k[j]), wide(run.v[j])

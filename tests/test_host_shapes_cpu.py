@@ -192,15 +192,15 @@ def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
 def split_operand_shapes(tmp_path_factory):
     exe = _compile(tmp_path_factory, "f32x3_check")
 
-    def ask(steps, accumulate=False, chains=False):
+    def ask(steps, accumulate=False, chains=False, halves=False):
         segs = lambda x: f"{len(x)} " + " ".join(f"{s} {n}" for s, n in x)
         lines = [f"{nq} {nkv} {d} {segs(qs)} {segs(ks)}" for d, nq, nkv, qs, ks in steps]
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         got = []
         for line in filter(None, out):
-            use, n64, tiles, *bwds, n_chains = map(int, line.split())
+            use, n64, tiles, *bwds, n_chains, q, q64, kv, kv_runs, added, added_runs = map(int, line.split())
             bwd, keys, rows64, runs = bwds[4:] if accumulate else bwds[:4]
-            got.append(n_chains if chains else ((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0,
+            got.append((q * (64 if q64 else 32), kv * kv_runs, added * added_runs) if halves else n_chains if chains else ((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0,
                                                 (64 if rows64 else 32) if bwd else 0, runs if bwd else 0))
         return got
 
@@ -212,6 +212,17 @@ def test_scores_are_summed_in_one_chain_unless_a_part_of_the_step_is_cut(split_o
     steps = [_step(*s) for s in ((5761, 130, 32, 16, 128, 130), (1264, 108, 48, 24, 128, 0), (300, 300, 4, 2, 128, 300), (1079, 162, 4, 1, 128, 162),
                                  (516, 93, 24, 8, 128, 93), (327, 161, 4, 1, 128, 161), (4096, 4096, 16, 4, 128, 4096), (4096, 4096, 24, 8, 64, 4096))]
     assert split_operand_shapes(steps, chains=True) == [1, 1, 1, 4, 4, 4, 4, 1]
+
+
+def test_an_fp32_half_by_itself_is_not_cut_where_that_is_slower(split_operand_shapes):
+    # rows of a dQ unit, units of a group of heads for dK / dV alone, and for dK / dV added to running sums (0: 16-row kernels).  us of dQ in 16-row kernels / as in
+    # the whole step: 92 / 126, 14 / 18, 13 / 19, 98 / 46, 283 / 192; of dK / dV 66 / 97, 118 / 164
+    steps = [_step(*s) for s in ((329, 1509, 24, 8, 128, 1509), (332, 138, 8, 1, 128, 138), (124, 1995, 16, 8, 128, 0), (821, 2097, 16, 2, 128, 0), (1081, 5315, 6, 2, 128, 5315),
+                                 (93, 2465, 24, 24, 128, 1232), (88, 4729, 32, 16, 128, 2364), (1000, 1000, 16, 2, 128, 0))]
+    got = split_operand_shapes(steps, halves=True)
+    assert [q for q, *_ in got[:5]] == [0, 0, 0, 32, 32] and [kv for _, kv, _ in got[5:7]] == [0, 0] and got[7] == (32, 2, 0)
+    # whole steps, us in 16-row kernels / cut: 318 / 496, 108 / 146, 664 / 620
+    assert [s[1] for s in split_operand_shapes([_step(135, 4439, 24, 24, 128, 4439), _step(93, 2465, 24, 24, 128, 1232), _step(1081, 5315, 6, 2, 128, 5315)])] == [0, 0, 32]
 
 
 def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(split_operand_shapes):
