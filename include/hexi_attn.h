@@ -142,7 +142,8 @@ int hexi_attn_merge_lse(int64_t n_rows, int32_t n_q_heads, int32_t head_dim,
  * runs of heads whose contributions are summed with floating-point atomics, whose order (and so
  * the last bits of dk/dv) can vary between runs where there are more than two runs to a group (two
  * under HEXI_ACCUMULATE).  The library cuts so where it expects to gain 15 % or more, or where the
- * launch fills the chip.  hexi_set_dkdv_run_len() overrides the run length
+ * launch fills the chip; with fp32 inputs into two runs at most, never under HEXI_ACCUMULATE, so that dk/dv
+ * stay reproducible.  hexi_set_dkdv_run_len() overrides the run length
  * chosen by the library.  HEXI_SKIP_DQ / HEXI_SKIP_DKDV
  * restrict the call to one of the two halves (which may be issued on different streams; a call for
  * both may run them in one launch, and may sum in another order than the halves by themselves); both
@@ -249,7 +250,8 @@ int hexi_sched_solve(const hexi_cluster* cluster, const hexi_model* model, const
  * Tuning / test knob of hexi_attn_bwd_chunk's dK/dV part (the GQA sum over the n_d local heads of a
  * group, Sec. 3.2): the number of q heads of one kv head that a workgroup walks into the same
  * accumulators.  0 = chosen by the library per call (the default); n >= 1 = at most n (clamped to
- * the largest group), in the 128-key workgroups also where a small launch would take smaller ones.
+ * the largest group), in the 128-key workgroups also where a small launch would take smaller ones.  With fp32
+ * inputs n >= the largest group forbids two runs to a group, and a smaller n changes nothing.
  * The initial value is read once, when the library is loaded, from the
  * environment variable HEXI_DKDV_RUN_LEN.  Process-wide; not synchronised with calls in flight on
  * other threads.  Returns the previous value.

@@ -61,7 +61,7 @@ hipError_t hexi_launch_fwd_f32(const FwdArgs& a, hipStream_t s)
 
 hipError_t hexi_launch_bwd_f32(const BwdArgs& a, hipStream_t s)
 {
-    if (const F32x3Bwd plan = hexi_f32x3_bwd(a.g, a.accumulate != 0, a.want_dq != 0, a.want_dkdv != 0); plan.use) return hexi_launch_bwd_f32x3(a, plan, s);
+    if (const F32x3Bwd plan = hexi_f32x3_bwd(a.g, a.accumulate != 0, a.want_dq != 0, a.want_dkdv != 0, hexi_dkdv_run_len); plan.use) return hexi_launch_bwd_f32x3(a, plan, s);
     F32Shape kv_shape, q_shape;
     hexi_f32_bwd_shapes(a.g, a.want_dq, a.want_dkdv, &kv_shape, &q_shape);
     auto launch = [&](F32Shape shape, bool dkdv, bool dq) {

@@ -478,7 +478,7 @@ inline F32x3Fwd hexi_f32x3_fwd_by_itself(const AttnGeom& g)
 // where dk and dv hold a running value, whose sum would show the order: the margin is wider there, 1.1 lost up to 9 % in some of the calls).
 // 128 columns, one run / two: 6000 x 800 x 8/1 heads 1888 / 1294 us, 3056 x 3000 x 6/2 703 / 701, 2048 x 2048 x 16/4 737 / 743; 16-row kernels / two
 // runs: 1500 x 2500 x 8/2 496 / 380, 777 x 1000 x 8/2 123 / 108.
-inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate)
+inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate, bool whole_groups = false)
 {
     struct Part { long long n; double mean, longest; F32Fit f; };
     const bool wide = g.d == 128;
@@ -516,7 +516,7 @@ inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate)
     consider(&kv32, &q64);
     if (!wide) consider(&kv64, &q64);
     const Part kv32_2 = halves(kv32), kv64_2 = halves(kv64);
-    if (!accumulate && group >= 2.0) {
+    if (!accumulate && !whole_groups && group >= 2.0) {
         best /= 1.03;                  // (a fixed cost of atomics that the fits do not hold)
         consider(&kv32_2, &q32);
         consider(&kv32_2, &q64);
@@ -571,9 +571,12 @@ inline F32Half hexi_f32x3_dkdv_alone(const AttnGeom& g, const F32x3Bwd& plan)
 // than the 16-row ones by themselves (us, 16-row / the whole step's: dQ of 329 rows x 1509 keys x 24 heads 92 / 126, of 124 x 1387 x 32 46 / 58, dK / dV of
 // 93 x 2465 x 24/24 with half of the keys seen 66 / 97).  A whole step wants the sum of its halves not 15 % slower: 135 x 4439 keys x 24/24, four
 // blocks of rows to a dK / dV unit, 318 / 496.
-inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate, bool want_dq = true, bool want_dkdv = true)
+// forced_run_len: hexi_set_dkdv_run_len(); there are whole groups and halves of them here, so one that holds a whole group forbids the halves.
+inline F32x3Bwd hexi_f32x3_bwd(const AttnGeom& g, bool accumulate, bool want_dq = true, bool want_dkdv = true, int forced_run_len = 0)
 {
-    F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g, accumulate);
+    int heads[HEXI_MAX_HEADS] = {}, largest = 0;
+    for (int h = 0; h < g.nq; ++h) largest = ++heads[(int)g.kv_of_q[h]] > largest ? heads[(int)g.kv_of_q[h]] : largest;
+    F32x3Bwd plan = hexi_f32x3_bwd_by_itself(g, accumulate, forced_run_len >= largest);
     if (!plan.use) return plan;
     if (g.d != 128) {
         plan.use = hexi_f32x3_at_64(g);

@@ -192,13 +192,16 @@ def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
 def split_operand_shapes(tmp_path_factory):
     exe = _compile(tmp_path_factory, "f32x3_check")
 
-    def ask(steps, accumulate=False, chains=False, halves=False):
+    def ask(steps, accumulate=False, chains=False, halves=False, forced=False):
         segs = lambda x: f"{len(x)} " + " ".join(f"{s} {n}" for s, n in x)
         lines = [f"{nq} {nkv} {d} {segs(qs)} {segs(ks)}" for d, nq, nkv, qs, ks in steps]
         out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout.split("\n")
         got = []
         for line in filter(None, out):
-            use, n64, tiles, *bwds, n_chains, q, q64, kv, kv_runs, added, added_runs = map(int, line.split())
+            use, n64, tiles, *bwds, n_chains, q, q64, kv, kv_runs, added, added_runs, runs_of_one, runs_of_all = map(int, line.split())
+            if forced:
+                got.append((runs_of_one, runs_of_all))
+                continue
             bwd, keys, rows64, runs = bwds[4:] if accumulate else bwds[:4]
             got.append((q * (64 if q64 else 32), kv * kv_runs, added * added_runs) if halves else n_chains if chains else ((32 if n64 == 0 else 64 if n64 == tiles else 96) if use else 0, keys if bwd else 0,
                                                 (64 if rows64 else 32) if bwd else 0, runs if bwd else 0))
@@ -212,6 +215,12 @@ def test_scores_are_summed_in_one_chain_unless_a_part_of_the_step_is_cut(split_o
     steps = [_step(*s) for s in ((5761, 130, 32, 16, 128, 130), (1264, 108, 48, 24, 128, 0), (300, 300, 4, 2, 128, 300), (1079, 162, 4, 1, 128, 162),
                                  (516, 93, 24, 8, 128, 93), (327, 161, 4, 1, 128, 161), (4096, 4096, 16, 4, 128, 4096), (4096, 4096, 24, 8, 64, 4096))]
     assert split_operand_shapes(steps, chains=True) == [1, 1, 1, 4, 4, 4, 4, 1]
+
+
+def test_a_forced_run_of_a_whole_group_holds_for_fp32_steps(split_operand_shapes):
+    from parity_util import F32X3_STEPS
+    two = [s for s, (*_, runs) in F32X3_STEPS if runs == 2]
+    assert len(two) > 3 and set(split_operand_shapes([_step(lq, lc, nq, nkv, d, lc) for lq, lc, nq, nkv, d in two], forced=True)) == {(2, 1)}
 
 
 def test_an_fp32_half_by_itself_is_not_cut_where_that_is_slower(split_operand_shapes):
