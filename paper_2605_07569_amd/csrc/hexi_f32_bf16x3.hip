@@ -332,8 +332,9 @@ template <class C, class F> __device__ __forceinline__ void scores(f32x16 (&s)[C
 }
 
 // acc[n][j], register 4 b + t: column NJ (8 b + 4 hh + t) + j of stationary row 32 n + l; p[n]: probabilities or dS as scores() leaves its results.
-// APART: the block's sum by itself, then added, for the long chains of dK / dV: one rounding of the running value in 32 rows instead of 12 (the backward
-// 4 % slower; dv of 3643 rows of 4 heads 1.1 times as far from fp64 as with hexi_f32.hip without it, 0.43 times with it).
+// APART: the block's sum by itself, then added, for dK / dV and for long chains of the others: one rounding of the running value in 32 rows instead of 12.
+// Against the fp32 instruction, error without / with it: dv of 3643 rows of 4 heads 1.1 / 0.43, o of 12000 keys x 128 columns 1.13 / 0.37, of 5000 keys
+// x 64 1.06 / 0.4.  A backward is 4 % slower with it in dK / dV, a forward 5 %.
 template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB], float& top)
 {
     constexpr int NB = C::NB;
@@ -477,7 +478,7 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
     const Log2Scale c(g.scale);
-    float top = 0.f;
+    float v_top = 0.f;
     put_stationary<C>(sm.t.q, static_cast<const float*>(a.q) + (long long)h * g.q_stride_head, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
     const unsigned char* stat = sm.t.q + 16 * lane;
@@ -490,48 +491,53 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
 #pragma unroll
     for (int n = 0; n < NB; ++n) { ref[n] = 0.f; limit[n] = -INFINITY; l_run[n] = 0.f; }
 
-    for (; b < n_blocks; b += NW) {
-        f32x16 s[NB];
-        ColBlock<C> vc;
-        landed<0>();
-        vc.load(v, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
-        __builtin_amdgcn_sched_barrier(0);
-        scores<C>(s, rows, slot, stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
-        __builtin_amdgcn_sched_barrier(0);
-        if (C::BLK * b + C::BLK > n_full) {
+    auto walk = [&](auto apart) {
+        for (; b < n_blocks; b += NW) {
+            f32x16 s[NB];
+            ColBlock<C> vc;
+            landed<0>();
+            vc.load(v, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
+            __builtin_amdgcn_sched_barrier(0);
+            scores<C>(s, rows, slot, stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
+            __builtin_amdgcn_sched_barrier(0);
+            if (C::BLK * b + C::BLK > n_full) {
 #pragma unroll
-            for (int n = 0; n < NB; ++n)
+                for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = -INFINITY;
-        }
+                    for (int r = 0; r < 16; ++r)
+                        if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = -INFINITY;
+            }
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            float mx = max3(s[n][0], s[n][1], s[n][2]);
+            for (int n = 0; n < NB; ++n) {
+                float mx = max3(s[n][0], s[n][1], s[n][2]);
 #pragma unroll
-            for (int r = 3; r < 15; r += 2) mx = max3(mx, s[n][r], s[n][r + 1]);
-            mx = max2(mx, s[n][15]);
-            if (__any(mx > limit[n])) {
-                const float top = max_across_halves(mx);
-                if (top > limit[n]) {
-                    const float to = top * c.hi, alpha = limit[n] == -INFINITY ? 0.f : fast_exp2(ref[n] - to);
-                    ref[n] = to;
-                    limit[n] = top + slack;
-                    l_run[n] *= alpha;
+                for (int r = 3; r < 15; r += 2) mx = max3(mx, s[n][r], s[n][r + 1]);
+                mx = max2(mx, s[n][15]);
+                if (__any(mx > limit[n])) {
+                    const float top = max_across_halves(mx);
+                    if (top > limit[n]) {
+                        const float to = top * c.hi, alpha = limit[n] == -INFINITY ? 0.f : fast_exp2(ref[n] - to);
+                        ref[n] = to;
+                        limit[n] = top + slack;
+                        l_run[n] *= alpha;
 #pragma unroll
-                    for (int i = 0; i < C::NJ; ++i) acc[n][i] *= alpha;
+                        for (int i = 0; i < C::NJ; ++i) acc[n][i] *= alpha;
+                    }
                 }
-            }
-            float part[4];
+                float part[4];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                s[n][r] = fast_exp2(fmaf(s[n][r], c.lo, fmaf(s[n][r], c.hi, -ref[n])));
-                part[r & 3] = r < 4 ? s[n][r] : part[r & 3] + s[n][r];
+                for (int r = 0; r < 16; ++r) {
+                    s[n][r] = fast_exp2(fmaf(s[n][r], c.lo, fmaf(s[n][r], c.hi, -ref[n])));
+                    part[r & 3] = r < 4 ? s[n][r] : part[r & 3] + s[n][r];
+                }
+                l_run[n] += (part[0] + part[1]) + (part[2] + part[3]);
             }
-            l_run[n] += (part[0] + part[1]) + (part[2] + part[3]);
+            accumulate<C, decltype(apart)::value>(acc, vc, s, v_top);
         }
-        accumulate<C, false>(acc, vc, s, top);
-    }
+    };
+    // the sums of o: 16 columns of 32 keys round 12 times, and a chain of more than about 2600 (7000) keys would end further from fp64 than in the 16-row units
+    if (n_vis > (D == 64 ? 2048 : 5120)) walk(std::true_type{});
+    else walk(std::false_type{});
 
     // Combine the splits and merge with the running (o, lse): weights per (row, split), then a row-contiguous pass.
     unsigned odd = g.scale >= 1048576.f;
@@ -541,7 +547,7 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
         l_run[n] = sum_across_halves(l_run[n]);
         odd |= (unsigned)!(l_run[n] < INFINITY);
     }
-    top = largest_of_wave(top);
+    v_top = largest_of_wave(v_top);
     __syncthreads();              // the operands are free
     stage_rows<C>(&sm.e.stage[wave * ROWS * C::PITCH], acc, lane, 1.0f);
     if (hh == 0) {
@@ -552,14 +558,14 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
         }
     }
     const int tid = threadIdx.x;
-    if (lane == 0) sm.e.top[wave] = top;
+    if (lane == 0) sm.e.top[wave] = v_top;
     __syncthreads();
     float lse_new = 0.f;
     if (tid < ROWS) lse_new = combine_rows<ROWS, NW>(a, h, row0, tid, sm.e.m, sm.e.l, sm.e.w, sm.e.wa);
     __syncthreads();
-    top = largest_of_workgroup(sm.e.top);
-    odd |= too_small(top);
-    const float least = CUT_LOSS * (float)n_vis * (256.f + top);      // (the probabilities' largest is 2^8)
+    v_top = largest_of_workgroup(sm.e.top);
+    odd |= too_small(v_top);
+    const float least = CUT_LOSS * (float)n_vis * (256.f + v_top);      // (the probabilities' largest is 2^8)
     constexpr int PARTS = ROWS * D / 4 / (64 * NW);
     f32x4 out[PARTS];
     Extremes ends;
@@ -650,7 +656,7 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
     const long long q_off = (long long)h * g.q_stride_head;
-    float ds_top = 0.f, top = 0.f;
+    float ds_top = 0.f, k_top = 0.f;
     put_stationary<C>(sm.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     put_stationary<C>(sm.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
@@ -658,53 +664,57 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
 
     f32x16 acc[NB][C::NJ];
     zero_acc<C>(acc);
-    for (; b < n_blocks; b += NW) {
-        f32x16 s[NB], dp[NB];
-        ColBlock<C> kc;
-        landed<0>();
-        scores<C>(s, rows, slot, q_stat, [&]() { rows.request(v, g.kv_stride_tok, C::BLK * b, g.lc, lane); });
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[n][r] = probability(s[n][r], c, nl_hi[n], nl_lo[n]);
-        landed<0>();
-        kc.load(k, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
-        __builtin_amdgcn_sched_barrier(0);
-        scores<C>(dp, rows, slot, g_stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[n][r] *= dp[n][r] - delta[n];
-        if (C::BLK * b + C::BLK > n_full) {
+    auto walk = [&](auto apart) {
+        for (; b < n_blocks; b += NW) {
+            f32x16 s[NB], dp[NB];
+            ColBlock<C> kc;
+            landed<0>();
+            scores<C>(s, rows, slot, q_stat, [&]() { rows.request(v, g.kv_stride_tok, C::BLK * b, g.lc, lane); });
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = 0.f;
+                for (int r = 0; r < 16; ++r) s[n][r] = probability(s[n][r], c, nl_hi[n], nl_lo[n]);
+            landed<0>();
+            kc.load(k, g.kv_stride_tok, C::BLK * b, g.lc, hh, l32);
+            __builtin_amdgcn_sched_barrier(0);
+            scores<C>(dp, rows, slot, g_stat, [&]() { if (b + NW < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * (b + NW), g.lc, lane); });
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[n][r] *= dp[n][r] - delta[n];
+            if (C::BLK * b + C::BLK > n_full) {
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (C::BLK * b + 8 * (r / 4) + 4 * hh + r % 4 >= vis[n]) s[n][r] = 0.f;
+            }
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, s[n][r], s[n][r + 1]);
+            accumulate<C, decltype(apart)::value>(acc, kc, s, k_top);
         }
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, s[n][r], s[n][r + 1]);
-        accumulate<C, false>(acc, kc, s, top);
-    }
+    };
+    if (n_vis > 64 * D) walk(std::true_type{});            // (dq of the 16-row units rounds more often in its scores: 8000 and 13000 keys)
+    else walk(std::false_type{});
     unsigned odd = g.scale >= 1048576.f;
     stationary_range<C>(sm.t[0], wave, lane, odd);
     float g_top = largest_of_wave(stationary_range<C>(sm.t[1], wave, lane, odd));
-    top = largest_of_wave(top);
+    k_top = largest_of_wave(k_top);
     ds_top = largest_of_wave(ds_top);
     __syncthreads();
     stage_rows<C>(&sm.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
     const int tid = threadIdx.x;
-    if (lane == 0) { sm.top[0][wave] = top; sm.top[1][wave] = g_top; sm.top[2][wave] = ds_top; }
+    if (lane == 0) { sm.top[0][wave] = k_top; sm.top[1][wave] = g_top; sm.top[2][wave] = ds_top; }
     __syncthreads();
-    top = largest_of_workgroup(sm.top[0]);
+    k_top = largest_of_workgroup(sm.top[0]);
     g_top = largest_of_workgroup(sm.top[1]);
     ds_top = largest_of_workgroup(sm.top[2]);
-    odd |= too_small(ds_top) | too_small(top);
-    const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top + top) + SCORE_LOSS * g_top * top);
+    odd |= too_small(ds_top) | too_small(k_top);
+    const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top + k_top) + SCORE_LOSS * g_top * k_top);
     constexpr int PARTS = ROWS * D / (64 * NW);
     float out[PARTS];             // consecutive lanes on consecutive floats
     Extremes ends;

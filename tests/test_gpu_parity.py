@@ -1076,6 +1076,22 @@ def test_f32_split_operands_with_infinite_values(lq, lc, nq, nkv, d):
     assert (o[rows][..., 0] == inf).all() and (o[rows][..., 1] == -inf).all() and o[rows][..., 2:4].isnan().all() and o[7].isnan().all()
 
 
+@pytest.mark.parametrize("lq,lc,nq,nkv,d,limit", [(579, 5000, 8, 2, 64, 5.2e-7), (338, 12000, 12, 3, 128, 7.8e-7)])
+def test_f32_long_rows_are_no_further_from_float64_where_operands_are_cut(lq, lc, nq, nkv, d, limit):
+    # o of rows that see many keys: relative errors on the fp32 instruction 5.3e-7 and 8.0e-7 (1.5 % between seeds), cut with one chain of sums 5.7e-7 and 9.1e-7
+    g = torch.Generator().manual_seed(lc)
+    q, k, v = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv)))
+    scale = float(np.float32(d ** -0.5))
+    o, lse = torch.empty((lq, nq, d), device=DEV), torch.empty((nq, lq), device=DEV)
+    t = [x.to(DEV) for x in (q, k, v)]
+    hexi.hexi_attn_fwd_chunk(hexi.desc_for(t[0], t[1], scale), [(lc, lq)], [(0, lc)], *t, o, lse)
+    rows = slice(0, lq, 8)
+    o_ref, lse_ref = oracle.attn_fwd(to64(q[rows]), np.arange(lc, lc + lq)[rows], to64(k), to64(v), np.arange(lc), scale)
+    _, rel = check("o", o[rows].cpu(), o_ref, "f32")
+    check("lse", lse[:, rows].cpu(), lse_ref, "f32")
+    assert rel < limit
+
+
 def _f32_step(q, k, v, d_o, off, scale, merged=False):
     """o, lse, dq, dk, dv of one fp32 step, rows from `off` against keys from 0; merged: o / lse into an empty running result, dk / dv added to zeros."""
     lq, lc = q.shape[0], k.shape[0]
