@@ -140,7 +140,18 @@ F32X3_STEPS = [((1079, 162, 4, 1, 128), (32, 32, 32, 2)), ((868, 112, 16, 8, 128
                ((516, 93, 24, 8, 128), (64, 0, 0, 0)), ((523, 882, 9, 3, 128), (32, 32, 64, 2)), ((172, 196, 48, 16, 128), (64, 32, 64, 1)),
                ((726, 224, 24, 24, 128), (96, 32, 64, 1)), ((327, 161, 4, 1, 128), (0, 32, 32, 2)), ((625, 231, 24, 24, 128), (64, 32, 64, 1)),
                ((651, 577, 8, 8, 64), (32, 32, 64, 1)), ((91, 611, 48, 16, 64), (32, 64, 64, 1)), ((113, 814, 96, 24, 64), (64, 64, 64, 1)),
-               ((693, 755, 24, 24, 64), (96, 64, 64, 1)), ((1196, 203, 32, 32, 64), (0, 0, 0, 0))]
+               ((693, 755, 24, 24, 64), (96, 64, 64, 1)), ((1196, 203, 32, 32, 64), (0, 0, 0, 0)),
+               ((68, 151, 32, 32, 128), (0, 32, 32, 1)), ((53, 171, 48, 24, 128), (0, 32, 32, 1)), ((753, 16, 32, 32, 128), (0, 0, 0, 0)),
+               ((820, 434, 32, 32, 128), (64, 32, 64, 1))]
+# Those whose dk / dv are added to running sums by these kernels at head_dim 128: with all keys visible, in the diagonal chunk.
+F32X3_ADDED = [(68, 151, 32, 32, 128), (53, 171, 48, 24, 128), (820, 434, 32, 32, 128)], [(753, 16, 32, 32, 128), (820, 434, 32, 32, 128)]
+
+# fp32 steps that stay with the 16-row kernels at head_dim 128, rows from the middle of the keys: (lq, lc, nq, nkv), shapes of dQ and of dK / dV (0: 64 rows, shared;
+# 1: 16 rows, split), chains of a score.
+F32_128_STEPS = [((196, 199, 64, 64), (0, 0), 4), ((199, 16, 64, 32), (0, 1), 1), ((400, 43, 32, 16), (0, 1), 4), ((16, 266, 96, 48), (1, 0), 1), ((49, 256, 128, 64), (1, 0), 4),
+                 ((70, 100, 2, 1), (1, 1), 1), ((513, 174, 8, 4), (1, 1), 4)]
+# Others that are cut, forward and backward, rows from the middle of the keys: keys of a dK / dV unit, rows of a dQ unit, units to a group.
+F32X3_MIDDLE_STEPS = [((685, 178, 6, 3, 128), (32, 32, 2)), ((625, 231, 24, 24, 128), (32, 64, 1)), ((871, 1364, 16, 16, 64), (64, 64, 1))]
 
 
 def f32x3_diagonal(lq, lc):

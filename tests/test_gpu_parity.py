@@ -12,7 +12,7 @@ import torch
 import oracle
 from paper_2605_07569_amd import hexi, replay
 from paper_2605_07569_amd import workloads as wl
-from parity_util import (F32_STEPS, F32X3_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
+from parity_util import (F32_128_STEPS, F32_STEPS, F32X3_MIDDLE_STEPS, F32X3_STEPS, LARGE_SHARD, LARGE_STEPS, ORDER_STEPS, PART_ROUND_STEPS, QUAD_DQ_STEPS, QUAD_FWD_STEPS, QUAD_SHARD, QUAD_STEPS,
                          SHARED_SHARD, SHARED_STEPS, UNSEEN_STEPS, WIDE_DQ_STEPS, check, chunk_slices, f32x3_diagonal, oracle_full, to64)
 
 pytestmark = pytest.mark.gpu
@@ -477,11 +477,11 @@ def test_measured_compute_rate_feeds_the_scheduler():
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 1, 1, 1), (2, 2, 15, 17), (3, 1, 16, 128), (2, 1, 17, 129), (2, 1, 129, 15), (4, 2, 300, 257), (16, 16, 1000, 1010)])
+@pytest.mark.parametrize("nq,nkv,lq,lc", [(2, 1, 1, 1), (2, 2, 15, 17), (3, 1, 16, 128), (2, 1, 17, 129), (2, 1, 129, 15), (4, 2, 300, 257), (16, 16, 1000, 1010), (64, 32, 199, 16), (96, 48, 16, 266)])
 def test_f32_workgroup_shapes(nq, nkv, lq, lc, d):
-    # lengths at the edges of the fp32 kernels' 16-row blocks and 128-row (split) / 32-row (shared) tiles; the last size
-    # is dealt to the shared shape (256 workgroups of 64 rows) at head_dim 128 and to two split workgroups a CU at 64, the others to the
-    # split one.  The second chunk is diagonal.
+    # lengths at the edges of the fp32 kernels' 16-row blocks and 128-row (split) / 32-row (shared) tiles; 1000 rows are dealt to the split-operand
+    # kernels at head_dim 128 and to two split workgroups a CU at 64, at 128 the forward and dQ of 199 rows and dK / dV of 266 keys are shared, the others
+    # split.  The second chunk is diagonal.
     w = _custom(f"f32_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
     run, inputs, ref = _run_and_compare(w, seed=lq * 1000 + lc + d)
     # dk / dv under HEXI_ACCUMULATE: the running value plus the gradient; dq_acc adds up over calls
@@ -604,10 +604,14 @@ def test_bf16_dq_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
     assert torch.all(dq.permute(1, 0, 2)[~torch.isfinite(lse)] == 0)
 
 
+# fp32 steps in every shape at head_dim 128 and in the split-operand kernels (asserted on the CPU), rows from the middle of the keys
+F32_MIDDLE_SIZES = [s + (128,) for s, *_ in F32_128_STEPS[:5]] + [s for s, _ in F32X3_MIDDLE_STEPS]
+
+
 @pytest.mark.parametrize("dead", [-float("inf"), float("inf")])
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)] + F32_MIDDLE_SIZES)
 def test_f32_backward_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
-    # the same in fp32, in both workgroup shapes, dk and dv included
+    # the same in fp32, in every workgroup shape of the 16-row kernels and in the split-operand ones, dk and dv included
     (q, k, v, d_o, lse, delta), qs, ks, scale, ref = _infinite_lse_case("f32", lq, lc, nq, nkv, d, dead)
     dq, dk, dv = torch.zeros((lq, nq, d), device=DEV), torch.empty((lc, nkv, d), device=DEV), torch.empty((lc, nkv, d), device=DEV)
     print(f"\n  infinite LSE: f32 {lq} x {lc} x {nq}/{nkv} x {d}", flush=True)
@@ -618,7 +622,7 @@ def test_f32_backward_of_rows_with_an_infinite_lse(lq, lc, nq, nkv, d, dead):
 
 
 @pytest.mark.parametrize("scale", [64 ** -0.5, 128 ** -0.5, 0.1, 0.05, 1.0])
-@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)])
+@pytest.mark.parametrize("lq,lc,nq,nkv,d", [(70, 100, 2, 1, 128), (70, 100, 2, 1, 64), (1000, 1010, 16, 16, 128), (1000, 1010, 16, 16, 64)] + F32_MIDDLE_SIZES)
 def test_f32_scores_that_overflow_downwards(lq, lc, nq, nkv, d, scale):
     # every seventh key's score is -1e40, i.e. -inf in fp32: the key weighs nothing, forward and backward, whatever the sign of
     # the low half of scale * log2(e)
@@ -816,12 +820,12 @@ def _dq_residuals(lq, lc, nq, nkv, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("nq,nkv,lq,lc", [(16, 2, 1000, 1010), (32, 16, 1000, 1010), (16, 16, 100, 1010), (6, 3, 77, 90)])
+@pytest.mark.parametrize("nq,nkv,lq,lc", [(16, 2, 1000, 1010), (32, 16, 1000, 1010), (16, 16, 100, 1010), (6, 3, 77, 90), (64, 32, 199, 16), (96, 48, 16, 266)])
 def test_f32_grouped_heads_in_both_shapes(nq, nkv, lq, lc, d):
-    # fp32 with several q heads per kv head: at head_dim 128 dQ in 64-row shared and dK / dV in 16-row split workgroups (two launches), both
-    # shared, the other way round, both split; at 64 split, two of them a CU in the second size, and dK / dV shared in the first chunk of the third
-    # (test_f32_shapes_at_head_dim_64 has the others).  The halves together and in calls of their own, with the same bits (no sum is
-    # spread over workgroups)
+    # fp32 with several q heads per kv head: at head_dim 128 operands cut in the diagonal chunk of the first size, heads in two runs, and in both of the
+    # second, dK / dV shared in 64-key workgroups in the third's and the last's first chunk, dQ in 64-row ones in 199 rows, the rest split; at 64 split, two of
+    # them a CU in the second size, and dK / dV shared in the first chunk of the third (test_f32_shapes_at_head_dim_64 has the others).  The halves
+    # together and in calls of their own, with the same bits: no sum is spread over more than two workgroups
     w = _custom(f"f32_gqa_{nq}_{lq}_{lc}_{d}", "f32", nq, nkv, d, lc + lq, [(lc, lq)], [[(0, lc)], [(lc, lq)]])
     run, inputs, ref = _run_and_compare(w, seed=lq + lc + d)
     dq = torch.zeros_like(run.dq)
@@ -1038,7 +1042,7 @@ def test_f32_split_operand_shapes(step, _):
 
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", [(172, 196, 48, 16, 128), (868, 112, 16, 8, 128), (651, 577, 8, 8, 64)])
 def test_f32_split_operands_at_the_ends_of_the_range(lq, lc, nq, nkv, d):
-    # q near the largest fp32 value (cut, not rounded: no piece is infinite), columns of v of 1e33 and 1e-30, scores whose upper product is -inf
+    # q near the largest fp32 value, columns of v of 1e33 and 1e-30, scores of -inf: left to the units on the fp32 instruction
     g = torch.Generator().manual_seed(lq)
     q, k, v, d_o = (torch.randn((n, h, d), generator=g) for n, h in ((lq, nq), (lc, nkv), (lc, nkv), (lq, nq)))
     v[..., 0] *= 1e33

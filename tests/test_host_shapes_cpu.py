@@ -171,6 +171,7 @@ def test_a_shared_forward_step_covers_every_row_once(tmp_path_factory):
 
 
 def test_f32_steps_take_the_shapes_they_are_meant_for(shapes):
+    # (the rule of the 16-row kernels, which a step that goes to the split-operand ones does not come to)
     from parity_util import F32_STEPS
     got = shapes([_step(lq, lc, nq, nkv, 64, off) for (lq, lc, nq, nkv, off), _ in F32_STEPS])
     assert [(g["f32_fwd"], g["f32_dq"], g["f32_dkdv"], g["f32_dq_alone"]) for g in got] == [s for _, s in F32_STEPS]
@@ -223,6 +224,17 @@ def test_a_forced_run_of_a_whole_group_holds_for_fp32_steps(split_operand_shapes
     assert len(two) > 3 and set(split_operand_shapes([_step(lq, lc, nq, nkv, d, lc) for lq, lc, nq, nkv, d in two], forced=True)) == {(2, 1)}
 
 
+def test_fp32_steps_that_stay_with_the_16_row_kernels_at_head_dim_128(shapes, split_operand_shapes):
+    from parity_util import F32_128_STEPS
+    steps = [_step(lq, lc, nq, nkv, 128, lc // 2) for (lq, lc, nq, nkv), *_ in F32_128_STEPS]
+    assert [(g["f32_dq"], g["f32_dkdv"]) for g in shapes(steps)] == [s for _, s, _ in F32_128_STEPS]
+    assert [b for _, b, *_ in split_operand_shapes(steps)] == [0] * len(steps) and split_operand_shapes(steps, chains=True) == [n for *_, n in F32_128_STEPS]
+    # the forward of all visible keys: 64-row workgroups, split operands, 64-row ones beside a cut backward, 16-row ones
+    steps = [_step(lq, lc, nq, nkv, 128, lc) for lq, lc, nq, nkv in ((199, 16, 64, 32), (1000, 1010, 16, 16), (404, 16, 32, 8), (100, 1010, 16, 16))]
+    assert [f[0] and "cut" or g["f32_fwd"] for f, g in zip(split_operand_shapes(steps), shapes(steps))] == [0, "cut", 0, 1]
+    assert split_operand_shapes(steps, chains=True) == [1, 4, 4, 1]
+
+
 def test_an_fp32_half_by_itself_is_not_cut_where_that_is_slower(split_operand_shapes):
     # rows of a dQ unit, units of a group of heads for dK / dV alone, and for dK / dV added to running sums (0: 16-row kernels).  us of dQ in 16-row kernels / as in
     # the whole step: 92 / 126, 14 / 18, 13 / 19, 98 / 46, 283 / 192; of dK / dV 66 / 97, 118 / 164
@@ -235,12 +247,18 @@ def test_an_fp32_half_by_itself_is_not_cut_where_that_is_slower(split_operand_sh
 
 
 def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(split_operand_shapes):
-    from parity_util import F32X3_STEPS, f32x3_diagonal
+    from parity_util import F32X3_ADDED, F32X3_MIDDLE_STEPS, F32X3_STEPS, f32x3_diagonal
     ask = split_operand_shapes
     assert ask([_step(lq, lc, nq, nkv, d, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS]) == [s for _, s in F32X3_STEPS]
+    # sums added to
+    visible, diagonal = F32X3_ADDED
+    assert all(b > 0 for _, b, *_ in ask([_step(lq, lc, nq, nkv, d, lc) for lq, lc, nq, nkv, d in visible], accumulate=True))
+    assert all(b > 0 for _, b, *_ in ask([(d, nq, nkv) + f32x3_diagonal(lq, lc) for lq, lc, nq, nkv, d in diagonal], accumulate=True))
     # masked blocks: diagonal chunks as well, forward and backward, with units of 32 and of 64
     diagonal = ask([(d, nq, nkv) + f32x3_diagonal(lq, lc) for (lq, lc, nq, nkv, d), _ in F32X3_STEPS])
     assert [diagonal[i] for i in (0, 7, 8, 13)] == [(0, 32, 32, 2), (0, 32, 32, 2), (64, 32, 64, 1), (64, 64, 64, 1)]
+    middle = ask([_step(lq, lc, nq, nkv, d, lc // 2) for (lq, lc, nq, nkv, d), _ in F32X3_MIDDLE_STEPS])
+    assert all(f > 0 for f, *_ in middle) and [tuple(b) for _, *b in middle] == [s for _, s in F32X3_MIDDLE_STEPS]
     # us measured before / with the split-operand kernels: forward 1163 / 770, 295 / 213, 164 / 113; backward 3641 / 3021, 863 / 725, 493 / 394; 79 / 100
     # forward of 100 rows; 17 / 23 and 43 / 48 of 1024 at head_dim 64
     taken = ask([_step(4096, 4096, 16, 4, 128, 4096), _step(3056, 3000, 6, 2, 128, 3000), _step(4096, 4096, 8, 8, 64, 0),
