@@ -151,7 +151,7 @@ F32X3_ADDED = [(68, 151, 32, 32, 128), (53, 171, 48, 24, 128), (820, 434, 32, 32
 F32_128_STEPS = [((196, 199, 64, 64), (0, 0), 4), ((199, 16, 64, 32), (0, 1), 1), ((400, 43, 32, 16), (0, 1), 4), ((16, 266, 96, 48), (1, 0), 1), ((49, 256, 128, 64), (1, 0), 4),
                  ((70, 100, 2, 1), (1, 1), 1), ((513, 174, 8, 4), (1, 1), 4)]
 # Others that are cut, forward and backward, rows from the middle of the keys: keys of a dK / dV unit, rows of a dQ unit, units to a group.
-F32X3_MIDDLE_STEPS = [((685, 178, 6, 3, 128), (32, 32, 2)), ((625, 231, 24, 24, 128), (32, 64, 1)), ((871, 1364, 16, 16, 64), (64, 64, 1))]
+F32X3_MIDDLE_STEPS = [((685, 178, 6, 3, 128), (32, 32, 2)), ((347, 270, 16, 16, 128), (32, 64, 1)), ((871, 1364, 16, 16, 64), (64, 64, 1))]
 
 
 def f32x3_diagonal(lq, lc):

@@ -1110,7 +1110,7 @@ def _f32_step(q, k, v, d_o, off, scale, merged=False):
 
 # (the kernels that cut operands, forward and backward: with heads in two runs, with 64-row units, at head_dim 64 with 32 and 64 keys)
 F32X3_VALUE_STEPS = [(523, 882, 9, 3, 128), (172, 196, 48, 16, 128), (651, 577, 8, 8, 64), (693, 755, 24, 24, 64)]
-F32X3_MASKED_STEPS = [(568, 167, 8, 2, 128), (625, 231, 24, 24, 128), (635, 1158, 24, 24, 64)]      # (rows from the middle of the keys)
+F32X3_MASKED_STEPS = [(568, 167, 8, 2, 128), (347, 270, 16, 16, 128), (625, 231, 24, 24, 128), (635, 1158, 24, 24, 64)]      # (rows from the middle of the keys)
 
 
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_VALUE_STEPS)
