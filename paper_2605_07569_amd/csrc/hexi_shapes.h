@@ -439,7 +439,7 @@ inline void hexi_f32_bwd_shapes(const AttnGeom& g, bool want_dq, bool want_dkdv,
 // fitted to 300 random calls of 60 to 7000 rows and keys and 1 to 32 heads (90 % of them within 12 %; the 16-row fit stands for all shapes of
 // those kernels, 90 % within 25 %).  Over 320 other random calls, geometric mean of the time before / after at head_dim 128: forward 1.19, whole
 // backward 1.11, under HEXI_ACCUMULATE 1.05; at 64, where few take them, 1.04, 1.02, 1.02.  us before / after, all keys visible: 4096 x 4096 x 16/4
-// heads x 128 forward 1163 / 770, backward 3641 / 3021; 3056 x 3000 x 6/2 x 128 295 / 213, 863 / 725; the other way round
+// heads x 128 forward 1139 / 759, backward 3634 / 3049; 3056 x 3000 x 6/2 x 128 295 / 215, 865 / 740; the other way round
 // 100 x 4000 x 8/2 x 128 forward 79 / 100, dQ 107 / 149, 777 x 1000 x 8/2 x 128 dK / dV with heads in one run 118 / 170.
 struct F32Fit { double launch, unit, per_k; };
 struct F32x3Fwd { bool use = false; int n64 = 0; };                                     // the last n64 64-row tiles (of all heads) as such, the others as two units
@@ -477,7 +477,7 @@ inline F32x3Fwd hexi_f32x3_fwd_by_itself(const AttnGeom& g)
 // A few long dK / dV units are what such a launch waits for: the heads of a group may be dealt to two of them, which add to cleared elements (not
 // where dk and dv hold a running value, whose sum would show the order: the margin is wider there, 1.1 lost up to 9 % in some of the calls).
 // 128 columns, one run / two: 6000 x 800 x 8/1 heads 1888 / 1294 us, 3056 x 3000 x 6/2 703 / 701, 2048 x 2048 x 16/4 737 / 743; 16-row kernels / two
-// runs: 1500 x 2500 x 8/2 496 / 380, 777 x 1000 x 8/2 123 / 108.
+// runs: 1500 x 2500 x 8/2 492 / 403, 777 x 1000 x 8/2 126 / 113.
 inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate, bool whole_groups = false)
 {
     struct Part { long long n; double mean, longest; F32Fit f; };
@@ -506,27 +506,26 @@ inline F32x3Bwd hexi_f32x3_bwd_by_itself(const AttnGeom& g, bool accumulate, boo
         }
         return launch + (n <= 256 ? longest : std::fmax(longest, sum / 256.0 + tail * longest));
     };
-    F32x3Bwd plan;
-    const Part *kv = &kv32, *q = &q32;
-    double best = us(kv, q, 0.35);
-    auto consider = [&](const Part* k2, const Part* q2) {
-        const double t = us(k2, q2, 0.35);
-        if (t < best) { best = t; kv = k2; q = q2; }
+    // the best units for a number of runs to a group
+    struct Choice { double us; int key_blocks; bool rows64; };
+    auto best_of = [&](const Part& k32, const Part& k64) {
+        Choice best{us(&k32, &q32, 0.35), 1, false};
+        if (const double t = us(&k32, &q64, 0.35); t < best.us) best = {t, 1, true};
+        if (const double t = wide ? best.us : us(&k64, &q64, 0.35); t < best.us) best = {t, 2, true};
+        return best;
     };
-    consider(&kv32, &q64);
-    if (!wide) consider(&kv64, &q64);
-    const Part kv32_2 = halves(kv32), kv64_2 = halves(kv64);
+    F32x3Bwd plan;
+    Choice best = best_of(kv32, kv64);
     if (!accumulate && !whole_groups && group >= 2.0) {
-        best /= 1.03;                  // (a fixed cost of atomics that the fits do not hold)
-        consider(&kv32_2, &q32);
-        consider(&kv32_2, &q64);
-        if (!wide) consider(&kv64_2, &q64);
-        if (kv != &kv32_2 && kv != &kv64_2) best *= 1.03;
+        const Choice two = best_of(halves(kv32), halves(kv64));
+        if (1.03 * two.us < best.us) {      // (a fixed cost of atomics that the fits do not hold)
+            best = two;
+            plan.runs = 2;
+        }
     }
-    plan.runs = kv == &kv32_2 || kv == &kv64_2 ? 2 : 1;
-    plan.key_blocks = kv == &kv64 || kv == &kv64_2 ? 2 : 1;
-    plan.rows64 = q == &q64;
-    plan.use = (!wide ? 1.15 : accumulate ? 1.25 : 1.1) * best < us(&kv16, &q16, wide ? 0.1 : 0.0);
+    plan.key_blocks = best.key_blocks;
+    plan.rows64 = best.rows64;
+    plan.use = (!wide ? 1.15 : accumulate ? 1.25 : 1.1) * best.us < us(&kv16, &q16, wide ? 0.1 : 0.0);
     return plan;
 }
 
