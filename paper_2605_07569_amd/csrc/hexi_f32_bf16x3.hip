@@ -1,13 +1,14 @@
 // fp32 attention with its products on the bf16 matrix instructions: every fp32 operand is cut into three bf16 values whose sum it is exactly (24 bits
-// in 8 + 8 + 8), and of the nine products of two cut operands the six that reach above 2^-24 of their product are added up in fp32.  A bf16
-// product is exact in fp32, v_mfma_f32_32x32x16_bf16 keeps denormals and its sums are rounded without bias (0.41 ulp rms over random
-// operands, v_mfma_f32_16x16x4_f32 0.54), so the results are no further from fp64 than those of the fp32 instruction (hexi_f32.hip), which rounds
-// more often: relative errors of o, dq, dk, dv at 4096 rows x 4096 keys x 16/4 heads x 128 1.2e-6, 1.4e-6, 2.4e-6, 2.4e-6 with it alone, 5e-7,
-// 7e-7, 5e-7, 5e-7 here; over 37 shapes of 256 to 6000 rows and keys, K scaled by 1 and by 3, no output is further off than before.
-// Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: the forward and dQ, 64 rows at a time, execute 1.1 PFLOP/s in
-// bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
-// the same card); dK / dV, with four splits of streamed operands for two, 0.9.  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here:
-// forward 1163 / 770, dQ 1554 / 1096, dK / dV 2366 / 1938; 4096 diagonal x 8 heads x 64, forward and backward: 164 / 113, 493 / 394.
+// in 8 + 8 + 8), and the six largest of the nine products of two cut operands are added up in fp32.  A bf16 product is exact in fp32; the three left out are up
+// to 2^-22 of the whole one (2^-25.4 rms), of either sign.  v_mfma_f32_32x32x16_bf16 keeps denormals and rounds its sums without bias (0.41 ulp rms
+// over random operands, v_mfma_f32_16x16x4_f32 0.54) and once in 16 products instead of 4, so the results are no further from fp64 than those of
+// the fp32 instruction (hexi_f32.hip): relative errors of o, dq, dk, dv at 4096 rows x 4096 keys x 16/4 heads x 128 1.2e-6, 1.4e-6, 2.4e-6, 2.4e-6 with
+// it alone, 5e-7, 7e-7, 5e-7, 5e-7 here; over 250 random steps of 64 to 16000 keys, K scaled by 1 and by 3, no output is further off.
+// Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: where 64-row units fill the chip, the forward and dQ execute 1.1 PFLOP/s
+// in bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
+// the same card); dK / dV the cutting of four streamed operands for two, 11.4 vector instructions to a matrix one, 0.9; shorter launches the length
+// of their units (28 to 34 % busy).  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here: forward 1139 / 759, dQ 1559 / 1095, dK / dV
+// 2367 / 1960; 4096 diagonal x 8 heads x 64, forward and backward: 168 / 121, 496 / 404.
 //
 // Shape.  Cutting costs 5.5 vector operations per element, and a vector operation beside a saturated matrix pipe takes 6 cycles (10 for the packing
 // ones) next to 32x32x16 and 8.5 (13) next to 16x16x32; v_dot2_f32_bf16, which would subtract a packed value in one operation, waits for the

@@ -1,7 +1,8 @@
-// fp32 path (no reduced precision anywhere): the contractions run on the fp32 matrix instruction
+// fp32 path on the fp32 matrix instruction, for the steps that hexi_f32x3_fwd() and hexi_f32x3_bwd() (hexi_shapes.h) leave to it, and for rows
+// whose values leave the range of the kernels of hexi_f32_bf16x3.hip: the contractions run on
 // v_mfma_f32_16x16x4_f32, whose products and sums are ordinary fp32 fused multiply-adds at twice the rate of the
 // vector unit's.  Forward, dQ (both q-stationary) and dK/dV (key-stationary, one kernel with dQ; P is recomputed from the
-// saved global LSE in both).  No sum is spread over workgroups, so every output has a fixed summation order.
+// saved global LSE in both).  No sum is spread over workgroups here, so every output of these kernels has a fixed summation order.
 //
 // Shape of a workgroup.  A wavefront owns 16 stationary rows (q rows, or keys in the dK/dV kernel): their operand
 // fragments and output accumulators live in its registers.  The other operand's rows are streamed through LDS by
@@ -20,7 +21,7 @@
 // What bounds it: the matrix pipes (256 flop / clk / CU, 157 TFLOP/s; a library product reaches 154).  A 16-byte LDS read
 // per lane feeds four MFMAs of 32 cycles, so LDS needs a quarter of its rate, and the vector work per 16 x 16 block of
 // scores (4 per lane) is ~40 operations against 2048 cycles of MFMA (D = 128).  Measured, executed flops of a launch that
-// fills the chip (4096 rows x 4096 keys x 16 heads x 128, shared shape): forward 121, dQ 134, dK/dV 134 TFLOP/s.  The plain-FMA
+// fills the chip (4096 rows x 4096 keys x 16 heads x 128, shared shape, a size that goes to hexi_f32_bf16x3.hip since): forward 121, dQ 134, dK/dV 134 TFLOP/s.  The plain-FMA
 // kernels before these read both operands of every product from LDS element by element and put 64 x nq / nkv rows
 // in flight per workgroup: 3055 rows x 12011 keys, 6 / 2 heads, forward + backward 54.8 ms, now 2.77 ms; 1024 rows x 2048
 // keys, 4 heads of 64: 1486 us, now 113 us (bound there by launch latency and by 2 wavefronts per SIMD walking 8 blocks each).

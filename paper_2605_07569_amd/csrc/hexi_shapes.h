@@ -345,7 +345,7 @@ inline void hexi_plan_bwd(const AttnGeom& g, int forced_run_len, bool want_dq, b
     if (accumulate && plan->split_keys && plan->fixed_order(plan->run_len) && whole_cost <= ORDER_MARGIN) plan->run_len = plan->group;
 }
 
-// The fp32 kernels (hexi_f32.hip): 64-row workgroups that share their tiles, or 16-row ones whose wavefronts split the streamed
+// The fp32 kernels on the fp32 instruction (hexi_f32_units.h): 64-row workgroups that share their tiles, or 16-row ones whose wavefronts split the streamed
 // rows, one or (head_dim 64) two of them on a CU.
 enum class F32Shape { SHARED, SPLIT, SPLIT_TWO };
 

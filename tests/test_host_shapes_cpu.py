@@ -259,7 +259,7 @@ def test_split_operand_fp32_steps_take_the_shapes_they_are_meant_for(split_opera
     assert [diagonal[i] for i in (0, 7, 8, 13)] == [(0, 32, 32, 2), (0, 32, 32, 2), (64, 32, 64, 1), (64, 64, 64, 1)]
     middle = ask([_step(lq, lc, nq, nkv, d, lc // 2) for (lq, lc, nq, nkv, d), _ in F32X3_MIDDLE_STEPS])
     assert all(f > 0 for f, *_ in middle) and [tuple(b) for _, *b in middle] == [s for _, s in F32X3_MIDDLE_STEPS]
-    # us measured before / with the split-operand kernels: forward 1163 / 770, 295 / 213, 164 / 113; backward 3641 / 3021, 863 / 725, 493 / 394; 79 / 100
+    # us measured before / with the split-operand kernels: forward 1139 / 759, 295 / 215, 168 / 121; backward 3634 / 3049, 865 / 740, 496 / 404; 79 / 100
     # forward of 100 rows; 17 / 23 and 43 / 48 of 1024 at head_dim 64
     taken = ask([_step(4096, 4096, 16, 4, 128, 4096), _step(3056, 3000, 6, 2, 128, 3000), _step(4096, 4096, 8, 8, 64, 0),
                  _step(100, 4000, 8, 2, 128, 4000), _step(1024, 1024, 4, 4, 64, 1024)])
