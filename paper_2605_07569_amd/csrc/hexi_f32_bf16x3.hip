@@ -23,9 +23,10 @@
 // Values.  A cut loses bits of a value below 2^-110 (2^-133 is the smallest bf16: up to 2^-134 of it), an infinite one has no rest (inf - inf), and the
 // probabilities of the forward, up to 2^8 here, may overflow in a sum that would not.  A unit therefore looks its operands and results over
 // (largest(), stationary_range(), Extremes) and, where the cut may show in a result, hands its rows to the units on the fp32 instruction
-// (hexi_f32_units.h) before anything is written: values, infinities and NaN come out as there.  For the results that are kept it costs one v_maximum3_f32
-// for two values of the columns and of dS: 3056 rows x 12011 keys x 6/2 heads x 128, forward and backward,
-// 2346 / 2352 us without / with it.
+// (hexi_f32_units.h) before anything is written: values, infinities and NaN come out as there.  For the results that are kept it costs the
+// forward one v_maximum3_f32 for two values of V and the backward one for two of dS, less than the sums that need no care for NaN any more give back: 3056
+// rows x 12011 keys x 6/2 heads x 128, forward and backward, 2334 / 2335 us without / with it, 90 random backward steps 0.999.  A step that is all NaN
+// takes three times as long.
 #include "hexi_internal.h"
 #include "hexi_mfma.h"
 #include "hexi_shapes.h"
@@ -121,10 +122,18 @@ template <int NW> __device__ __forceinline__ float largest_of_workgroup(const fl
 // What a unit's results depend on besides the products themselves.  Stationary values are to be zero or within [2^-100, 2^60): their cuts lose
 // nothing, and what the cuts of streamed values lose moves a score (in units of log2, scale below 2^20) by 2^-127 2^60 2^21 at most.  Then a sum of n products p v is off by
 // n 2^-134 (max p + max v) besides its roundings, and p itself, a dS, by 2^-127 max s with s the stationary values of dP: nothing that 24 bits of
-// the result show if it is zero or not below 2^24 times that.
+// the result show if it is zero or not below 2^24 times that.  The backward takes P and dS times 2^40, which lose nothing then, so that max v need not be
+// known (in the second term it is taken for 2^10); dS that are all below what dP loses, or below 2^-100, are too small.
 constexpr float SMALLEST = 7.88860905e-31f;                            // 2^-100
 constexpr float CUT_LOSS = 7.70371978e-34f, SCORE_LOSS = 9.86076132e-32f;      // 2^24 2^-134, 2^24 2^-127
+constexpr float UP = 1099511627776.f, DOWN = 1.f / UP;                 // 2^40
+__device__ __forceinline__ unsigned scale_out_of_range(float x) { return (unsigned)!(x < 1048576.f) | (unsigned)!(x > 1e-18f); }      // (its product with DOWN is no denormal)
 __device__ __forceinline__ unsigned too_small(float largest_value) { return (unsigned)(largest_value > 0.f) & (unsigned)(largest_value < SMALLEST); }
+__device__ __forceinline__ unsigned ds_too_small(float ds_up, float s)
+{
+    return (unsigned)(ds_up > 0.f) & ((unsigned)(ds_up < SMALLEST * UP) | (unsigned)(ds_up < SCORE_LOSS * UP * s));
+}
+
 // Results: their largest magnitude and the smallest that is not zero, as its bits without the sign, less one.
 struct Extremes {
     float top = 0.f;
@@ -135,7 +144,10 @@ struct Extremes {
         top = largest(top, a, b);
         low = min(low, min(bits(a), bits(b)));
     }
-    __device__ __forceinline__ unsigned not_finite_or_below(float least) const { return (unsigned)!(top < INFINITY) | (unsigned)(low < bits(least)); }
+    __device__ __forceinline__ unsigned not_finite_or_below(float least) const
+    {
+        return (unsigned)!(top < INFINITY) | (unsigned)(low < bits(largest(1.4e-45f, least, least)));      // (a limit that underflows is the smallest value)
+    }
 };
 // Whether any thread of the workgroup finds its values so; votes: a word of LDS for each wavefront.
 template <int NW> __device__ __forceinline__ bool any_of_workgroup(unsigned x, unsigned* votes, int tid)
@@ -257,10 +269,10 @@ template <class C> struct ColBlock {
                 }
         }
     }
-    __device__ __forceinline__ Split3 split(int u, int j, float& top) const      // top: their largest magnitude so far
+    template <bool TOP> __device__ __forceinline__ Split3 split(int u, int j, float& top) const      // TOP: top is their largest magnitude so far
     {
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) top = largest(top, x[u][e][j], x[u][e + 1][j]);
+        for (int e = 0; e < 8 && TOP; e += 2) top = largest(top, x[u][e][j], x[u][e + 1][j]);
         return split8(x[u][0][j], x[u][1][j], x[u][2][j], x[u][3][j], x[u][4][j], x[u][5][j], x[u][6][j], x[u][7][j]);
     }
 };
@@ -336,7 +348,7 @@ template <class C, class F> __device__ __forceinline__ void scores(f32x16 (&s)[C
 // APART: the block's sum by itself, then added, for dK / dV and for long chains of the others: one rounding of the running value in 32 rows instead of 12.
 // Against the fp32 instruction, error without / with it: dv of 3643 rows of 4 heads 1.1 / 0.43, o of 12000 keys x 128 columns 1.13 / 0.37, of 5000 keys
 // x 64 1.06 / 0.4.  A backward is 4 % slower with it in dK / dV, a forward 5 %.
-template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB], float& top)
+template <class C, bool APART, bool TOP> __device__ __forceinline__ void accumulate(f32x16 (&acc)[C::NB][C::NJ], const ColBlock<C>& v, const f32x16 (&p)[C::NB], float& top)
 {
     constexpr int NB = C::NB;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -348,14 +360,14 @@ template <class C, bool APART> __device__ __forceinline__ void accumulate(f32x16
     };
     split_p(0);
     if (APART) split_p(1);
-    Split3 t = v.split(0, 0, top);
+    Split3 t = v.template split<TOP>(0, 0, top);
     f32x16 sum[NB];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int st = 0; st < 2 * C::NJ; ++st) {
         const int u = APART ? st % 2 : st / C::NJ, j = APART ? st / 2 : st % C::NJ, st1 = st + 1;
         Split3 next = t;
-        if (st1 < 2 * C::NJ) next = v.split(APART ? st1 % 2 : st1 / C::NJ, APART ? st1 / 2 : st1 % C::NJ, top);
+        if (st1 < 2 * C::NJ) next = v.template split<TOP>(APART ? st1 % 2 : st1 / C::NJ, APART ? st1 / 2 : st1 % C::NJ, top);
         f32x16* to[NB];
 #pragma unroll
         for (int n = 0; n < NB; ++n) to[n] = APART ? &sum[n] : &acc[n][j];
@@ -533,7 +545,7 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
                 }
                 l_run[n] += (part[0] + part[1]) + (part[2] + part[3]);
             }
-            accumulate<C, decltype(apart)::value>(acc, vc, s, v_top);
+            accumulate<C, decltype(apart)::value, true>(acc, vc, s, v_top);
         }
     };
     // the sums of o: 16 columns of 32 keys round 12 times, and a chain of more than about 2600 (7000) keys would end further from fp64 than in the 16-row units
@@ -541,7 +553,7 @@ template <int D, int NB> __device__ __forceinline__ bool fwd_unit(const FwdArgs&
     else walk(std::false_type{});
 
     // Combine the splits and merge with the running (o, lse): weights per (row, split), then a row-contiguous pass.
-    unsigned odd = g.scale >= 1048576.f;
+    unsigned odd = scale_out_of_range(g.scale);
     stationary_range<C>(sm.t.q, wave, lane, odd);
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
@@ -616,14 +628,14 @@ __global__ void __launch_bounds__(256, 1) fwd_f32x3_kernel(const FwdArgs a, cons
 
 template <class C> union X3BwdSmem {
     struct { unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES]; };
-    struct { float stage[C::STAGE_FLOATS], top[3][C::NW]; unsigned votes[C::NW]; };
+    struct { float stage[C::STAGE_FLOATS], top[2][C::NW]; unsigned votes[C::NW]; };
 };
 template <class C> union X3KvSmem {
     struct {
         unsigned char t[2][C::PIECES], rows[C::NW][C::BLOCK_BYTES];
         float scalars[C::NW][3][32];                       // the row scalars of each wavefront's block: -LSE log2(e) in two floats, Delta
     };
-    struct { float stage[2][C::STAGE_FLOATS], top[4][C::NW]; unsigned votes[C::NW]; };
+    struct { float stage[2][C::STAGE_FLOATS], top[2][C::NW]; unsigned votes[C::NW]; };
 };
 
 // dQ: S^T = K Q^T and dP^T = V dO^T per block, dS^T = P^T (dP^T - Delta), dQ^T += K^T dS^T.
@@ -648,7 +660,7 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
         const int row = row0 + 32 * n + l32, row_c = row < g.lq ? row : g.lq - 1;
         vis[n] = row < g.lq ? seg_rows_le(g.ks, seg_pos_of_row(g.qs, row)) : 0;
         neg_lse_log2(a.lse[(long long)h * g.lq + row_c], nl_hi[n], nl_lo[n]);
-        delta[n] = a.delta[(long long)h * g.lq + row_c];
+        delta[n] = UP * a.delta[(long long)h * g.lq + row_c];
     }
     const float* k = static_cast<const float*>(a.k) + (long long)kvh * g.kv_stride_head;
     const float* v = static_cast<const float*>(a.v) + (long long)kvh * g.kv_stride_head;
@@ -657,7 +669,7 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
     int b = wave;
     if (b < n_blocks) rows.request(k, g.kv_stride_tok, C::BLK * b, g.lc, lane);
     const long long q_off = (long long)h * g.q_stride_head;
-    float ds_top = 0.f, k_top = 0.f;
+    float ds_top = 0.f;
     put_stationary<C>(sm.t[0], static_cast<const float*>(a.q) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     put_stationary<C>(sm.t[1], static_cast<const float*>(a.d_o) + q_off, g.q_stride_tok, row0, g.lq, wave, lane);
     __syncthreads();
@@ -684,7 +696,7 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[n][r] *= dp[n][r] - delta[n];
+                for (int r = 0; r < 16; ++r) s[n][r] *= fmaf(dp[n][r], UP, -delta[n]);
             if (C::BLK * b + C::BLK > n_full) {
 #pragma unroll
                 for (int n = 0; n < NB; ++n)
@@ -696,26 +708,24 @@ template <int D, int NB> __device__ __forceinline__ bool dq_unit(const BwdArgs& 
             for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, s[n][r], s[n][r + 1]);
-            accumulate<C, decltype(apart)::value>(acc, kc, s, k_top);
+            accumulate<C, decltype(apart)::value, false>(acc, kc, s, ds_top);
         }
     };
     if (n_vis > 64 * D) walk(std::true_type{});            // (dq of the 16-row units rounds more often in its scores: 8000 and 13000 keys)
     else walk(std::false_type{});
-    unsigned odd = g.scale >= 1048576.f;
+    unsigned odd = scale_out_of_range(g.scale);
     stationary_range<C>(sm.t[0], wave, lane, odd);
     float g_top = largest_of_wave(stationary_range<C>(sm.t[1], wave, lane, odd));
-    k_top = largest_of_wave(k_top);
     ds_top = largest_of_wave(ds_top);
     __syncthreads();
-    stage_rows<C>(&sm.stage[wave * ROWS * C::PITCH], acc, lane, g.scale);
+    stage_rows<C>(&sm.stage[wave * ROWS * C::PITCH], acc, lane, g.scale * DOWN);
     const int tid = threadIdx.x;
-    if (lane == 0) { sm.top[0][wave] = k_top; sm.top[1][wave] = g_top; sm.top[2][wave] = ds_top; }
+    if (lane == 0) { sm.top[0][wave] = g_top; sm.top[1][wave] = ds_top; }
     __syncthreads();
-    k_top = largest_of_workgroup(sm.top[0]);
-    g_top = largest_of_workgroup(sm.top[1]);
-    ds_top = largest_of_workgroup(sm.top[2]);
-    odd |= too_small(ds_top) | too_small(k_top);
-    const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top + k_top) + SCORE_LOSS * g_top * k_top);
+    g_top = largest_of_workgroup(sm.top[0]);
+    ds_top = largest_of_workgroup(sm.top[1]);
+    odd |= ds_too_small(ds_top, g_top);
+    const float least = g.scale * (float)n_vis * (CUT_LOSS * (ds_top * DOWN) + 1024.f * SCORE_LOSS * g_top);
     constexpr int PARTS = ROWS * D / (64 * NW);
     float out[PARTS];             // consecutive lanes on consecutive floats
     Extremes ends;
@@ -783,7 +793,7 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
     f32x16 dk[NB][C::NJ], dv[NB][C::NJ];
     zero_acc<C>(dk);
     zero_acc<C>(dv);
-    float ds_top = 0.f, q_top = 0.f, g_top = 0.f;
+    float ds_top = 0.f;
     {
         // this wavefront's next block: number b of head h; the blocks of all heads in one sequence are dealt to the wavefronts in turn
         int b = block0 + wave;
@@ -825,7 +835,7 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
 #pragma unroll
                 for (int n = 0; n < NB; ++n)
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) p[n][4 * q + t] = probability(p[n][4 * q + t], c, nl_hi[t], nl_lo[t]);
+                    for (int t = 0; t < 4; ++t) p[n][4 * q + t] = UP * probability(p[n][4 * q + t], c, nl_hi[t], nl_lo[t]);
             }
             if (r0 < row_full || key_ragged || r0 + BLK > g.lq) {
 #pragma unroll
@@ -858,15 +868,13 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
             for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) ds_top = largest(ds_top, ds[n][r], ds[n][r + 1]);
-            accumulate<C, true>(dv, gc, p, g_top);
-            accumulate<C, true>(dk, qc, ds, q_top);
+            accumulate<C, true, false>(dv, gc, p, ds_top);
+            accumulate<C, true, false>(dk, qc, ds, ds_top);
         }
     }
-    unsigned odd = g.scale >= 1048576.f;
+    unsigned odd = scale_out_of_range(g.scale);
     stationary_range<C>(sm.t[0], wave, lane, odd);
     const float v_top = largest_of_wave(stationary_range<C>(sm.t[1], wave, lane, odd));
-    q_top = largest_of_wave(q_top);
-    g_top = largest_of_wave(g_top);
     ds_top = largest_of_wave(ds_top);
     // consecutive lanes on consecutive floats where they are added with atomics, on consecutive 16 bytes where they are stored
     constexpr int PARTS = ROWS * D / (64 * NW);
@@ -886,16 +894,15 @@ template <int D, int NB> __device__ __forceinline__ bool dkdv_unit(const BwdArgs
         return ends;
     };
     __syncthreads();
-    stage_rows<C>(&sm.stage[0][wave * ROWS * C::PITCH], dv, lane, 1.0f);
-    stage_rows<C>(&sm.stage[1][wave * ROWS * C::PITCH], dk, lane, g.scale);
-    if (lane == 0) { sm.top[0][wave] = q_top; sm.top[1][wave] = g_top; sm.top[2][wave] = v_top; sm.top[3][wave] = ds_top; }
+    stage_rows<C>(&sm.stage[0][wave * ROWS * C::PITCH], dv, lane, DOWN);
+    stage_rows<C>(&sm.stage[1][wave * ROWS * C::PITCH], dk, lane, g.scale * DOWN);
+    if (lane == 0) { sm.top[0][wave] = v_top; sm.top[1][wave] = ds_top; }
     __syncthreads();
     float out_v[PARTS], out_k[PARTS];
     const Extremes ends_v = gather(out_v, sm.stage[0]), ends_k = gather(out_k, sm.stage[1]);
-    const float q_all = largest_of_workgroup(sm.top[0]), g_all = largest_of_workgroup(sm.top[1]), v_all = largest_of_workgroup(sm.top[2]),
-                ds_all = largest_of_workgroup(sm.top[3]);
-    odd |= too_small(ds_all) | too_small(q_all) | too_small(g_all) | ends_v.not_finite_or_below(n_rows * CUT_LOSS * (2.f + g_all)) |
-           ends_k.not_finite_or_below(g.scale * n_rows * (CUT_LOSS * (ds_all + q_all) + SCORE_LOSS * v_all * q_all));
+    const float v_all = largest_of_workgroup(sm.top[0]), ds_all = largest_of_workgroup(sm.top[1]);
+    odd |= ds_too_small(ds_all, v_all) | ends_v.not_finite_or_below(n_rows * 2.f * CUT_LOSS) |
+           ends_k.not_finite_or_below(g.scale * n_rows * (CUT_LOSS * (ds_all * DOWN) + 1024.f * SCORE_LOSS * v_all));
     if (any_of_workgroup<NW>(odd, sm.votes, tid)) return false;
     auto write_out = [&](float* to, const float (&out)[PARTS]) {
 #pragma unroll

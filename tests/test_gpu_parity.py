@@ -1115,23 +1115,24 @@ F32X3_MASKED_STEPS = [(568, 167, 8, 2, 128), (347, 270, 16, 16, 128), (625, 231,
 
 @pytest.mark.parametrize("lq,lc,nq,nkv,d", F32X3_VALUE_STEPS)
 @pytest.mark.parametrize("units", [dict(v=1e-36), dict(d_o=1e-36), dict(d_o=1e-32), dict(q=1e36, k=1e-36), dict(q=1e-36, k=1e36), dict(v=1e-25, d_o=1e-10),
+                                   dict(d_o=3e30), dict(d_o=1e20, v=1e10), dict(q=1e10, k=1e10, scale=1e-21), dict(q=1e-5, k=1e-5, scale=1e9),
                                    dict(q=1e-36, k=1e36, d_o=1e-30, v=1e30)], ids=str)
 def test_f32_keeps_its_range_where_operands_are_cut(lq, lc, nq, nkv, d, units):
     # operands with magnitudes near the ends of fp32's range: every output keeps its relative accuracy
     g = torch.Generator().manual_seed(lq)
     x = {n: torch.randn((rows, h, d), generator=g) for n, rows, h in (("q", lq, nq), ("k", lc, nkv), ("v", lc, nkv), ("d_o", lq, nq))}
-    for name, unit in units.items():
-        x[name] *= unit
     u = {n: units.get(n, 1.0) for n in x}
-    scale = float(np.float32(0.1))
+    for name, unit in u.items():
+        x[name] *= unit
+    scale = float(np.float32(units.get("scale", 0.1)))
     got = _f32_step(*x.values(), lc, scale)
     in_units = {n: to64(x[n]) / u[n] for n in x}
     qk = u["q"] * u["k"]
     ref = oracle.attn_bwd(in_units["q"], np.arange(lc, lc + lq), in_units["k"], in_units["v"], np.arange(lc), in_units["d_o"], scale * qk)
     o_ref, lse_ref = oracle.attn_fwd(in_units["q"], np.arange(lc, lc + lq), in_units["k"], in_units["v"], np.arange(lc), scale * qk)
     g_v = u["v"] * u["d_o"]
-    for name, t, want, unit in (("o", got[0], o_ref, u["v"]), ("lse", got[1], lse_ref, 1.0), ("dq", got[2], ref["dq"], g_v * qk / u["q"]),
-                                ("dk", got[3], ref["dk"], g_v * qk / u["k"]), ("dv", got[4], ref["dv"], u["d_o"])):
+    for name, t, want, unit in (("o", got[0], o_ref, u["v"]), ("lse", got[1], lse_ref, 1.0), ("dq", got[2], ref["dq"], g_v / u["q"]),
+                                ("dk", got[3], ref["dk"], g_v / u["k"]), ("dv", got[4], ref["dv"], u["d_o"])):
         if unit > (1e-33 if name in ("dq", "dk") else 1e-37):      # (dS, and below 1e-38 everything, has fewer than 24 bits in fp32)
             check(name, t.double() / unit, want, "f32")
 
