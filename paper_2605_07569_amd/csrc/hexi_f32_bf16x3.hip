@@ -6,7 +6,7 @@
 // it alone, 5e-7, 7e-7, 5e-7, 5e-7 here; over 250 random steps of 64 to 16000 keys, K scaled by 1 and by 3, no output is further off.
 // Six bf16 products cost 6 / 16 of the fp32 one.  What bounds these kernels then: where 64-row units fill the chip, the forward and dQ execute 1.1 PFLOP/s
 // in bf16, at the power limit (1.95 GHz, matrix pipes 53 % busy; a library product of 8192 x 8192 x 8192 on random bf16 operands reaches 1.16 on
-// the same card); dK / dV the cutting of four streamed operands for two, 11.4 vector instructions to a matrix one, 0.9; shorter launches the length
+// the same card); dK / dV the cutting of four streamed operands for two, 11.2 vector instructions to a matrix one, 0.9; shorter launches the length
 // of their units (28 to 34 % busy).  us, 4096 x 4096 x 16/4 heads x 128, all keys visible, hexi_f32.hip / here: forward 1139 / 759, dQ 1559 / 1095, dK / dV
 // 2367 / 1960; 4096 diagonal x 8 heads x 64, forward and backward: 168 / 121, 496 / 404.
 //
